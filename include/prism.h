@@ -64,7 +64,7 @@
  *     are PRISM_EINVAL.
  *   - Size limits: at most 2^31 - 1 entries per matrix, counted with both
  *     sides rounded up to the next multiple of 256 (bf16 with min(m, n) >=
- *     512), 128 or 64 (fp32 with min(m, n) <= 256), and batch <=
+ *     512), 128 (bf16, fp32 with min(m, n) >= 4096, DB Newton) or 64, and batch <=
  *     PRISM_MAX_BATCH matrices per call; beyond them PRISM_EUNSUPPORTED.
  */
 #ifndef PRISM_H

@@ -283,7 +283,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* 
     GemmDesc r = g;                                      // T = P A_k,:
     r.A = Pk; r.strideA = per_mat; r.lda = np; r.B = rowk; r.strideB = per_mat; r.ldb = np;
     r.C = Trow; r.strideC = tstride; r.ldc = np; r.M = OB; r.N = np; r.skip_n0 = k * OB; r.skip_n1 = (k + 1) * OB;
-    rc = launch_gemm_f32(r, 128, 128, s);
+    rc = launch_gemm_f32(r, s);
     if (rc != PRISM_OK) return rc;
     GemmDesc u = g;                                      // A_ij <- A_ij - A_ik T_j, i, j outside the pivot block
     u.A = colk; u.strideA = per_mat; u.lda = np; u.B = Trow; u.strideB = tstride; u.ldb = np;
@@ -293,13 +293,13 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* 
     // A half-swept symmetric matrix is symmetric within the swept and within the unswept blocks and
     // antisymmetric between them, and the update keeps that: upper triangle of tiles only
     u.sym = 1; u.sym_skew_bound = k * OB;
-    rc = launch_gemm_f32(u, 128, 128, s);
+    rc = launch_gemm_f32(u, s);
     if (rc != PRISM_OK) return rc;
     GemmDesc c = g;                                      // U = -A_:,k P
     c.A = colk; c.strideA = per_mat; c.lda = np; c.B = Pk; c.strideB = per_mat; c.ldb = np;
     c.C = Ucol; c.strideC = ustride; c.ldc = OB; c.M = np; c.N = OB; c.acc_neg = 1;
     c.skip_m0 = k * OB; c.skip_m1 = (k + 1) * OB;
-    rc = launch_gemm_f32(c, 128, 128, s);
+    rc = launch_gemm_f32(c, s);
     if (rc != PRISM_OK) return rc;
     hipLaunchKernelGGL(panel_copy_kernel, dim3((unsigned)(((long long)OB * np / 4 + NT - 1) / NT), batch), dim3(NT), 0, s,
                        Trow, tstride, np, rowk, per_mat, np, OB, np, k * OB, (k + 1) * OB, 0, ctrl);

@@ -123,7 +123,9 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   if (dt == PRISM_BF16) {
     P.tile = P.S >= 512 ? 256 : 128;   // padding granularity; the tile is chosen per launch
   } else {
-    P.tile = P.S <= 256 ? 64 : 128;
+    // Newton: the block elimination wants large pivot blocks.  Others: the padding costs more than 64 x 64
+    // tiles do (n = 300: 320 against 384) until the sides are large
+    P.tile = P.S <= 256 || (P.S < 4096 && fn != PRISM_FN_SQRT_NEWTON) ? 64 : 128;
   }
   P.Sp = round_up(P.S, P.tile);
   P.Lp = round_up(P.L, P.tile);
@@ -194,8 +196,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   P.ksplit = 0; P.o_gpart = 0;
   static const int no_split_k = ab_switch("PRISM_NO_SPLIT_K");
   if (fn == PRISM_FN_POLAR && !no_split_k && !shared_shapes && batch <= 8 && P.Lp >= 8192 && P.Sp > 64) {
-    const int tg = dt == PRISM_BF16 ? 128 : P.tile;
-    const long long nt = P.Sp / tg, tri = nt * (nt + 1) / 2, full = nt * nt;
+    const long long nt = (P.Sp + 127) / 128, tri = nt * (nt + 1) / 2, full = nt * nt;
     if (tri * batch <= 48) {
       for (int parts = 32; parts >= 2; --parts)
         if (P.Lp % (parts * 32) == 0 && P.Lp / parts >= 1024 && full * batch * parts <= 4096) { P.ksplit = parts; break; }
@@ -364,18 +365,17 @@ int f32_sym() {
   static const int off = ab_switch("PRISM_F32_NO_SYM");
   return off ? 0 : 1;
 }
-int sym_parts(int nt, int sym) { return sym ? nt * (nt + 1) / 2 : nt * nt; }
 
 int run_polar_f32(Run& r) {
   const Plan& P = r.P;
-  const int Sp = P.Sp, Lp = P.Lp, T = P.tile;
+  const int Sp = P.Sp, Lp = P.Lp;
   const long long SS = (long long)Sp * Sp, LS = (long long)Lp * Sp;
   float* X[2] = {r.at<float>(P.o_x[0]), r.at<float>(P.o_x[1])};
   float* R = r.at<float>(P.o_r);
   float* Q = P.d == 2 ? r.at<float>(P.o_q) : nullptr;
   const bool polar = P.fn != PRISM_FN_SIGN;
   const int sym = polar ? f32_sym() : 0;
-  const int nparts = sym_parts(Sp / T, sym);
+  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
   static const int no_small = ab_switch("PRISM_NO_SMALL_KERNEL");
   if (polar && Sp == 64 && Lp == 64 && P.ngroups == 1 && !no_small) {
     // the whole iteration in one workgroup per matrix, one launch for all iterations: with five
@@ -409,7 +409,7 @@ int run_polar_f32(Run& r) {
                                (long long)Kp * Sp, Sp, Sp, Kp, 1);
         sp.batch = P.ksplit; sp.epi = EPI_STORE; sp.C = gpart + (long long)b * P.ksplit * SS; sp.strideC = SS; sp.ldc = Sp;
         sp.ctrl = r.ctrl + b; sp.ctrl_fixed = 1;
-        CHECK_LAUNCH(launch_gemm_f32(sp, T, T, r.s));
+        CHECK_LAUNCH(launch_gemm_f32(sp, r.s));
       }
       GramReduceArgs ra = {};
       ra.part = gpart; ra.parts = P.ksplit; ra.np = Sp; ra.n_true = P.S;
@@ -418,7 +418,7 @@ int run_polar_f32(Run& r) {
       CHECK_LAUNCH(check_hip());
     } else {
       ProfScope ps(PK_F32_RESID, r.s);
-      CHECK_LAUNCH(launch_gemm_f32(g, T, T, r.s));
+      CHECK_LAUNCH(launch_gemm_f32(g, r.s));
     }
     if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
     CHECK_LAUNCH(r.solve(k, (polar && P.ksplit) ? gram_reduce_parts(Sp) : nparts));
@@ -428,13 +428,13 @@ int run_polar_f32(Run& r) {
       GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, polar ? 1 : 0);  // mirrored R: R^2 = R^T R
       q.sym = sym;
       q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
-      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, T, T, r.s)); }
+      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
       Bop = Q;
     }
     GemmDesc a = f32_desc(r, X[cur], Sp, LS, Bop, Sp, SS, Lp, Sp, Sp, 0);      // X + X Q
     a.epi = EPI_AXPY; a.C = X[cur ^ 1]; a.strideC = LS; a.ldc = Sp; a.Cin = X[cur]; a.strideCin = LS; a.ldcin = Sp;
     a.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(a, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(a, r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -613,7 +613,7 @@ int run_polar_bf16(Run& r) {
 
 int run_sqrt_f32(Run& r) {
   const Plan& P = r.P;
-  const int Sp = P.Sp, T = P.tile;
+  const int Sp = P.Sp;
   const long long SS = (long long)Sp * Sp;
   float* X[2] = {r.at<float>(P.o_x[0]), r.at<float>(P.o_x[1])};
   float* Y[2] = {r.at<float>(P.o_y[0]), r.at<float>(P.o_y[1])};
@@ -622,14 +622,14 @@ int run_sqrt_f32(Run& r) {
   // X_k and Y_k commute up to kappa * eps only: every product keeps all its tiles.  (Mirroring only
   // Y X and R^2 is stable but costs the root an order of magnitude of accuracy from kappa ~ 1e4 on.)
   const int sym = 0;
-  const int nparts = sym_parts(Sp / T, sym);
+  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
     GemmDesc g = f32_desc(r, Y[cur], Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);    // G = Y X
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, T, T, r.s)); }
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
     if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
     CHECK_LAUNCH(r.solve(k, nparts));
     if (k == r.max_iters) break;
@@ -638,17 +638,17 @@ int run_sqrt_f32(Run& r) {
       GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
       q.sym = sym;
       q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
-      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, T, T, r.s)); }
+      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
       Pm = Q;
     }
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, Pm, Sp, SS, Sp, Sp, Sp, 0);        // X + X Q
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     GemmDesc ay = f32_desc(r, Pm, Sp, SS, Y[cur], Sp, SS, Sp, Sp, Sp, 0);        // Y + Q Y
     ay.epi = EPI_AXPY; ay.C = Y[cur ^ 1]; ay.strideC = SS; ay.ldc = Sp; ay.Cin = Y[cur]; ay.strideCin = SS; ay.ldcin = Sp;
     ay.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -657,31 +657,31 @@ int run_sqrt_f32(Run& r) {
 // Chebyshev inverse (App. A.4): R = I - A_s X, Q = R + alpha R^2, X <- X + X Q
 int run_inverse_f32(Run& r) {
   const Plan& P = r.P;
-  const int Sp = P.Sp, T = P.tile;
+  const int Sp = P.Sp;
   const long long SS = (long long)Sp * Sp;
   float* X[2] = {r.at<float>(P.o_x[0]), r.at<float>(P.o_x[1])};
   const float* As = r.at<float>(P.o_y[0]);
   float* R = r.at<float>(P.o_r);
   float* Q = r.at<float>(P.o_q);
   const int sym = 0;   // A_s X_k is symmetric up to kappa * eps only: all tiles
-  const int nparts = sym_parts(Sp / T, sym);
+  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
     GemmDesc g = f32_desc(r, As, Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, T, T, r.s)); }
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
     if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
     CHECK_LAUNCH(r.solve(k, nparts));
     if (k == r.max_iters) break;
     GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
     q.sym = sym;
     q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 1.0f;
-    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, T, T, r.s)); }
+    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, Q, Sp, SS, Sp, Sp, Sp, 0);
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -691,7 +691,7 @@ int run_inverse_f32(Run& r) {
 // M <- 2a(1-a) I + (1-a)^2 M + a^2 N.  The stop test of iteration k runs before the inverse.
 int run_sqrt_newton_f32(Run& r) {
   const Plan& P = r.P;
-  const int Sp = P.Sp, T = P.tile;
+  const int Sp = P.Sp;
   const long long SS = (long long)Sp * Sp;
   float* X[2] = {r.at<float>(P.o_x[0]), r.at<float>(P.o_x[1])};
   float* Y[2] = {r.at<float>(P.o_y[0]), r.at<float>(P.o_y[1])};
@@ -715,11 +715,11 @@ int run_sqrt_newton_f32(Run& r) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, N, Sp, SS, Sp, Sp, Sp, 0);
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.cin_one_minus_alpha = 1; ax.coef_is_alpha = 1; ax.sym = sym;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     GemmDesc ay = f32_desc(r, Y[cur], Sp, SS, N, Sp, SS, Sp, Sp, Sp, 0);
     ay.epi = EPI_AXPY; ay.C = Y[cur ^ 1]; ay.strideC = SS; ay.ldc = Sp; ay.Cin = Y[cur]; ay.strideCin = SS; ay.ldcin = Sp;
     ay.cin_one_minus_alpha = 1; ay.coef_is_alpha = 1; ay.sym = sym;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, r.s)); }
     { ProfScope ps(PK_DB_UPDATE_M, r.s); launch_db_update_m(M, N, Sp, P.S, P.batch, r.ctrl, r.rho, nparts, r.s); }
     CHECK_LAUNCH(check_hip());
     cur ^= 1;
@@ -729,7 +729,7 @@ int run_sqrt_newton_f32(Run& r) {
 
 int run_inv_root_f32(Run& r) {
   const Plan& P = r.P;
-  const int Sp = P.Sp, T = P.tile, p = P.p;
+  const int Sp = P.Sp, p = P.p;
   const long long SS = (long long)Sp * Sp;
   float* X[2] = {r.at<float>(P.o_x[0]), r.at<float>(P.o_x[1])};
   double* M[2] = {r.at<double>(P.o_y[0]), r.at<double>(P.o_y[1])};
@@ -746,7 +746,7 @@ int run_inv_root_f32(Run& r) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.coef_is_alpha = 1; ax.sym = f32_sym();   // X never re-enters M; the power chain below keeps all tiles
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, T, T, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     // (I + alpha R)^q = I + E_q, built on the part beyond the identity so that fp32 rounding acts
     // on the small quantity only: E_1 = alpha R, squaring E <- 2E + E E, times T: E <- E + E_1 + E E_1.
     // E_1 itself is never stored: wherever it is an operand R stands in and the epilogue supplies
@@ -757,14 +757,14 @@ int run_inv_root_f32(Run& r) {
       sq.epi = EPI_AXPY; sq.C = dst; sq.strideC = SS; sq.ldc = Sp; sq.Cin = Eop; sq.strideCin = SS; sq.ldcin = Sp; sq.c_in = 2.0f;
       if (!E) { sq.cin_alpha_pow = 1; sq.coef_is_alpha = 2; }
       ProfScope ps(PK_F32_STORE, r.s);
-      return launch_gemm_f32(sq, T, T, r.s);
+      return launch_gemm_f32(sq, r.s);
     };
     auto times_t = [&](const float* U, float* dst) -> int {                      // U + alpha R + alpha U R
       GemmDesc mu = f32_desc(r, U, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
       mu.epi = EPI_AXPY; mu.C = dst; mu.strideC = SS; mu.ldc = Sp; mu.Cin = U; mu.strideCin = SS; mu.ldcin = Sp; mu.c_in = 1.0f;
       mu.Cin2 = R; mu.cin2_alpha_pow = 1; mu.coef_is_alpha = 1;
       ProfScope ps(PK_F32_STORE, r.s);
-      return launch_gemm_f32(mu, T, T, r.s);
+      return launch_gemm_f32(mu, r.s);
     };
     auto m_times = [&](const float* E, const double* Min, double* Mout, float* Rout) -> int {   // Mout = Min + E Min in fp64
       GemmDesc mn = {};
@@ -1442,6 +1442,7 @@ int prism_gemm_f32(const float* A, const float* B, float* C, int batch, int M, i
   g.M = M; g.N = N; g.K = K; g.a_km = a_km & 1; g.sym = (a_km >> 1) & 1; g.batch = batch; g.epi = EPI_STORE;
   g.C = C; g.strideC = (long long)M * N; g.ldc = N;
   const int tn = (N == 16 || N == 32 || N == 64) ? N : 128;
+  if (tn == 128) return launch_gemm_f32(g, (hipStream_t)stream);
   return launch_gemm_f32(g, (tn == 64 && M % 128) ? 64 : 128, tn, (hipStream_t)stream);
 }
 

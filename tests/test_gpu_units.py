@@ -33,6 +33,22 @@ def test_gemm_f32(prism, a_km, shape):
     assert np.linalg.norm(C - ref) / np.linalg.norm(ref) < 1e-6
 
 
+@pytest.mark.parametrize("a_km", [False, True])
+@pytest.mark.parametrize("M,N,K,batch", [(64, 192, 16, 1), (192, 128, 32, 2), (320, 320, 48, 1), (192, 192, 1040, 1), (128, 256, 272, 1),
+                                         (1024, 1024, 80, 16), (1024, 1024, 256, 16)])
+def test_gemm_f32_ring_edges(prism, a_km, M, N, K, batch):
+    """K of fewer slabs than the LDS ring, of a whole number of turns and of one to three slabs more, partial
+    sums with a remainder; 64 x 64 tiles and (the last two) 128 x 128 ones.  Bound: sums of K terms rounded
+    at 2^-24 in partial sums of 256 stay below sqrt(256) 2^-24 = 1e-6 of the result's norm."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(batch, M, K, generator=g, device="cuda")
+    B = torch.randn(batch, K, N, generator=g, device="cuda")
+    C = prism.gemm_f32(A.transpose(1, 2).contiguous() if a_km else A, B, a_km=a_km)
+    for b in {0, batch - 1}:
+        ref = A[b].double() @ B[b].double()
+        assert float((C[b].double() - ref).norm() / ref.norm()) < 1e-6
+
+
 @pytest.mark.parametrize("n,ld,batch", [(64, 16, 2), (192, 32, 2), (768, 16, 2), (1024, 32, 2), (4096, 32, 2),
                                         (1024, 16, 16), (2048, 32, 8), (1152, 32, 15), (768, 16, 12), (1088, 32, 16), (2048, 64, 2),
                                         # one and two chunks of 256 k (shorter than the kernel's ring), 128-row workgroups
