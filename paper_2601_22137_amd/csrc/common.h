@@ -247,10 +247,10 @@ void launch_gram_reduce(const GramReduceArgs& a, int batch, hipStream_t s);
 void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np, hipStream_t s);
 
 // ---- dbnewton.hip : pieces of the DB Newton iteration (App. A.2) ----
-// N = M (copy), then the in-place inverse of the SPD matrices N[batch][np][np] by block Gauss-Jordan.
-// panels: scratch of spd_inverse_scratch_floats(np, batch) floats (may be null when that is 0).
+// N = M^{-1} of the SPD matrices M[batch][np][np] by block Gauss-Jordan.  scratch: spd_inverse_scratch_floats(np, batch)
+// floats, 16-byte aligned.
 long long spd_inverse_scratch_floats(int np, int batch);
-int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* panels, hipStream_t s);
+int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* scratch, hipStream_t s);
 // partial sums of <D0,D0>, <D0,D2>, <D2,D2> (D0 = M - I, D2 = M + N - 2I) -> the five coefficient partials
 void launch_db_moments(const float* M, const float* N, int np, int n_true, int batch, const Ctrl* ctrl, double* cpart,
                        int ngroups, hipStream_t s);

@@ -7,19 +7,17 @@
 //   M_{k+1} = 2a(1-a) I + (1-a)^2 M_k + a^2 N_k
 // Block Gauss-Jordan: for every pivot block k
 //   P = A_kk^{-1},  A_kj <- P A_kj  (j != k),  A_ij <- A_ij - A_ik A_kj  (i, j != k),  A_ik <- -A_ik P  (i != k),  A_kk <- P
-// with the three block updates as launches of the fp32 GEMM kernel.  Two levels: pivot blocks of
-// 512 or 256 (such rank updates are compute bound: >= 64 flop per byte of the matrix they sweep; with
-// blocks of 64 the sweep is HBM bound), each inverted by the same
-// elimination with blocks of 64, whose 64 x 64 pivots one workgroup inverts in fp64.  With blocks
-// of 64 the updates run in place (one 64 x 64 tile covers a block); with the large blocks the new pivot
-// row and column panels go to scratch and are copied back.
+// Two levels: outer pivot blocks of 512 or 256, whose rank updates are launches of the fp32 GEMM kernel (>= 64 flop per
+// byte of the matrix they sweep; with blocks of 64 the sweep is HBM bound), each inverted by the same
+// elimination with pivots of 64, which one workgroup inverts in fp64 (larger ones would be fewer steps, but an
+// inverse of order 128 rounded to fp32 costs the ill-conditioned cases accuracy: 2.9e-4 against 2e-4 at cond 1e4).
+// The new row and column panels of an outer block go to scratch and are copied back.
 #include "common.h"
 
 namespace prism {
 namespace {
 
 constexpr int NT = 256;
-constexpr int BS = 64;   // block size of the elimination
 
 __global__ __launch_bounds__(NT) void copy_kernel(const float* __restrict__ src, float* __restrict__ dst, long long per_mat,
                                                   const Ctrl* __restrict__ ctrl) {
@@ -29,48 +27,287 @@ __global__ __launch_bounds__(NT) void copy_kernel(const float* __restrict__ src,
   if (i < per_mat) *(float4*)(dst + (long long)b * per_mat + i) = *(const float4*)(src + (long long)b * per_mat + i);
 }
 
-// In-place inverse of the 64 x 64 diagonal block k of every matrix.  Thread t owns row t / 4,
-// columns 16 (t % 4) .. +15 in registers (fp64); per elimination step the old pivot row and pivot
-// column are exchanged through a double-buffered LDS line, one barrier per step.
-__global__ __launch_bounds__(NT) void diag_inv_kernel(float* __restrict__ A, long long stride, int ld, int k,
-                                                      const Ctrl* __restrict__ ctrl) {
-  const int b = blockIdx.x;
-  if (ctrl && ctrl[b].done) return;
-  __shared__ double rowbuf[2][BS], colbuf[2][BS];
-  const int t = threadIdx.x, i = t >> 2, c0 = (t & 3) * 16;
-  float* blk = A + (long long)b * stride + (long long)(k * BS + i) * ld + k * BS + c0;
-  double v[16];
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int BS = 64;   // pivots of the elimination
+
+// value of lane P of every group of 16 lanes, to all lanes of the group
+template <int P> __device__ inline double bcast16(double v) {
+  const long long w = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)w, 0x150 + P, 0xF, 0xF, false);           // row_newbcast:P
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(w >> 32), 0x150 + P, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <int L> __device__ inline double from_lane(double v) {   // uniform
+  const long long w = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)w, L), hi = __builtin_amdgcn_readlane((int)(w >> 32), L);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// One elimination step of the 16 x 16 inverse below: pivot P.
+template <int P> __device__ inline void invert16_step(double (&e)[4], int lr, int lq) {
+  constexpr int G = P >> 2, C = P & 3;           // the pivot column sits in lane group G, register C
+  const double inv = 1.0 / from_lane<G * 16 + P>(e[C]);
+  const double f = __shfl(e[C], G * 16 + lr, 64);
+  double rw[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 x = *(const float4*)(blk + 4 * q);
-    v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+  for (int s = 0; s < 4; ++s) rw[s] = bcast16<P>(e[s]) * inv;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const bool pc = s == C && lq == G;
+    if (lr == P) e[s] = pc ? inv : rw[s];
+    else e[s] = pc ? -f * inv : e[s] - f * rw[s];
   }
-  for (int p = 0; p < BS; ++p) {
-    const int buf = p & 1;
-    if (i == p) {
+}
+// Inverse of a 16 x 16 matrix held by one wave: lane (lr = l % 16, lq = l / 16), register s: entry [lr][4 lq + s].
+template <int P = 0> __device__ inline void invert16(double (&e)[4], int lr, int lq) {
+  invert16_step<P>(e, lr, lq);
+  if constexpr (P + 1 < 16) invert16<P + 1>(e, lr, lq);
+}
+
+// LDS written and read by the same wave: the operations of a wave complete in order, only the
+// compiler has to keep them so
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inverse of a 64 x 64 matrix by one workgroup (four wavefronts) in fp64.  Wave w holds rows 16 w .. 16 w + 15 as
+// the accumulators of v_mfma_f64_16x16x4_f64 (acc[j], register r of lane (lr, lq): row 4 r + lq, column 16 j + lr).
+// Block Gauss-Jordan with 16 x 16 pivots D, one barrier per pivot: the owner of the pivot row shares it through
+// LDS; every wave inverts D by itself (handing the inverse round would cost a second barrier); wave i forms
+// B = A_ik D^-1 and takes A_ij -= B A_kj (j != k), A_ik = -B; the owner takes A_kj = D^-1 A_kj, A_kk = D^-1.
+// B is formed as its transpose, whose accumulator layout is the operand layout of the update.
+constexpr int RSD = BS + 16;               // rows 128 bytes apart modulo 256: two lane groups fall on different banks
+struct Inv64Lds {
+  double row[2][16][RSD];                  // pivot row, double buffered
+  double scr[4][16][17];                   // per wave: transposes
+};
+__device__ inline void invert64(f64x4 (&acc)[4], Inv64Lds& m) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double (*scr)[17] = m.scr[w];
+#pragma unroll 1
+  for (int k = 0; k < 4; ++k) {
+    double (*pr)[RSD] = m.row[k & 1];      // the other buffer may still be read from the step before
+    if (w == k) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) rowbuf[buf][c0 + e] = v[e];
-    }
-    if ((p >> 4) == (t & 3)) {
-      double f = 0.0;
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) f = (e == (p & 15)) ? v[e] : f;
-      colbuf[buf][i] = f;
-    }
-    __syncthreads();
-    const double inv = 1.0 / rowbuf[buf][p];
-    const double f = colbuf[buf][i];
-    if (i == p) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) v[e] = (c0 + e == p) ? inv : v[e] * inv;
+        for (int r = 0; r < 4; ++r) pr[4 * r + lq][16 * j + lr] = acc[j][r];
     } else {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) v[e] = (c0 + e == p) ? -f * inv : v[e] - f * (rowbuf[buf][c0 + e] * inv);
+      for (int j = 0; j < 4; ++j)
+        if (j == k) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) scr[4 * r + lq][lr] = acc[j][r];
+        }
     }
+    __syncthreads();
+    double e[4];                           // the owner inverts D, the others D^T (symmetric up to rounding only)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) e[s] = w == k ? pr[lr][16 * k + 4 * lq + s] : pr[4 * lq + s][16 * k + lr];
+    invert16(e, lr, lq);
+    f64x4 own;                             // new block k of this wave
+    if (w == k) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f64x4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(e[s], pr[4 * lq + s][16 * j + lr], c, 0, 0, 0);
+        acc[j] = c;
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) scr[lr][4 * lq + s] = e[s];
+    } else {
+      f64x4 bt = {0.0, 0.0, 0.0, 0.0};     // register r: B[lr][4 r + lq]
+#pragma unroll
+      for (int s = 0; s < 4; ++s) bt = __builtin_amdgcn_mfma_f64_16x16x4f64(e[s], scr[lr][4 * lq + s], bt, 0, 0, 0);
+      wave_lds_fence();
+      bt = -bt;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bt[s], pr[4 * s + lq][16 * j + lr], acc[j], 0, 0, 0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) scr[lr][4 * s + lq] = bt[s];
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) own[r] = scr[4 * r + lq][lr];
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j == k) acc[j] = own;
+  }
+}
+
+// P = inverse of the leading 64 x 64 block of every matrix (the first pivot of an elimination)
+__global__ __launch_bounds__(NT) void first_pivot_kernel(const float* __restrict__ S, long long stride, int ld,
+                                                         float* __restrict__ P, const Ctrl* __restrict__ ctrl) {
+  const int b = blockIdx.x;
+  if (ctrl && ctrl[b].done) return;
+  __shared__ Inv64Lds m;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4, w = threadIdx.x >> 6;
+  const float* blk = S + (long long)b * stride + (long long)(16 * w + lq) * ld + lr;
+  f64x4 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[j][r] = (double)blk[(long long)(4 * r) * ld + 16 * j];
+  invert64(acc, m);
+  float* out = P + (long long)b * 2 * BS * BS;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(16 * w + 4 * r + lq) * BS + 16 * j + lr] = (float)acc[j][r];
+}
+
+// 32 x 32 quadrant of a 64 x 64 x 64 product: acc[i][j] = A B, both operands in LDS, rows of SL floats.
+// k order: lane group lq takes k = 16 c + 4 lq + e at step e, so that A comes as one 16-byte read per row and
+// chunk; with SL = 68 the four rows of a B read lie 64 bytes apart modulo 256.
+constexpr int SL = BS + 4;
+__device__ inline void mma64(const float* As, const float* Bs, int m0, int n0, f32x4 (&acc)[2][2]) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    f32x4 a[2];
+    float bv[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = *(const f32x4*)(As + (m0 + 16 * i + lr) * SL + 16 * c + 4 * lq);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bv[j][e] = Bs[(16 * c + 4 * lq + e) * SL + n0 + 16 * j + lr];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], bv[j][e], acc[i][j], 0, 0, 0);
+  }
+}
+
+// One elimination step with the 64 x 64 pivot k of every n x n matrix, from S to D (a tile is read by many
+// workgroups, so not in place): one workgroup per 64 x 64 tile,
+//   D_kk = P, D_kj = P S_kj, D_ik = -S_ik P, D_ij = S_ij - S_ik (P S_kj),
+// P = S_kk^-1 from the step before.  The workgroup of tile (k + 1, k + 1), the first of its matrix, goes on to
+// invert it: P of the next step.  What bounds it: on small matrices that inverse (a serial chain; the other tiles
+// finish meanwhile), on large ones the sweep of S and D.  Every workgroup forms P S_kj for itself, twice the
+// products of the update alone, instead of a launch of its own for the pivot row and one for the column.
+// 2 x 2048^2, a block of 512: 8 steps of 17 us; the pivot kernel of one barrier per row (87 us) and the three products
+// that this replaces took 8 times 105 us.  A call of four iterations: 18.8 -> 7.0 ms.
+struct StepArgs {
+  const float* S; long long sstride; int sld;
+  float* D; long long dstride; int dld;
+  float* P;                                  // [batch][2][64][64]: slot k & 1 is read, the other written
+  int nt, k;
+  const Ctrl* ctrl;
+};
+__global__ __launch_bounds__(NT) void jordan_step_kernel(StepArgs g) {
+  const int b = blockIdx.y;
+  if (g.ctrl && g.ctrl[b].done) return;
+  __shared__ __align__(16) union {
+    float t[3][BS * SL];                     // P, S_kj (later P S_kj), S_ik (later the new tile)
+    Inv64Lds inv;                            // over the first two
+  } m;
+  static_assert(sizeof(Inv64Lds) <= 2 * BS * SL * sizeof(float), "the inverse leaves the third array alone");
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4, w = t >> 6;
+  const int next = g.k + 1 < g.nt ? (g.k + 1) * (g.nt + 1) : 0;
+  const int idx = blockIdx.x == 0 ? next : ((int)blockIdx.x == next ? 0 : (int)blockIdx.x);
+  const int ti = idx / g.nt, tj = idx - ti * g.nt;
+  const bool prow = ti == g.k, pcol = tj == g.k;
+  const float* S = g.S + (long long)b * g.sstride;
+  const float* P = g.P + ((long long)b * 2 + (g.k & 1)) * BS * BS;
+  float* D = g.D + (long long)b * g.dstride + (long long)(ti * BS) * g.dld + tj * BS;
+  const int r0 = t >> 4, c0 = (t & 15) * 4;   // copies: 16 rows of 16 bytes per thread and pass
+  f32x4 vp[4], vb[4], va[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + 16 * q;
+    vp[q] = *(const f32x4*)(P + r * BS + c0);
+    vb[q] = pcol ? vp[q] : *(const f32x4*)(S + (long long)(g.k * BS + r) * g.sld + tj * BS + c0);
+    va[q] = prow ? vp[q] : *(const f32x4*)(S + (long long)(ti * BS + r) * g.sld + g.k * BS + c0);
+  }
+  if (prow && pcol) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(f32x4*)(D + (long long)(r0 + 16 * q) * g.dld + c0) = vp[q];
+    return;
+  }
+  const int m0 = (w >> 1) * 32, n0 = (w & 1) * 32;
+  f32x4 old[2][2], acc[2][2];
+  if (!prow && !pcol) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          old[i][j][r] = S[(long long)(ti * BS + m0 + 16 * i + 4 * lq + r) * g.sld + tj * BS + n0 + 16 * j + lr];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) old[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    *(float4*)(blk + 4 * q) = make_float4((float)v[4 * q], (float)v[4 * q + 1], (float)v[4 * q + 2], (float)v[4 * q + 3]);
+  for (int q = 0; q < 4; ++q) {
+    const int o = (r0 + 16 * q) * SL + c0;
+    *(f32x4*)&m.t[0][o] = vp[q]; *(f32x4*)&m.t[1][o] = vb[q]; *(f32x4*)&m.t[2][o] = va[q];
+  }
+  __syncthreads();
+  if (!pcol) {                               // T = P S_kj
+    mma64(m.t[0], m.t[1], m0, n0, acc);
+    if (!prow) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) m.t[1][(m0 + 16 * i + 4 * lq + r) * SL + n0 + 16 * j + lr] = acc[i][j][r];
+      __syncthreads();
+    }
+  }
+  if (!prow) {                               // old - S_ik T, or -S_ik P
+    mma64(m.t[2], m.t[1], m0, n0, acc);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = old[i][j] - acc[i][j];
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) D[(long long)(m0 + 16 * i + 4 * lq + r) * g.dld + n0 + 16 * j + lr] = acc[i][j][r];
+  if (g.k + 1 >= g.nt || blockIdx.x != 0) return;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m.t[2][(m0 + 16 * i + 4 * lq + r) * SL + n0 + 16 * j + lr] = acc[i][j][r];
+  __syncthreads();
+  f64x4 v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[j][r] = (double)m.t[2][(16 * w + 4 * r + lq) * SL + 16 * j + lr];
+  invert64(v, m.inv);
+  float* out = g.P + ((long long)b * 2 + ((g.k + 1) & 1)) * BS * BS;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(16 * w + 4 * r + lq) * BS + 16 * j + lr] = (float)v[j][r];
 }
 
 // grid (groups, batch): partial sums of the three inner products over the true n x n part; the
@@ -220,70 +457,72 @@ __global__ __launch_bounds__(NT) void panel_copy_kernel(const float* __restrict_
   *(float4*)(dst + (long long)b * dstride + (long long)r * dld + c) = *(const float4*)(src + (long long)b * sstride + (long long)r * sld + c);
 }
 
-// In-place inverse of the n x n SPD matrices at A (leading dimension ld, batch stride `stride`)
-// by block Gauss-Jordan with blocks of 64; n a multiple of 64.
-int gauss_jordan_64(float* A, long long stride, int ld, int n, int batch, const Ctrl* ctrl, hipStream_t s) {
-  const int nb = n / BS;
-  for (int k = 0; k < nb; ++k) {
-    hipLaunchKernelGGL(diag_inv_kernel, dim3(batch), dim3(NT), 0, s, A, stride, ld, k, ctrl);
-    if (nb == 1) break;
-    float* Pk = A + (long long)k * BS * ld + k * BS;     // diagonal block (now P)
-    float* rowk = A + (long long)k * BS * ld;            // block row k
-    float* colk = A + k * BS;                            // block column k
-    GemmDesc g = {};
-    g.batch = batch; g.ctrl = ctrl; g.K = BS; g.epi = EPI_STORE; g.c_in = 1.0f;
-    g.strideA = g.strideB = g.strideC = g.strideCin = stride;
-    g.lda = g.ldb = g.ldc = g.ldcin = ld;
-    GemmDesc r = g;                                      // A_kj <- P A_kj, j != k
-    r.A = Pk; r.B = rowk; r.C = rowk; r.M = BS; r.N = n; r.skip_n0 = k * BS; r.skip_n1 = (k + 1) * BS;
-    int rc = launch_gemm_f32(r, BS, BS, s);
-    if (rc != PRISM_OK) return rc;
-    GemmDesc u = g;                                      // A_ij <- A_ij - A_ik A_kj, i, j != k
-    u.A = colk; u.B = rowk; u.C = A; u.Cin = A; u.M = n; u.N = n; u.epi = EPI_AXPY; u.acc_neg = 1;
-    u.skip_m0 = u.skip_n0 = k * BS; u.skip_m1 = u.skip_n1 = (k + 1) * BS;
-    rc = launch_gemm_f32(u, BS, BS, s);
-    if (rc != PRISM_OK) return rc;
-    GemmDesc c = g;                                      // A_ik <- -A_ik P, i != k
-    c.A = colk; c.B = Pk; c.C = colk; c.M = n; c.N = BS; c.acc_neg = 1; c.skip_m0 = k * BS; c.skip_m1 = (k + 1) * BS;
-    rc = launch_gemm_f32(c, BS, BS, s);
-    if (rc != PRISM_OK) return rc;
+// Inverse of n x n SPD matrices by block Gauss-Jordan with pivots of 64, n a multiple of 64: from src to out, through
+// tmp (each with its leading dimension and batch stride).  src may be out if n / 64 is even, tmp if it is odd.
+struct Mat { float* p; long long stride; int ld; };
+void gauss_jordan_64(Mat src, Mat out, Mat tmp, float* P, int n, int batch, const Ctrl* ctrl, hipStream_t s) {
+  const int nt = n / BS;
+  hipLaunchKernelGGL(first_pivot_kernel, dim3(batch), dim3(NT), 0, s, src.p, src.stride, src.ld, P, ctrl);
+  for (int k = 0; k < nt; ++k) {
+    const Mat dst = ((nt - 1 - k) & 1) ? tmp : out;
+    StepArgs a = {};
+    a.S = src.p; a.sstride = src.stride; a.sld = src.ld; a.D = dst.p; a.dstride = dst.stride; a.dld = dst.ld;
+    a.P = P; a.nt = nt; a.k = k; a.ctrl = ctrl;
+    hipLaunchKernelGGL(jordan_step_kernel, dim3(nt * nt, batch), dim3(NT), 0, s, a);
+    src = dst;
   }
-  return PRISM_OK;
 }
 
-// outer pivot block: 512 or 256 when it divides the order (0: blocks of 64 only)
-int outer_block(int np) { return (np > 512 && np % 512 == 0) ? 512 : ((np > 256 && np % 256 == 0) ? 256 : 0); }
+// Outer pivot block: 512 or 256 when it divides the order; 0: pivots of 64 all the way, as long as the tiles of a
+// sweep run in one round (three workgroups per CU), where a sweep costs little more than its pivot.  Measured,
+// direct / with outer blocks: 768 x 2 (288 tiles) 243 / 320 us, 1024 x 1 (256) 300 / 387, 512 x 8 (512) 226 / 219,
+// 1024 x 4 (1024) 604 / 454, 2048 x 2 (2048) 1074 / 979, 4096 x 1 (4096) 3204 / 2213.
+int outer_block(int np, int batch) {
+  if ((long long)(np / BS) * (np / BS) * batch <= 768) return 0;
+  return (np > 512 && np % 512 == 0) ? 512 : ((np > 256 && np % 256 == 0) ? 256 : 0);
+}
 
 }  // namespace
 
-long long spd_inverse_scratch_floats(int np, int batch) { return 2ll * outer_block(np) * np * batch; }
+// pivot inverses, the second buffer of the elimination and, with outer blocks, the new row and column panels
+long long spd_inverse_scratch_floats(int np, int batch) {
+  const long long OB = outer_block(np, batch), n = OB ? OB : np;
+  return (2ll * BS * BS + n * n + 2 * OB * np) * batch;
+}
 
-int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* panels, hipStream_t s) {
-  if (np % BS || batch <= 0) return PRISM_EINVAL;
+int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* scratch, hipStream_t s) {
+  if (np % BS || batch <= 0 || !scratch) return PRISM_EINVAL;
   const long long per_mat = (long long)np * np;
-  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((per_mat / 4 + NT - 1) / NT), batch), dim3(NT), 0, s, M, N, per_mat, ctrl);
-  if (spd_inverse_scratch_floats(np, batch) == 0) {
-    const int rc = gauss_jordan_64(N, per_mat, np, np, batch, ctrl, s);
-    if (rc != PRISM_OK) return rc;
+  const int OB = outer_block(np, batch);
+  float* P = scratch;
+  const long long tn = OB ? OB : np;
+  const Mat tmp = {P + 2ll * BS * BS * batch, tn * tn, (int)tn};
+  auto copy = [&](const float* from, float* to) {
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((per_mat / 4 + NT - 1) / NT), batch), dim3(NT), 0, s, from, to, per_mat, ctrl);
+  };
+  if (OB == 0) {
+    const Mat out = {N, per_mat, np};
+    Mat src = {const_cast<float*>(M), per_mat, np};
+    if (M == N && ((np / BS) & 1)) { copy(M, tmp.p); src = tmp; }
+    gauss_jordan_64(src, out, tmp, P, np, batch, ctrl, s);
     return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
   }
-  if (!panels) return PRISM_EINVAL;
-  const int OB = outer_block(np);
-  float* Trow = panels;                                   // [batch][OB][np]: P A_k,:
-  float* Ucol = panels + (long long)batch * OB * np;      // [batch][np][OB]: -A_:,k P
+  if (M != N) copy(M, N);
+  float* Trow = tmp.p + tn * tn * batch;                  // [batch][OB][np]: P A_k,:
+  float* Ucol = Trow + (long long)batch * OB * np;        // [batch][np][OB]: -A_:,k P
   const long long tstride = (long long)OB * np, ustride = (long long)np * OB;
   for (int k = 0; k < np / OB; ++k) {
     float* Pk = N + (long long)k * OB * np + k * OB;
     float* rowk = N + (long long)k * OB * np;
     float* colk = N + k * OB;
-    int rc = gauss_jordan_64(Pk, per_mat, np, OB, batch, ctrl, s);    // P = A_kk^{-1}, in place
-    if (rc != PRISM_OK) return rc;
+    const Mat piv = {Pk, per_mat, np};
+    gauss_jordan_64(piv, piv, tmp, P, OB, batch, ctrl, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
     GemmDesc g = {};
     g.batch = batch; g.ctrl = ctrl; g.K = OB; g.epi = EPI_STORE; g.c_in = 1.0f;
     GemmDesc r = g;                                      // T = P A_k,:
     r.A = Pk; r.strideA = per_mat; r.lda = np; r.B = rowk; r.strideB = per_mat; r.ldb = np;
     r.C = Trow; r.strideC = tstride; r.ldc = np; r.M = OB; r.N = np; r.skip_n0 = k * OB; r.skip_n1 = (k + 1) * OB;
-    rc = launch_gemm_f32(r, s);
+    int rc = launch_gemm_f32(r, s);
     if (rc != PRISM_OK) return rc;
     GemmDesc u = g;                                      // A_ij <- A_ij - A_ik T_j, i, j outside the pivot block
     u.A = colk; u.strideA = per_mat; u.lda = np; u.B = Trow; u.strideB = tstride; u.ldb = np;

@@ -35,9 +35,10 @@ def _spd(n, batch, cond, seed):
     return out
 
 
-@pytest.mark.parametrize("n,batch,cond", [(64, 3, 20.0), (128, 2, 50.0), (320, 2, 30.0), (256, 2, 30.0), (1024, 2, 30.0), (2048, 1, 20.0)])
+@pytest.mark.parametrize("n,batch,cond", [(64, 3, 20.0), (128, 2, 50.0), (320, 2, 30.0), (256, 2, 30.0), (192, 1, 30.0), (768, 6, 30.0), (1024, 2, 30.0), (2048, 1, 20.0)])
 def test_spd_inverse(prism, n, batch, cond):
-    """Block Gauss-Jordan against numpy's inverse: one to sixteen elimination blocks.  The forward
+    """Block Gauss-Jordan against numpy's inverse: odd and even numbers of pivots, pivots alone and within outer
+    blocks of 256 and 512.  The forward
     error of an fp32 inverse scales with cond * 2^-24."""
     A = _spd(n, batch, cond, 40 + n)
     out = prism.spd_inverse(torch.from_numpy(A).cuda()).cpu().numpy()
