@@ -392,7 +392,8 @@ def run_config(name, K, Wm, args, torch, prism, W):
                 fl += per_iter * nit
                 # HBM-bound kernels: the chain reads R once per product, the moments read the chain
                 # vectors once, pre-scaling reads the input once and writes the iterate once
-                chain_bytes += k * wl.nv * float(S) * S * wl.r_bytes
+                # (once in all up to order 1024, where one launch holds its rows for all products)
+                chain_bytes += k * (wl.nv if S > 1024 else 1) * float(S) * S * wl.r_bytes
                 moment_bytes += k * wl.nv * float(S) * wl.ld * 4
                 prep_bytes += 2.0 * m * n * h.dtype.itemsize
         fl *= nprof

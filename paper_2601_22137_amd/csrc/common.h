@@ -116,9 +116,10 @@ int launch_gemm_bf16(const Bf16Desc& g, int tile_m, int tile_n, hipStream_t s);
 int launch_gemm_bf16_multi(const Bf16Desc* groups, int ngroups, int tile_m, int tile_n, hipStream_t s);
 
 // ---- sketch.hip ----
-// v0[k - k_first][rows_total][ld] for k = k_first .. k_first + k_count - 1
+// v0[k - k_first][rows_total][ld] for k = k_first .. k_first + k_count - 1; blocked: each as
+// [rows_total / 16][ld / 16][lane][4], lane = 16 q + c holding rows 4 q .. 4 q + 3 of column c of the 16 x 16 block
 void launch_sketch(float* v0, int rows_total, int n, int ld, int p_s, uint64_t seed, int k_first, int k_count, int fn,
-                   hipStream_t s);
+                   hipStream_t s, bool blocked = false);
 void launch_gauss_parts(uint32_t first, uint32_t count, double* r, double* c, double* sn,
                         hipStream_t s);
 
@@ -132,8 +133,6 @@ int launch_chain(const float* R, long long strideR, int ldr, const float* Vin, l
 bool chain_takes_small_kernel(int n, int ld, int batch, bool rb);
 // Rb: bf16 copy of R [batch][n][ldr]; D: its exact fp32 diagonal, entry i of matrix b at D[b * strideD + i * ldd]
 // (ldd = ld of R + 1 reads it out of the full fp32 matrix, ldd = 1 out of a compact array)
-int launch_chain_tiny(const float* R, long long strideR, int ldr, const float* V0, long long strideV0, float* Vout,
-                      long long strideJ, long long strideB, int nv, int ld, int batch, const Ctrl* ctrl, hipStream_t s);
 bool chain_bf16_supported(int n, int ld, int batch, int ldr);
 // bf16 R, launches too large for the 16-row kernel: V is read as three bf16 planes (the exact 8 + 8 + 8 bit
 // split of its fp32 entries) laid out [matrix][k / 256][plane][column][unit'][8 k] (chain.hip); Vin (fp32) serves the
@@ -175,6 +174,23 @@ struct SolveArgs {
 void launch_moments(const SolveArgs& a, int batch, hipStream_t s);
 void launch_solve(const SolveArgs& a, int batch, hipStream_t s);
 
+// The sketch chain, the moments and the solve of one iteration in one launch (fit_kernel), for matrices of padded
+// order up to 2048 (fit_fused_supported).
+constexpr int FIT_SYNC_WORDS = 32;   // one counter per matrix, 128 bytes apart; zero between launches
+struct FitArgs {
+  SolveArgs sv;              // mode 0; ngroups = rows / 16 partial coefficient sums per matrix
+  const void* R;             // [batch][rows][ldr] fp32, or its bf16 copy (b16) with the exact diagonal in D
+  long long strideR; int ldr;
+  int b16;
+  const float* D; long long strideD; int ldd;
+  const float* V0;           // S_k^T in blocks (see launch_sketch)
+  float* V;                  // scratch: 2 x [batch][rows][ld]
+  unsigned* sync;            // [batch][FIT_SYNC_WORDS]
+  int nv;
+};
+bool fit_fused_supported(int rows, int ld, int batch);
+int launch_fit(const FitArgs& a, int batch, hipStream_t s);
+
 // fp32 polar factor of matrices whose padded iterate is 64 x 64: every iteration (residual, sketch
 // chain, fit, update) runs inside one workgroup per matrix, the iterate never leaves the LDS and one
 // launch replaces the five launches per iteration of the general path.
@@ -198,6 +214,7 @@ struct PrepArgs {
   const void* src;
   double* sumsq_part; int nsum;             // [batch][nsum]
   Ctrl* ctrl; prism_info* info;
+  unsigned* sync;                           // [batch][FIT_SYNC_WORDS]: zeroed
   // outputs (which are used depends on fn/dt)
   float* X32; float* Y32; double* M64; float* R32;   // fp32 paths (inverse: Y32 = A / ||A||_F)
   uint16_t* Xa_hi; uint16_t* Xa_lo;                  // bf16 polar: iterate [Lp][Sp], high and low halves

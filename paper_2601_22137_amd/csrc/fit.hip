@@ -12,6 +12,7 @@
 //      safeguarded by bisection, then m
 //      is compared at the end points and those roots; the smallest alpha wins ties.
 // Nothing returns to the host: alpha_k, the done flag and the report stay on the device.
+//   fit_kernel: chain, moments and solve in one launch, for matrices up to order 1024 (2048).
 //   small_polar_kernel: for fp32 polar factors whose padded iterate is 64 x 64, the whole method
 //   (residual, chain, fit, update, for all iterations) in one workgroup per matrix.
 #include "common.h"
@@ -20,6 +21,8 @@ namespace prism {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;
 constexpr int MAXC = 2 * PRISM_MAX_ROOT + 1;  // coefficients of m
@@ -231,14 +234,19 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
     __syncthreads();
     if (t < MAXC) s_c[t] = c_local[t];
   } else {
-    if (a.ngroups == 1 && a.fn != PRISM_FN_SQRT_NEWTON) {   // small matrices: the moments are accumulated right here
-      accumulate_for(a, b, 0, 1, a.cpart + (long long)b * MAXC);
-      __threadfence_block();
-      __syncthreads();
-    }
-    if (t < MAXC) {   // coefficient s = sum of the group partials, in group order
+    // coefficient s = sum of the group partials: thread (share, s) adds up every SHARES-th group, then the shares
+    // in order
+    constexpr int SHARES = NT / MAXC;
+    __shared__ double s_share[SHARES][MAXC];
+    if (t < SHARES * MAXC) {
       double v = 0.0;
-      for (int gidx = 0; gidx < a.ngroups; ++gidx) v += a.cpart[((long long)b * a.ngroups + gidx) * MAXC + t];
+      for (int gidx = t / MAXC; gidx < a.ngroups; gidx += SHARES) v += a.cpart[((long long)b * a.ngroups + gidx) * MAXC + t % MAXC];
+      s_share[t / MAXC][t % MAXC] = v;
+    }
+    __syncthreads();
+    if (t < MAXC) {
+      double v = 0.0;
+      for (int q = 0; q < SHARES && q < a.ngroups; ++q) v += s_share[q][t];
       s_c[t] = v;
     }
   }
@@ -549,7 +557,308 @@ __global__ __launch_bounds__(NT) void small_polar_kernel(SmallPolarArgs a) {
   }
 }
 
+// ---- chain, moments and solve of one iteration in one launch ----
+// The chain V_j = R V_{j-1} of a matrix, up to order 2048, by a cluster of G = n / (16 RB) workgroups: each owns 16 RB
+// rows of R, fetches them once, keeps them in registers for all products (its waves take the chunks of 64 k by
+// turns) and hands its rows of V_j to the others through memory; then every workgroup forms the moments of its rows
+// and the one that arrives last solves for alpha.
+// What bounds it: latency, 4 to 5 us per product (hand-over 2.6 us, products, partial sums).  Order 320: 26 us, 768: 31 us,
+// 16 matrices of order 1024 (fp32): 76 us in one launch, where the chain products, the moments and the solve took seven
+// of 6 to 25 us each, and 2.6 us instead of 18 us for every iteration enqueued past convergence.
+// Calls: fp32 polar 6 x 500 x 299 1.29 -> 0.77 ms, mixed small inverse roots 9.3 -> 5.4, sign 4 x 1000^2 3.02 -> 2.57, one
+// 768 x 3072 bf16 gradient 0.56 -> 0.50.
+// Hand-over: V and the coefficient partials are written and read past the caches that are not coherent between XCDs
+// (agent scope), and a wave has seen its stores complete (vmcnt) before its workgroup
+// counts itself in.  Agent-scope fences instead write back and invalidate whole L2s: 8 to 25 us per hand-over
+// with 256 workgroups.
+// Every wait ends: workgroups are dispatched in order, so in every hardware queue at most one cluster is resident in
+// part (G <= 64 workgroups, at most 8 per XCD) and all others run to their end and make room for it.  The
+// wait is bounded all the same; running out marks the matrix as diverged.
+//   V_0 .. V_{nv-1} in memory, V_1 on in two slots by turns: [n / 16][LD / 16][lane][4], lane (lr, lq) with rows 4 lq + r,
+//   r = 0..3, of column lr of the 16 x 16 block: what a lane holds of a product's result is its operand of the next, and a
+//   wave moves 1 KiB without gaps.
+// The order of all sums is a function of n and the sketch width alone (the moments are kept per 16 rows), so the bits
+// do not depend on RB.
+template <bool B16> struct RRow;   // four consecutive k of one row of R
+template <> struct RRow<false> {
+  typedef float elem;
+  f32x4 v;
+  __device__ void load(const float* p) { v = *(const f32x4*)p; }
+  __device__ float get(int e) const { return v[e]; }
+};
+template <> struct RRow<true> {
+  typedef unsigned short elem;
+  u32x2 v;
+  __device__ void load(const unsigned short* p) { v = *(const u32x2*)p; }
+  __device__ float get(int e) const { return __uint_as_float((e & 1) ? (v[e >> 1] & 0xFFFF0000u) : (v[e >> 1] << 16)); }
+};
+typedef unsigned long long u64;
+// 16 bytes past the caches that are not coherent between XCDs (sc1, as agent-scope atomics have it; those exist up
+// to 8 bytes only); `bytes` bounds the array
+__device__ inline f32x4 load_shared16(const float* base, int bytes, int offset) {
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000);
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, offset, 0, 16));
+}
+__device__ inline void store_shared16(float* base, int bytes, int offset, f32x4 v) {
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, offset, 0, 16);
+}
+
+// coefficient partials of 16 rows (own[j * stride + element]), by one wave
+template <class BL>
+__device__ void block_moments(const float* own, int stride, int count, double* out) {
+  constexpr int NV = BL::NV, NW = BL::NW, NC = 2 * NW - 1;
+  const int lane = threadIdx.x & 63;
+  double c[NC];
+#pragma unroll
+  for (int s = 0; s < NC; ++s) c[s] = 0.0;
+  for (int idx = lane; idx < count; idx += 64) {
+    double v[NV], w[NW];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = (double)own[j * stride + idx];
+    BL::make(v, w);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+      for (int l = 0; l < NW; ++l) c[i + l] += w[i] * w[l];
+  }
+#pragma unroll
+  for (int s = 0; s < NC; ++s) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c[s] += __shfl_down(c[s], off, 64);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int s = 0; s < MAXC; ++s) {
+      const double v = s < NC ? c[s < NC ? s : 0] : 0.0;
+      __hip_atomic_store((u64*)out + s, __builtin_bit_cast(u64, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+__device__ __noinline__ void block_moments_for(int fn, int p, int d, const float* own, int stride, int count, double* out) {
+  if (fn == PRISM_FN_INV_ROOT) {
+    switch (p) {
+      case 1: block_moments<BlocksInv<1>>(own, stride, count, out); break;
+      case 2: block_moments<BlocksInv<2>>(own, stride, count, out); break;
+      case 3: block_moments<BlocksInv<3>>(own, stride, count, out); break;
+      case 4: block_moments<BlocksInv<4>>(own, stride, count, out); break;
+      case 5: block_moments<BlocksInv<5>>(own, stride, count, out); break;
+      case 6: block_moments<BlocksInv<6>>(own, stride, count, out); break;
+      case 7: block_moments<BlocksInv<7>>(own, stride, count, out); break;
+      default: block_moments<BlocksInv<8>>(own, stride, count, out); break;
+    }
+  } else if (fn == PRISM_FN_INVERSE) {
+    block_moments<BlocksCheb>(own, stride, count, out);
+  } else if (d == 1) {
+    block_moments<Blocks<1>>(own, stride, count, out);
+  } else {
+    block_moments<Blocks<2>>(own, stride, count, out);
+  }
+}
+
+constexpr int FIT_SPIN_LIMIT = 1 << 23;   // polls of a microsecond or so
+
+// KW waves, each with every KW-th chunk of 64 k, NCH chunks at most (n <= 64 KW NCH)
+template <bool B16, int LD, int RB, int NCH, int KW>
+__global__ __launch_bounds__(64 * KW, !B16 && RB * NCH * LD >= 256 ? 1 : 2) void fit_kernel(FitArgs a) {
+  constexpr int NBLK = LD / 16, NQ = RB * NBLK, ROWS = 16 * RB;
+  constexpr int NACC = NBLK == 1 ? 4 : (NBLK == 2 && KW == 4 ? 2 : 1);   // independent accumulators (the same for every RB)
+  constexpr int CG = NBLK == 1 && RB == 1 ? 2 : 1;            // chunks whose operands are requested together
+  extern __shared__ __align__(16) float fit_lds[];
+  f32x4 (*red)[NQ][64] = (f32x4 (*)[NQ][64])fit_lds;          // [KW] partial sums
+  float* own = fit_lds + KW * NQ * 256;                       // [nv][ROWS][LD]: this workgroup's rows of V_1 .. V_nv
+  __shared__ float dfix[ROWS];
+  __shared__ int s_go;
+  const SolveArgs& sv = a.sv;
+  const int b = blockIdx.y, G = gridDim.x, n = sv.rows;
+  if (sv.ctrl[b].done) return;
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int row0 = blockIdx.x * ROWS, nchunks = n / 64;
+  typedef typename RRow<B16>::elem elem;
+  const elem* R = (const elem*)a.R + (long long)b * a.strideR + (long long)row0 * a.ldr;
+  RRow<B16> ra[RB][NCH][4];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i)
+    if (w + KW * i < nchunks) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) ra[rb][i][s].load(R + (16 * rb + lr) * a.ldr + (w + KW * i) * 64 + 16 * s + 4 * lq);
+    }
+  if (B16 && t < ROWS) {   // exact diagonal minus the rounded one
+    const unsigned short h = ((const unsigned short*)R)[t * a.ldr + row0 + t];
+    dfix[t] = a.D[(long long)b * a.strideD + (long long)(row0 + t) * a.ldd] - __uint_as_float((unsigned)h << 16);
+  }
+  if (B16) __syncthreads();
+  unsigned* sync = a.sync + (long long)b * FIT_SYNC_WORDS;
+#pragma unroll 1
+  for (int j = 1; j <= a.nv; ++j) {
+    const float* Vin = j == 1 ? a.V0 : a.V + ((long long)(j & 1) * gridDim.y + b) * n * LD;        // V_{j-1}, [LD][n]
+    float* Vout = a.V + ((long long)((j + 1) & 1) * gridDim.y + b) * n * LD;
+    const int vbytes = n * LD * 4;
+    if constexpr (B16) {   // widened at each use: the compiler would keep the fp32 values of all products instead
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < NCH; ++i)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(ra[rb][i][s].v));
+    }
+    f32x4 acc[RB][NBLK][NACC];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+        for (int u = 0; u < NACC; ++u) acc[rb][q][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 vf[2][CG][NBLK][4];
+    auto request = [&](int i0) {
+#pragma unroll
+      for (int i = 0; i < CG; ++i)
+        if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
+#pragma unroll
+          for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) vf[(i0 / CG) & 1][i][q][s] = load_shared16(Vin, vbytes, (((w + KW * (i0 + i)) * 4 + s) * NBLK + q) * 1024 + lane * 16);
+        }
+    };
+    request(0);
+#pragma unroll
+    for (int i0 = 0; i0 < NCH; i0 += CG) {
+      if (i0 + CG < NCH) request(i0 + CG);
+#pragma unroll
+      for (int i = 0; i < CG; ++i)
+        if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+                  acc[rb][q][(4 * s + e) % NACC] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                      ra[rb][i0 + i < NCH ? i0 + i : 0][s].get(e), vf[(i0 / CG) & 1][i][q][s][e], acc[rb][q][(4 * s + e) % NACC], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int q = 0; q < NBLK; ++q) {
+#pragma unroll
+        for (int h = NACC / 2; h > 0; h >>= 1)
+#pragma unroll
+          for (int u = 0; u < h; ++u) acc[rb][q][u] += acc[rb][q][u + h];
+        red[w][rb * NBLK + q][lane] = acc[rb][q][0];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < (NQ + KW - 1) / KW; ++i) {
+      const int x = w + KW * i;
+      if (x < NQ) {
+        const int row = 16 * (x / NBLK) + 4 * lq, col = 16 * (x % NBLK) + lr;
+        f32x4 v = (red[0][x][lane] + red[1][x][lane]) + (red[2][x][lane] + red[3][x][lane]);
+        if constexpr (KW == 8) v += (red[4][x][lane] + red[5][x][lane]) + (red[6][x][lane] + red[7][x][lane]);
+        if (B16) {
+          f32x4 prev;
+          if (j == 1) prev = *(const f32x4*)(a.V0 + (row0 / 16 * NBLK + x) * 256 + lane * 4);
+          else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) prev[r] = own[((j - 2) * ROWS + row + r) * LD + col];
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] += dfix[row + r] * prev[r];
+        }
+        if (j < a.nv) store_shared16(Vout, vbytes, (row0 / 16 * NBLK + x) * 1024 + lane * 16, v);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) own[((j - 1) * ROWS + row + r) * LD + col] = v[r];
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have reached memory
+    __syncthreads();
+    if (j < a.nv && G > 1) {
+      if (t == 0) {
+        __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int go = 0;
+        for (int i = 0; i < FIT_SPIN_LIMIT && !go; ++i) {
+          go = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (unsigned)(G * j);
+          if (!go) __builtin_amdgcn_s_sleep(1);
+        }
+        s_go = go;
+        if (!go) {
+          sv.ctrl[b].status = PRISM_INFO_DIVERGED; sv.ctrl[b].iters = sv.k; sv.ctrl[b].done = 1;
+          sv.info[b].status = PRISM_INFO_DIVERGED; sv.info[b].iters = sv.k;
+        }
+      }
+      __syncthreads();
+      if (!s_go) return;
+    }
+  }
+  for (int rb = w; rb < RB; rb += KW)
+    block_moments_for(sv.fn, sv.p, sv.d, own + rb * 16 * LD, ROWS * LD, 16 * LD,
+                      sv.cpart + ((long long)b * sv.ngroups + row0 / 16 + rb) * MAXC);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0) {
+    const unsigned before = G > 1 ? __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    s_go = G == 1 || before == (unsigned)(G * a.nv - 1);
+    if (s_go && G > 1) __hip_atomic_store(sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+  }
+  __syncthreads();
+  if (!s_go) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the partials of the others
+  solve_body(sv, b);
+}
+
+template <bool B16, int LD, int RB, int NCH, int KW>
+int launch_fit_t(const FitArgs& a, int batch, hipStream_t s) {
+  const int rows = 16 * RB;
+  const size_t lds = ((size_t)RB * (LD / 16) * KW * 256 + (size_t)a.nv * rows * LD) * sizeof(float);
+  const auto kern = fit_kernel<B16, LD, RB, NCH, KW>;
+  if (lds > 48 * 1024) {
+    const int rc = allow_dynamic_lds((const void*)kern, (int)lds);
+    if (rc != PRISM_OK) return rc;
+  }
+  hipLaunchKernelGGL(kern, dim3(a.sv.rows / rows, batch), dim3(64 * KW), lds, s, a);
+  return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+}
+// Rows per workgroup: 16 while those are at most two workgroups per CU, then 32 (two row blocks share the operands of
+// V): 16 x 768 (bf16 R, 768 blocks) 72 / 55 us with 16 / 32 rows, 16 x 1024 (1024 blocks) 137 / 76, 4 x 1024 (256) 43 / 52,
+// 1 x 768 (48) 31 / 38.  Order 64: one workgroup has all rows and hands nothing over.
+template <bool B16, int LD>
+int launch_fit_ld(const FitArgs& a, int batch, hipStream_t s) {
+  const int n = a.sv.rows;
+  const long long blocks = (long long)(n / 16) * batch;
+  if constexpr (LD == 64) {
+    return n <= 512 ? launch_fit_t<B16, LD, 1, 2, 4>(a, batch, s) : launch_fit_t<B16, LD, 1, 4, 4>(a, batch, s);
+  } else {
+    if (n > 1024) return launch_fit_t<B16, LD, 2, 4, 8>(a, batch, s);
+    if (n == 64) return launch_fit_t<B16, LD, 4, 1, 4>(a, batch, s);
+    if (blocks >= 512) return n <= 512 ? launch_fit_t<B16, LD, 2, 2, 4>(a, batch, s) : launch_fit_t<B16, LD, 2, 4, 4>(a, batch, s);
+    return n <= 512 ? launch_fit_t<B16, LD, 1, 2, 4>(a, batch, s) : launch_fit_t<B16, LD, 1, 4, 4>(a, batch, s);
+  }
+}
+
 }  // namespace
+
+// Above order 1024 only while the workgroups (32 rows) are at most 1.5 per CU: with more, the streaming chain kernels, which
+// also leave more of the chip to the products of other parts of a batch, are ahead (16 x 1536 per part of a grouped
+// call: 17.8 against 19.2 ms per step); 8 x 2048 in two halves, fused / not: bf16 polar 4.7 / 5.2 ms, sign 29.7 / 30.6.
+bool fit_fused_supported(int rows, int ld, int batch) {
+  if (rows % 64) return false;
+  return rows <= 1024 || (rows <= 2048 && ld <= 32 && (long long)(rows / 32) * batch <= 384);
+}
+
+int launch_fit(const FitArgs& a, int batch, hipStream_t s) {
+  if (a.sv.rows % 64 || a.sv.rows > (a.sv.ld <= 32 ? 2048 : 1024) || a.sv.ngroups != a.sv.rows / 16 || a.nv < 2 || a.nv > PRISM_MAX_ROOT + 1 ||
+      batch <= 0 || a.ldr % 4 || (a.b16 && a.sv.ld > 32))
+    return PRISM_EINVAL;
+  if (a.b16) return a.sv.ld == 16 ? launch_fit_ld<true, 16>(a, batch, s) : launch_fit_ld<true, 32>(a, batch, s);
+  if (a.sv.ld == 16) return launch_fit_ld<false, 16>(a, batch, s);
+  if (a.sv.ld == 32) return launch_fit_ld<false, 32>(a, batch, s);
+  return launch_fit_ld<false, 64>(a, batch, s);
+}
 
 int launch_small_polar(const SmallPolarArgs& a, int batch, hipStream_t s) {
   if (a.sv.rows != SN || (a.sv.ld != 16 && a.sv.ld != 32 && a.sv.ld != 64) || a.sv.ngroups != 1 || a.sv.nparts != 1 ||

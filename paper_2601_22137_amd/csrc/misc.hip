@@ -107,6 +107,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
     c.alpha = 0.0f; c.res0 = 0.0f; c.res1 = 0.0f; c.res2 = 0.0f;
     c.norm = norm; c.scale = scale;
     a.ctrl[b] = c;
+    a.sync[(long long)b * FIT_SYNC_WORDS] = 0u;
     a.info[b].iters = 0;
     a.info[b].status = c.status;
   }
@@ -194,6 +195,7 @@ __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
     c.alpha = 0.0f; c.res0 = 0.0f; c.res1 = 0.0f; c.res2 = 0.0f;
     c.norm = norm; c.scale = scale;
     a.ctrl[b] = c;
+    a.sync[(long long)b * FIT_SYNC_WORDS] = 0u;
     a.info[b].iters = 0;
     a.info[b].status = c.status;
   }

@@ -82,7 +82,7 @@ struct Plan {
   int nsum;        // partial sums of the Frobenius norm per matrix
   int max_parts;   // residual partials per matrix
   // byte offsets into the workspace
-  size_t o_ctrl, o_info, o_sumsq, o_rho, o_v0, o_v, o_cpart;
+  size_t o_ctrl, o_info, o_sync, o_sumsq, o_rho, o_v0, o_v, o_cpart;
   size_t o_vp0, o_vp;                             // bf16 polar: bf16 planes of the sketches and of V_1 .. V_{nv-1}
   bool has_planes;
   int ngroups;     // workgroups per matrix of the moments kernel
@@ -141,19 +141,20 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   const size_t SS = (size_t)P.Sp * P.Sp, LS = (size_t)P.Lp * P.Sp, B = (size_t)batch;
   P.o_ctrl = take(B * sizeof(Ctrl));
   P.o_info = take(B * sizeof(prism_info));
+  P.o_sync = take(B * FIT_SYNC_WORDS * sizeof(unsigned));
   P.o_sumsq = take(B * P.nsum * sizeof(double));
   P.o_rho = take(B * P.max_parts * sizeof(float));
   P.o_v0 = take((size_t)PRISM_MAX_ITERS * P.Sp * P.ld * sizeof(float));   // S_k^T for every k, generated once per call
   P.o_v = take((size_t)P.nv * B * P.Sp * P.ld * sizeof(float));
   {
     const long long el = (long long)P.Sp * P.ld;
-    P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);   // 1: done inside the solve kernel
+    P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);
     if (fn == PRISM_FN_SQRT_NEWTON) {   // the moments run over the n x n matrices themselves
       const long long mm = (long long)P.Sp * P.Sp / 65536;
       P.ngroups = mm < 1 ? 1 : (mm > 64 ? 64 : (int)mm);
     }
   }
-  P.o_cpart = take(B * P.ngroups * 17 * sizeof(double));
+  P.o_cpart = take(B * (P.ngroups > P.Sp / 16 ? P.ngroups : P.Sp / 16) * 17 * sizeof(double));
   if (dt == PRISM_BF16 && P.ld <= 32 && P.p_s > 0) {   // operands of the plane chain kernel: 3 x 2 bytes per entry
     P.o_vp0 = take((size_t)PRISM_MAX_ITERS * P.Sp * P.ld * 6);
     P.o_vp = take((size_t)(P.nv - 1) * B * P.Sp * P.ld * 6);
@@ -292,11 +293,6 @@ struct Run {
             int ldd = 0) {
     const int Sp = P.Sp, ld = P.ld;
     const long long vs = (long long)P.batch * Sp * ld;
-    if (Sp == 64 && !Rb) {   // whole chain in one launch
-      ProfScope ps(PK_CHAIN, s);
-      return launch_chain_tiny(R, (long long)Sp * Sp, Sp, v0 + (long long)(k - first_fit) * Sp * ld, 0, v, vs,
-                               (long long)Sp * ld, P.nv, ld, P.batch, ctrl, s);
-    }
     for (int j = 1; j <= P.nv; ++j) {
       const float* vin = (j == 1) ? v0 + (long long)(k - first_fit) * Sp * ld : v + (j - 2) * vs;
       const long long sin = (j == 1) ? 0 : (long long)Sp * ld;
@@ -317,7 +313,35 @@ struct Run {
     return PRISM_OK;
   }
 
-  int solve(int k, int nparts, int phase = 0) {
+  // The coefficient of iteration k: chain, moments, solve.  One launch where fit_kernel takes the matrices (a rule on
+  // order and batch of a call on one group, so that grouped and single calls agree); without a fit the solve only.
+  int fit(int k, int nparts, const float* R, const uint16_t* Rb = nullptr, const float* D = nullptr, long long strideD = 0,
+          int ldd = 0) {
+    if (!fit_needed(k)) return solve(k, nparts);
+    if (!fused()) {
+      CHECK_LAUNCH(chain(R, k, Rb, D, strideD, ldd));
+      return solve(k, nparts);
+    }
+    FitArgs f = {};
+    f.sv = solve_args(k, nparts, 0);
+    f.sv.ngroups = P.Sp / 16;
+    f.b16 = Rb != nullptr; f.R = Rb ? (const void*)Rb : (const void*)R; f.strideR = (long long)P.Sp * P.Sp; f.ldr = P.Sp;
+    f.D = D; f.strideD = strideD; f.ldd = ldd;
+    f.V0 = v0 + (long long)(k - first_fit) * P.Sp * P.ld; f.V = v; f.nv = P.nv;
+    f.sync = at<unsigned>(P.o_sync);
+    ProfScope ps(PK_CHAIN, s);
+    return launch_fit(f, P.batch, s);
+  }
+  bool fused() const {
+    return fit_fused_supported(P.Sp, P.ld, chain_sel_batch ? chain_sel_batch : P.batch) && !small_polar();
+  }
+  // fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
+  bool small_polar() const {
+    static const int off = ab_switch("PRISM_NO_SMALL_KERNEL");
+    return !off && P.fn == PRISM_FN_POLAR && P.dt == PRISM_F32 && P.Sp == 64 && P.Lp == 64 && P.ngroups == 1;
+  }
+
+  SolveArgs solve_args(int k, int nparts, int phase) const {
     SolveArgs a = {};
     a.phase = phase;
     a.fn = P.fn; a.k = k; a.d = P.d; a.p = P.p; a.n = P.S; a.rows = P.Sp; a.ld = P.ld;
@@ -328,6 +352,10 @@ struct Run {
     a.sched_alpha = k < sched_len ? sched[k] : 0.0f;
     a.last = (k == max_iters);
     a.cpart = at<double>(P.o_cpart); a.ngroups = P.ngroups;
+    return a;
+  }
+  int solve(int k, int nparts, int phase = 0) {
+    const SolveArgs a = solve_args(k, nparts, phase);
     if (a.mode == 0 && !a.last && a.ngroups > 1 && P.fn != PRISM_FN_SQRT_NEWTON) {
       ProfScope ps(PK_MOMENTS, s);
       launch_moments(a, P.batch, s);
@@ -342,7 +370,7 @@ struct Run {
   // bf16 chain products too large for the 16-row kernel read V as bf16 planes
   bool planes() const {
     const int sel = chain_sel_batch ? chain_sel_batch : P.batch;
-    return vp0 && chain_bf16_supported(P.Sp, P.ld, sel, P.Sp) && !chain_takes_small_kernel(P.Sp, P.ld, sel, true);
+    return vp0 && !fused() && chain_bf16_supported(P.Sp, P.ld, sel, P.Sp) && !chain_takes_small_kernel(P.Sp, P.ld, sel, true);
   }
 };
 
@@ -376,8 +404,7 @@ int run_polar_f32(Run& r) {
   const bool polar = P.fn != PRISM_FN_SIGN;
   const int sym = polar ? f32_sym() : 0;
   const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
-  static const int no_small = ab_switch("PRISM_NO_SMALL_KERNEL");
-  if (polar && Sp == 64 && Lp == 64 && P.ngroups == 1 && !no_small) {
+  if (r.small_polar()) {
     // the whole iteration in one workgroup per matrix, one launch for all iterations: with five
     // launches per iteration a call on such matrices is nothing but launch latency
     SmallPolarArgs sa = {};
@@ -420,8 +447,7 @@ int run_polar_f32(Run& r) {
       ProfScope ps(PK_F32_RESID, r.s);
       CHECK_LAUNCH(launch_gemm_f32(g, r.s));
     }
-    if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
-    CHECK_LAUNCH(r.solve(k, (polar && P.ksplit) ? gram_reduce_parts(Sp) : nparts));
+    CHECK_LAUNCH(r.fit(k, (polar && P.ksplit) ? gram_reduce_parts(Sp) : nparts, R));
     if (k == r.max_iters) break;
     const float* Bop = R;
     if (P.d == 2) {
@@ -572,12 +598,10 @@ int run_polar_bf16(Run& r) {
       ProfScope ps(PK_BF16_GRAM, r.s);
       CHECK_LAUNCH(launch_gemm_bf16_multi(gd, ng, Tg.m, Tg.n, r.s));
     }
-    if (r.fit_needed(k)) {
-      if (lean) CHECK_LAUNCH(r.chain(R, k, Rb, Dg, Sp, 1));
-      else if (chain_b) CHECK_LAUNCH(r.chain(R, k, Rb, R, SS, Sp + 1));
-      else CHECK_LAUNCH(r.chain(R, k));
-    }
-    CHECK_LAUNCH(r.solve(k, P.ksplit ? gram_reduce_parts(Sp) : nparts));
+    const int np = P.ksplit ? gram_reduce_parts(Sp) : nparts;
+    if (lean) CHECK_LAUNCH(r.fit(k, np, R, Rb, Dg, Sp, 1));
+    else if (chain_b) CHECK_LAUNCH(r.fit(k, np, R, Rb, R, SS, Sp + 1));
+    else CHECK_LAUNCH(r.fit(k, np, R));
     if (k == r.max_iters) break;
     const uint16_t* Bop = Rb;
     if (P.d == 2) {   // one launch over the matrices of all groups: R has the same order everywhere
@@ -630,8 +654,7 @@ int run_sqrt_f32(Run& r) {
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
     { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
-    if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
-    CHECK_LAUNCH(r.solve(k, nparts));
+    CHECK_LAUNCH(r.fit(k, nparts, R));
     if (k == r.max_iters) break;
     const float* Pm = R;
     if (P.d == 2) {
@@ -672,8 +695,7 @@ int run_inverse_f32(Run& r) {
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
     { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
-    if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
-    CHECK_LAUNCH(r.solve(k, nparts));
+    CHECK_LAUNCH(r.fit(k, nparts, R));
     if (k == r.max_iters) break;
     GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
     q.sym = sym;
@@ -740,8 +762,7 @@ int run_inv_root_f32(Run& r) {
   int cur = 0, mc = 0;   // current X and M buffers
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
-    if (r.fit_needed(k)) CHECK_LAUNCH(r.chain(R, k));
-    CHECK_LAUNCH(r.solve(k, k == 0 ? nparts0 : nparts));
+    CHECK_LAUNCH(r.fit(k, k == 0 ? nparts0 : nparts, R));
     if (k == r.max_iters) break;
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
@@ -876,6 +897,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   pa.fn = fn; pa.dt = dt; pa.batch = batch; pa.m = m; pa.n = n; pa.S = P.S; pa.L = P.L; pa.Sp = P.Sp; pa.Lp = P.Lp;
   pa.transpose = P.transpose; pa.root_p = root_p; pa.src = a;
   pa.sumsq_part = r.at<double>(P.o_sumsq); pa.nsum = P.nsum; pa.ctrl = r.ctrl; pa.info = r.info;
+  pa.sync = r.at<unsigned>(P.o_sync);
   pa.rho_part = r.rho; pa.tile = P.tile;
   FinalArgs fa = {};
   fa.fn = fn; fa.dt = dt; fa.batch = batch; fa.m = m; fa.n = n; fa.S = P.S; fa.L = P.L; fa.Sp = P.Sp; fa.Lp = P.Lp;
@@ -903,7 +925,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); }
   if (P.p_s > 0 && max_iters > r.first_fit && fn != PRISM_FN_SQRT_NEWTON) {
     ProfScope ps(PK_SKETCH, r.s);
-    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s);
+    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s, r.fused());
     if (r.planes()) CHECK_LAUNCH(launch_split_planes(r.v0, r.vp0, P.Sp, P.ld, max_iters - r.first_fit, r.s));
   }
   rc = check_hip();
@@ -948,6 +970,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     const int bg = groups[g].batch * batch_scale, b0 = groups[0].batch * batch_scale;
     if (chain_takes_small_kernel(Pg[g].Sp, Pg[g].ld, bg, true) != chain_takes_small_kernel(Pg[0].Sp, Pg[0].ld, b0, true) ||
         chain_takes_small_kernel(Pg[g].Sp, Pg[g].ld, bg, false) != chain_takes_small_kernel(Pg[0].Sp, Pg[0].ld, b0, false) ||
+        fit_fused_supported(Pg[g].Sp, Pg[g].ld, bg) != fit_fused_supported(Pg[0].Sp, Pg[0].ld, b0) ||
         chain_bf16_supported(Pg[g].Sp, Pg[g].ld, bg, Pg[g].Sp) != chain_bf16_supported(Pg[0].Sp, Pg[0].ld, b0, Pg[0].Sp))
       return PRISM_EUNSUPPORTED;
     btot += groups[g].batch;
@@ -1002,6 +1025,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     pa.S = P.S; pa.L = x.L; pa.Sp = P.Sp; pa.Lp = x.Lp; pa.transpose = x.transpose; pa.root_p = 0; pa.src = x.x;
     pa.sumsq_part = r.at<double>(P.o_sumsq) + (long long)x.boff * P.nsum; pa.nsum = P.nsum;
     pa.ctrl = r.ctrl + x.boff; pa.info = r.info + x.boff; pa.rho_part = r.rho; pa.tile = P.tile;
+    pa.sync = r.at<unsigned>(P.o_sync) + (long long)x.boff * FIT_SYNC_WORDS;
     fa.fn = PRISM_FN_POLAR; fa.dt = PRISM_BF16; fa.batch = x.batch; fa.m = x.m; fa.n = x.n;
     fa.S = P.S; fa.L = x.L; fa.Sp = P.Sp; fa.Lp = x.Lp; fa.transpose = x.transpose; fa.dst = x.x; fa.dst2 = nullptr;
     fa.ctrl = r.ctrl + x.boff;
@@ -1018,7 +1042,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   }
   if (P.p_s > 0 && max_iters > r.first_fit) {
     ProfScope ps(PK_SKETCH, r.s);
-    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s);
+    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s, r.fused());
     if (r.planes()) CHECK_LAUNCH(launch_split_planes(r.v0, r.vp0, P.Sp, P.ld, max_iters - r.first_fit, r.s));
   }
   rc = check_hip();

@@ -101,9 +101,9 @@ __device__ inline void box_muller(unsigned int xa, unsigned int xb, float& z0, f
   z1 = (float)(r * s);
 }
 
-// v0[rows_total][ld]: row j < n holds column j of S_k (entries r < p_s), everything else zero.
+// v0[rows_total][ld]: row j < n holds column j of S_k (entries r < p_s), everything else zero; blocked: see common.h.
 __global__ void sketch_kernel(float* v0, int rows_total, int n, int ld, int p_s, unsigned int k0,
-                              unsigned int k1, unsigned int iter, unsigned int tag) {
+                              unsigned int k1, unsigned int iter, unsigned int tag, int blocked) {
   const int groups = (ld + 3) / 4;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long long)rows_total * groups) return;
@@ -121,7 +121,9 @@ __global__ void sketch_kernel(float* v0, int rows_total, int n, int ld, int p_s,
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int r = 4 * q + e;
-    if (r < ld) v0[(long long)j * ld + r] = (r < p_s) ? z[e] : 0.0f;
+    const long long o = blocked ? ((long long)(j / 16) * (ld / 16) + r / 16) * 256 + ((j % 16) / 4 * 16 + r % 16) * 4 + j % 4
+                                : (long long)j * ld + r;
+    if (r < ld) v0[o] = (r < p_s) ? z[e] : 0.0f;
   }
 }
 
@@ -139,12 +141,12 @@ __global__ void gauss_parts_kernel(unsigned int first, unsigned int count, doubl
 }  // namespace
 
 void launch_sketch(float* v0, int rows_total, int n, int ld, int p_s, uint64_t seed, int k_first, int k_count, int fn,
-                   hipStream_t s) {
+                   hipStream_t s, bool blocked) {
   const long long total = (long long)rows_total * ((ld + 3) / 4);
   const int nb = (int)((total + 255) / 256);
   hipLaunchKernelGGL(sketch_kernel, dim3(nb, k_count), dim3(256), 0, s, v0, rows_total, n, ld, p_s,
                      (unsigned int)(seed & 0xFFFFFFFFull), (unsigned int)(seed >> 32), (unsigned int)k_first,
-                     (unsigned int)fn);
+                     (unsigned int)fn, blocked ? 1 : 0);
 }
 
 void launch_gauss_parts(uint32_t first, uint32_t count, double* r, double* c, double* sn, hipStream_t s) {

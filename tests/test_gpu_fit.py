@@ -1,0 +1,66 @@
+"""The one-launch fit (sketch chain, moments, coefficient) against the fp64 oracle: the fitted coefficients of
+the first updates, at both sides of every limit of its variants (order 64, 512, 1024, 2048; 16 and 32 rows
+per workgroup; sketches of 16, 32 and 64 columns; the longest chain), and equal bits for equal matrices whatever
+their place in a batch.
+
+The chain is carried out in fp32 from the matrix R that the iteration itself has (relative error of a coefficient: a few
+n * 2^-24 of partial sums that average out, measured below 1e-6); R of the second update carries the rounding of
+the first.  bf16 polar factors fit from the bf16 R with the exact diagonal: 2e-2 as in the parity tests.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import prism_ref as O
+from paper_2601_22137_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+SEED = W.SKETCH_SEED
+
+
+@pytest.fixture(scope="module")
+def prism():
+    from paper_2601_22137_amd import prism as P
+    P.lib()
+    return P
+
+
+@pytest.mark.parametrize("n,batch,sketch,p", [
+    (40, 3, 16, 4), (64, 5, 40, 4), (65, 2, 16, 4), (130, 2, 32, 2), (512, 1, 16, 4), (512, 17, 8, 4), (513, 1, 16, 4),
+    (300, 1, 16, 8), (1000, 1, 32, 4), (1024, 9, 16, 4), (1024, 1, 64, 4), (1025, 1, 16, 4), (2048, 1, 32, 2)])
+def test_inverse_root_coefficients(prism, n, batch, sketch, p):
+    A = W.c4_shampoo_spd(n=n, batch=1)
+    x = torch.from_numpy(np.repeat(A, batch, axis=0)).cuda()
+    rec = prism.inv_root(x, p, 2, sketch, SEED, 0.0).read()
+    ref, oinfo = O.inv_root(A[0], p, 2, sketch, SEED, 0.0)
+    assert np.abs(rec[0]["alpha"][:2] - np.array(oinfo["alpha"][:2])).max() <= 1e-5
+    out = x.cpu().numpy()
+    assert np.linalg.norm(out[0] - ref) <= 1e-5 * np.linalg.norm(ref)
+    assert all(np.array_equal(out[0], out[b]) for b in range(1, batch))
+    assert all(np.array_equal(rec[0]["alpha"][:2], rec[b]["alpha"][:2]) for b in range(1, batch))
+
+
+@pytest.mark.parametrize("n,batch,sketch", [(128, 2, 16), (512, 20, 32), (768, 1, 16), (768, 12, 16), (1024, 1, 32), (1280, 1, 16)])
+def test_bf16_polar_coefficients(prism, n, batch, sketch):
+    A = W.c3_polar_large(n=n, batch=1, sigma_decades=2.0)
+    bits = W.to_bf16_bits(A) if A.dtype != np.uint16 else A
+    x = torch.from_numpy(np.repeat(bits, batch, axis=0).view(np.int16)).cuda().view(torch.bfloat16)
+    rec = prism.polar(x, 5, 2, sketch, SEED, 0.0).read()
+    _, oinfo = O.polar(W.from_bf16_bits(bits)[0], 5, 2, sketch, SEED, 0.0)
+    assert np.abs(rec[0]["alpha"][:2] - np.array(oinfo["alpha"][:2])).max() <= 2e-2
+    out = x.view(torch.int16).cpu().numpy()
+    assert all(np.array_equal(out[0], out[b]) for b in range(1, batch))
+
+
+@pytest.mark.parametrize("degree", [3, 5])
+def test_sign_coefficients_many_matrices(prism, degree):
+    """More clusters than fit the chip at a time (2000 matrices of 8 workgroups)."""
+    A = W.sign_indefinite(n=128, batch=2)
+    x = torch.from_numpy(np.tile(A, (1000, 1, 1))).cuda()
+    rec = prism.sign(x, degree, 3, 16, SEED, 0.0).read()
+    out = x.cpu().numpy()
+    for b in range(2):
+        ref, oinfo = O.sign(A[b], degree, 3, 16, SEED, 0.0)
+        assert np.abs(rec[b]["alpha"][:3] - np.array(oinfo["alpha"][:3])).max() <= 1e-4
+        assert np.linalg.norm(out[b] - ref) <= 1e-4 * np.linalg.norm(ref)
+        assert np.array_equal(out[b::2], np.broadcast_to(out[b], out[b::2].shape))
