@@ -38,7 +38,7 @@ struct GemmDesc {
   int M, N, K;          // padded sizes: multiples of the tile sizes
   int a_km;             // A stored [K][M] instead of [M][K]
   int sym;              // the exact result is symmetric: compute the upper triangle of tiles, mirror the rest
-  int ctrl_fixed;       // ctrl[0] applies to every batch entry (the parts of a split-K product)
+  int ctrl_parts;       // split-K products: batch entries per matrix, i.e. per control block (0: one each)
   int tile_blocks;      // set by the launcher: tiles are taken in blocks of 8 x 8 (plain products, grids of 8 x 8 multiples)
   int batch;
   // epilogue operands
@@ -72,7 +72,7 @@ int launch_gemm_f64a(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s); 
 
 // ---- gemm_bf16.hip : bf16 matrix-core NT GEMMs (both operands K-contiguous) ----
 enum Bf16Epi {
-  BEPI_STORE = 0,   // C(fp32) = acc
+  BEPI_STORE = 0,   // C(fp32) = acc (symmetric products: the computed tiles only)
   BEPI_GRAM = 1,    // R = I - acc: R32 (fp32) and Rb (bf16), rho partial
   BEPI_POLYQ = 2,   // Q(bf16) = c1 * R32 + alpha * acc
   BEPI_APPLY = 3    // X' = Xhi + (1 + c) Xlo + acc -> Xa_hi', Xa_lo' ([L][S]); acc = Xhi B
@@ -96,10 +96,10 @@ struct Bf16Desc {
   const uint16_t* Xhi; const uint16_t* Xlo;          // APPLY: current iterate (same layout as Cb)
   float c1;
   int coef_is_alpha;                                 // APPLY: multiply acc by ctrl.alpha (d = 1)
-  float* rho_part;                                   // GRAM: partial sums of R^2, one slot per computed tile: b * tiles + tile
+  float* rho_part; int rho_stride;                   // GRAM: partial sums of R^2, slot b * rho_stride + tile for every computed tile; zeros behind
   const Ctrl* ctrl;
   int xcd_blocks;                                    // set by launch_gemm_bf16: 4 x 8 tile blocks per XCD
-  int ctrl_fixed;                                    // ctrl[0] applies to every batch entry (the parts of a split-K product)
+  int ctrl_parts;                                    // split-K products: batch entries per matrix, i.e. per control block (0: one each)
 };
 // One launch over up to BF16_MAX_GROUPS products of the same kind (epilogue, symmetry) and
 // different shapes: workgroup index -> (group, matrix, tile) through the running tile counts.
@@ -247,19 +247,25 @@ struct InfoScatter {
 };
 void launch_scatter_info(const InfoScatter& a, hipStream_t s);
 
-// Second pass of a split-K Gram product: R = I - sum_p part_p (zero outside the leading n x n block),
+// Second pass of split-K Gram products: R = I - sum_p part_p (zero outside the leading n x n block),
 // summed in part order, exactly symmetric (the lower triangle is the mirror image of the upper one).
+// The matrices come in up to BF16_MAX_GROUPS ranges with partial products and a number of parts of their own.
 struct GramReduceArgs {
-  const float* part;        // [batch][parts][np][np]
-  int parts, np, n_true;
+  int ngroups;
+  const float* part[BF16_MAX_GROUPS];   // [matrices of the range][parts][np][np]
+  int parts[BF16_MAX_GROUPS];
+  int boff[BF16_MAX_GROUPS];            // first matrix of the range in the arrays below
+  int first[BF16_MAX_GROUPS + 1];       // ... and in the launch
+  int np, n_true;
   float* R32;               // [batch][np][np] or null
   uint16_t* Rb;             // bf16 copy [batch][np][np] or null
   float* diag;              // exact diagonal [batch][np] or null
-  float* rho_part;          // [batch][tiles]: tiles = (np / 64) (np / 64 + 1) / 2 partial sums of R^2
+  float* rho_part;          // [batch][rho_stride]: gram_reduce_parts(np) partial sums of R^2, then zeros
+  int rho_stride;
   const Ctrl* ctrl;
 };
 int gram_reduce_parts(int np);
-void launch_gram_reduce(const GramReduceArgs& a, int batch, hipStream_t s);
+void launch_gram_reduce(const GramReduceArgs& a, hipStream_t s);
 // E = alpha R, one matrix per blockIdx.y; skipped when done
 void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np, hipStream_t s);
 

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void g
     tm = rem / tiles_n;
     tn = rem - tm * tiles_n;
   }
-  const int cb = g.ctrl_fixed ? 0 : b;   // split-K launches: every batch entry is a part of the same matrix
+  const int cb = g.ctrl_parts ? b / g.ctrl_parts : b;   // split-K launches: the batch entries are parts of matrices
   if (g.ctrl && g.ctrl[cb].done) return;
   const float alpha = g.ctrl ? g.ctrl[cb].alpha : 1.0f;
 
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void g
       }
     }
   } else {
-    static_assert(EPI == BEPI_STORE && !SYM, "GRAM and POLYQ exist as symmetric products only");
+    static_assert(EPI == BEPI_STORE, "the remaining kind");
 #pragma unroll
     for (int i = 0; i < NBM; ++i)
 #pragma unroll
@@ -564,8 +564,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void g
     if (t == 0) {
       float sum = (red[0] + red[1]) + (red[2] + red[3]);
       if (NW == 8) sum += (red[4] + red[5]) + (red[6] + red[7]);
-      g.rho_part[(long long)b * per_mat + rem] = sum;
+      g.rho_part[(long long)b * g.rho_stride + rem] = sum;
     }
+    if (rem == 0)
+      for (int i = per_mat + t; i < g.rho_stride; i += 64 * NW) g.rho_part[(long long)b * g.rho_stride + i] = 0.0f;
   }
 }
 
@@ -611,14 +613,15 @@ int launch_t(Bf16Multi& mg, hipStream_t s) {
     if ((long long)(g.M / TM) * (g.N / TN) * g.batch <= 0) return PRISM_EINVAL;
     if (g.sym && (g.M != g.N || g.A != g.B)) return PRISM_EINVAL;
     if ((g.epi == BEPI_GRAM || g.epi == BEPI_POLYQ) && !g.sym) return PRISM_EINVAL;   // symmetric products only
-    if (g.epi == BEPI_STORE && (g.sym || !g.C32)) return PRISM_EINVAL;
+    if (g.epi == BEPI_STORE && (!g.C32 || (g.sym && km != 3))) return PRISM_EINVAL;
     // without the fp32 matrix: GRAM with a diagonal array, POLYQ with R in bf16
-    if (g.epi == BEPI_GRAM && !g.C32 && !g.diag) return PRISM_EINVAL;
+    if (g.epi == BEPI_GRAM && ((!g.C32 && !g.diag) || g.rho_stride < tiles_per_matrix<TM, TN, true>(g))) return PRISM_EINVAL;
     if (g.epi == BEPI_POLYQ && !g.C32 && !g.Cin16) return PRISM_EINVAL;
   }
   // operand layouts (km: bit 0 = A stored [K][M], bit 1 = B stored [K][N]) per kind of product
   switch (epi) {
     case BEPI_STORE:
+      if (sym) return launch_te<TM, TN, BEPI_STORE, true, true, true>(mg, s);
       if (km == 3) return launch_te<TM, TN, BEPI_STORE, false, true, true>(mg, s);
       if (km == 2) return launch_te<TM, TN, BEPI_STORE, false, false, true>(mg, s);
       if (km == 0) return launch_te<TM, TN, BEPI_STORE, false>(mg, s);

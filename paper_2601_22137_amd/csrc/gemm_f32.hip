@@ -141,7 +141,7 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
     tm = rem / tiles_n;
     tn = rem - tm * tiles_n;
   }
-  const int cb = g.ctrl_fixed ? 0 : b;   // split-K launches: every batch entry is a part of the same matrix
+  const int cb = g.ctrl_parts ? b / g.ctrl_parts : b;   // split-K launches: the batch entries are parts of matrices
   if (g.ctrl && g.ctrl[cb].done) return;
   // block Gauss-Jordan: the pivot row / column block has launches of its own
   if ((tm * TM >= g.skip_m0 && tm * TM < g.skip_m1) || (tn * TN >= g.skip_n0 && tn * TN < g.skip_n1)) return;

@@ -22,8 +22,14 @@ __device__ inline unsigned short f2bf(float x) {
 }
 __device__ inline float bf2f(unsigned short h) { return __uint_as_float(((unsigned int)h) << 16); }
 
-__device__ inline double load_src(const void* src, int dt, long long idx) {
-  return dt == PRISM_BF16 ? (double)bf2f(((const unsigned short*)src)[idx]) : (double)((const float*)src)[idx];
+// Sum of a matrix's partials, on every lane: a strided share per lane, then a fixed tree (as one serial loop per thread
+// it was a latency chain of nsum loads in front of every tile).
+__device__ inline double total_sumsq(const double* part, int nsum) {
+  double v = 0.0;
+  for (int i = threadIdx.x & 63; i < nsum; i += 64) v += part[i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
 }
 
 // sumsq_part[b][blockIdx.x] = sum of squares of a strided share of matrix b (fp64).
@@ -32,31 +38,44 @@ __device__ inline double load_src(const void* src, int dt, long long idx) {
 // the launches over several groups reproduce so that every matrix gets the same partial sums)
 __device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
   const long long total = (long long)a.m * a.n;
-  const long long base = (long long)b * total;
   double acc = 0.0;
   const long long first = (long long)bx * NT + threadIdx.x, step = (long long)gx * NT;
-  if (a.dt == PRISM_BF16 && (total & 7) == 0) {          // 16-byte loads: 8 bf16 at a time
-    const u32x4* v = (const u32x4*)((const unsigned short*)a.src + base);
-    for (long long i = first; i < total / 8; i += step) {
-      const u32x4 w = v[i];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double x0 = (double)__uint_as_float(w[e] << 16), x1 = (double)__uint_as_float(w[e] & 0xFFFF0000u);
-        acc += x0 * x0 + x1 * x1;
-      }
+  // 16-byte loads, four in flight; the entries ahead of the first 16-byte boundary and behind the last go to the
+  // first workgroup
+  auto sweep = [&](auto* src, auto add16, auto add1) {
+    constexpr int PER = 16 / (int)sizeof(*src);
+    long long head = (long long)((0 - (uintptr_t)src) & 15) / (long long)sizeof(*src);
+    if (head > total) head = total;
+    const long long nv = (total - head) / PER;
+    const u32x4* v = (const u32x4*)(src + head);
+    long long i = first;
+    for (; i + 3 * step < nv; i += 4 * step) {
+      const u32x4 w0 = v[i], w1 = v[i + step], w2 = v[i + 2 * step], w3 = v[i + 3 * step];
+      add16(w0); add16(w1); add16(w2); add16(w3);
     }
-  } else if (a.dt == PRISM_F32 && (total & 3) == 0) {
-    const f32x4* v = (const f32x4*)((const float*)a.src + base);
-    for (long long i = first; i < total / 4; i += step) {
-      const f32x4 w = v[i];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc += (double)w[e] * (double)w[e];
+    for (; i < nv; i += step) add16(v[i]);
+    if (bx == 0) {
+      if ((long long)threadIdx.x < head) add1(src[threadIdx.x]);
+      if (head + nv * PER + threadIdx.x < total) add1(src[head + nv * PER + threadIdx.x]);
     }
+  };
+  if (a.dt == PRISM_BF16) {
+    sweep((const unsigned short*)a.src + (long long)b * total,
+          [&](const u32x4& w) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const double x0 = (double)__uint_as_float(w[e] << 16), x1 = (double)__uint_as_float(w[e] & 0xFFFF0000u);
+              acc += x0 * x0 + x1 * x1;
+            }
+          },
+          [&](unsigned short h) { acc += (double)bf2f(h) * (double)bf2f(h); });
   } else {
-    for (long long i = first; i < total; i += step) {
-      const double v = load_src(a.src, a.dt, base + i);
-      acc += v * v;
-    }
+    sweep((const float*)a.src + (long long)b * total,
+          [&](const u32x4& w) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc += (double)__uint_as_float(w[e]) * (double)__uint_as_float(w[e]);
+          },
+          [&](float x) { acc += (double)x * (double)x; });
   }
   __shared__ double red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -76,13 +95,12 @@ __global__ __launch_bounds__(NT) void sumsq_multi_kernel(PrepMulti m) {
   sumsq_body(a, w % a.nsum, w / a.nsum, a.nsum);
 }
 
-// One workgroup per 64 x 64 tile of the padded internal iterate [Lp][Sp].
+// fp32: one workgroup per 64 x 64 tile of the padded internal iterate [Lp][Sp].
 __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
   const int b = blockIdx.y;
   const int tiles_c = a.Sp / 64;
   const int tr = blockIdx.x / tiles_c, tc = blockIdx.x % tiles_c;
-  double ss = 0.0;
-  for (int i = 0; i < a.nsum; ++i) ss += a.sumsq_part[(long long)b * a.nsum + i];
+  const double ss = total_sumsq(a.sumsq_part + (long long)b * a.nsum, a.nsum);
   const bool finite = (ss == ss) && ss < 1.0e300;
   const bool zero = finite && ss == 0.0;
   const double norm = sqrt(ss);
@@ -124,7 +142,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
     double v = 0.0;
     if (r < a.L && c < a.S) {
       const long long si = a.transpose ? ((long long)c * a.n + r) : ((long long)r * a.n + c);
-      v = load_src(a.src, a.dt, (long long)b * mat + si) * scale;
+      v = (double)((const float*)a.src)[(long long)b * mat + si] * scale;
     }
     const long long o = (long long)b * a.Lp * a.Sp + (long long)r * a.Sp + c;
     if (a.fn == PRISM_FN_SIGN) {
@@ -141,13 +159,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
       a.Y32[o] = (float)v;                                                                    // A_s
       a.X32[(long long)b * a.Lp * a.Sp + (long long)c * a.Sp + r] = (float)v;                 // X_0 = A_s^T
     } else if (a.fn == PRISM_FN_POLAR) {
-      if (a.dt == PRISM_BF16) {
-        const unsigned short hi = f2bf((float)v);
-        a.Xa_hi[o] = hi;
-        if (a.Xa_lo) a.Xa_lo[o] = f2bf((float)v - bf2f(hi));
-      } else {
-        a.X32[o] = (float)v;
-      }
+      a.X32[o] = (float)v;
     } else if (a.fn == PRISM_FN_SQRT) {
       a.X32[o] = (float)v;
       a.Y32[o] = (r == c && r < a.S) ? 1.0f : 0.0f;
@@ -173,15 +185,40 @@ __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
   }
 }
 
-// bf16 polar, both sides multiples of 8: one workgroup per 64 x 64 tile of the CALLER's matrix.
-// The tile is read with 16-byte loads along the caller's rows, scaled and split into high and low
-// halves; a tall or square matrix goes straight into the internal [Lp][Sp] iterate, a wide one
-// (the iterate is its transpose) through an LDS transpose, everything as 16-byte vectors.
+// bf16 polar: one workgroup per 64 x 128 tile of the CALLER's matrix (padded).  The tile is read with 16-byte loads along
+// the caller's rows (VEC; entry by entry where the rows are no multiples of 16 bytes), scaled and split into high and
+// low halves; a tall or square matrix goes straight into the internal [Lp][Sp] iterate, a wide one (the iterate is its
+// transpose) through an LDS transpose, everything as 16-byte vectors.  HBM bound (50257 x 768: norm and copy-in
+// 73 + 98 us as entry-wise passes, now 14 + 36).
+constexpr int PC = 128;                    // columns per tile
+// Entry (row, i) of a transposed tile of `units` 16-byte units per row: the units are rotated by row / 8, so that the
+// 2-byte writes of a wave (rows 8 apart) spread over the banks.
+__device__ inline int rotated(int row, int i, int units) { return (((i >> 3) + (row >> 3)) & (units - 1)) * 8 + (i & 7); }
+// 8 consecutive entries of the caller's matrix from column c of a row on (zeros from column n on)
+template <bool VEC> __device__ inline u32x4 load8(const unsigned short* row, int c, int n) {
+  if constexpr (VEC) return *(const u32x4*)(row + c);
+  u32x4 w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const unsigned lo = c + 2 * e < n ? row[c + 2 * e] : 0u, hi = c + 2 * e + 1 < n ? row[c + 2 * e + 1] : 0u;
+    w[e] = lo | (hi << 16);
+  }
+  return w;
+}
+template <bool VEC>
 __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
-  const int tiles_c = (a.transpose ? a.Lp : a.Sp) / 64;             // tiles over the padded, caller-oriented matrix
+  const int tiles_c = (a.transpose ? a.Lp : a.Sp) / PC;             // tiles over the padded, caller-oriented matrix
   const int tr = bx / tiles_c, tc = bx % tiles_c;
-  double ss = 0.0;
-  for (int i = 0; i < a.nsum; ++i) ss += a.sumsq_part[(long long)b * a.nsum + i];
+  const unsigned short* src = (const unsigned short*)a.src + (long long)b * a.m * a.n;
+  u32x4 in[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {              // 1024 vectors of 8 per tile, requested ahead of the norm
+    const int v = threadIdx.x + it * NT;
+    const int r = tr * 64 + (v >> 4), c = tc * PC + (v & 15) * 8;
+    in[it] = u32x4{0u, 0u, 0u, 0u};
+    if (r < a.m && c < a.n) in[it] = load8<VEC>(src + (long long)r * a.n, c, a.n);
+  }
+  const double ss = total_sumsq(a.sumsq_part + (long long)b * a.nsum, a.nsum);
   const bool finite = (ss == ss) && ss < 1.0e300;
   const bool zero = finite && ss == 0.0;
   const double norm = sqrt(ss);
@@ -204,30 +241,27 @@ __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
     for (int i = threadIdx.x; i < PRISM_MAX_ITERS; i += NT) a.info[b].alpha[i] = 0.0f;
   }
   const long long mat_int = (long long)a.Lp * a.Sp;
-  __shared__ float tile_hi[64][65], tile_lo[64][65];
-  const unsigned short* src = (const unsigned short*)a.src + (long long)b * a.m * a.n;
+  __shared__ __align__(16) unsigned short tile_hi[PC][72], tile_lo[PC][72];
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int v = threadIdx.x + it * NT;          // 512 vectors of 8 per tile
-    const int lr = v >> 3, lc = (v & 7) * 8;
-    const int r = tr * 64 + lr, c = tc * 64 + lc;
-    u32x4 w = {0u, 0u, 0u, 0u};
-    if (r < a.m && c < a.n) w = *(const u32x4*)(src + (long long)r * a.n + c);
+  for (int it = 0; it < 4; ++it) {
+    const int v = threadIdx.x + it * NT;
+    const int lr = v >> 4, lc = (v & 15) * 8;
     u32x4 hi, lo;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x0 = __uint_as_float(w[e] << 16) * scale, x1 = __uint_as_float(w[e] & 0xFFFF0000u) * scale;
+      const unsigned w = in[it][e];
+      const float x0 = __uint_as_float(w << 16) * scale, x1 = __uint_as_float(w & 0xFFFF0000u) * scale;
       const unsigned short h0 = f2bf(x0), h1 = f2bf(x1);
-      const unsigned short l0 = f2bf(x0 - bf2f(h0)), l1 = f2bf(x1 - bf2f(h1));
       hi[e] = (unsigned)h0 | ((unsigned)h1 << 16);
-      lo[e] = (unsigned)l0 | ((unsigned)l1 << 16);
+      if (a.Xa_lo) lo[e] = (unsigned)f2bf(x0 - bf2f(h0)) | ((unsigned)f2bf(x1 - bf2f(h1)) << 16);
       if (a.transpose) {
-        tile_hi[lc + 2 * e][lr] = bf2f(h0); tile_hi[lc + 2 * e + 1][lr] = bf2f(h1);
-        tile_lo[lc + 2 * e][lr] = bf2f(l0); tile_lo[lc + 2 * e + 1][lr] = bf2f(l1);
+        const int p = rotated(lc, lr, 8);
+        tile_hi[lc + 2 * e][p] = h0; tile_hi[lc + 2 * e + 1][p] = h1;
+        if (a.Xa_lo) { tile_lo[lc + 2 * e][p] = (unsigned short)lo[e]; tile_lo[lc + 2 * e + 1][p] = (unsigned short)(lo[e] >> 16); }
       }
     }
     if (!a.transpose) {  // rows / columns beyond the caller's matrix but inside the padded array are written as zeros
-      const long long o = (long long)b * mat_int + (long long)r * a.Sp + c;
+      const long long o = (long long)b * mat_int + (long long)(tr * 64 + lr) * a.Sp + tc * PC + lc;
       *(u32x4*)(a.Xa_hi + o) = hi;
       if (a.Xa_lo) *(u32x4*)(a.Xa_lo + o) = lo;
     }
@@ -235,92 +269,96 @@ __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
   if (!a.transpose) return;
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
+  for (int it = 0; it < 4; ++it) {
     const int v = threadIdx.x + it * NT;
     const int lc = v >> 3, lr = (v & 7) * 8;      // row lc of the transposed tile, 8 consecutive source rows
-    const int r = tr * 64 + lr, c = tc * 64 + lc;
-    u32x4 hi, lo;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      hi[e] = (unsigned)f2bf(tile_hi[lc][lr + 2 * e]) | ((unsigned)f2bf(tile_hi[lc][lr + 2 * e + 1]) << 16);
-      lo[e] = (unsigned)f2bf(tile_lo[lc][lr + 2 * e]) | ((unsigned)f2bf(tile_lo[lc][lr + 2 * e + 1]) << 16);
-    }
-    const long long o = (long long)b * mat_int + (long long)c * a.Sp + r;   // internal row = caller's column
-    *(u32x4*)(a.Xa_hi + o) = hi;
-    if (a.Xa_lo) *(u32x4*)(a.Xa_lo + o) = lo;
+    const long long o = (long long)b * mat_int + (long long)(tc * PC + lc) * a.Sp + tr * 64 + lr;   // internal row = caller's column
+    *(u32x4*)(a.Xa_hi + o) = *(const u32x4*)&tile_hi[lc][rotated(lc, lr, 8)];
+    if (a.Xa_lo) *(u32x4*)(a.Xa_lo + o) = *(const u32x4*)&tile_lo[lc][rotated(lc, lr, 8)];
   }
 }
-__global__ __launch_bounds__(NT) void prepare_bf16_kernel(PrepArgs a) { prepare_bf16_body(a, blockIdx.x, blockIdx.y); }
+template <bool VEC> __global__ __launch_bounds__(NT) void prepare_bf16_kernel(PrepArgs a) { prepare_bf16_body<VEC>(a, blockIdx.x, blockIdx.y); }
 __global__ __launch_bounds__(NT) void prepare_bf16_multi_kernel(PrepMulti m) {
   int w = blockIdx.x, gi = 0;
   while (gi + 1 < m.ngroups && w >= m.start[gi + 1]) ++gi;
   w -= m.start[gi];
   const PrepArgs& a = m.d[gi];
-  const int tiles = (a.Lp / 64) * (a.Sp / 64);
-  prepare_bf16_body(a, w % tiles, w / tiles);
+  const int tiles = (a.Lp / 64) * (a.Sp / PC);
+  prepare_bf16_body<true>(a, w % tiles, w / tiles);
 }
 
-// bf16 polar, both sides multiples of 8: the result is the high half of the iterate.  One workgroup
-// per 64 x 64 tile of the caller's matrix: a tall or square one is copied with 16-byte vectors, a
-// wide one (the iterate is its transpose) goes through an LDS transpose.
+// bf16 polar, rows of the caller's matrix in 16-byte vectors (VEC; entry by entry otherwise): the result is the high half of
+// the iterate.  One workgroup per 64 x 128 tile of the caller's matrix: a tall or
+// square one is copied, a wide one (the iterate is its transpose) goes through an LDS transpose.  HBM bound
+// (50257 x 768: 88 us entry by entry, now 24).
+template <bool VEC> __device__ inline void store8(unsigned short* row, int c, int n, const u32x4& w) {
+  if constexpr (VEC) {
+    *(u32x4*)(row + c) = w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (c + 2 * e < n) row[c + 2 * e] = (unsigned short)w[e];
+      if (c + 2 * e + 1 < n) row[c + 2 * e + 1] = (unsigned short)(w[e] >> 16);
+    }
+  }
+}
+template <bool VEC>
 __device__ inline void finalize_bf16_body(const FinalArgs& a, int bx, int b) {
   const Ctrl c = a.ctrl[b];
   if (c.status == PRISM_INFO_NONFINITE || c.status == PRISM_INFO_ZERO) return;
   const int par = c.iters & 1;
-  const unsigned short* srcm = a.Xa_hi[par] + (long long)b * a.Lp * a.Sp;
+  const long long mat_int = (long long)b * a.Lp * a.Sp;
+  const unsigned short* hi = a.Xa_hi[par] + mat_int;
   unsigned short* dst = (unsigned short*)a.dst + (long long)b * a.m * a.n;
   if (!a.transpose && a.Xa_hi[par] == (const unsigned short*)a.dst) return;   // the caller's array was that iterate buffer: in place
-  const int tiles_c = (a.n + 63) / 64;
+  const int tiles_c = (a.n + PC - 1) / PC;
   const int tr = bx / tiles_c, tc = bx % tiles_c;
   if (!a.transpose) {
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
+    for (int it = 0; it < 4; ++it) {
       const int v = threadIdx.x + it * NT;
-      const int r = tr * 64 + (v >> 3), col = tc * 64 + (v & 7) * 8;
-      if (r < a.m && col < a.n) *(u32x4*)(dst + (long long)r * a.n + col) = *(const u32x4*)(srcm + (long long)r * a.Sp + col);
+      const int r = tr * 64 + (v >> 4), col = tc * PC + (v & 15) * 8;
+      const long long o = (long long)r * a.Sp + col;
+      if (r < a.m && col < a.n) store8<VEC>(dst + (long long)r * a.n, col, a.n, *(const u32x4*)(hi + o));
     }
     return;
   }
-  // caller's tile (rows tr, columns tc) = transpose of the internal tile (rows tc, columns tr)
-  __shared__ unsigned short tile[64][72];
+  // caller's tile (64 rows tr, 128 columns tc) = transpose of the internal tile (128 rows tc, 64 columns tr)
+  __shared__ __align__(16) unsigned short tile[64][PC + 8];
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
+  for (int it = 0; it < 4; ++it) {
     const int v = threadIdx.x + it * NT;
     const int lr = v >> 3, lc = (v & 7) * 8;                 // internal row (caller's column), 8 internal columns
-    const int ri = tc * 64 + lr, ci = tr * 64 + lc;
+    const int ri = tc * PC + lr, ci = tr * 64 + lc;
     u32x4 w = {0u, 0u, 0u, 0u};
-    if (ri < a.Lp && ci < a.Sp) w = *(const u32x4*)(srcm + (long long)ri * a.Sp + ci);
+    const long long o = (long long)ri * a.Sp + ci;
+    if (ri < a.Lp && ci < a.Sp) w = *(const u32x4*)(hi + o);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      tile[lc + 2 * e][lr] = (unsigned short)(w[e] & 0xFFFFu);
-      tile[lc + 2 * e + 1][lr] = (unsigned short)(w[e] >> 16);
+      tile[lc + 2 * e][rotated(lc, lr, 16)] = (unsigned short)(w[e] & 0xFFFFu);
+      tile[lc + 2 * e + 1][rotated(lc, lr, 16)] = (unsigned short)(w[e] >> 16);
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
+  for (int it = 0; it < 4; ++it) {
     const int v = threadIdx.x + it * NT;
-    const int lr = v >> 3, lc = (v & 7) * 8;                 // caller's row within the tile, 8 caller's columns
-    const int r = tr * 64 + lr, col = tc * 64 + lc;
-    if (r < a.m && col < a.n) {
-      u32x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (unsigned)tile[lr][lc + 2 * e] | ((unsigned)tile[lr][lc + 2 * e + 1] << 16);
-      *(u32x4*)(dst + (long long)r * a.n + col) = w;
-    }
+    const int lr = v >> 4, lc = (v & 15) * 8;                // caller's row within the tile, 8 caller's columns
+    const int r = tr * 64 + lr, col = tc * PC + lc;
+    if (r < a.m && col < a.n) store8<VEC>(dst + (long long)r * a.n, col, a.n, *(const u32x4*)&tile[lr][rotated(lr, lc, 16)]);
   }
 }
-__global__ __launch_bounds__(NT) void finalize_bf16_kernel(FinalArgs a) { finalize_bf16_body(a, blockIdx.x, blockIdx.y); }
+template <bool VEC> __global__ __launch_bounds__(NT) void finalize_bf16_kernel(FinalArgs a) { finalize_bf16_body<VEC>(a, blockIdx.x, blockIdx.y); }
 __global__ __launch_bounds__(NT) void finalize_bf16_multi_kernel(FinalMulti m) {
   int w = blockIdx.x, gi = 0;
   while (gi + 1 < m.ngroups && w >= m.start[gi + 1]) ++gi;
   w -= m.start[gi];
   const FinalArgs& a = m.d[gi];
-  const int tiles = ((a.m + 63) / 64) * ((a.n + 63) / 64);
-  finalize_bf16_body(a, w % tiles, w / tiles);
+  const int tiles = ((a.m + 63) / 64) * ((a.n + PC - 1) / PC);
+  finalize_bf16_body<true>(a, w % tiles, w / tiles);
 }
 
-// One thread per element of the caller's array.
+// fp32: one thread per element of the caller's array.
 __global__ __launch_bounds__(NT) void finalize_kernel(FinalArgs a) {
   const int b = blockIdx.y;
   const Ctrl c = a.ctrl[b];
@@ -335,13 +373,7 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinalArgs a) {
   if (a.fn == PRISM_FN_INVERSE) {
     ((float*)a.dst)[(long long)b * mat + i] = (float)((double)a.X32[par][o] / c.norm);
   } else if (a.fn == PRISM_FN_POLAR) {
-    if (a.dt == PRISM_BF16) {
-      float x = bf2f(a.Xa_hi[par][o]);
-      if (a.Xa_lo[par]) x += bf2f(a.Xa_lo[par][o]);
-      ((unsigned short*)a.dst)[(long long)b * mat + i] = f2bf(x);
-    } else {
-      ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
-    }
+    ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
   } else if (a.fn == PRISM_FN_SQRT_NEWTON) {
     ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
     ((float*)a.dst2)[(long long)b * mat + i] = a.Y32[par][o];
@@ -366,7 +398,9 @@ __global__ __launch_bounds__(NT) void make_e_kernel(float* E, const float* R, co
 
 // One workgroup per 64 x 64 tile on or above the diagonal; thread t: row t / 4, 16 consecutive columns.
 __global__ __launch_bounds__(NT) void gram_reduce_kernel(GramReduceArgs a) {
-  const int b = blockIdx.y;
+  int gi = 0;
+  while (gi + 1 < a.ngroups && (int)blockIdx.y >= a.first[gi + 1]) ++gi;
+  const int bl = blockIdx.y - a.first[gi], b = a.boff[gi] + bl;
   if (a.ctrl[b].done) return;
   const int nt = a.np / 64;
   int left = blockIdx.x, tm = 0;
@@ -380,8 +414,21 @@ __global__ __launch_bounds__(NT) void gram_reduce_kernel(GramReduceArgs a) {
     f32x4 acc[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const float* src = a.part + (long long)b * a.parts * SS + (long long)(m0 + r) * a.np + n0 + c0;
-    for (int p = 0; p < a.parts; ++p)
+    const int parts = a.parts[gi];
+    const float* src = a.part[gi] + (long long)bl * parts * SS + (long long)(m0 + r) * a.np + n0 + c0;
+    int p = 0;
+    for (; p + 4 <= parts; p += 4) {   // four parts requested at a time, added in order
+      f32x4 v[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[u][q] = *(const f32x4*)(src + (long long)(p + u) * SS + 4 * q);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += v[u][q];
+    }
+    for (; p < parts; ++p)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[q] += *(const f32x4*)(src + (long long)p * SS + 4 * q);
 #pragma unroll
@@ -429,15 +476,17 @@ __global__ __launch_bounds__(NT) void gram_reduce_kernel(GramReduceArgs a) {
   for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
   __syncthreads();
-  if (threadIdx.x == 0) a.rho_part[(long long)b * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) a.rho_part[(long long)b * a.rho_stride + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (blockIdx.x == 0)
+    for (int i = gridDim.x + threadIdx.x; i < a.rho_stride; i += NT) a.rho_part[(long long)b * a.rho_stride + i] = 0.0f;
 }
 
 }  // namespace
 
 int gram_reduce_parts(int np) { return (np / 64) * (np / 64 + 1) / 2; }
 
-void launch_gram_reduce(const GramReduceArgs& a, int batch, hipStream_t s) {
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(gram_reduce_parts(a.np), batch), dim3(NT), 0, s, a);
+void launch_gram_reduce(const GramReduceArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(gram_reduce_parts(a.np), a.first[a.ngroups]), dim3(NT), 0, s, a);
 }
 
 void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np, hipStream_t s) {
@@ -449,15 +498,14 @@ void launch_sumsq(const PrepArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(sumsq_kernel, dim3(a.nsum, a.batch), dim3(NT), 0, s, a);
 }
 
-static bool bf16_vector_path(int fn, int dt, int m, int n, const void* user) {
-  return fn == PRISM_FN_POLAR && dt == PRISM_BF16 && m % 8 == 0 && n % 8 == 0 && ((uintptr_t)user & 15) == 0;
-}
+// rows of the caller's matrices are whole 16-byte vectors
+static bool bf16_vector_rows(int n, const void* user) { return n % 8 == 0 && ((uintptr_t)user & 15) == 0; }
 
 void launch_prepare(const PrepArgs& a, hipStream_t s) {
-  if (bf16_vector_path(a.fn, a.dt, a.m, a.n, a.src)) {
-    // tiles over the padded caller-oriented matrix, so that the padding is written too
-    const int tiles = (a.Lp / 64) * (a.Sp / 64);
-    hipLaunchKernelGGL(prepare_bf16_kernel, dim3(tiles, a.batch), dim3(NT), 0, s, a);
+  if (a.dt == PRISM_BF16) {
+    const dim3 grid((unsigned)((a.Lp / 64) * (a.Sp / PC)), a.batch);   // the padding is written too
+    if (bf16_vector_rows(a.n, a.src)) hipLaunchKernelGGL(prepare_bf16_kernel<true>, grid, dim3(NT), 0, s, a);
+    else hipLaunchKernelGGL(prepare_bf16_kernel<false>, grid, dim3(NT), 0, s, a);
     return;
   }
   const int tiles = (a.Lp / 64) * (a.Sp / 64);
@@ -473,11 +521,11 @@ bool launch_prep_multi(const PrepArgs* groups, int ngroups, hipStream_t s) {
   long long ts = 0, tp = 0;
   for (int i = 0; i < ngroups; ++i) {
     const PrepArgs& a = groups[i];
-    if (!bf16_vector_path(a.fn, a.dt, a.m, a.n, a.src)) return false;
+    if (a.dt != PRISM_BF16 || !bf16_vector_rows(a.n, a.src)) return false;
     ms.d[i] = mp.d[i] = a;
     ms.start[i] = (int)ts; mp.start[i] = (int)tp;
     ts += (long long)a.nsum * a.batch;
-    tp += (long long)(a.Lp / 64) * (a.Sp / 64) * a.batch;
+    tp += (long long)(a.Lp / 64) * (a.Sp / PC) * a.batch;
     if (ts > 0x7fffffff || tp > 0x7fffffff) return false;
   }
   ms.start[ngroups] = (int)ts; mp.start[ngroups] = (int)tp;
@@ -493,10 +541,10 @@ bool launch_finalize_multi(const FinalArgs* groups, int ngroups, hipStream_t s) 
   long long t = 0;
   for (int i = 0; i < ngroups; ++i) {
     const FinalArgs& a = groups[i];
-    if (!bf16_vector_path(a.fn, a.dt, a.m, a.n, a.dst)) return false;
+    if (a.dt != PRISM_BF16 || !bf16_vector_rows(a.n, a.dst)) return false;
     mf.d[i] = a;
     mf.start[i] = (int)t;
-    t += (long long)((a.m + 63) / 64) * ((a.n + 63) / 64) * a.batch;
+    t += (long long)((a.m + 63) / 64) * ((a.n + PC - 1) / PC) * a.batch;
     if (t > 0x7fffffff) return false;
   }
   mf.start[ngroups] = (int)t;
@@ -505,9 +553,10 @@ bool launch_finalize_multi(const FinalArgs* groups, int ngroups, hipStream_t s) 
 }
 
 void launch_finalize(const FinalArgs& a, hipStream_t s) {
-  if (bf16_vector_path(a.fn, a.dt, a.m, a.n, a.dst)) {
-    const int tiles = ((a.m + 63) / 64) * ((a.n + 63) / 64);
-    hipLaunchKernelGGL(finalize_bf16_kernel, dim3((unsigned)tiles, a.batch), dim3(NT), 0, s, a);
+  if (a.dt == PRISM_BF16) {
+    const dim3 grid((unsigned)(((a.m + 63) / 64) * ((a.n + PC - 1) / PC)), a.batch);
+    if (bf16_vector_rows(a.n, a.dst)) hipLaunchKernelGGL(finalize_bf16_kernel<true>, grid, dim3(NT), 0, s, a);
+    else hipLaunchKernelGGL(finalize_bf16_kernel<false>, grid, dim3(NT), 0, s, a);
     return;
   }
   const long long mat = (long long)a.m * a.n;

@@ -94,10 +94,15 @@ struct Plan {
   size_t total;
 };
 
+// Internal flag of make_plan: no split-K Gram product.  Its partial products need scratch of their own; a call whose
+// workspace is large enough without them only takes the one-pass product.
+constexpr unsigned FLAG_NO_SPLIT_K = 1u << 31;
+
 // shared_shapes: the plan of a launch sequence over several shape groups with the same short side;
-// the iterate buffers are then laid out per group by the caller (offsets o_x* stay 0)
+// the iterate buffers are then laid out per group by the caller (offsets o_x* stay 0).  sel_batch: the batch of the
+// whole group where `batch` is a part of it (0: the same)
 int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int sketch_dim, int root_p,
-              unsigned flags, bool shared_shapes = false) {
+              unsigned flags, bool shared_shapes = false, int sel_batch = 0) {
   if (batch <= 0 || m <= 0 || n <= 0) return PRISM_EINVAL;
   if (degree != 3 && degree != 5) return PRISM_EINVAL;
   if (sketch_dim < 0 || sketch_dim > PRISM_MAX_SKETCH) return PRISM_EINVAL;
@@ -129,11 +134,47 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   }
   P.Sp = round_up(P.S, P.tile);
   P.Lp = round_up(P.L, P.tile);
+  // Polar factor of a few tall matrices: X^T X has few tiles and a long K loop, which would leave
+  // most CUs idle; the loop is then cut into parts that run as separate workgroups and a second
+  // pass adds the partial products up (in part order, so results stay run-to-run identical).
+  P.ksplit = 0;
+  static const int no_split_k = ab_switch("PRISM_NO_SPLIT_K");
+  if (fn == PRISM_FN_POLAR && !no_split_k && !shared_shapes && !(flags & FLAG_NO_SPLIT_K) && P.Sp > 64) {
+    const long long nt = (P.Sp + 127) / 128, gb = sel_batch ? sel_batch : batch, tri = nt * (nt + 1) / 2 * gb, full = nt * nt * gb;
+    if (dt == PRISM_BF16 && tri <= 64 && (gb == 1 || (gb <= 8 && P.L >= 8192))) {
+      // A single matrix, or up to eight long ones (with several matrices the launch, which a grouped call shares between
+      // its shapes, is full enough: three layers of width 512, split 0.61 ms, not 0.54).  Parts by the time they are expected
+      // to take, in us, from what was measured (order 768, 128 x 128 tiles): a slab of 32 k 0.37 while the CUs have one
+      // workgroup each, the second pass 6, and per part 1.6e-6 per entry or the latency of its loads, the update 2.7e-9 per
+      // row and squared order (the parts are of equal length and add up to whole tiles, so a number of parts that does
+      // not suit L pads the iterate).  One 768 x 3072 matrix: Gram product 35 -> 20 us; 50257 x 768: 88 -> 73 us; 768 x 768
+      // stays one pass (9 us).
+      const double s2 = (double)P.Sp * P.Sp;
+      auto cost = [&](long long Kp, int parts) {
+        const double load = (double)tri * parts / 256.0;
+        return Kp * 0.0116 * (load > 1.0 ? load : 1.0) + (double)Kp * parts * s2 * 2.7e-9 + (parts > 1 ? 6.0 + parts * (s2 * 1.6e-6 > 0.35 ? s2 * 1.6e-6 : 0.35) : 0.0);
+      };
+      double best = cost(P.Lp, 1);
+      const int Lp0 = P.Lp;
+      for (int parts = 2; parts <= 64 && parts * tri <= 384 && parts * 256 <= Lp0; ++parts) {
+        int unit = P.tile;                    // Kp parts has to be a multiple of the tile, Kp one of 32
+        for (int q = parts; unit > 32 && q % 2 == 0; q /= 2) unit /= 2;
+        const int Kp = round_up((P.L + parts - 1) / parts, unit);
+        if (cost(Kp, parts) < best) { best = cost(Kp, parts); P.ksplit = parts; P.Lp = Kp * parts; }
+      }
+    } else if (dt == PRISM_F32 && batch <= 8 && P.Lp >= 8192 && tri <= 48) {
+      for (int parts = 32; parts >= 2; --parts)
+        if (P.Lp % (parts * 32) == 0 && P.Lp / parts >= 1024 && full * parts <= 4096) { P.ksplit = parts; break; }
+    }
+  }
   if ((long long)P.Sp * P.Lp > (1ll << 31) - 1) {   // the kernels keep some offsets within a matrix in 32 bits
     set_last_error("a matrix may hold at most 2^31 - 1 entries after its sides are rounded up to tile multiples");
     return PRISM_EUNSUPPORTED;
   }
-  P.nsum = 64;
+  // shares of the Frobenius norm: 32 to 64 KiB each, so that one large matrix fills the chip (64 shares of a 77 MB matrix
+  // took 99 us) and a batch of small ones is not launched 64 times over
+  P.nsum = (int)(((long long)m * n + 16383) / 16384);
+  if (P.nsum > 512) P.nsum = 512;
   const int t0 = (P.Sp / 64) * (P.Lp / 64);   // prepare-step tiles (inverse root residual of M_0)
   P.max_parts = t0;
   size_t off = 0;
@@ -191,19 +232,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
     P.o_r = take(B * SS * 4);
     for (int i = 0; i < 3; ++i) P.o_t[i] = take(B * SS * 4);
   }
-  // Polar factor of a few tall matrices: X^T X has few tiles and a long K loop, which would leave
-  // most CUs idle; the loop is then cut into parts that run as separate workgroups and a second
-  // pass adds the partial products up (in part order, so results stay run-to-run identical).
-  P.ksplit = 0; P.o_gpart = 0;
-  static const int no_split_k = ab_switch("PRISM_NO_SPLIT_K");
-  if (fn == PRISM_FN_POLAR && !no_split_k && !shared_shapes && batch <= 8 && P.Lp >= 8192 && P.Sp > 64) {
-    const long long nt = (P.Sp + 127) / 128, tri = nt * (nt + 1) / 2, full = nt * nt;
-    if (tri * batch <= 48) {
-      for (int parts = 32; parts >= 2; --parts)
-        if (P.Lp % (parts * 32) == 0 && P.Lp / parts >= 1024 && full * batch * parts <= 4096) { P.ksplit = parts; break; }
-    }
-    if (P.ksplit) P.o_gpart = take(B * P.ksplit * SS * 4);
-  }
+  P.o_gpart = P.ksplit ? take(B * P.ksplit * SS * 4) : 0;
   P.total = off;
   return PRISM_OK;
 }
@@ -280,6 +309,8 @@ struct Run {
     void* x;                                   // caller's array
     uint16_t* Xhi[2]; uint16_t* Xlo[2];        // iterate [Lp][Sp], double buffered
     bool aliased;                              // buffer 1 is the caller's array
+    double* sumsq; int nsum;                   // partial sums of the Frobenius norms (several groups)
+    int ksplit; float* gpart;                  // parts of the K loop of X^T X (0: one pass) and their products
   };
   std::vector<XGroup> xg;
   int chain_sel_batch = 0;                     // batch size that picks the chain kernels (0: the whole batch)
@@ -435,13 +466,13 @@ int run_polar_f32(Run& r) {
         GemmDesc sp = f32_desc(r, X[cur] + (long long)b * LS, Sp, (long long)Kp * Sp, X[cur] + (long long)b * LS, Sp,
                                (long long)Kp * Sp, Sp, Sp, Kp, 1);
         sp.batch = P.ksplit; sp.epi = EPI_STORE; sp.C = gpart + (long long)b * P.ksplit * SS; sp.strideC = SS; sp.ldc = Sp;
-        sp.ctrl = r.ctrl + b; sp.ctrl_fixed = 1;
+        sp.ctrl = r.ctrl + b; sp.ctrl_parts = P.ksplit;
         CHECK_LAUNCH(launch_gemm_f32(sp, r.s));
       }
       GramReduceArgs ra = {};
-      ra.part = gpart; ra.parts = P.ksplit; ra.np = Sp; ra.n_true = P.S;
-      ra.R32 = R; ra.rho_part = r.rho; ra.ctrl = r.ctrl;
-      launch_gram_reduce(ra, P.batch, r.s);
+      ra.ngroups = 1; ra.part[0] = gpart; ra.parts[0] = P.ksplit; ra.first[1] = P.batch; ra.np = Sp; ra.n_true = P.S;
+      ra.R32 = R; ra.rho_part = r.rho; ra.rho_stride = gram_reduce_parts(Sp); ra.ctrl = r.ctrl;
+      launch_gram_reduce(ra, r.s);
       CHECK_LAUNCH(check_hip());
     } else {
       ProfScope ps(PK_F32_RESID, r.s);
@@ -545,7 +576,9 @@ int run_polar_bf16(Run& r) {
   const bool lean = chain_b && sym && !P.split;
   float* Dg = R;
   const int ntg = Sp / Tg.m;
-  const int nparts = (Tg.m / Tg.n) * ntg * (ntg + 1) / 2;   // tiles (= residual partial sums) per matrix
+  int nparts = (Tg.m / Tg.n) * ntg * (ntg + 1) / 2;   // residual partial sums per matrix: tiles of the Gram product
+  for (const Run::XGroup& x : r.xg)
+    if (x.ksplit && nparts < gram_reduce_parts(Sp)) nparts = gram_reduce_parts(Sp);   // ... or of its second pass
   // launch order of the groups: longest K first, so that the short tiles fill the last round
   int order[BF16_MAX_GROUPS];
   for (int i = 0; i < ng; ++i) order[i] = i;
@@ -554,54 +587,49 @@ int run_polar_bf16(Run& r) {
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
-    if (P.ksplit) {   // single group of a few tall matrices
-      const Run::XGroup& x = r.xg[0];
-      const long long LS = (long long)x.Lp * Sp;
-      ProfScope ps(PK_BF16_GRAM, r.s);
-      const int Kp = x.Lp / P.ksplit;
-      const int T1 = (P.tile == 256 && (long long)(Sp / 256) * (Sp / 256) * P.ksplit >= 256) ? 256 : 128;   // square tiles
-      float* gpart = r.at<float>(P.o_gpart);
-      for (int b = 0; b < P.batch; ++b) {   // the parts of one matrix are the batch of a plain product
-        Bf16Desc sp = {};
-        // part p = rows [p Kp, (p + 1) Kp) of the [Lp][Sp] iterate, read as [K][M]
-        sp.A = x.Xhi[cur] + (long long)b * LS; sp.B = sp.A; sp.strideA = (long long)Kp * Sp; sp.strideB = sp.strideA;
-        sp.lda = Sp; sp.ldb = Sp; sp.km = 3;
-        sp.M = Sp; sp.N = Sp; sp.K = Kp; sp.batch = P.ksplit; sp.epi = BEPI_STORE;
-        sp.C32 = gpart + (long long)b * P.ksplit * SS; sp.strideC32 = SS; sp.ldc32 = Sp;
-        sp.ctrl = r.ctrl + b; sp.ctrl_fixed = 1;
-        CHECK_LAUNCH(launch_gemm_bf16(sp, T1, T1, r.s));
-      }
+    {
+      Bf16Desc gd[BF16_MAX_GROUPS], sd[BF16_MAX_GROUPS];   // one pass, split
+      int n1 = 0, n2 = 0;
       GramReduceArgs ra = {};
-      ra.part = gpart; ra.parts = P.ksplit; ra.np = Sp; ra.n_true = P.S;
-      ra.R32 = lean ? nullptr : R; ra.Rb = Rb; ra.diag = lean ? Dg : nullptr; ra.rho_part = r.rho; ra.ctrl = r.ctrl;
-      launch_gram_reduce(ra, P.batch, r.s);
-      CHECK_LAUNCH(check_hip());
-    } else {
-      Bf16Desc gd[BF16_MAX_GROUPS];
       for (int i = 0; i < ng; ++i) {
         const Run::XGroup& x = r.xg[order[i]];
-        const long long LS = (long long)x.Lp * Sp;
-        Bf16Desc& g = gd[i];
+        Bf16Desc& g = x.ksplit ? sd[n2] : gd[n1++];
         g = Bf16Desc{};
         g.sym = sym;
         // X^T X straight from the [Lp][Sp] iterate: both operands stored [K][M]
-        g.A = x.Xhi[cur]; g.strideA = LS; g.lda = Sp; g.B = x.Xhi[cur]; g.strideB = LS; g.ldb = Sp; g.km = 3;
-        g.M = Sp; g.N = Sp; g.K = x.Lp; g.batch = x.batch; g.epi = BEPI_GRAM; g.n_true = P.S;
+        g.A = x.Xhi[cur]; g.lda = Sp; g.B = x.Xhi[cur]; g.ldb = Sp; g.km = 3;
+        g.M = Sp; g.N = Sp; g.ctrl = r.ctrl + x.boff;
+        if (x.ksplit) {
+          // part p of a matrix = rows [p Kp, (p + 1) Kp) of its iterate: the parts of all matrices are one batch, Kp Sp apart
+          g.K = x.Lp / x.ksplit; g.batch = x.batch * x.ksplit; g.strideA = g.strideB = (long long)g.K * Sp;
+          g.epi = BEPI_STORE; g.C32 = x.gpart; g.strideC32 = SS; g.ldc32 = Sp; g.ctrl_parts = x.ksplit;
+          ra.part[n2] = x.gpart; ra.parts[n2] = x.ksplit; ra.boff[n2] = x.boff; ra.first[n2 + 1] = ra.first[n2] + x.batch;
+          ++n2;
+          continue;
+        }
+        g.K = x.Lp; g.batch = x.batch; g.strideA = g.strideB = (long long)x.Lp * Sp; g.epi = BEPI_GRAM; g.n_true = P.S;
         g.C32 = lean ? nullptr : R + x.boff * SS; g.strideC32 = SS; g.ldc32 = Sp;
         // with the bf16 chain only the R^2 epilogue and the chain's diagonal read the fp32 matrix: both stay
         // inside the tiles the Gram product computes when its tile rows are whole multiples of those of R^2
         g.upper32 = (chain_b && Tg.m % Tq.m == 0) ? 1 : 0;
         g.Cb = Rb + x.boff * SS; g.strideCb = SS; g.ldcb = Sp;
         g.diag = lean ? Dg + (long long)x.boff * Sp : nullptr; g.strideDiag = Sp;
-        g.rho_part = r.rho + (long long)x.boff * nparts; g.ctrl = r.ctrl + x.boff;
+        g.rho_part = r.rho + (long long)x.boff * nparts; g.rho_stride = nparts;
       }
       ProfScope ps(PK_BF16_GRAM, r.s);
-      CHECK_LAUNCH(launch_gemm_bf16_multi(gd, ng, Tg.m, Tg.n, r.s));
+      if (n1) CHECK_LAUNCH(launch_gemm_bf16_multi(gd, n1, Tg.m, Tg.n, r.s));
+      if (n2) {
+        CHECK_LAUNCH(launch_gemm_bf16_multi(sd, n2, 128, 128, r.s));
+        ra.ngroups = n2; ra.np = Sp; ra.n_true = P.S;
+        ra.R32 = lean ? nullptr : R; ra.Rb = Rb; ra.diag = lean ? Dg : nullptr; ra.rho_part = r.rho; ra.rho_stride = nparts;
+        ra.ctrl = r.ctrl;
+        launch_gram_reduce(ra, r.s);
+        CHECK_LAUNCH(check_hip());
+      }
     }
-    const int np = P.ksplit ? gram_reduce_parts(Sp) : nparts;
-    if (lean) CHECK_LAUNCH(r.fit(k, np, R, Rb, Dg, Sp, 1));
-    else if (chain_b) CHECK_LAUNCH(r.fit(k, np, R, Rb, R, SS, Sp + 1));
-    else CHECK_LAUNCH(r.fit(k, np, R));
+    if (lean) CHECK_LAUNCH(r.fit(k, nparts, R, Rb, Dg, Sp, 1));
+    else if (chain_b) CHECK_LAUNCH(r.fit(k, nparts, R, Rb, R, SS, Sp + 1));
+    else CHECK_LAUNCH(r.fit(k, nparts, R));
     if (k == r.max_iters) break;
     const uint16_t* Bop = Rb;
     if (P.d == 2) {   // one launch over the matrices of all groups: R has the same order everywhere
@@ -877,6 +905,10 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   if (empty) return make_plan(r.P, fn, 1, m ? m : 1, n ? n : 1, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u);
   int rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u);
   if (rc != PRISM_OK) return rc;
+  if (r.P.ksplit && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
+    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K);
+    if (rc != PRISM_OK) return rc;
+  }
   r.s = (hipStream_t)stream;
   rc = get_workspace(r.P.total, r.s, opt, &r.ws);
   if (rc != PRISM_OK) return rc;
@@ -909,6 +941,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
       x.Xhi[i] = r.at<uint16_t>(P.o_xhi[i]);
       x.Xlo[i] = P.split ? r.at<uint16_t>(P.o_xlo[i]) : nullptr;
     }
+    x.ksplit = P.ksplit; x.gpart = r.at<float>(P.o_gpart);
     alias_output(P, x);
     r.xg.push_back(x);
     bf16_prep_final(P, x, pa, fa);
@@ -962,9 +995,10 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   long long btot = 0;
   for (int g = 0; g < ngroups; ++g) {
     if (groups[g].batch <= 0 || groups[g].m <= 0 || groups[g].n <= 0 || !groups[g].x) return PRISM_EUNSUPPORTED;   // empty or invalid: per-group path
-    const int rc = make_plan(Pg[g], PRISM_FN_POLAR, groups[g].batch, groups[g].m, groups[g].n, PRISM_BF16, degree, sketch_dim, 0, flags);
+    const int rc = make_plan(Pg[g], PRISM_FN_POLAR, groups[g].batch, groups[g].m, groups[g].n, PRISM_BF16, degree, sketch_dim, 0, flags, false,
+                             groups[g].batch * batch_scale);
     if (rc != PRISM_OK) return rc;
-    if (Pg[g].S != Pg[0].S || Pg[g].Sp != Pg[0].Sp || Pg[g].tile != Pg[0].tile || Pg[g].ksplit) return PRISM_EUNSUPPORTED;
+    if (Pg[g].S != Pg[0].S || Pg[g].Sp != Pg[0].Sp || Pg[g].tile != Pg[0].tile) return PRISM_EUNSUPPORTED;
     // every group must get the chain kernels of its own call (batch_scale: the groups passed in are
     // 1 / batch_scale of the caller's groups each)
     const int bg = groups[g].batch * batch_scale, b0 = groups[0].batch * batch_scale;
@@ -983,13 +1017,15 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   // iterate buffers per group behind the shared part
   size_t off_bytes = P.total;
   auto take = [&](size_t bytes) { size_t o = off_bytes; off_bytes = align256(off_bytes + bytes); return o; };
-  size_t o_xhi[BF16_MAX_GROUPS][2], o_xlo[BF16_MAX_GROUPS][2];
+  size_t o_xhi[BF16_MAX_GROUPS][2], o_xlo[BF16_MAX_GROUPS][2], o_gpart[BF16_MAX_GROUPS], o_sumsq[BF16_MAX_GROUPS];
   for (int g = 0; g < ngroups; ++g) {
     const size_t bytes = (size_t)groups[g].batch * Pg[g].Lp * Pg[g].Sp * 2;
     for (int i = 0; i < 2; ++i) {
       o_xhi[g][i] = take(bytes);
       o_xlo[g][i] = P.split ? take(bytes) : 0;
     }
+    o_sumsq[g] = take((size_t)groups[g].batch * Pg[g].nsum * sizeof(double));
+    o_gpart[g] = Pg[g].ksplit ? take((size_t)groups[g].batch * Pg[g].ksplit * P.Sp * P.Sp * 4) : 0;
   }
   P.total = off_bytes;
   r.s = (hipStream_t)stream;
@@ -1015,6 +1051,8 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
       x.Xhi[i] = r.at<uint16_t>(o_xhi[g][i]);
       x.Xlo[i] = P.split ? r.at<uint16_t>(o_xlo[g][i]) : nullptr;
     }
+    x.ksplit = Pg[g].ksplit; x.gpart = r.at<float>(o_gpart[g]);
+    x.sumsq = r.at<double>(o_sumsq[g]); x.nsum = Pg[g].nsum;
     alias_output(P, x);
     r.xg.push_back(x);
     boff += x.batch;
@@ -1023,7 +1061,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     pa = PrepArgs{}; fa = FinalArgs{};
     pa.fn = PRISM_FN_POLAR; pa.dt = PRISM_BF16; pa.batch = x.batch; pa.m = x.m; pa.n = x.n;
     pa.S = P.S; pa.L = x.L; pa.Sp = P.Sp; pa.Lp = x.Lp; pa.transpose = x.transpose; pa.root_p = 0; pa.src = x.x;
-    pa.sumsq_part = r.at<double>(P.o_sumsq) + (long long)x.boff * P.nsum; pa.nsum = P.nsum;
+    pa.sumsq_part = x.sumsq; pa.nsum = x.nsum;
     pa.ctrl = r.ctrl + x.boff; pa.info = r.info + x.boff; pa.rho_part = r.rho; pa.tile = P.tile;
     pa.sync = r.at<unsigned>(P.o_sync) + (long long)x.boff * FIT_SYNC_WORDS;
     fa.fn = PRISM_FN_POLAR; fa.dt = PRISM_BF16; fa.batch = x.batch; fa.m = x.m; fa.n = x.n;
@@ -1348,6 +1386,8 @@ int prism_polar_static(void* x, int batch, int m, int n, prism_dtype dt, int deg
     Plan P;
     const int rc = make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags);
     if (rc != PRISM_OK) return rc;
+    if (P.ksplit && P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES)   // as the driver does with a workspace of this size
+      (void)make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags | FLAG_NO_SPLIT_K);
     if (P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES) {
       set_last_error("prism_polar_static: this call needs more than PRISM_STATIC_SCRATCH_BYTES of scratch; use prism_polar_ex");
       return PRISM_EUNSUPPORTED;
