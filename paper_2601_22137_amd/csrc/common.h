@@ -205,6 +205,19 @@ struct SmallPolarArgs {
 };
 int launch_small_polar(const SmallPolarArgs& a, int batch, hipStream_t s);
 
+// Coupled inverse Newton iteration (root order up to 4, sketch up to 32 columns) of matrices of padded order 64, likewise.
+struct SmallRootArgs {
+  SolveArgs sv;              // as above; rho_part: residual of M_0
+  float* X[2];               // [batch][64][64]: X_0 in X[0], result left in X[iterations & 1]
+  const double* M;           // M_0
+  const float* R;            // I - M_0
+  const float* V0;           // S_k^T for k = first_fit, first_fit + 1, ...: [.][64][ld]
+  int nv;                    // products in the chain (p + 1)
+  int p_s, first_fit, warm, sched_len;
+  float sched[PRISM_MAX_ITERS];
+};
+int launch_small_root(const SmallRootArgs& a, int batch, hipStream_t s);
+
 // ---- misc.hip ----
 struct PrepArgs {
   int fn; int dt; int batch; int m, n;     // caller's shape

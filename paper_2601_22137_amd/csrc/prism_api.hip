@@ -364,8 +364,11 @@ struct Run {
     return launch_fit(f, P.batch, s);
   }
   bool fused() const {
-    return fit_fused_supported(P.Sp, P.ld, chain_sel_batch ? chain_sel_batch : P.batch) && !small_polar();
+    return fit_fused_supported(P.Sp, P.ld, chain_sel_batch ? chain_sel_batch : P.batch) && !small_polar() && !small_root();
   }
+  // inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
+  // the launches of that are full: 1024 matrices, p = 4, 0.76 against 1.36 ms)
+  bool small_root() const { return P.fn == PRISM_FN_INV_ROOT && P.Sp == 64 && P.p <= 4 && P.ld <= 32; }
   // fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
   bool small_polar() const {
     static const int off = ab_switch("PRISM_NO_SMALL_KERNEL");
@@ -787,6 +790,16 @@ int run_inv_root_f32(Run& r) {
   float* Tm[3] = {r.at<float>(P.o_t[0]), r.at<float>(P.o_t[1]), r.at<float>(P.o_t[2])};
   const int nparts0 = (Sp / 64) * (Sp / 64);  // residual of M_0 comes from the prepare step (64 x 64 tiles)
   const int nparts = (Sp / 64) * (Sp / 64);   // later ones from the fp64 product (64 x 64 tiles)
+  if (r.small_root()) {
+    SmallRootArgs a = {};
+    a.sv = r.solve_args(0, 1, 0);
+    a.sv.last = 0;
+    a.X[0] = X[0]; a.X[1] = X[1]; a.M = M[0]; a.R = R; a.V0 = r.v0; a.nv = P.nv;
+    a.p_s = P.p_s; a.first_fit = r.first_fit; a.warm = r.warm; a.sched_len = r.sched_len;
+    for (int i = 0; i < r.sched_len; ++i) a.sched[i] = r.sched[i];
+    ProfScope ps(PK_F32_APPLY, r.s);
+    return launch_small_root(a, P.batch, r.s);
+  }
   int cur = 0, mc = 0;   // current X and M buffers
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;

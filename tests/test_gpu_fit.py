@@ -1,5 +1,6 @@
 """The one-launch fit (sketch chain, moments, coefficient) against the fp64 oracle: the fitted coefficients of
-the first updates, at both sides of every limit of its variants (order 64, 512, 1024, 2048; 16 and 32 rows
+the first updates, at both sides of every limit of its variants (order 64, which inverse
+roots up to p = 4 spend in one workgroup, 512, 1024, 2048; 16 and 32 rows
 per workgroup; sketches of 16, 32 and 64 columns; the longest chain), and equal bits for equal matrices whatever
 their place in a batch.
 
@@ -26,7 +27,7 @@ def prism():
 
 
 @pytest.mark.parametrize("n,batch,sketch,p", [
-    (40, 3, 16, 4), (64, 5, 40, 4), (65, 2, 16, 4), (130, 2, 32, 2), (512, 1, 16, 4), (512, 17, 8, 4), (513, 1, 16, 4),
+    (40, 3, 16, 4), (64, 2, 8, 1), (33, 2, 32, 2), (64, 300, 16, 3), (7, 1, 16, 4), (64, 5, 40, 4), (50, 2, 16, 5), (65, 2, 16, 4), (130, 2, 32, 2), (512, 1, 16, 4), (512, 17, 8, 4), (513, 1, 16, 4),
     (300, 1, 16, 8), (1000, 1, 32, 4), (1024, 9, 16, 4), (1024, 1, 64, 4), (1025, 1, 16, 4), (2048, 1, 32, 2)])
 def test_inverse_root_coefficients(prism, n, batch, sketch, p):
     A = W.c4_shampoo_spd(n=n, batch=1)
