@@ -136,7 +136,7 @@ __global__ __launch_bounds__(NT) void moments_kernel(SolveArgs a) {
   accumulate_for(a, b, grp, ngrp, a.cpart + ((long long)b * ngrp + grp) * MAXC);
 }
 
-// One workgroup, matrix b: stop rule and coefficient of iteration a.k.  Every return is taken by all
+// One workgroup (NT threads or more), matrix b: stop rule and coefficient of iteration a.k.  Every return is taken by all
 // threads of the workgroup together.
 // rho_local (LDS, one double) stands in for the residual partials in global memory and c_local
 // (LDS, MAXC doubles) for the coefficient partials when the caller has them on chip.
@@ -155,10 +155,10 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
   __shared__ double s_rho[4];
   if (!rho_local) {
     double part = 0.0;
-    for (int i = t; i < a.nparts; i += NT) part += (double)a.rho_part[(long long)b * a.nparts + i];
+    for (int i = t; t < NT && i < a.nparts; i += NT) part += (double)a.rho_part[(long long)b * a.nparts + i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
-    if ((t & 63) == 0) s_rho[t >> 6] = part;
+    if (t < NT && (t & 63) == 0) s_rho[t >> 6] = part;
     __syncthreads();
   }
   if (a.phase == 2) {
