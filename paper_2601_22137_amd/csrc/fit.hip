@@ -136,14 +136,89 @@ __global__ __launch_bounds__(NT) void moments_kernel(SolveArgs a) {
   accumulate_for(a, b, grp, ngrp, a.cpart + ((long long)b * ngrp + grp) * MAXC);
 }
 
+// The root of f in [xa, xb], f(xa) = fa and f(xb) of opposite signs: Newton's method kept inside the bracket [l, h] (f(l) has
+// the sign of fa); a step that would leave the bracket, or that shrinks too slowly, is replaced by a bisection step.
+// eval(x, f, df) gives f and its derivative.
+template <typename E> __device__ inline double bracketed_root(double xa, double xb, double fa, E eval) {
+  double l = xa, h = xb;
+  double x = 0.5 * (l + h), dx = h - l, dxold = dx, fx, dfx;
+  eval(x, fx, dfx);
+  for (int it = 0; it < 200; ++it) {
+    if (fx == 0.0) break;
+    if ((fx < 0.0) == (fa < 0.0)) l = x; else h = x;
+    const bool leaves = !((((x - h) * dfx - fx) * ((x - l) * dfx - fx)) < 0.0);
+    const bool slow = fabs(2.0 * fx) > fabs(dxold * dfx);
+    dxold = dx;
+    double xn;
+    if (leaves || slow) { dx = 0.5 * (h - l); xn = l + dx; }
+    else { dx = fx / dfx; xn = x - dx; }
+    if (xn == x || !(xn > l && xn < h)) break;   // the bracket is down to neighbouring numbers
+    x = xn;
+    if (fabs(dx) <= 2.0e-16 * fabs(x)) break;
+    eval(x, fx, dfx);
+  }
+  return x;
+}
+
+// Minimiser of a quartic on [lo, hi], ties to the smallest: one thread, everything in registers (through LDS, level by
+// level of the derivative chain, the same took 2 us more per iteration in barriers and LDS round trips: one 64 x 32 polar
+// factor 158 -> 139 us, fp32 polar 6 x 500 x 299 760 -> 735).  The roots of
+// m' lie between lo, the roots of m'' (closed form, the larger in magnitude first and the other from their product)
+// and hi.
+__device__ inline double minimise_quartic(double c0, double c1, double c2, double c3, double c4, double lo, double hi) {
+  const double q0 = c1, q1 = 2.0 * c2, q2 = 3.0 * c3, q3 = 4.0 * c4;
+  const double b0 = q1, b1 = 2.0 * q2, b2 = 3.0 * q3;
+  auto value = [&](double x) { return (((c4 * x + c3) * x + c2) * x + c1) * x + c0; };
+  auto slope = [&](double x, double& f, double& df) {
+    f = ((q3 * x + q2) * x + q1) * x + q0;
+    df = (b2 * x + b1) * x + b0;
+  };
+  double e0 = hi, e1 = hi;                     // roots of m'' inside (lo, hi), in order; hi: none
+  if (b2 == 0.0) {
+    if (b1 != 0.0) e0 = -b0 / b1;
+  } else {
+    const double disc = b1 * b1 - 4.0 * b2 * b0;
+    if (disc >= 0.0) {
+      const double q = -0.5 * (b1 + (b1 < 0.0 ? -sqrt(disc) : sqrt(disc)));
+      const double r0 = q / b2, r1 = q != 0.0 ? b0 / q : r0;
+      e0 = r0 < r1 ? r0 : r1;
+      e1 = r0 < r1 ? r1 : r0;
+    }
+  }
+  e0 = e0 < lo ? lo : (e0 > hi ? hi : e0);
+  e1 = e1 < lo ? lo : (e1 > hi ? hi : e1);
+  double best = lo, bestv = value(lo);
+  double xa = lo, fa, df;
+  slope(lo, fa, df);
+  for (int i = 0; i < 3; ++i) {
+    const double xb = i == 0 ? e0 : (i == 1 ? e1 : hi);
+    double fb;
+    slope(xb, fb, df);
+    if ((fa < 0.0) != (fb < 0.0)) {
+      const double x = fa == 0.0 ? xa : (fb == 0.0 ? xb : bracketed_root(xa, xb, fa, slope));
+      const double v = value(x);
+      if (v < bestv) { bestv = v; best = x; }
+    }
+    xa = xb;
+    fa = fb;
+  }
+  const double vh = value(hi);
+  if (vh < bestv) best = hi;
+  return best;
+}
+
 // One workgroup (NT threads or more), matrix b: stop rule and coefficient of iteration a.k.  Every return is taken by all
 // threads of the workgroup together.
 // rho_local (LDS, one double) stands in for the residual partials in global memory and c_local
 // (LDS, MAXC doubles) for the coefficient partials when the caller has them on chip.
-__device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = nullptr, double* c_local = nullptr) {
+// ctl_local (LDS): the matrix's control block, when the caller keeps it on chip.
+__device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = nullptr, double* c_local = nullptr,
+                           Ctrl* ctl_local = nullptr) {
   const int t = threadIdx.x;
-  Ctrl* ctl = &a.ctrl[b];
-  if (ctl->done) return;
+  Ctrl* ctl = ctl_local ? ctl_local : &a.ctrl[b];
+  const int done = ctl->done;
+  const float res0 = ctl->res0, res1 = ctl->res1, res2 = ctl->res2;   // in the shadow of the first load
+  if (done) return;
   prism_info* info = a.info + b;
   __shared__ int s_stop;
   __shared__ double s_c[MAXC];
@@ -171,8 +246,11 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
     if (!(res == res) || res > 1.0e300) status = PRISM_INFO_DIVERGED;
     else if (a.tol > 0.0 && res <= a.tol) status = PRISM_INFO_CONVERGED;
     else if (a.k == a.max_iters) status = PRISM_INFO_BUDGET;
-    else if (a.tol > 0.0 && a.k >= 2 && res > (double)ctl->res1 && ctl->res1 > ctl->res2 && res > (double)ctl->res0)
+    else if (a.tol > 0.0 && a.k >= 2 && res > (double)res1 && res1 > res2 && res > (double)res0)
       status = PRISM_INFO_DIVERGED;
+    // one lane is active, so the status is uniform; told so, the compiler keeps the two sets of stores below apart
+    // (with a branch on the lane's own value it merged their addresses and the report went to the wrong block)
+    status = __builtin_amdgcn_readfirstlane(status);
     if (status >= 0) {
       ctl->status = status;
       ctl->iters = a.k;
@@ -182,7 +260,7 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
       s_stop = 1;
     } else {
       if (a.k == 0) ctl->res0 = (float)res;
-      ctl->res2 = ctl->res1;
+      ctl->res2 = res1;
       ctl->res1 = (float)res;
       ctl->iters = a.k + 1;     // the update of this iteration is already enqueued behind us
       info->iters = a.k + 1;
@@ -271,6 +349,15 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
     if (t == 0) { ctl->alpha = (float)lo; info->alpha[a.k] = (float)lo; }
     return;
   }
+  if (deg == 4) {   // Newton-Schulz family, DB Newton
+    if (t == 0) {
+      const double best = minimise_quartic(s_c[0], s_c[1], s_c[2], s_c[3], s_c[4], lo, hi);
+      ctl->alpha = (float)best;
+      info->alpha[a.k] = (float)best;
+      if (best < hi - 1e-6) ctl->plain = 1;   // as below
+    }
+    return;
+  }
   // derivative chain: s_q[j] = (j+1)-th derivative of m, degree deg-1-j
   if (t == 0) {
     for (int i = 0; i <= dq; ++i) s_q[0][i] = (double)(i + 1) * s_c[i + 1];
@@ -300,27 +387,10 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
       if (fa == 0.0) { found = xa; has = 1; }
       else if (t == nr && fb == 0.0) { found = xb; has = 1; }
       else if ((fa < 0.0) != (fb < 0.0) && fb != 0.0) {
-        // Newton's method kept inside the bracket [l, h] (f(l) has the sign of fa): a step that
-        // would leave the bracket, or that shrinks too slowly, is replaced by a bisection step.
-        // The derivative of level j is level j + 1 of the chain.
-        double l = xa, h = xb;
-        double x = 0.5 * (l + h), dx = h - l, dxold = dx;
-        double fx = horner(s_q[j], pdeg, x), dfx = horner(s_q[j + 1], pdeg - 1, x);
-        for (int it = 0; it < 200; ++it) {
-          if (fx == 0.0) break;
-          if ((fx < 0.0) == (fa < 0.0)) l = x; else h = x;
-          const bool leaves = !((((x - h) * dfx - fx) * ((x - l) * dfx - fx)) < 0.0);
-          const bool slow = fabs(2.0 * fx) > fabs(dxold * dfx);
-          dxold = dx;
-          double xn;
-          if (leaves || slow) { dx = 0.5 * (h - l); xn = l + dx; }
-          else { dx = fx / dfx; xn = x - dx; }
-          if (xn == x || !(xn > l && xn < h)) break;   // the bracket is down to neighbouring numbers
-          x = xn;
-          if (fabs(dx) <= 2.0e-16 * fabs(x)) break;
-          fx = horner(s_q[j], pdeg, x);
-          dfx = horner(s_q[j + 1], pdeg - 1, x);
-        }
+        const double x = bracketed_root(xa, xb, fa, [&](double y, double& f, double& df) {
+          f = horner(s_q[j], pdeg, y);
+          df = horner(s_q[j + 1], pdeg - 1, y);   // the derivative of level j is level j + 1 of the chain
+        });
         found = x;
         has = 1;
       }
@@ -436,10 +506,12 @@ __global__ __launch_bounds__(NT) void small_polar_kernel(SmallPolarArgs a) {
   __shared__ double s_part[4];
   __shared__ double s_rho;
   __shared__ double s_coef[MAXC];
+  __shared__ Ctrl s_ctl;             // the control block: in memory, every iteration would wait for it several times
   const int b = blockIdx.x, t = threadIdx.x;
   SolveArgs sv = a.sv;
-  Ctrl* ctl = &sv.ctrl[b];
-  if (ctl->done) return;   // zero or non-finite input: reported by the prepare step
+  if (sv.ctrl[b].done) return;   // zero or non-finite input: reported by the prepare step
+  if (t == 0) s_ctl = sv.ctrl[b];
+  Ctrl* ctl = &s_ctl;
   if (sv.ld == 16) { sv.V = Ts + SN * 16; sv.vstride = SN * 16; sv.bstride = 0; }
   const int lane = t & 63, wave = t >> 6, lr = lane & 15, lk = lane >> 4;
   const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;   // this wave's quadrant of a 64 x 64 result
@@ -513,8 +585,7 @@ __global__ __launch_bounds__(NT) void small_polar_kernel(SmallPolarArgs a) {
     sv.k = k;
     sv.mode = k < a.sched_len ? 3 : (a.p_s == 0 ? 1 : (k < a.warm ? 2 : 0));
     sv.sched_alpha = k < a.sched_len ? a.sched[k] : 0.0f;
-    solve_body(sv, b, &s_rho, s_coef);
-    __threadfence_block();
+    solve_body(sv, b, &s_rho, s_coef, ctl);
     __syncthreads();
     if (ctl->done) break;
     const float alpha = ctl->alpha;
@@ -551,6 +622,7 @@ __global__ __launch_bounds__(NT) void small_polar_kernel(SmallPolarArgs a) {
     __syncthreads();
   }
   {
+    if (t == 0) sv.ctrl[b] = s_ctl;
     float* Xg = a.X[ctl->iters & 1] + (long long)b * SN * SN;
     for (int idx = t; idx < SN * SN / 4; idx += NT) {
       const int r = idx >> 4, c = (idx & 15) * 4;
@@ -581,10 +653,12 @@ __global__ __launch_bounds__(NT) void small_root_kernel(SmallRootArgs a) {
   __shared__ double s_part[4];
   __shared__ double s_rho;
   __shared__ double s_coef[MAXC];
+  __shared__ Ctrl s_ctl;             // the control block: in memory, every iteration would wait for it several times
   const int b = blockIdx.x, t = threadIdx.x;
   SolveArgs sv = a.sv;
-  Ctrl* ctl = &sv.ctrl[b];
-  if (ctl->done) return;   // zero or non-finite input: reported by the prepare step
+  if (sv.ctrl[b].done) return;   // zero or non-finite input: reported by the prepare step
+  if (t == 0) s_ctl = sv.ctrl[b];
+  Ctrl* ctl = &s_ctl;
   const int lane = t & 63, wave = t >> 6, lr = lane & 15, lk = lane >> 4, ld = sv.ld;
   const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
   sv.V = Ts + SN * ld; sv.vstride = SN * ld; sv.bstride = 0;
@@ -622,8 +696,7 @@ __global__ __launch_bounds__(NT) void small_root_kernel(SmallRootArgs a) {
     sv.k = k;
     sv.mode = k < a.sched_len ? 3 : (a.p_s == 0 ? 1 : (k < a.warm ? 2 : 0));
     sv.sched_alpha = k < a.sched_len ? a.sched[k] : 0.0f;
-    solve_body(sv, b, &s_rho, s_coef);
-    __threadfence_block();
+    solve_body(sv, b, &s_rho, s_coef, ctl);
     __syncthreads();
     if (ctl->done || k == sv.max_iters) break;
     const float alpha = ctl->alpha;
@@ -705,6 +778,7 @@ __global__ __launch_bounds__(NT) void small_root_kernel(SmallRootArgs a) {
     if (t == 0) s_rho = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
     __syncthreads();
   }
+  if (t == 0) sv.ctrl[b] = s_ctl;
   float* Xg = a.X[ctl->iters & 1] + (long long)b * SN * SN;
   for (int idx = t; idx < SN * SN / 4; idx += NT) {
     const int r = idx >> 4, c = (idx & 15) * 4;
