@@ -63,11 +63,16 @@ struct GemmDesc {
   const Ctrl* ctrl;     // may be null (test entry points)
 };
 
+// Two products of the same shape and kind in one launch: workgroups [0, first) belong to the first
+struct GemmPair { GemmDesc d[2]; int first; };
+
 // tile: 64 or 128 (square tiles), or skinny N (16/32/64) with tile_m 64/128 for the sketch chain
 int launch_gemm_f32(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s);
 // square tiles chosen from the size of the launch (M, N multiples of 64); f32_tiles: tiles of one matrix then
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s);
 int f32_tiles(int M, int N, int batch, int sym);
+// both products in one launch: same M, N, K, batch, epilogue, symmetry and operand layout
+int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
 int launch_gemm_f64a(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s);  // A float, B/C double
 
 // ---- gemm_bf16.hip : bf16 matrix-core NT GEMMs (both operands K-contiguous) ----

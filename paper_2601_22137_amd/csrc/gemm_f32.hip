@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include <cstdlib>
+#include <initializer_list>
 
 #include "common.h"
 
@@ -102,8 +103,17 @@ template <typename E, int T> struct KMajor {
 };
 
 // ST: slabs in the ring.  Two workgroups per CU with 128 x 128 tiles (register bound), more with small ones.
-template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int ST, int EPI, bool A_KM, bool SYM>
-__global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kernel(GemmDesc g) {
+// PAIR: two products in a launch (a variant of its own: choosing the descriptor costs every launch 1 to 2 us).
+template <bool PAIR> struct GemmArg { typedef GemmDesc type; };
+template <> struct GemmArg<true> { typedef GemmPair type; };
+template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int ST, int EPI, bool A_KM, bool SYM, bool PAIR>
+__global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kernel(typename GemmArg<PAIR>::type arg) {
+  int wg0 = 0, which = 0;
+  if constexpr (PAIR) {
+    which = (int)blockIdx.x >= arg.first;   // uniform
+    wg0 = which ? arg.first : 0;
+  }
+  const GemmDesc& g = [&]() -> const GemmDesc& { if constexpr (PAIR) return arg.d[which]; else return arg; }();
   constexpr int WTM = TM / WGM, WTN = TN / WGN;  // wave tile
   constexpr int BM = WTM / 16, BN = WTN / 16;    // 16x16 blocks per wave
   static_assert(WGM * WGN == 4 && BM >= 1 && BN >= 1 && TM >= 64, "bad tiling");
@@ -121,7 +131,7 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
   const int tiles_m = g.M / TM, tiles_n = g.N / TN;
   const int per_mat = SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int total = per_mat * g.batch;
-  int wg = blockIdx.x;
+  int wg = (int)blockIdx.x - wg0;
   if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);  // one XCD = one contiguous tile range
   const int b = wg / per_mat;
   const int rem = wg - b * per_mat;
@@ -437,50 +447,63 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
   }
 }
 
+// One product, or two of the same shape and kind (GemmPair::d[1].batch > 0)
 template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int EPI, bool A_KM, bool SYM>
-int launch_one(const GemmDesc& g, int total, hipStream_t s) {
+int launch_one(const GemmPair& g, int total, hipStream_t s) {
   constexpr int ST = 4;
   const size_t lds = (size_t)ST * (TM * 64 + KMajor<TB, TN>::BYTES);
-  const auto kern = gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM>;
-  if (lds > 32 * 1024) {
-    const int rc = allow_dynamic_lds((const void*)kern, (int)lds);
-    if (rc != PRISM_OK) return rc;
-  }
-  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, g);
-  return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+  auto launch = [&](auto kern, int wgs, const auto& arg) -> int {
+    if (lds > 32 * 1024) {
+      const int rc = allow_dynamic_lds((const void*)kern, (int)lds);
+      if (rc != PRISM_OK) return rc;
+    }
+    hipLaunchKernelGGL(kern, dim3(wgs), dim3(NT), lds, s, arg);
+    return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+  };
+  if (g.d[1].batch == 0) return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, false>, total, g.d[0]);
+  if constexpr (sizeof(TC) == 4 && EPI == EPI_AXPY && !A_KM)
+    return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, true>, 2 * total, g);
+  return PRISM_EINVAL;
 }
 
 template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int EPI>
-int launch_epi(const GemmDesc& g, int total, hipStream_t s) {
+int launch_epi(const GemmPair& g, int total, hipStream_t s) {
   if constexpr (sizeof(TC) == 8) {
     return launch_one<TC, TB, TM, TN, WGM, WGN, EPI, false, false>(g, total, s);
   } else {
     if constexpr (TM == TN) {
-      if (g.sym) {
-        return g.a_km ? launch_one<TC, TB, TM, TN, WGM, WGN, EPI, true, true>(g, total, s)
+      if (g.d[0].sym) {
+        return g.d[0].a_km ? launch_one<TC, TB, TM, TN, WGM, WGN, EPI, true, true>(g, total, s)
                       : launch_one<TC, TB, TM, TN, WGM, WGN, EPI, false, true>(g, total, s);
       }
     }
-    return g.a_km ? launch_one<TC, TB, TM, TN, WGM, WGN, EPI, true, false>(g, total, s)
+    return g.d[0].a_km ? launch_one<TC, TB, TM, TN, WGM, WGN, EPI, true, false>(g, total, s)
                   : launch_one<TC, TB, TM, TN, WGM, WGN, EPI, false, false>(g, total, s);
   }
 }
 
 template <typename TC, typename TB, int TM, int TN, int WGM, int WGN>
-int launch_cfg(const GemmDesc& g, hipStream_t s) {
-  if (g.M % TM || g.N % TN || g.K % BK || g.K < BK || g.lda % 4 || g.ldb % 4 || g.ldc % 4) return PRISM_EINVAL;
-  if ((g.epi == EPI_POLYQ || g.epi == EPI_AXPY) && (!g.Cin || g.ldcin % 4)) return PRISM_EINVAL;
+int launch_cfg(const GemmDesc& g, hipStream_t s, const GemmDesc* g2 = nullptr) {
+  for (const GemmDesc* q : {&g, g2}) {
+    if (!q) continue;
+    if (q->M % TM || q->N % TN || q->K % BK || q->K < BK || q->lda % 4 || q->ldb % 4 || q->ldc % 4) return PRISM_EINVAL;
+    if ((q->epi == EPI_POLYQ || q->epi == EPI_AXPY) && (!q->Cin || q->ldcin % 4)) return PRISM_EINVAL;
+  }
+  if (g2 && (g2->M != g.M || g2->N != g.N || g2->batch != g.batch || g2->epi != g.epi || g2->a_km != g.a_km || g2->sym != g.sym)) return PRISM_EINVAL;
   const int tm = g.M / TM, tn = g.N / TN;
-  GemmDesc gb = g;
+  GemmPair gb = {};
+  gb.d[0] = g;
+  if (g2) gb.d[1] = *g2;
   long long total = (long long)tm * tn * g.batch;
   if (g.sym) {
     if (TM != TN || sizeof(TC) == 8 || g.M != g.N) return PRISM_EINVAL;
     total = (long long)tm * (tm + 1) / 2 * g.batch;
   } else {
     static const int no_blocks = ab_switch("PRISM_F32_NO_TILE_BLOCKS");
-    gb.tile_blocks = !no_blocks && tm % 8 == 0 && tn % 8 == 0 && tm * tn > 64;
+    gb.d[0].tile_blocks = gb.d[1].tile_blocks = !no_blocks && tm % 8 == 0 && tn % 8 == 0 && tm * tn > 64;
   }
-  if (total <= 0 || total > 0x7fffffff) return PRISM_EINVAL;
+  if (total <= 0 || total > 0x3fffffff) return PRISM_EINVAL;
+  gb.first = (int)total;
   if constexpr (sizeof(TC) == 8) {
     if (g.epi == EPI_STORE) return launch_epi<TC, TB, TM, TN, WGM, WGN, EPI_STORE>(gb, (int)total, s);
     if (g.epi == EPI_MNEXT) return launch_epi<TC, TB, TM, TN, WGM, WGN, EPI_MNEXT>(gb, (int)total, s);
@@ -530,6 +553,11 @@ int f32_tiles(int M, int N, int batch, int sym) {   // tiles per matrix, i.e. re
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s) {
   const int T = f32_tile(g.M, g.N, g.batch, g.sym);
   return launch_gemm_f32(g, T, T, s);
+}
+
+int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
+  const int T = f32_tile(a.M, a.N, 2 * a.batch, a.sym);
+  return T == 128 ? launch_cfg<float, float, 128, 128, 2, 2>(a, s, &b) : launch_cfg<float, float, 64, 64, 2, 2>(a, s, &b);
 }
 
 int launch_gemm_f64a(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s) {

@@ -698,11 +698,10 @@ int run_sqrt_f32(Run& r) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, Pm, Sp, SS, Sp, Sp, Sp, 0);        // X + X Q
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     GemmDesc ay = f32_desc(r, Pm, Sp, SS, Y[cur], Sp, SS, Sp, Sp, Sp, 0);        // Y + Q Y
     ay.epi = EPI_AXPY; ay.C = Y[cur ^ 1]; ay.strideC = SS; ay.ldc = Sp; ay.Cin = Y[cur]; ay.strideCin = SS; ay.ldcin = Sp;
     ay.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32_pair(ax, ay, r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -768,11 +767,10 @@ int run_sqrt_newton_f32(Run& r) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, N, Sp, SS, Sp, Sp, Sp, 0);
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.cin_one_minus_alpha = 1; ax.coef_is_alpha = 1; ax.sym = sym;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
     GemmDesc ay = f32_desc(r, Y[cur], Sp, SS, N, Sp, SS, Sp, Sp, Sp, 0);
     ay.epi = EPI_AXPY; ay.C = Y[cur ^ 1]; ay.strideC = SS; ay.ldc = Sp; ay.Cin = Y[cur]; ay.strideCin = SS; ay.ldcin = Sp;
     ay.cin_one_minus_alpha = 1; ay.coef_is_alpha = 1; ay.sym = sym;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ay, r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32_pair(ax, ay, r.s)); }
     { ProfScope ps(PK_DB_UPDATE_M, r.s); launch_db_update_m(M, N, Sp, P.S, P.batch, r.ctrl, r.rho, nparts, r.s); }
     CHECK_LAUNCH(check_hip());
     cur ^= 1;
@@ -807,8 +805,15 @@ int run_inv_root_f32(Run& r) {
     if (k == r.max_iters) break;
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
-    ax.coef_is_alpha = 1; ax.sym = f32_sym();   // X never re-enters M; the power chain below keeps all tiles
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
+    ax.coef_is_alpha = 1;
+    // The update of X and the first square of the chain below depend on R alone.  Where neither fills the chip they share a
+    // launch (all tiles of both); otherwise X goes by itself, on its upper triangle of tiles (X never re-enters M).
+    const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * P.batch <= 1024;
+    if (!paired) {
+      ax.sym = f32_sym();
+      ProfScope ps(PK_F32_APPLY, r.s);
+      CHECK_LAUNCH(launch_gemm_f32(ax, r.s));
+    }
     // (I + alpha R)^q = I + E_q, built on the part beyond the identity so that fp32 rounding acts
     // on the small quantity only: E_1 = alpha R, squaring E <- 2E + E E, times T: E <- E + E_1 + E E_1.
     // E_1 itself is never stored: wherever it is an operand R stands in and the epilogue supplies
@@ -819,7 +824,7 @@ int run_inv_root_f32(Run& r) {
       sq.epi = EPI_AXPY; sq.C = dst; sq.strideC = SS; sq.ldc = Sp; sq.Cin = Eop; sq.strideCin = SS; sq.ldcin = Sp; sq.c_in = 2.0f;
       if (!E) { sq.cin_alpha_pow = 1; sq.coef_is_alpha = 2; }
       ProfScope ps(PK_F32_STORE, r.s);
-      return launch_gemm_f32(sq, r.s);
+      return !E && paired ? launch_gemm_f32_pair(ax, sq, r.s) : launch_gemm_f32(sq, r.s);
     };
     auto times_t = [&](const float* U, float* dst) -> int {                      // U + alpha R + alpha U R
       GemmDesc mu = f32_desc(r, U, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
