@@ -131,7 +131,11 @@ enum {
    * then runs its groups, or the one launch sequence over all of them, one after the other; a
    * single-shape call is not split into half batches).  Results unchanged.  For callers that time
    * kernels one by one or must not have work on streams they do not own. */
-  PRISM_FLAG_SINGLE_STREAM = 4u
+  PRISM_FLAG_SINGLE_STREAM = 4u,
+  /* For tests, results unchanged.  The workgroups that fit alpha_k for one matrix wait for each other's
+   * rows of the sketch chain for a bounded time and then compute what is missing themselves (the
+   * others may find no place on the GPU beside other work).  With this flag they never wait. */
+  PRISM_FLAG_FIT_NO_WAIT = 8u
 };
 
 typedef struct {

@@ -181,7 +181,10 @@ void launch_solve(const SolveArgs& a, int batch, hipStream_t s);
 
 // The sketch chain, the moments and the solve of one iteration in one launch (fit_kernel), for matrices of padded
 // order up to 2048 (fit_fused_supported).
-constexpr int FIT_SYNC_WORDS = 32;   // one counter per matrix, 128 bytes apart; zero between launches
+constexpr int FIT_MAX_CLUSTER = 64;                       // workgroups per matrix
+constexpr int FIT_SYNC_WORDS = FIT_MAX_CLUSTER + 32;      // per matrix: products done by block of rows, and a counter on a cache line of its own
+constexpr int FIT_EPOCH = 16;                             // more than the products of one launch
+constexpr int FIT_POLLS = 128;                            // a microsecond or two each
 struct FitArgs {
   SolveArgs sv;              // mode 0; ngroups = rows / 16 partial coefficient sums per matrix
   const void* R;             // [batch][rows][ldr] fp32, or its bf16 copy (b16) with the exact diagonal in D
@@ -189,8 +192,10 @@ struct FitArgs {
   int b16;
   const float* D; long long strideD; int ldd;
   const float* V0;           // S_k^T in blocks (see launch_sketch)
-  float* V;                  // scratch: 2 x [batch][rows][ld]
-  unsigned* sync;            // [batch][FIT_SYNC_WORDS]
+  float* V;                  // scratch: (nv - 1) x [batch][rows][ld]
+  unsigned* sync;            // [batch][FIT_SYNC_WORDS], zero before the first launch of a call
+  unsigned epoch;            // FIT_EPOCH * iteration
+  int polls;                 // after this many a workgroup computes itself what it waits for
   int nv;
 };
 bool fit_fused_supported(int rows, int ld, int batch);

@@ -800,10 +800,15 @@ __global__ __launch_bounds__(NT) void small_root_kernel(SmallRootArgs a) {
 // (agent scope), and a wave has seen its stores complete (vmcnt) before its workgroup
 // counts itself in.  Agent-scope fences instead write back and invalidate whole L2s: 8 to 25 us per hand-over
 // with 256 workgroups.
-// Every wait ends: workgroups are dispatched in order, so in every hardware queue at most one cluster is resident in
-// part (G <= 64 workgroups, at most 8 per XCD) and all others run to their end and make room for it.  The
-// wait is bounded all the same; running out marks the matrix as diverged.
-//   V_0 .. V_{nv-1} in memory, V_1 on in two slots by turns: [n / 16][LD / 16][lane][4], lane (lr, lq) with rows 4 lq + r,
+// Nobody depends on a workgroup that is not running: a wait is bounded (a.polls), and a workgroup whose partners' rows
+// are still missing then (they may have no place on the chip: other launches, fewer CUs) computes those rows itself,
+// block by block, with the same sums in the same order.  The partner writes the same bits again when it gets to run:
+// every V_j has memory of its own, and what it reads has not changed.  Behind the chain nobody waits.
+// sync: per matrix and block of rows the last product done, counted through all launches of a call (epoch + j; zeroed by
+// the prepare step); and a counter of the products that workgroups have done for their own rows.  G j of them: all rows of
+// V_j are there, because a workgroup goes on to product j + 1 only when they are.  The counter is what is polled (all
+// flags of a matrix at every poll: 1 us more per product).
+//   V_0 .. V_{nv-1} in memory: [n / 16][LD / 16][lane][4], lane (lr, lq) with rows 4 lq + r,
 //   r = 0..3, of column lr of the 16 x 16 block: what a lane holds of a product's result is its operand of the next, and a
 //   wave moves 1 KiB without gaps.
 // The order of all sums is a function of n and the sketch width alone (the moments are kept per 16 rows), so the bits
@@ -885,8 +890,6 @@ __device__ __noinline__ void block_moments_for(int fn, int p, int d, const float
   }
 }
 
-constexpr int FIT_SPIN_LIMIT = 1 << 23;   // polls of a microsecond or so
-
 // KW waves, each with every KW-th chunk of 64 k, NCH chunks at most (n <= 64 KW NCH)
 template <bool B16, int LD, int RB, int NCH, int KW>
 __global__ __launch_bounds__(64 * KW, !B16 && RB * NCH * LD >= 256 ? 1 : 2) void fit_kernel(FitArgs a) {
@@ -897,145 +900,165 @@ __global__ __launch_bounds__(64 * KW, !B16 && RB * NCH * LD >= 256 ? 1 : 2) void
   f32x4 (*red)[NQ][64] = (f32x4 (*)[NQ][64])fit_lds;          // [KW] partial sums
   float* own = fit_lds + KW * NQ * 256;                       // [nv][ROWS][LD]: this workgroup's rows of V_1 .. V_nv
   __shared__ float dfix[ROWS];
-  __shared__ int s_go;
+  __shared__ int s_next;
   const SolveArgs& sv = a.sv;
-  const int b = blockIdx.y, G = gridDim.x, n = sv.rows;
+  const int b = blockIdx.y, G = gridDim.x, n = sv.rows, mine = blockIdx.x;
   if (sv.ctrl[b].done) return;
   const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int row0 = blockIdx.x * ROWS, nchunks = n / 64;
+  const int nchunks = n / 64;
   typedef typename RRow<B16>::elem elem;
-  const elem* R = (const elem*)a.R + (long long)b * a.strideR + (long long)row0 * a.ldr;
   RRow<B16> ra[RB][NCH][4];
+  auto load_rows = [&](int row0) {
+    const elem* R = (const elem*)a.R + (long long)b * a.strideR + (long long)row0 * a.ldr;
 #pragma unroll
-  for (int i = 0; i < NCH; ++i)
-    if (w + KW * i < nchunks) {
+    for (int i = 0; i < NCH; ++i)
+      if (w + KW * i < nchunks) {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) ra[rb][i][s].load(R + (16 * rb + lr) * a.ldr + (w + KW * i) * 64 + 16 * s + 4 * lq);
+          for (int s = 0; s < 4; ++s) ra[rb][i][s].load(R + (16 * rb + lr) * a.ldr + (w + KW * i) * 64 + 16 * s + 4 * lq);
+      }
+    if (B16 && t < ROWS) {   // exact diagonal minus the rounded one
+      const unsigned short h = ((const unsigned short*)R)[t * a.ldr + row0 + t];
+      dfix[t] = a.D[(long long)b * a.strideD + (long long)(row0 + t) * a.ldd] - __uint_as_float((unsigned)h << 16);
     }
-  if (B16 && t < ROWS) {   // exact diagonal minus the rounded one
-    const unsigned short h = ((const unsigned short*)R)[t * a.ldr + row0 + t];
-    dfix[t] = a.D[(long long)b * a.strideD + (long long)(row0 + t) * a.ldd] - __uint_as_float((unsigned)h << 16);
-  }
-  if (B16) __syncthreads();
-  unsigned* sync = a.sync + (long long)b * FIT_SYNC_WORDS;
+    if (B16) __syncthreads();
+  };
+  int held = mine;              // whose rows of R the registers hold
+  load_rows(mine * ROWS);
+  unsigned* done = a.sync + (long long)b * FIT_SYNC_WORDS;   // products done, by block of rows
+  unsigned* count = done + FIT_MAX_CLUSTER;                   // ... and counted over the workgroups, each for its own rows
+  const int vbytes = n * LD * 4;
 #pragma unroll 1
   for (int j = 1; j <= a.nv; ++j) {
-    const float* Vin = j == 1 ? a.V0 : a.V + ((long long)(j & 1) * gridDim.y + b) * n * LD;        // V_{j-1}, [LD][n]
-    float* Vout = a.V + ((long long)((j + 1) & 1) * gridDim.y + b) * n * LD;
-    const int vbytes = n * LD * 4;
-    if constexpr (B16) {   // widened at each use: the compiler would keep the fp32 values of all products instead
+    const float* Vin = j == 1 ? a.V0 : a.V + ((long long)(j - 2) * gridDim.y + b) * n * LD;        // V_{j-1}
+    float* Vout = a.V + ((long long)(j - 1) * gridDim.y + b) * n * LD;
+#pragma unroll 1
+    for (int blk = mine; blk >= 0;) {   // this workgroup's rows, then others that are missing
+      const int row0 = blk * ROWS;
+      if (blk != held) { held = blk; load_rows(row0); }
+      if constexpr (B16) {   // widened at each use: the compiler would keep the fp32 values of all products instead
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int i = 0; i < NCH; ++i)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(ra[rb][i][s].v));
+      }
+      f32x4 acc[RB][NBLK][NACC];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int i = 0; i < NCH; ++i)
+        for (int q = 0; q < NBLK; ++q)
 #pragma unroll
-          for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(ra[rb][i][s].v));
-    }
-    f32x4 acc[RB][NBLK][NACC];
+          for (int u = 0; u < NACC; ++u) acc[rb][q][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 vf[2][CG][NBLK][4];
+      auto request = [&](int i0) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+        for (int i = 0; i < CG; ++i)
+          if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
 #pragma unroll
-      for (int q = 0; q < NBLK; ++q)
+            for (int q = 0; q < NBLK; ++q)
 #pragma unroll
-        for (int u = 0; u < NACC; ++u) acc[rb][q][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 vf[2][CG][NBLK][4];
-    auto request = [&](int i0) {
-#pragma unroll
-      for (int i = 0; i < CG; ++i)
-        if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
-#pragma unroll
-          for (int q = 0; q < NBLK; ++q)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) vf[(i0 / CG) & 1][i][q][s] = load_shared16(Vin, vbytes, (((w + KW * (i0 + i)) * 4 + s) * NBLK + q) * 1024 + lane * 16);
-        }
-    };
-    request(0);
-#pragma unroll
-    for (int i0 = 0; i0 < NCH; i0 += CG) {
-      if (i0 + CG < NCH) request(i0 + CG);
-#pragma unroll
-      for (int i = 0; i < CG; ++i)
-        if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-              for (int q = 0; q < NBLK; ++q)
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-                  acc[rb][q][(4 * s + e) % NACC] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                      ra[rb][i0 + i < NCH ? i0 + i : 0][s].get(e), vf[(i0 / CG) & 1][i][q][s][e], acc[rb][q][(4 * s + e) % NACC], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int q = 0; q < NBLK; ++q) {
-#pragma unroll
-        for (int h = NACC / 2; h > 0; h >>= 1)
-#pragma unroll
-          for (int u = 0; u < h; ++u) acc[rb][q][u] += acc[rb][q][u + h];
-        red[w][rb * NBLK + q][lane] = acc[rb][q][0];
-      }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < (NQ + KW - 1) / KW; ++i) {
-      const int x = w + KW * i;
-      if (x < NQ) {
-        const int row = 16 * (x / NBLK) + 4 * lq, col = 16 * (x % NBLK) + lr;
-        f32x4 v = (red[0][x][lane] + red[1][x][lane]) + (red[2][x][lane] + red[3][x][lane]);
-        if constexpr (KW == 8) v += (red[4][x][lane] + red[5][x][lane]) + (red[6][x][lane] + red[7][x][lane]);
-        if (B16) {
-          f32x4 prev;
-          if (j == 1) prev = *(const f32x4*)(a.V0 + (row0 / 16 * NBLK + x) * 256 + lane * 4);
-          else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) prev[r] = own[((j - 2) * ROWS + row + r) * LD + col];
+              for (int s = 0; s < 4; ++s) vf[(i0 / CG) & 1][i][q][s] = load_shared16(Vin, vbytes, (((w + KW * (i0 + i)) * 4 + s) * NBLK + q) * 1024 + lane * 16);
           }
+      };
+      request(0);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] += dfix[row + r] * prev[r];
-        }
-        if (j < a.nv) store_shared16(Vout, vbytes, (row0 / 16 * NBLK + x) * 1024 + lane * 16, v);
+      for (int i0 = 0; i0 < NCH; i0 += CG) {
+        if (i0 + CG < NCH) request(i0 + CG);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) own[((j - 1) * ROWS + row + r) * LD + col] = v[r];
+        for (int i = 0; i < CG; ++i)
+          if (i0 + i < NCH && w + KW * (i0 + i) < nchunks) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                  for (int rb = 0; rb < RB; ++rb)
+                    acc[rb][q][(4 * s + e) % NACC] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        ra[rb][i0 + i < NCH ? i0 + i : 0][s].get(e), vf[(i0 / CG) & 1][i][q][s][e], acc[rb][q][(4 * s + e) % NACC], 0, 0, 0);
+          }
       }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have reached memory
-    __syncthreads();
-    if (j < a.nv && G > 1) {
-      if (t == 0) {
-        __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int go = 0;
-        for (int i = 0; i < FIT_SPIN_LIMIT && !go; ++i) {
-          go = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (unsigned)(G * j);
-          if (!go) __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int q = 0; q < NBLK; ++q) {
+#pragma unroll
+          for (int h = NACC / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int u = 0; u < h; ++u) acc[rb][q][u] += acc[rb][q][u + h];
+          red[w][rb * NBLK + q][lane] = acc[rb][q][0];
         }
-        s_go = go;
-        if (!go) {
-          sv.ctrl[b].status = PRISM_INFO_DIVERGED; sv.ctrl[b].iters = sv.k; sv.ctrl[b].done = 1;
-          sv.info[b].status = PRISM_INFO_DIVERGED; sv.info[b].iters = sv.k;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < (NQ + KW - 1) / KW; ++i) {
+        const int x = w + KW * i;
+        if (x < NQ) {
+          const int row = 16 * (x / NBLK) + 4 * lq, col = 16 * (x % NBLK) + lr;
+          f32x4 v = (red[0][x][lane] + red[1][x][lane]) + (red[2][x][lane] + red[3][x][lane]);
+          if constexpr (KW == 8) v += (red[4][x][lane] + red[5][x][lane]) + (red[6][x][lane] + red[7][x][lane]);
+          const int vo = (row0 / 16 * NBLK + x) * 1024 + lane * 16;   // these entries in V
+          if (B16) {
+            f32x4 prev;
+            if (j == 1 || blk != mine) prev = load_shared16(Vin, vbytes, vo);
+            else {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) prev[r] = own[((j - 2) * ROWS + row + r) * LD + col];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] += dfix[row + r] * prev[r];
+          }
+          if (j < a.nv) store_shared16(Vout, vbytes, vo, v);
+          if (blk == mine) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) own[((j - 1) * ROWS + row + r) * LD + col] = v[r];
+          }
         }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have reached memory
+      __syncthreads();
+      if (j == a.nv || G == 1) break;
+      if (w == 0) {
+        const unsigned want = a.epoch + j;
+        int next = -1;
+        if (lane == 0) {
+          __hip_atomic_fetch_max(done + blk, want, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (blk == mine) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          bool all = false;
+          for (int i = blk == mine ? a.polls : 0; i > 0 && !all; --i) {
+            all = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (unsigned)(G * j);
+            if (!all) __builtin_amdgcn_s_sleep(1);
+          }
+          next = all ? -1 : 0;
+        }
+        if (__builtin_amdgcn_readfirstlane(next) == 0) {   // whose rows are missing?  The next behind this workgroup's own, round about
+          const unsigned have = lane < G ? __hip_atomic_load(done + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want;
+          u64 missing = __ballot(have < want && lane != mine && lane != blk);
+          missing = missing >> mine | missing << ((64 - mine) & 63);
+          next = missing ? (mine + __builtin_ctzll(missing)) & 63 : -1;
+        }
+        if (lane == 0) s_next = next;
       }
       __syncthreads();
-      if (!s_go) return;
+      blk = __builtin_amdgcn_readfirstlane(s_next);
     }
   }
   for (int rb = w; rb < RB; rb += KW)
     block_moments_for(sv.fn, sv.p, sv.d, own + rb * 16 * LD, ROWS * LD, 16 * LD,
-                      sv.cpart + ((long long)b * sv.ngroups + row0 / 16 + rb) * MAXC);
+                      sv.cpart + ((long long)b * sv.ngroups + mine * RB + rb) * MAXC);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (t == 0) {
-    const unsigned before = G > 1 ? __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    s_go = G == 1 || before == (unsigned)(G * a.nv - 1);
-    if (s_go && G > 1) __hip_atomic_store(sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    const int last = G == 1 || __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(G * a.nv - 1);
+    if (last && G > 1) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    s_next = last;
   }
   __syncthreads();
-  if (!s_go) return;
+  if (!s_next) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the partials of the others
   solve_body(sv, b);
 }
@@ -1043,6 +1066,7 @@ __global__ __launch_bounds__(64 * KW, !B16 && RB * NCH * LD >= 256 ? 1 : 2) void
 template <bool B16, int LD, int RB, int NCH, int KW>
 int launch_fit_t(const FitArgs& a, int batch, hipStream_t s) {
   const int rows = 16 * RB;
+  if (a.sv.rows % rows || a.sv.rows / rows > FIT_MAX_CLUSTER || a.sv.rows > 64 * KW * NCH) return PRISM_EINVAL;
   const size_t lds = ((size_t)RB * (LD / 16) * KW * 256 + (size_t)a.nv * rows * LD) * sizeof(float);
   const auto kern = fit_kernel<B16, LD, RB, NCH, KW>;
   if (lds > 48 * 1024) {
@@ -1080,7 +1104,7 @@ bool fit_fused_supported(int rows, int ld, int batch) {
 }
 
 int launch_fit(const FitArgs& a, int batch, hipStream_t s) {
-  if (a.sv.rows % 64 || a.sv.rows > (a.sv.ld <= 32 ? 2048 : 1024) || a.sv.ngroups != a.sv.rows / 16 || a.nv < 2 || a.nv > PRISM_MAX_ROOT + 1 ||
+  if (a.sv.rows % 64 || a.sv.rows > (a.sv.ld <= 32 ? 2048 : 1024) || a.sv.ngroups != a.sv.rows / 16 || a.nv < 2 || a.nv > PRISM_MAX_ROOT + 1 || a.polls < 0 ||
       batch <= 0 || a.ldr % 4 || (a.b16 && a.sv.ld > 32))
     return PRISM_EINVAL;
   if (a.b16) return a.sv.ld == 16 ? launch_fit_ld<true, 16>(a, batch, s) : launch_fit_ld<true, 32>(a, batch, s);

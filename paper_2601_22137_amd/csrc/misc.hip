@@ -125,13 +125,13 @@ __global__ __launch_bounds__(NT) void prepare_kernel(PrepArgs a) {
     c.alpha = 0.0f; c.res0 = 0.0f; c.res1 = 0.0f; c.res2 = 0.0f;
     c.norm = norm; c.scale = scale;
     a.ctrl[b] = c;
-    a.sync[(long long)b * FIT_SYNC_WORDS] = 0u;
     a.info[b].iters = 0;
     a.info[b].status = c.status;
   }
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i <= PRISM_MAX_ITERS; i += NT) a.info[b].residual[i] = -1.0f;
     for (int i = threadIdx.x; i < PRISM_MAX_ITERS; i += NT) a.info[b].alpha[i] = 0.0f;
+    for (int i = threadIdx.x; i < FIT_SYNC_WORDS; i += NT) a.sync[(long long)b * FIT_SYNC_WORDS + i] = 0u;
   }
 
   float rho = 0.0f;
@@ -232,13 +232,13 @@ __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
     c.alpha = 0.0f; c.res0 = 0.0f; c.res1 = 0.0f; c.res2 = 0.0f;
     c.norm = norm; c.scale = scale;
     a.ctrl[b] = c;
-    a.sync[(long long)b * FIT_SYNC_WORDS] = 0u;
     a.info[b].iters = 0;
     a.info[b].status = c.status;
   }
   if (bx == 0) {
     for (int i = threadIdx.x; i <= PRISM_MAX_ITERS; i += NT) a.info[b].residual[i] = -1.0f;
     for (int i = threadIdx.x; i < PRISM_MAX_ITERS; i += NT) a.info[b].alpha[i] = 0.0f;
+    for (int i = threadIdx.x; i < FIT_SYNC_WORDS; i += NT) a.sync[(long long)b * FIT_SYNC_WORDS + i] = 0u;
   }
   const long long mat_int = (long long)a.Lp * a.Sp;
   __shared__ __align__(16) unsigned short tile_hi[PC][72], tile_lo[PC][72];

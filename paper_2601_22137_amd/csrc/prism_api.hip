@@ -293,6 +293,7 @@ struct Run {
   uint16_t* vp0 = nullptr;             // bf16 planes of the sketches / of V_1 .. (bf16 polar, large launches)
   uint16_t* vp = nullptr;
   int max_iters, warm;
+  int fit_polls = FIT_POLLS;
   const float* sched; int sched_len;   // caller's coefficients for the leading updates (host array)
   int first_fit;                       // first update whose coefficient is fitted
   double tol;
@@ -359,7 +360,7 @@ struct Run {
     f.b16 = Rb != nullptr; f.R = Rb ? (const void*)Rb : (const void*)R; f.strideR = (long long)P.Sp * P.Sp; f.ldr = P.Sp;
     f.D = D; f.strideD = strideD; f.ldd = ldd;
     f.V0 = v0 + (long long)(k - first_fit) * P.Sp * P.ld; f.V = v; f.nv = P.nv;
-    f.sync = at<unsigned>(P.o_sync);
+    f.sync = at<unsigned>(P.o_sync); f.epoch = FIT_EPOCH * (unsigned)k; f.polls = fit_polls;
     ProfScope ps(PK_CHAIN, s);
     return launch_fit(f, P.batch, s);
   }
@@ -938,6 +939,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   r.v = r.at<float>(P.o_v);
   if (P.has_planes) { r.vp0 = r.at<uint16_t>(P.o_vp0); r.vp = r.at<uint16_t>(P.o_vp); }
   r.max_iters = max_iters; r.tol = tol; r.seed = seed; r.warm = opt ? opt->warm_iters : 0;
+  if (opt && (opt->flags & PRISM_FLAG_FIT_NO_WAIT)) r.fit_polls = 0;
   r.sched = opt ? opt->alpha_schedule : nullptr;
   r.sched_len = opt ? opt->schedule_len : 0;
   if (fn == PRISM_FN_SQRT_NEWTON) r.warm = 0;   // no upper end to start from: the coefficient is not clamped to a fit interval
@@ -1056,6 +1058,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   r.v = r.at<float>(P.o_v);
   if (P.has_planes) { r.vp0 = r.at<uint16_t>(P.o_vp0); r.vp = r.at<uint16_t>(P.o_vp); }
   r.max_iters = max_iters; r.tol = tol; r.seed = seed; r.warm = opt ? opt->warm_iters : 0;
+  if (opt && (opt->flags & PRISM_FLAG_FIT_NO_WAIT)) r.fit_polls = 0;
   r.sched = opt ? opt->alpha_schedule : nullptr;
   r.sched_len = opt ? opt->schedule_len : 0;
   r.first_fit = r.warm > r.sched_len ? r.warm : r.sched_len;

@@ -18,6 +18,7 @@ MAX_ITERS = 64
 FLAG_BF16_PLAIN_ITERATE = 1
 FLAG_SHARED_GPU = 2
 FLAG_SINGLE_STREAM = 4
+FLAG_FIT_NO_WAIT = 8
 OK, EINVAL, EUNSUPPORTED, ENOMEM, EHIP = 0, 1, 2, 3, 4
 INFO_CONVERGED, INFO_BUDGET, INFO_NONFINITE, INFO_ZERO, INFO_DIVERGED = 0, 1, 2, 3, 4
 

@@ -65,3 +65,32 @@ def test_sign_coefficients_many_matrices(prism, degree):
         assert np.abs(rec[b]["alpha"][:3] - np.array(oinfo["alpha"][:3])).max() <= 1e-4
         assert np.linalg.norm(out[b] - ref) <= 1e-4 * np.linalg.norm(ref)
         assert np.array_equal(out[b::2], np.broadcast_to(out[b], out[b::2].shape))
+
+
+@pytest.mark.parametrize("n,batch,sketch", [(65, 3, 16), (300, 2, 16), (512, 20, 32), (500, 17, 8), (1000, 1, 32), (1024, 9, 16),
+                                            (600, 2, 64), (1024, 1, 40), (1100, 2, 16), (2048, 1, 32)])
+def test_rows_computed_for_a_missing_partner_fp32(prism, n, batch, sketch):
+    """A workgroup does not depend on the others of its matrix being resident: with the wait cut to nothing every one
+    computes what it finds missing itself, with the same bits."""
+    A = W.c4_shampoo_spd(n=n, batch=batch)
+    recs, outs = [], []
+    for flags in (0, prism.FLAG_FIT_NO_WAIT):
+        x = torch.from_numpy(A.copy()).cuda()
+        recs.append(prism.inv_root(x, 2, 4, sketch, SEED, 0.0, flags=flags).read())
+        outs.append(x.cpu().numpy())
+    assert np.array_equal(recs[0]["alpha"], recs[1]["alpha"]) and np.array_equal(recs[0]["residual"], recs[1]["residual"])
+    assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n,batch,sketch", [(128, 2, 16), (500, 20, 32), (768, 1, 16), (768, 12, 16), (1024, 1, 32), (1280, 1, 16), (1300, 2, 32)])
+@pytest.mark.parametrize("plain", [False, True])
+def test_rows_computed_for_a_missing_partner_bf16(prism, n, batch, sketch, plain):
+    A = W.c3_polar_large(n=n, batch=batch, sigma_decades=2.0)
+    base = prism.FLAG_BF16_PLAIN_ITERATE if plain else 0
+    recs, outs = [], []
+    for flags in (base, base | prism.FLAG_FIT_NO_WAIT):
+        x = torch.from_numpy(A.view(np.int16)).cuda().view(torch.bfloat16)
+        recs.append(prism.polar(x, 5, 4, sketch, SEED, 0.0, flags=flags).read())
+        outs.append(x.view(torch.int16).cpu().numpy())
+    assert np.array_equal(recs[0]["alpha"], recs[1]["alpha"]) and np.array_equal(recs[0]["residual"], recs[1]["residual"])
+    assert np.array_equal(outs[0], outs[1])
