@@ -184,7 +184,9 @@ void launch_solve(const SolveArgs& a, int batch, hipStream_t s);
 constexpr int FIT_MAX_CLUSTER = 64;                       // workgroups per matrix
 constexpr int FIT_SYNC_WORDS = FIT_MAX_CLUSTER + 32;      // per matrix: products done by block of rows, and a counter on a cache line of its own
 constexpr int FIT_EPOCH = 16;                             // more than the products of one launch
-constexpr int FIT_POLLS = 128;                            // a microsecond or two each
+// Polls of a microsecond or two before a workgroup computes itself what it waits for: well above what a partner is late by
+// when other launches run beside this one (16 layers of width 768 in four parts: 3.25 ms with 128 polls, 3.23 with 4096).
+constexpr int FIT_POLLS = 1024;
 struct FitArgs {
   SolveArgs sv;              // mode 0; ngroups = rows / 16 partial coefficient sums per matrix
   const void* R;             // [batch][rows][ldr] fp32, or its bf16 copy (b16) with the exact diagonal in D
