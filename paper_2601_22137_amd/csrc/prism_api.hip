@@ -97,6 +97,7 @@ struct Plan {
 // Internal flag of make_plan: no split-K Gram product.  Its partial products need scratch of their own; a call whose
 // workspace is large enough without them only takes the one-pass product.
 constexpr unsigned FLAG_NO_SPLIT_K = 1u << 31;
+constexpr long long MAX_ENTRIES = (1ll << 31) - 1;   // of a matrix, sides padded
 
 // shared_shapes: the plan of a launch sequence over several shape groups with the same short side;
 // the iterate buffers are then laid out per group by the caller (offsets o_x* stay 0).  sel_batch: the batch of the
@@ -111,7 +112,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   if (fn != PRISM_FN_POLAR && m != n) return PRISM_EINVAL;
   if (fn == PRISM_FN_INV_ROOT && (root_p < 1 || root_p > PRISM_MAX_ROOT || degree != 3)) return PRISM_EINVAL;
   if (fn != PRISM_FN_POLAR && dt == PRISM_BF16) return PRISM_EUNSUPPORTED;
-  if ((long long)m * n > (1ll << 31) - 1) { set_last_error("a matrix may hold at most 2^31 - 1 entries"); return PRISM_EUNSUPPORTED; }
+  if ((long long)m * n > MAX_ENTRIES) { set_last_error("a matrix may hold at most 2^31 - 1 entries"); return PRISM_EUNSUPPORTED; }
   if (batch > PRISM_MAX_BATCH) { set_last_error("more than PRISM_MAX_BATCH matrices in one group"); return PRISM_EUNSUPPORTED; }
   P = Plan();
   P.fn = fn; P.dt = dt; P.batch = batch; P.m = m; P.n = n;
@@ -160,6 +161,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
         int unit = P.tile;                    // Kp parts has to be a multiple of the tile, Kp one of 32
         for (int q = parts; unit > 32 && q % 2 == 0; q /= 2) unit /= 2;
         const int Kp = round_up((P.L + parts - 1) / parts, unit);
+        if ((long long)P.Sp * Kp * parts > MAX_ENTRIES) continue;   // the padding must not cost a matrix its place within the limit
         if (cost(Kp, parts) < best) { best = cost(Kp, parts); P.ksplit = parts; P.Lp = Kp * parts; }
       }
     } else if (dt == PRISM_F32 && batch <= 8 && P.Lp >= 8192 && tri <= 48) {
@@ -167,7 +169,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
         if (P.Lp % (parts * 32) == 0 && P.Lp / parts >= 1024 && full * parts <= 4096) { P.ksplit = parts; break; }
     }
   }
-  if ((long long)P.Sp * P.Lp > (1ll << 31) - 1) {   // the kernels keep some offsets within a matrix in 32 bits
+  if ((long long)P.Sp * P.Lp > MAX_ENTRIES) {   // the kernels keep some offsets within a matrix in 32 bits
     set_last_error("a matrix may hold at most 2^31 - 1 entries after its sides are rounded up to tile multiples");
     return PRISM_EUNSUPPORTED;
   }

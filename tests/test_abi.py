@@ -78,3 +78,12 @@ def test_profile_arrays_sized_by_the_header_macro_are_accepted(lib):
     cnt = (ctypes.c_longlong * kinds)()
     assert lib.prism_profile_collect(ms, cnt, kinds) == P.OK
     assert lib.prism_profile_collect(ms, cnt, kinds - 1) == P.EINVAL
+
+
+@pytest.mark.parametrize("m,n", [(8_388_000, 256), (16_777_000, 128), (256, 8_388_000), (4_194_000, 512)])
+def test_parts_of_a_gram_product_do_not_add_to_the_size_limit(lib, m, n):
+    """A single long matrix close to 2^31 - 1 entries: cutting its Gram product into parts of equal length must not pad it
+    past the limit, which counts the sides rounded up to tiles only."""
+    from paper_2601_22137_amd import prism as P
+    out = ctypes.c_size_t(0)
+    assert lib.prism_workspace_bytes(P.FN_POLAR, 1, m, n, P.BF16, 5, 8, 0, ctypes.byref(out)) == P.OK
