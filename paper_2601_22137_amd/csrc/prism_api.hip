@@ -164,9 +164,13 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
         if ((long long)P.Sp * Kp * parts > MAX_ENTRIES) continue;   // the padding must not cost a matrix its place within the limit
         if (cost(Kp, parts) < best) { best = cost(Kp, parts); P.ksplit = parts; P.Lp = Kp * parts; }
       }
-    } else if (dt == PRISM_F32 && batch <= 8 && P.Lp >= 8192 && tri <= 48) {
-      for (int parts = 32; parts >= 2; --parts)
-        if (P.Lp % (parts * 32) == 0 && P.Lp / parts >= 1024 && full * parts <= 4096) { P.ksplit = parts; break; }
+    } else if (dt == PRISM_F32 && batch <= 8 && P.L > 8192 - 128 && tri <= 48) {
+      // as many parts of 1024 rows and more as there may be; they are of equal length and add up to multiples of 64
+      // (L need not suit them: 58241 rows, 911 times 64 when rounded up by itself, get 32 parts of 1824)
+      for (int parts = 32; parts >= 2; --parts) {
+        const int Kp = round_up((P.L + parts - 1) / parts, parts % 2 ? 64 : 32);
+        if (Kp >= 1024 && full * parts <= 4096 && (long long)P.Sp * Kp * parts <= MAX_ENTRIES) { P.ksplit = parts; P.Lp = Kp * parts; break; }
+      }
     }
   }
   if ((long long)P.Sp * P.Lp > MAX_ENTRIES) {   // the kernels keep some offsets within a matrix in 32 bits

@@ -87,3 +87,19 @@ def test_parts_of_a_gram_product_do_not_add_to_the_size_limit(lib, m, n):
     from paper_2601_22137_amd import prism as P
     out = ctypes.c_size_t(0)
     assert lib.prism_workspace_bytes(P.FN_POLAR, 1, m, n, P.BF16, 5, 8, 0, ctypes.byref(out)) == P.OK
+
+
+@pytest.mark.parametrize("m,n,parts", [(58241, 484, 32), (484, 58241, 32), (8065, 300, 7), (65473, 1000, 32), (20000, 200, 19), (9000, 700, 8)])
+def test_fp32_gram_product_of_a_tall_matrix_keeps_its_parts(lib, m, n, parts):
+    """Whatever the length: the scratch of a single matrix holds at least `parts` partial products of 64-padded order (batches
+    of more than eight have none)."""
+    from paper_2601_22137_amd import prism as P
+    out = ctypes.c_size_t(0)
+
+    def size(batch):
+        assert lib.prism_workspace_bytes(P.FN_POLAR, batch, m, n, P.F32, 5, 8, 0, ctypes.byref(out)) == P.OK
+        return out.value
+    per_matrix = (size(40) - size(20)) // 20
+    common = size(20) - 20 * per_matrix
+    order = (min(m, n) + 63) // 64 * 64
+    assert size(1) - common - per_matrix >= parts * order * order * 4

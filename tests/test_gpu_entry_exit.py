@@ -49,3 +49,17 @@ def test_split_gram_product_fits_in_less_scratch(prism):
     ws = torch.empty(one_pass, device="cuda", dtype=torch.uint8)
     prism.polar(y, 5, 5, 16, 7, 0.0, workspace=ws)
     assert torch.linalg.norm(x.double() - y.double()) <= 1e-2 * torch.linalg.norm(x.double())
+
+
+@pytest.mark.parametrize("m,n,batch", [(9001, 300, 1), (8065, 70, 3), (130, 12011, 2)])
+def test_polar_fp32_split_gram_product_of_any_length(prism, m, n, batch):
+    """fp32: lengths that no number of parts divides.  Converged to 1e-6; the sums over 10^4 rows, in parts of 10^3 and those in
+    chunks of 256, keep the error near 2^-24 sqrt(256): the fp32 bar of 1e-5."""
+    torch.manual_seed(m + n)
+    x = torch.randn(batch, m, n, device="cuda")
+    a = x.cpu().numpy().astype(np.float64)
+    prism.polar(x, 5, 30, 16, 7, 1e-6)
+    got = x.cpu().numpy().astype(np.float64)
+    for b in range(batch):
+        u, _, vh = np.linalg.svd(a[b], full_matrices=False)
+        assert np.linalg.norm(got[b] - u @ vh) <= 1e-5 * np.sqrt(min(m, n))
