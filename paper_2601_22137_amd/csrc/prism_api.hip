@@ -82,7 +82,7 @@ struct Plan {
   int nsum;        // partial sums of the Frobenius norm per matrix
   int max_parts;   // residual partials per matrix
   // byte offsets into the workspace
-  size_t o_ctrl, o_info, o_sync, o_sumsq, o_rho, o_v0, o_v, o_cpart;
+  size_t o_ctrl, o_info, o_sync, o_sumsq, o_rho, o_v0, o_v, o_cpart, o_fit_cpart;
   size_t o_vp0, o_vp;                             // bf16 polar: bf16 planes of the sketches and of V_1 .. V_{nv-1}
   bool has_planes;
   int ngroups;     // workgroups per matrix of the moments kernel
@@ -188,11 +188,15 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   const size_t SS = (size_t)P.Sp * P.Sp, LS = (size_t)P.Lp * P.Sp, B = (size_t)batch;
   P.o_ctrl = take(B * sizeof(Ctrl));
   P.o_info = take(B * sizeof(prism_info));
-  P.o_sync = take(B * FIT_SYNC_WORDS * sizeof(unsigned));
-  P.o_sumsq = take(B * P.nsum * sizeof(double));
   P.o_rho = take(B * P.max_parts * sizeof(float));
   P.o_v0 = take((size_t)PRISM_MAX_ITERS * P.Sp * P.ld * sizeof(float));   // S_k^T for every k, generated once per call
   P.o_v = take((size_t)P.nv * B * P.Sp * P.ld * sizeof(float));
+  // Room in V: until the fit begins the norm's partial sums lie at its head (4 KiB a matrix at most, in V_1 .. V_{nv-1}).
+  // fit_kernel does not store V_nv, and has its counters and coefficient partials there (384 + 8.5 Sp bytes
+  // a matrix, of 64 Sp and more).
+  P.o_sumsq = P.o_v;
+  P.o_sync = P.o_v + (size_t)(P.nv - 1) * B * P.Sp * P.ld * sizeof(float);
+  P.o_fit_cpart = P.o_sync + B * FIT_SYNC_WORDS * sizeof(unsigned);
   {
     const long long el = (long long)P.Sp * P.ld;
     P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);
@@ -201,7 +205,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
       P.ngroups = mm < 1 ? 1 : (mm > 64 ? 64 : (int)mm);
     }
   }
-  P.o_cpart = take(B * (P.ngroups > P.Sp / 16 ? P.ngroups : P.Sp / 16) * 17 * sizeof(double));
+  P.o_cpart = take(B * P.ngroups * 17 * sizeof(double));
   if (dt == PRISM_BF16 && P.ld <= 32 && P.p_s > 0) {   // operands of the plane chain kernel: 3 x 2 bytes per entry
     P.o_vp0 = take((size_t)PRISM_MAX_ITERS * P.Sp * P.ld * 6);
     P.o_vp = take((size_t)(P.nv - 1) * B * P.Sp * P.ld * 6);
@@ -362,7 +366,7 @@ struct Run {
     }
     FitArgs f = {};
     f.sv = solve_args(k, nparts, 0);
-    f.sv.ngroups = P.Sp / 16;
+    f.sv.ngroups = P.Sp / 16; f.sv.cpart = at<double>(P.o_fit_cpart);
     f.b16 = Rb != nullptr; f.R = Rb ? (const void*)Rb : (const void*)R; f.strideR = (long long)P.Sp * P.Sp; f.ldr = P.Sp;
     f.D = D; f.strideD = strideD; f.ldd = ldd;
     f.V0 = v0 + (long long)(k - first_fit) * P.Sp * P.ld; f.V = v; f.nv = P.nv;

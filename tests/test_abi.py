@@ -103,3 +103,11 @@ def test_fp32_gram_product_of_a_tall_matrix_keeps_its_parts(lib, m, n, parts):
     common = size(20) - 20 * per_matrix
     order = (min(m, n) + 63) // 64 * 64
     assert size(1) - common - per_matrix >= parts * order * order * 4
+
+
+@pytest.mark.parametrize("batch,m,n,dtype,degree,sketch", [(94, 116, 1, 1, 3, 32), (44, 67, 458, 0, 5, 32), (35, 811, 66, 0, 3, 8), (104, 81, 138, 0, 3, 32)])
+def test_largest_batches_of_the_static_entry_point(lib, batch, m, n, dtype, degree, sketch):
+    """Batches that leave less than half a matrix of the static array unused: what the fit keeps beside the iterates must
+    not take that."""
+    from paper_2601_22137_amd import prism as P
+    assert P.workspace_bytes(P.FN_POLAR, batch, m, n, dtype, degree, sketch) <= P.STATIC_SCRATCH_BYTES
