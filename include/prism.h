@@ -265,7 +265,8 @@ int prism_sqrt_newton_ex(void* a, void* inv_out, int batch, int m, int n, prism_
  * The internal streams have default priority and fork from and join back into `stream` (event
  * record / wait only: the call stays asynchronous and capturable once the library's workspaces
  * exist, i.e. after one eager call with the same arguments on the same stream).  Every group is
- * computed exactly as by its own single-group call: same kernels, same bits. */
+ * computed exactly as by its own single-group call: same kernels, same bits (the residuals in the reports of bf16
+ * calls agree to rounding: their partial sums follow the tiles of the launch). */
 typedef struct {
   void* x;          /* device: [batch][m][n], replaced in place as by the single-group call */
   void* inv_out;    /* device: second output of prism_sqrt / prism_sqrt_newton, else NULL */

@@ -595,11 +595,11 @@ bool chain_bf16_supported(int n, int ld, int batch, int ldr) {
 int launch_chain_planes(const unsigned short* Rb, long long strideR, int ldr, const float* D, long long strideD, int ldd,
                         const float* Vin, long long strideVin, const unsigned short* Pin, long long stridePin, float* Vout,
                         long long strideVout, unsigned short* Pout, long long stridePout, int n, int ld, int batch,
-                        const Ctrl* ctrl, hipStream_t s, int sel_batch) {
+                        const Ctrl* ctrl, hipStream_t s) {
   if (!Rb || !D || !Vin || !Pin || !Vout || n % PCH || ldr % 8 || batch <= 0 || (ld != 16 && ld != 32)) return PRISM_EINVAL;
   const int lds = 3 * 3 * ld * 512;   // STAGES stages of three planes, 256 k each
-  // 128-row workgroups when they still fill at least half the chip (judged by sel_batch, see launch_chain)
-  const bool two = n % (2 * ROWS) == 0 && (long long)(n / (2 * ROWS)) * (sel_batch > 0 ? sel_batch : batch) >= 128;
+  // 128-row workgroups when they still fill at least half the chip (the sums are the same either way)
+  const bool two = n % (2 * ROWS) == 0 && (long long)(n / (2 * ROWS)) * batch >= 128;
   const void* kern = two ? (ld == 16 ? (const void*)chain_planes_kernel<16, 2> : (const void*)chain_planes_kernel<32, 2>)
                          : (ld == 16 ? (const void*)chain_planes_kernel<16, 1> : (const void*)chain_planes_kernel<32, 1>);
   const int rc = allow_dynamic_lds(kern, lds);

@@ -41,6 +41,7 @@ struct GemmDesc {
   int ctrl_parts;       // split-K products: batch entries per matrix, i.e. per control block (0: one each)
   int tile_blocks;      // set by the launcher: tiles are taken in blocks of 8 x 8 (plain products, grids of 8 x 8 multiples)
   int batch;
+  int sel_batch;        // batch that picks the tile, where these matrices are a part of a larger one (0: batch)
   // epilogue operands
   int epi;
   int n_true;           // unpadded order for masks
@@ -129,8 +130,8 @@ void launch_gauss_parts(uint32_t first, uint32_t count, double* r, double* c, do
                         hipStream_t s);
 
 // ---- chain.hip : V_out = R V_in for the sketch chain (HBM bound; R read once, straight into registers) ----
-// sel_batch: the batch size that picks the kernel variant (0: batch).  A launch over the matrices of
-// several shape groups passes the size of one group, so that each matrix gets the kernel, hence the
+// sel_batch: the batch size that picks the kernel (0: batch).  A launch over a part of a batch, or over the matrices of
+// several shape groups, passes the whole batch of its group, so that each matrix gets the kernel, hence the
 // summation order and the bits, of a call on its own group.
 int launch_chain(const float* R, long long strideR, int ldr, const float* Vin, long long strideVin, float* Vout,
                  long long strideVout, int n, int ld, int batch, const Ctrl* ctrl, hipStream_t s, int sel_batch = 0);
@@ -145,7 +146,7 @@ bool chain_bf16_supported(int n, int ld, int batch, int ldr);
 int launch_chain_planes(const unsigned short* Rb, long long strideR, int ldr, const float* D, long long strideD, int ldd,
                         const float* Vin, long long strideVin, const unsigned short* Pin, long long stridePin, float* Vout,
                         long long strideVout, unsigned short* Pout, long long stridePout, int n, int ld, int batch,
-                        const Ctrl* ctrl, hipStream_t s, int sel_batch = 0);
+                        const Ctrl* ctrl, hipStream_t s);
 int launch_split_planes(const float* V, unsigned short* P, int n, int ld, int count, hipStream_t s);
 int launch_chain_bf16(const unsigned short* Rb, long long strideR, int ldr, const float* D, long long strideD, int ldd,
                       const float* Vin, long long strideVin, float* Vout, long long strideVout, int n, int ld, int batch,
@@ -200,7 +201,8 @@ struct FitArgs {
   int polls;                 // after this many a workgroup computes itself what it waits for
   int nv;
 };
-bool fit_fused_supported(int rows, int ld, int batch);
+// batch: the caller's; halves: its launches are for one half of it each, by default
+bool fit_fused_supported(int rows, int ld, int batch, bool b16, bool halves);
 int launch_fit(const FitArgs& a, int batch, hipStream_t s);
 
 // fp32 polar factor of matrices whose padded iterate is 64 x 64: every iteration (residual, sketch
@@ -297,8 +299,9 @@ void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np
 // ---- dbnewton.hip : pieces of the DB Newton iteration (App. A.2) ----
 // N = M^{-1} of the SPD matrices M[batch][np][np] by block Gauss-Jordan.  scratch: spd_inverse_scratch_floats(np, batch)
 // floats, 16-byte aligned.
-long long spd_inverse_scratch_floats(int np, int batch);
-int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* scratch, hipStream_t s);
+// sel_batch: the batch that picks blocks and tiles, where these matrices are a part of a larger one.
+long long spd_inverse_scratch_floats(int np, int batch, int sel_batch);
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, hipStream_t s);
 // partial sums of <D0,D0>, <D0,D2>, <D2,D2> (D0 = M - I, D2 = M + N - 2I) -> the five coefficient partials
 void launch_db_moments(const float* M, const float* N, int np, int n_true, int batch, const Ctrl* ctrl, double* cpart,
                        int ngroups, hipStream_t s);

@@ -485,15 +485,15 @@ int outer_block(int np, int batch) {
 }  // namespace
 
 // pivot inverses, the second buffer of the elimination and, with outer blocks, the new row and column panels
-long long spd_inverse_scratch_floats(int np, int batch) {
-  const long long OB = outer_block(np, batch), n = OB ? OB : np;
+long long spd_inverse_scratch_floats(int np, int batch, int sel_batch) {
+  const long long OB = outer_block(np, sel_batch), n = OB ? OB : np;
   return (2ll * BS * BS + n * n + 2 * OB * np) * batch;
 }
 
-int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* ctrl, float* scratch, hipStream_t s) {
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, hipStream_t s) {
   if (np % BS || batch <= 0 || !scratch) return PRISM_EINVAL;
   const long long per_mat = (long long)np * np;
-  const int OB = outer_block(np, batch);
+  const int OB = outer_block(np, sel_batch);
   float* P = scratch;
   const long long tn = OB ? OB : np;
   const Mat tmp = {P + 2ll * BS * BS * batch, tn * tn, (int)tn};
@@ -518,7 +518,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, const Ctrl* 
     const Mat piv = {Pk, per_mat, np};
     gauss_jordan_64(piv, piv, tmp, P, OB, batch, ctrl, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
     GemmDesc g = {};
-    g.batch = batch; g.ctrl = ctrl; g.K = OB; g.epi = EPI_STORE; g.c_in = 1.0f;
+    g.batch = batch; g.sel_batch = sel_batch; g.ctrl = ctrl; g.K = OB; g.epi = EPI_STORE; g.c_in = 1.0f;
     GemmDesc r = g;                                      // T = P A_k,:
     r.A = Pk; r.strideA = per_mat; r.lda = np; r.B = rowk; r.strideB = per_mat; r.ldb = np;
     r.C = Trow; r.strideC = tstride; r.ldc = np; r.M = OB; r.N = np; r.skip_n0 = k * OB; r.skip_n1 = (k + 1) * OB;

@@ -1095,12 +1095,16 @@ int launch_fit_ld(const FitArgs& a, int batch, hipStream_t s) {
 
 }  // namespace
 
-// Above order 1024 only while the workgroups (32 rows) are at most 1.5 per CU: with more, the streaming chain kernels, which
-// also leave more of the chip to the products of other parts of a batch, are ahead (16 x 1536 per part of a grouped
-// call: 17.8 against 19.2 ms per step); 8 x 2048 in two halves, fused / not: bf16 polar 4.7 / 5.2 ms, sign 29.7 / 30.6.
-bool fit_fused_supported(int rows, int ld, int batch) {
+// Above order 1024 while the workgroups (32 rows, one per CU with bf16 R) fit the chip at a time; with more of them the
+// streaming chain kernels, which also leave more of the chip to the products of the other half, are ahead.  bf16 polar, eight
+// updates, ms fused / streaming: 1 x 2048 1.30 / 1.41, 4 x 2048 (256 workgroups) 2.20 / 2.33, 6 x 1536 (288) 1.82 / 1.70,
+// 7 x 1300 (280) 2.48 / 2.29; in halves 8 x 1536 (192 each) 2.11 / 2.25, 12 x 1300 (240) 3.25 / 3.07,
+// 8 x 2048 (256) 3.52 / 3.73 with a sketch of 16 and 3.92 / 3.82 with 32, 16 x 1536 (384) 3.83 / 3.56.  fp32, where the
+// products weigh more: sign 4 x 2048 6.12 / 6.25, 6 x 1536 4.25 / 4.30, 8 x 2048 12.05 / 12.20, 16 x 1536 11.28 / 11.07.
+bool fit_fused_supported(int rows, int ld, int batch, bool b16, bool halves) {
   if (rows % 64) return false;
-  return rows <= 1024 || (rows <= 2048 && ld <= 32 && (long long)(rows / 32) * batch <= 384);
+  const long long wgs = (long long)(rows / 32) * (halves ? batch / 2 : batch);
+  return rows <= 1024 || (rows <= 2048 && ld <= 32 && wgs <= (b16 ? (halves ? 192 : 256) : 384));
 }
 
 int launch_fit(const FitArgs& a, int batch, hipStream_t s) {

@@ -551,12 +551,12 @@ int f32_tiles(int M, int N, int batch, int sym) {   // tiles per matrix, i.e. re
 }
 
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s) {
-  const int T = f32_tile(g.M, g.N, g.batch, g.sym);
+  const int T = f32_tile(g.M, g.N, g.sel_batch ? g.sel_batch : g.batch, g.sym);
   return launch_gemm_f32(g, T, T, s);
 }
 
 int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
-  const int T = f32_tile(a.M, a.N, 2 * a.batch, a.sym);
+  const int T = f32_tile(a.M, a.N, 2 * (a.sel_batch ? a.sel_batch : a.batch), a.sym);
   return T == 128 ? launch_cfg<float, float, 128, 128, 2, 2>(a, s, &b) : launch_cfg<float, float, 64, 64, 2, 2>(a, s, &b);
 }
 

@@ -227,7 +227,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
     for (int i = 0; i < 2; ++i) { P.o_x[i] = take(B * SS * 4); P.o_y[i] = take(B * SS * 4); }
     P.o_r = take(B * SS * 4);        // M_k
     P.o_q = take(B * SS * 4);        // N_k = M_k^{-1}
-    P.o_t[0] = take((size_t)spd_inverse_scratch_floats(P.Sp, batch) * 4 + 256);   // pivot panels of the inverse
+    P.o_t[0] = take((size_t)spd_inverse_scratch_floats(P.Sp, batch, sel_batch ? sel_batch : batch) * 4 + 256);   // pivot panels of the inverse
   } else if (fn == PRISM_FN_INVERSE) {
     for (int i = 0; i < 2; ++i) P.o_x[i] = take(B * SS * 4);
     P.o_y[0] = take(B * SS * 4);     // A / ||A||_F
@@ -291,6 +291,9 @@ int check_hip() {
   return PRISM_OK;
 }
 
+// Batches that run as two halves unless the caller asks otherwise (run_auto)
+bool in_halves(int batch, int S) { return batch >= 8 && batch % 2 == 0 && S >= 1024; }
+
 struct Run {
   Plan P;
   char* ws;
@@ -324,7 +327,9 @@ struct Run {
     int ksplit; float* gpart;                  // parts of the K loop of X^T X (0: one pass) and their products
   };
   std::vector<XGroup> xg;
-  int chain_sel_batch = 0;                     // batch size that picks the chain kernels (0: the whole batch)
+  // Kernels whose sums differ in order are chosen by the caller's batch of these matrices, however it is enqueued (whole,
+  // as two halves, as a group of a grouped call), so that the results are the same bits.
+  int sel_batch = 0;
 
   template <typename T> T* at(size_t off) const { return (T*)(ws + off); }
 
@@ -344,13 +349,13 @@ struct Run {
         const uint16_t* pin = (j == 1) ? vp0 + (long long)(k - first_fit) * pe : vp + (long long)(j - 2) * P.batch * pe;
         uint16_t* pout = j < P.nv ? vp + (long long)(j - 1) * P.batch * pe : nullptr;
         CHECK_LAUNCH(launch_chain_planes(Rb, (long long)Sp * Sp, Sp, D, strideD, ldd, vin, sin, pin, j == 1 ? 0 : pe,
-                                         v + (j - 1) * vs, (long long)Sp * ld, pout, pe, Sp, ld, P.batch, ctrl, s, chain_sel_batch));
+                                         v + (j - 1) * vs, (long long)Sp * ld, pout, pe, Sp, ld, P.batch, ctrl, s));
       } else if (Rb)
         CHECK_LAUNCH(launch_chain_bf16(Rb, (long long)Sp * Sp, Sp, D, strideD, ldd, vin, sin, v + (j - 1) * vs,
-                                       (long long)Sp * ld, Sp, ld, P.batch, ctrl, s, chain_sel_batch));
+                                       (long long)Sp * ld, Sp, ld, P.batch, ctrl, s, sel_batch));
       else
         CHECK_LAUNCH(launch_chain(R, (long long)Sp * Sp, Sp, vin, sin, v + (j - 1) * vs, (long long)Sp * ld, Sp, ld,
-                                  P.batch, ctrl, s, chain_sel_batch));
+                                  P.batch, ctrl, s, sel_batch));
     }
     return PRISM_OK;
   }
@@ -375,7 +380,7 @@ struct Run {
     return launch_fit(f, P.batch, s);
   }
   bool fused() const {
-    return fit_fused_supported(P.Sp, P.ld, chain_sel_batch ? chain_sel_batch : P.batch) && !small_polar() && !small_root();
+    return fit_fused_supported(P.Sp, P.ld, sel_batch, P.dt == PRISM_BF16, in_halves(sel_batch, P.S)) && !small_polar() && !small_root();
   }
   // inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
   // the launches of that are full: 1024 matrices, p = 4, 0.76 against 1.36 ms)
@@ -414,8 +419,7 @@ struct Run {
   bool fit_needed(int k) const { return P.p_s > 0 && k >= first_fit && k < max_iters; }
   // bf16 chain products too large for the 16-row kernel read V as bf16 planes
   bool planes() const {
-    const int sel = chain_sel_batch ? chain_sel_batch : P.batch;
-    return vp0 && !fused() && chain_bf16_supported(P.Sp, P.ld, sel, P.Sp) && !chain_takes_small_kernel(P.Sp, P.ld, sel, true);
+    return vp0 && !fused() && chain_bf16_supported(P.Sp, P.ld, sel_batch, P.Sp) && !chain_takes_small_kernel(P.Sp, P.ld, sel_batch, true);
   }
 };
 
@@ -423,7 +427,7 @@ GemmDesc f32_desc(const Run& r, const float* A, int lda, long long sa, const flo
                   int M, int N, int K, int a_km) {
   GemmDesc g = {};
   g.A = A; g.strideA = sa; g.lda = lda; g.B = B; g.strideB = sb; g.ldb = ldb;
-  g.M = M; g.N = N; g.K = K; g.a_km = a_km; g.batch = r.P.batch; g.n_true = r.P.S; g.ctrl = r.ctrl;
+  g.M = M; g.N = N; g.K = K; g.a_km = a_km; g.batch = r.P.batch; g.sel_batch = r.sel_batch; g.n_true = r.P.S; g.ctrl = r.ctrl;
   g.c_in = 1.0f;
   return g;
 }
@@ -448,7 +452,7 @@ int run_polar_f32(Run& r) {
   float* Q = P.d == 2 ? r.at<float>(P.o_q) : nullptr;
   const bool polar = P.fn != PRISM_FN_SIGN;
   const int sym = polar ? f32_sym() : 0;
-  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
+  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
   if (r.small_polar()) {
     // the whole iteration in one workgroup per matrix, one launch for all iterations: with five
     // launches per iteration a call on such matrices is nothing but launch latency
@@ -479,7 +483,7 @@ int run_polar_f32(Run& r) {
       for (int b = 0; b < P.batch; ++b) {   // the parts of one matrix are the batch of a plain product
         GemmDesc sp = f32_desc(r, X[cur] + (long long)b * LS, Sp, (long long)Kp * Sp, X[cur] + (long long)b * LS, Sp,
                                (long long)Kp * Sp, Sp, Sp, Kp, 1);
-        sp.batch = P.ksplit; sp.epi = EPI_STORE; sp.C = gpart + (long long)b * P.ksplit * SS; sp.strideC = SS; sp.ldc = Sp;
+        sp.batch = P.ksplit; sp.sel_batch = 0; sp.epi = EPI_STORE; sp.C = gpart + (long long)b * P.ksplit * SS; sp.strideC = SS; sp.ldc = Sp;
         sp.ctrl = r.ctrl + b; sp.ctrl_parts = P.ksplit;
         CHECK_LAUNCH(launch_gemm_f32(sp, r.s));
       }
@@ -585,8 +589,7 @@ int run_polar_bf16(Run& r) {
   // Only with the plain bf16 iterate: with the split one the linear term of Q = R/2 + alpha R^2 keeps
   // the fp32 R (taking it from the bf16 copy raises the residual floor by a few 1e-4, which at
   // tol = 1e-2 cost the reduced config-3 case one more iteration than the oracle).
-  const int sel = r.chain_sel_batch ? r.chain_sel_batch : P.batch;
-  const bool chain_b = !chain_f32 && Sp > 64 && (P.p_s == 0 || chain_bf16_supported(Sp, P.ld, sel, Sp));   // order 64: one-launch fp32 chain
+  const bool chain_b = !chain_f32 && Sp > 64 && (P.p_s == 0 || chain_bf16_supported(Sp, P.ld, r.sel_batch, Sp));   // order 64: one-launch fp32 chain
   const bool lean = chain_b && sym && !P.split;
   float* Dg = R;
   const int ntg = Sp / Tg.m;
@@ -688,7 +691,7 @@ int run_sqrt_f32(Run& r) {
   // X_k and Y_k commute up to kappa * eps only: every product keeps all its tiles.  (Mirroring only
   // Y X and R^2 is stable but costs the root an order of magnitude of accuracy from kappa ~ 1e4 on.)
   const int sym = 0;
-  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
+  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
@@ -728,7 +731,7 @@ int run_inverse_f32(Run& r) {
   float* R = r.at<float>(P.o_r);
   float* Q = r.at<float>(P.o_q);
   const int sym = 0;   // A_s X_k is symmetric up to kappa * eps only: all tiles
-  const int nparts = f32_tiles(Sp, Sp, P.batch, sym);
+  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
@@ -768,7 +771,7 @@ int run_sqrt_newton_f32(Run& r) {
     if (k == r.max_iters && r.tol <= 0.0) break;
     CHECK_LAUNCH(r.solve(k, k == 0 ? nparts0 : nparts, 1));
     if (k == r.max_iters) break;
-    { ProfScope ps(PK_SPD_INVERSE, r.s); CHECK_LAUNCH(launch_spd_inverse(M, N, Sp, P.batch, r.ctrl, r.at<float>(P.o_t[0]), r.s)); }
+    { ProfScope ps(PK_SPD_INVERSE, r.s); CHECK_LAUNCH(launch_spd_inverse(M, N, Sp, P.batch, r.sel_batch, r.ctrl, r.at<float>(P.o_t[0]), r.s)); }
     {   // also without a fit: the probe of the inverse shares the partials with the moments
       ProfScope ps(PK_DB_MOMENTS, r.s);
       launch_db_moments(M, N, Sp, P.S, P.batch, r.ctrl, r.at<double>(P.o_cpart), P.ngroups, r.s);
@@ -819,7 +822,7 @@ int run_inv_root_f32(Run& r) {
     ax.coef_is_alpha = 1;
     // The update of X and the first square of the chain below depend on R alone.  Where neither fills the chip they share a
     // launch (all tiles of both); otherwise X goes by itself, on its upper triangle of tiles (X never re-enters M).
-    const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * P.batch <= 1024;
+    const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * r.sel_batch <= 1024;
     if (!paired) {
       ax.sym = f32_sym();
       ProfScope ps(PK_F32_APPLY, r.s);
@@ -919,7 +922,7 @@ void bf16_prep_final(const Plan& P, const Run::XGroup& x, PrepArgs& pa, FinalArg
 }
 
 int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int dt, int degree, int max_iters,
-        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt) {
+        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, int sel_batch = 0) {
   set_last_error("");
   const bool empty = batch == 0 || m == 0 || n == 0;   // nothing to compute; the arguments are still checked
   if (batch < 0 || m < 0 || n < 0) return PRISM_EINVAL;
@@ -932,10 +935,11 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
     return PRISM_EINVAL;
   Run r;
   if (empty) return make_plan(r.P, fn, 1, m ? m : 1, n ? n : 1, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u);
-  int rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u);
+  if (sel_batch == 0) sel_batch = batch;
+  int rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u, false, sel_batch);
   if (rc != PRISM_OK) return rc;
   if (r.P.ksplit && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
-    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K);
+    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K, false, sel_batch);
     if (rc != PRISM_OK) return rc;
   }
   r.s = (hipStream_t)stream;
@@ -954,6 +958,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   r.sched_len = opt ? opt->schedule_len : 0;
   if (fn == PRISM_FN_SQRT_NEWTON) r.warm = 0;   // no upper end to start from: the coefficient is not clamped to a fit interval
   r.first_fit = r.warm > r.sched_len ? r.warm : r.sched_len;
+  r.sel_batch = sel_batch;
 
   PrepArgs pa = {};
   pa.fn = fn; pa.dt = dt; pa.batch = batch; pa.m = m; pa.n = n; pa.S = P.S; pa.L = P.L; pa.Sp = P.Sp; pa.Lp = P.Lp;
@@ -1034,7 +1039,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     const int bg = groups[g].batch * batch_scale, b0 = groups[0].batch * batch_scale;
     if (chain_takes_small_kernel(Pg[g].Sp, Pg[g].ld, bg, true) != chain_takes_small_kernel(Pg[0].Sp, Pg[0].ld, b0, true) ||
         chain_takes_small_kernel(Pg[g].Sp, Pg[g].ld, bg, false) != chain_takes_small_kernel(Pg[0].Sp, Pg[0].ld, b0, false) ||
-        fit_fused_supported(Pg[g].Sp, Pg[g].ld, bg) != fit_fused_supported(Pg[0].Sp, Pg[0].ld, b0) ||
+        fit_fused_supported(Pg[g].Sp, Pg[g].ld, bg, true, in_halves(bg, Pg[g].S)) != fit_fused_supported(Pg[0].Sp, Pg[0].ld, b0, true, in_halves(b0, Pg[0].S)) ||
         chain_bf16_supported(Pg[g].Sp, Pg[g].ld, bg, Pg[g].Sp) != chain_bf16_supported(Pg[0].Sp, Pg[0].ld, b0, Pg[0].Sp))
       return PRISM_EUNSUPPORTED;
     btot += groups[g].batch;
@@ -1072,7 +1077,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   r.sched = opt ? opt->alpha_schedule : nullptr;
   r.sched_len = opt ? opt->schedule_len : 0;
   r.first_fit = r.warm > r.sched_len ? r.warm : r.sched_len;
-  r.chain_sel_batch = groups[0].batch * batch_scale;
+  r.sel_batch = groups[0].batch * batch_scale;
   int boff = 0;
   for (int g = 0; g < ngroups; ++g) {
     Run::XGroup x = {};
@@ -1266,7 +1271,8 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
     o.info = groups[gi].info;
     o.flags |= PRISM_FLAG_SHARED_GPU;
     first_error = run(fn, groups[gi].x, groups[gi].inv_out, root_p, groups[gi].batch, groups[gi].m, groups[gi].n, dt,
-                      degree, max_iters, sketch_dim, seed, tol, f->streams[gi % GROUP_STREAMS], &o);
+                      degree, max_iters, sketch_dim, seed, tol, f->streams[gi % GROUP_STREAMS], &o,
+                      from_auto_split ? ngroups * groups[gi].batch : 0);
   }
   // Join every forked stream back into the caller's, on every exit: after an error too, and past a
   // failing record or wait of one stream (the others are still joined, so that no forked work is
@@ -1288,7 +1294,7 @@ int run_auto(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n
              int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt) {
   static const int no_split = ab_switch("PRISM_NO_BATCH_SPLIT");
   const int S = m < n ? m : n;
-  if (no_split || !a || batch < 8 || (batch & 1) || S < 1024 || (opt && opt->workspace) || (opt && (opt->flags & PRISM_FLAG_SINGLE_STREAM)) || g_prof_on)
+  if (no_split || !a || !in_halves(batch, S) || (opt && opt->workspace) || (opt && (opt->flags & PRISM_FLAG_SINGLE_STREAM)) || g_prof_on)
     return run(fn, a, inv_out, root_p, batch, m, n, dt, degree, max_iters, sketch_dim, seed, tol, stream, opt);
   const size_t esz = dt == PRISM_BF16 ? 2 : 4;
   const size_t half = (size_t)(batch / 2) * m * n * esz;
@@ -1482,12 +1488,12 @@ int prism_sqrt_newton_ex(void* a, void* inv_out, int batch, int m, int n, prism_
 int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream) {
   if (!a || !out || batch <= 0 || batch > PRISM_MAX_BATCH || n <= 0 || n % 64) return PRISM_EINVAL;
   char* ws = nullptr;
-  const size_t bytes = (size_t)spd_inverse_scratch_floats(n, batch) * 4;
+  const size_t bytes = (size_t)spd_inverse_scratch_floats(n, batch, batch) * 4;
   if (bytes) {
     const int rc = get_workspace(bytes, (hipStream_t)stream, nullptr, &ws);
     if (rc != PRISM_OK) return rc;
   }
-  return launch_spd_inverse(a, out, n, batch, nullptr, (float*)ws, (hipStream_t)stream);
+  return launch_spd_inverse(a, out, n, batch, batch, nullptr, (float*)ws, (hipStream_t)stream);
 }
 
 int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int root_p, prism_dtype dt, int degree,

@@ -220,3 +220,51 @@ def test_calls_from_two_host_threads(prism):
     assert not errors, errors
     for j in range(2):
         assert torch.equal(got[j], want[j]), j
+
+
+def _ways(prism, run, grouped, make, ws_bytes):
+    """The same matrices through a plain call (run as two halves), on one stream, in a caller's workspace and as a group beside
+    another one: outputs (as integers) and reports."""
+    res = []
+    for kind in ("plain", "single", "workspace", "grouped"):
+        x = make()
+        if kind == "grouped":
+            rec = grouped(x)
+        elif kind == "workspace":
+            rec = run(x, 0, torch.empty(ws_bytes, dtype=torch.uint8, device="cuda"))
+        else:
+            rec = run(x, prism.FLAG_SINGLE_STREAM if kind == "single" else 0, None)
+        torch.cuda.synchronize()
+        res.append((kind, x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32).cpu(), rec.read()))
+    return res
+
+
+@pytest.mark.parametrize("n,batch,sketch", [(2048, 8, 32), (1536, 8, 16), (1300, 12, 32), (1100, 16, 16)])
+def test_same_bits_however_a_batch_is_enqueued_bf16(prism, n, batch, sketch):
+    torch.manual_seed(n)
+    a = torch.randn(batch, n, n, device="cuda").to(torch.bfloat16)
+    other = torch.randn(batch, 2 * n, n, device="cuda").to(torch.bfloat16)
+    res = _ways(prism, lambda x, flags, ws: prism.polar(x, 5, 9, sketch, SEED, 0.0, flags=flags, workspace=ws),
+                lambda x: prism.run_grouped(prism.FN_POLAR, [x, other.clone()], 5, 9, sketch, SEED, 0.0)[1][0], a.clone,
+                prism.workspace_bytes(prism.FN_POLAR, batch, n, n, prism.BF16, 5, sketch))
+    for kind, out, rec in res[1:]:
+        assert torch.equal(out, res[0][1]), kind
+        assert np.array_equal(rec["alpha"], res[0][2]["alpha"]), kind
+
+
+@pytest.mark.parametrize("n,batch,sketch", [(2048, 8, 16), (1024, 8, 16), (1024, 16, 8), (1500, 10, 32)])
+def test_same_bits_however_a_batch_is_enqueued_fp32(prism, n, batch, sketch):
+    """Residuals too: their partial sums follow the tiles of the product.  (Updates enough for coefficients inside their
+    interval, here and above: at its end all kernels agree.)"""
+    torch.manual_seed(n)
+    a = torch.randn(batch, n, n, device="cuda")
+    a = a @ a.transpose(1, 2).contiguous() / n + 0.01 * torch.eye(n, device="cuda")
+    other = torch.eye(64, device="cuda").repeat(1, 1, 1)
+    for fn, call, args in ((prism.FN_SIGN, lambda x, f, ws: prism.sign(x, 5, 12, sketch, SEED, 0.0, flags=f, workspace=ws), (5, 12, sketch)),
+                           (prism.FN_INV_ROOT, lambda x, f, ws: prism.inv_root(x, 2, 8, sketch, SEED, 0.0, flags=f, workspace=ws), (3, 8, sketch))):
+        p = 2 if fn == prism.FN_INV_ROOT else 0
+        res = _ways(prism, call, lambda x: prism.run_grouped(fn, [x, other.clone()], *args, SEED, 0.0, root_p=p)[1][0], a.clone,
+                    prism.workspace_bytes(fn, batch, n, n, prism.F32, args[0], sketch, p))
+        for kind, out, rec in res[1:]:
+            assert torch.equal(out, res[0][1]), (fn, kind)
+            assert rec.tobytes() == res[0][2].tobytes(), (fn, kind)
