@@ -40,24 +40,23 @@ __device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
   const long long total = (long long)a.m * a.n;
   double acc = 0.0;
   const long long first = (long long)bx * NT + threadIdx.x, step = (long long)gx * NT;
-  // 16-byte loads, four in flight; the entries ahead of the first 16-byte boundary and behind the last go to the
-  // first workgroup
+  // 16-byte loads, four in flight, from wherever the matrix starts: which thread adds up which entry follows from the
+  // shape, not from the address.  The entries behind the last whole vector go to the first workgroup.
   auto sweep = [&](auto* src, auto add16, auto add1) {
     constexpr int PER = 16 / (int)sizeof(*src);
-    long long head = (long long)((0 - (uintptr_t)src) & 15) / (long long)sizeof(*src);
-    if (head > total) head = total;
-    const long long nv = (total - head) / PER;
-    const u32x4* v = (const u32x4*)(src + head);
+    const long long nv = total / PER;
+    auto load = [&](long long i) {
+      u32x4 w;
+      __builtin_memcpy(&w, src + i * PER, 16);   // aligned to the element only
+      return w;
+    };
     long long i = first;
     for (; i + 3 * step < nv; i += 4 * step) {
-      const u32x4 w0 = v[i], w1 = v[i + step], w2 = v[i + 2 * step], w3 = v[i + 3 * step];
+      const u32x4 w0 = load(i), w1 = load(i + step), w2 = load(i + 2 * step), w3 = load(i + 3 * step);
       add16(w0); add16(w1); add16(w2); add16(w3);
     }
-    for (; i < nv; i += step) add16(v[i]);
-    if (bx == 0) {
-      if ((long long)threadIdx.x < head) add1(src[threadIdx.x]);
-      if (head + nv * PER + threadIdx.x < total) add1(src[head + nv * PER + threadIdx.x]);
-    }
+    for (; i < nv; i += step) add16(load(i));
+    if (bx == 0 && nv * PER + threadIdx.x < total) add1(src[nv * PER + threadIdx.x]);
   };
   if (a.dt == PRISM_BF16) {
     sweep((const unsigned short*)a.src + (long long)b * total,
