@@ -211,12 +211,13 @@ __device__ inline double minimise_quartic(double c0, double c1, double c2, doubl
 // threads of the workgroup together.
 // rho_local (LDS, one double) stands in for the residual partials in global memory and c_local
 // (LDS, MAXC doubles) for the coefficient partials when the caller has them on chip.
-// ctl_local (LDS): the matrix's control block, when the caller keeps it on chip.
+// ctl_local (LDS): the matrix's control block, when the caller keeps it on chip; it is not done then.  (Nobody may look: thread 0
+// can have set `done` before a late wave gets to the test, and that wave would leave alone.)
 __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = nullptr, double* c_local = nullptr,
                            Ctrl* ctl_local = nullptr) {
   const int t = threadIdx.x;
   Ctrl* ctl = ctl_local ? ctl_local : &a.ctrl[b];
-  const int done = ctl->done;
+  const int done = ctl_local ? 0 : ctl->done;
   const float res0 = ctl->res0, res1 = ctl->res1, res2 = ctl->res2;   // in the shadow of the first load
   if (done) return;
   prism_info* info = a.info + b;
