@@ -106,7 +106,8 @@ template <typename E, int T> struct KMajor {
 // PAIR: two products in a launch (a variant of its own: choosing the descriptor costs every launch 1 to 2 us).
 template <bool PAIR> struct GemmArg { typedef GemmDesc type; };
 template <> struct GemmArg<true> { typedef GemmPair type; };
-template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int ST, int EPI, bool A_KM, bool SYM, bool PAIR>
+// WIDE: offsets within the tile of an operand beyond 32 bits (a variant of its own: they cost registers in the loop).
+template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int ST, int EPI, bool A_KM, bool SYM, bool PAIR, bool WIDE>
 __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kernel(typename GemmArg<PAIR>::type arg) {
   int wg0 = 0, which = 0;
   if constexpr (PAIR) {
@@ -171,29 +172,30 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
   // every lane fetches the unit that belongs at its place.
   // K-contiguous A: rows of 64 bytes (16 k), four to a 256-byte line, unit (row & 3, c) at slot
   // ((row & 3) * 4 + c) ^ (line & 15), conflict free for 16 consecutive rows reading the same c.
-  unsigned aoff[LDA], boff[LDB];
+  typedef std::conditional_t<WIDE, unsigned long long, unsigned> off_t;
+  off_t aoff[LDA], boff[LDB];
   if constexpr (A_KM) {
 #pragma unroll
     for (int it = 0; it < LDA; ++it) {
       const int unit = (it * 4 + wave) * 64 + lane, k = unit / AL::UNITS, u = (unit % AL::UNITS) ^ (AL::UPP * ((k >> 2) & AL::MASK));
-      aoff[it] = (unsigned)(k * g.lda + u * 4) * 4u;
+      aoff[it] = ((off_t)k * (unsigned)g.lda + u * 4) * 4u;
     }
   } else {
     const int lu = (lane & 15) ^ ((wave * 4 + lq) & 15);
 #pragma unroll
-    for (int it = 0; it < LDA; ++it) aoff[it] = (unsigned)(((it * 4 + wave) * 16 + 4 * lq + (lu >> 2)) * g.lda + (lu & 3) * 4) * 4u;
+    for (int it = 0; it < LDA; ++it) aoff[it] = ((off_t)((it * 4 + wave) * 16 + 4 * lq + (lu >> 2)) * (unsigned)g.lda + (lu & 3) * 4) * 4u;
   }
 #pragma unroll
   for (int it = 0; it < LDB; ++it) {
     const int unit = (it * 4 + wave) * B_LANES + lane, k = unit / BL::UNITS, u = (unit % BL::UNITS) ^ (BL::UPP * ((k >> 2) & BL::MASK));
-    boff[it] = (unsigned)k * (unsigned)g.ldb * (unsigned)sizeof(TB) + (unsigned)u * 16u;
+    boff[it] = (off_t)k * (unsigned)g.ldb * (unsigned)sizeof(TB) + (unsigned)u * 16u;
   }
   // Requests are unconditional, so that the number of younger ones in flight is a constant at every wait.
   // Past the end the offsets collapse to zero: the whole wave then fetches the same 16 bytes of the
   // first slab (and nobody reads the result).
   const int KT = g.K / BK;
   auto issue_load = [&](int kt, int slot, int u) {   // u in [0, NL): first the LDA of A, then the LDB of B
-    const unsigned keep = kt < KT ? ~0u : 0u;        // uniform
+    const off_t keep = kt < KT ? ~(off_t)0 : 0;      // uniform
     if (kt >= KT) kt = 0;
     if (u < LDA) {
       unsigned char* dst = smem + slot * STAGE + wave * 1024 + u * 4096;
@@ -460,9 +462,17 @@ int launch_one(const GemmPair& g, int total, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(wgs), dim3(NT), lds, s, arg);
     return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
   };
-  if (g.d[1].batch == 0) return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, false>, total, g.d[0]);
+  const GemmDesc& d = g.d[0];
+  const unsigned long long span_a = A_KM ? 16ull * d.lda + TM : (unsigned long long)TM * d.lda, span_b = 16ull * d.ldb + TN;
+  const bool wide = span_a * 4 > 0xffffffffull || span_b * sizeof(TB) > 0xffffffffull;
+  if (wide) {   // plain products only: the operands of the iterations are far smaller
+    if constexpr (EPI == EPI_STORE)
+      if (g.d[1].batch == 0) return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, false, true>, total, d);
+    return PRISM_EINVAL;
+  }
+  if (g.d[1].batch == 0) return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, false, false>, total, d);
   if constexpr (sizeof(TC) == 4 && EPI == EPI_AXPY && !A_KM)
-    return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, true>, 2 * total, g);
+    return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, true, false>, 2 * total, g);
   return PRISM_EINVAL;
 }
 

@@ -198,3 +198,19 @@ def test_box_muller_factors_exhaustive_bit_exact(prism):
         assert np.array_equal(r.cpu().numpy().view(np.uint64), wr.view(np.uint64)), first
         assert np.array_equal(c.cpu().numpy().view(np.uint64), np.ascontiguousarray(wc).view(np.uint64)), first
         assert np.array_equal(s.cpu().numpy().view(np.uint64), np.ascontiguousarray(ws).view(np.uint64)), first
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_gemm_row_offsets_beyond_32_bits(prism, f64):
+    """A [M][K] with rows so long that the last ones of a tile start more than 2^32 bytes behind the first.  Whole numbers in
+    the last columns, zeros before: exact."""
+    M, N = (64, 64) if f64 else (128, 16)
+    K = (1 << 32) // (4 * (M - 1)) // 64 * 64 + 192
+    assert (M - 2) * K * 4 < 1 << 32 < (M - 1) * K * 4
+    A = torch.zeros((1, M, K), device="cuda")
+    B = torch.zeros((1, K, N), device="cuda", dtype=torch.float64 if f64 else torch.float32)
+    A[0, :, -3:] = torch.arange(1, M + 1, device="cuda", dtype=torch.float32)[:, None]
+    B[0, -3:] = torch.arange(1, N + 1, device="cuda", dtype=B.dtype)
+    C = (prism.gemm_f64a if f64 else prism.gemm_f32)(A, B)
+    want = 3.0 * torch.outer(torch.arange(1, M + 1), torch.arange(1, N + 1)).double()
+    assert torch.equal(C[0].double().cpu(), want)
