@@ -72,7 +72,7 @@ int launch_gemm_f32(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s);
 // square tiles chosen from the size of the launch (M, N multiples of 64); f32_tiles: tiles of one matrix then
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s);
 int f32_tiles(int M, int N, int batch, int sym);
-// both products in one launch: same M, N, K, batch, epilogue, symmetry and operand layout
+// both products in one launch: same M, N, K, batch, epilogue and operand layout; symmetric: both, neither or the first
 int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
 int launch_gemm_f64a(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s);  // A float, B/C double
 

@@ -127,17 +127,19 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
   constexpr int NL = LDA + LDB;
   extern __shared__ __align__(1024) unsigned char smem[];
 
-  // SYM (square fp32 products whose exact result is symmetric): only the tiles on and above the
-  // diagonal are computed; every off-diagonal tile is also stored mirrored.
+  // sym (square fp32 products whose exact result is symmetric): only the tiles on and above the
+  // diagonal are computed; every off-diagonal tile is also stored mirrored.  Of a pair, the first alone may be (PAIR
+  // without SYM).
+  const bool sym = SYM || (PAIR && g.sym);
   const int tiles_m = g.M / TM, tiles_n = g.N / TN;
-  const int per_mat = SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  const int per_mat = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int total = per_mat * g.batch;
   int wg = (int)blockIdx.x - wg0;
   if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);  // one XCD = one contiguous tile range
   const int b = wg / per_mat;
   const int rem = wg - b * per_mat;
   int tm, tn;
-  if (SYM) {
+  if (sym) {
     int left = rem;
     tm = 0;
     while (left >= tiles_m - tm) { left -= tiles_m - tm; ++tm; }
@@ -408,14 +410,14 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
           }
         }
         *(f32x4*)((float*)g.C + (long long)b * g.strideC + (long long)gi * g.ldc + gj) = v;
-        if (SYM && tm != tn) {
+        if (sym && tm != tn) {
           if (skew) v = -v;
 #pragma unroll
           for (int r = 0; r < 4; ++r) ((float*)g.C)[(long long)b * g.strideC + (long long)(gj + r) * g.ldc + gi] = v[r];
         }
       }
     }
-    if (SYM && tm != tn) part *= 2.0f;
+    if (sym && tm != tn) part *= 2.0f;
   } else {
     // register r of lane l: row 4 r + lq of the block, column lr
 #pragma unroll
@@ -451,7 +453,7 @@ __global__ __launch_bounds__(NT, (TM * TN >= 128 * 128 ? 2 : 3)) void gemm_kerne
 
 // One product, or two of the same shape and kind (GemmPair::d[1].batch > 0)
 template <typename TC, typename TB, int TM, int TN, int WGM, int WGN, int EPI, bool A_KM, bool SYM>
-int launch_one(const GemmPair& g, int total, hipStream_t s) {
+int launch_one(const GemmPair& g, int total, hipStream_t s) {   // total: workgroups of the launch
   constexpr int ST = 4;
   const size_t lds = (size_t)ST * (TM * 64 + KMajor<TB, TN>::BYTES);
   auto launch = [&](auto kern, int wgs, const auto& arg) -> int {
@@ -472,7 +474,7 @@ int launch_one(const GemmPair& g, int total, hipStream_t s) {
   }
   if (g.d[1].batch == 0) return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, false, false>, total, d);
   if constexpr (sizeof(TC) == 4 && EPI == EPI_AXPY && !A_KM)
-    return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, true, false>, 2 * total, g);
+    return launch(gemm_kernel<TC, TB, TM, TN, WGM, WGN, ST, EPI, A_KM, SYM, true, false>, total, g);
   return PRISM_EINVAL;
 }
 
@@ -482,7 +484,7 @@ int launch_epi(const GemmPair& g, int total, hipStream_t s) {
     return launch_one<TC, TB, TM, TN, WGM, WGN, EPI, false, false>(g, total, s);
   } else {
     if constexpr (TM == TN) {
-      if (g.d[0].sym) {
+      if (g.d[0].sym && (g.d[1].batch == 0 || g.d[1].sym)) {
         return g.d[0].a_km ? launch_one<TC, TB, TM, TN, WGM, WGN, EPI, true, true>(g, total, s)
                       : launch_one<TC, TB, TM, TN, WGM, WGN, EPI, false, true>(g, total, s);
       }
@@ -499,21 +501,26 @@ int launch_cfg(const GemmDesc& g, hipStream_t s, const GemmDesc* g2 = nullptr) {
     if (q->M % TM || q->N % TN || q->K % BK || q->K < BK || q->lda % 4 || q->ldb % 4 || q->ldc % 4) return PRISM_EINVAL;
     if ((q->epi == EPI_POLYQ || q->epi == EPI_AXPY) && (!q->Cin || q->ldcin % 4)) return PRISM_EINVAL;
   }
-  if (g2 && (g2->M != g.M || g2->N != g.N || g2->batch != g.batch || g2->epi != g.epi || g2->a_km != g.a_km || g2->sym != g.sym)) return PRISM_EINVAL;
+  if (g2 && (g2->M != g.M || g2->N != g.N || g2->batch != g.batch || g2->epi != g.epi || g2->a_km != g.a_km || (g2->sym && !g.sym))) return PRISM_EINVAL;
   const int tm = g.M / TM, tn = g.N / TN;
   GemmPair gb = {};
   gb.d[0] = g;
   if (g2) gb.d[1] = *g2;
-  long long total = (long long)tm * tn * g.batch;
-  if (g.sym) {
-    if (TM != TN || sizeof(TC) == 8 || g.M != g.N) return PRISM_EINVAL;
-    total = (long long)tm * (tm + 1) / 2 * g.batch;
-  } else {
-    static const int no_blocks = ab_switch("PRISM_F32_NO_TILE_BLOCKS");
-    gb.d[0].tile_blocks = gb.d[1].tile_blocks = !no_blocks && tm % 8 == 0 && tn % 8 == 0 && tm * tn > 64;
+  long long total = 0;
+  static const int no_blocks = ab_switch("PRISM_F32_NO_TILE_BLOCKS");
+  for (GemmDesc& d : gb.d) {
+    if (d.batch == 0) continue;
+    gb.first = (int)total;             // where the last one begins
+    if (d.sym) {
+      if (TM != TN || sizeof(TC) == 8 || d.M != d.N) return PRISM_EINVAL;
+      total += (long long)tm * (tm + 1) / 2 * d.batch;
+    } else {
+      d.tile_blocks = !no_blocks && tm % 8 == 0 && tn % 8 == 0 && tm * tn > 64;
+      total += (long long)tm * tn * d.batch;
+    }
+    if (total > 0x3fffffff) return PRISM_EINVAL;
   }
-  if (total <= 0 || total > 0x3fffffff) return PRISM_EINVAL;
-  gb.first = (int)total;
+  if (total <= 0) return PRISM_EINVAL;
   if constexpr (sizeof(TC) == 8) {
     if (g.epi == EPI_STORE) return launch_epi<TC, TB, TM, TN, WGM, WGN, EPI_STORE>(gb, (int)total, s);
     if (g.epi == EPI_MNEXT) return launch_epi<TC, TB, TM, TN, WGM, WGN, EPI_MNEXT>(gb, (int)total, s);
@@ -566,7 +573,7 @@ int launch_gemm_f32(const GemmDesc& g, hipStream_t s) {
 }
 
 int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
-  const int T = f32_tile(a.M, a.N, 2 * (a.sel_batch ? a.sel_batch : a.batch), a.sym);
+  const int T = f32_tile(a.M, a.N, 2 * (a.sel_batch ? a.sel_batch : a.batch), a.sym && b.sym);
   return T == 128 ? launch_cfg<float, float, 128, 128, 2, 2>(a, s, &b) : launch_cfg<float, float, 64, 64, 2, 2>(a, s, &b);
 }
 

@@ -819,12 +819,11 @@ int run_inv_root_f32(Run& r) {
     if (k == r.max_iters) break;
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
-    ax.coef_is_alpha = 1;
+    ax.coef_is_alpha = 1; ax.sym = f32_sym();   // X never re-enters M; the power chain below keeps all tiles
     // The update of X and the first square of the chain below depend on R alone.  Where neither fills the chip they share a
-    // launch (all tiles of both); otherwise X goes by itself, on its upper triangle of tiles (X never re-enters M).
+    // launch.
     const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * r.sel_batch <= 1024;
     if (!paired) {
-      ax.sym = f32_sym();
       ProfScope ps(PK_F32_APPLY, r.s);
       CHECK_LAUNCH(launch_gemm_f32(ax, r.s));
     }

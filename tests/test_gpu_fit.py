@@ -94,3 +94,19 @@ def test_rows_computed_for_a_missing_partner_bf16(prism, n, batch, sketch, plain
         outs.append(x.view(torch.int16).cpu().numpy())
     assert np.array_equal(recs[0]["alpha"], recs[1]["alpha"]) and np.array_equal(recs[0]["residual"], recs[1]["residual"])
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n,p", [(40, 4), (100, 4), (300, 2), (512, 3), (1000, 5)])
+def test_inverse_root_alone_and_in_a_batch(prism, n, p):
+    """One matrix, where the update of X shares a launch with the first square, and a batch, where it does not: the same bits,
+    and the mirrored half of X bit for bit outside the 64 x 64 blocks on the diagonal."""
+    A = torch.from_numpy(W.c4_shampoo_spd(n=n, batch=1)).cuda()
+    x, y = A.clone(), A.repeat(41 if n < 1000 else 3, 1, 1)
+    prism.inv_root(x, p, 30, 16, SEED, 1e-5)
+    prism.inv_root(y, p, 30, 16, SEED, 1e-5)
+    assert torch.equal(x[0], y[0]) and torch.equal(x[0], y[-1])
+    d = x[0] - x[0].T
+    for i in range(0, n, 64):
+        d[i:i + 64, i:i + 64] = 0
+    assert not d.any()
+    assert float((x[0] - x[0].T).norm()) <= 2e-6 * float(x[0].norm())   # on the diagonal to rounding: 30 updates of 2^-24
