@@ -1044,6 +1044,15 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     btot += groups[g].batch;
   }
   if (btot > PRISM_MAX_BATCH) return PRISM_EUNSUPPORTED;
+  // Beside split Gram products the few other ones go with them, as products of one part (same R): two launches instead of
+  // three.  One layer (four shapes), three updates without a fit, us: width 256 170 -> 142 (no split: 143), 512 200 -> 166 (193),
+  // 768 286 -> 250 (284), 1280 622 -> 579 (583).
+  bool any_split = false;
+  for (int g = 0; g < ngroups; ++g) any_split = any_split || Pg[g].ksplit;
+  for (int g = 0; g < ngroups && any_split; ++g) {
+    const long long nt = (Pg[g].Sp + 127) / 128;
+    if (!Pg[g].ksplit && nt * (nt + 1) / 2 * groups[g].batch <= 64) Pg[g].ksplit = 1;
+  }
   Run r;
   int rc = make_plan(r.P, PRISM_FN_POLAR, (int)btot, Pg[0].S, Pg[0].S, PRISM_BF16, degree, sketch_dim, 0, flags, true);
   if (rc != PRISM_OK) return rc;

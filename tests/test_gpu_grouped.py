@@ -268,3 +268,18 @@ def test_same_bits_however_a_batch_is_enqueued_fp32(prism, n, batch, sketch):
         for kind, out, rec in res[1:]:
             assert torch.equal(out, res[0][1]), (fn, kind)
             assert rec.tobytes() == res[0][2].tobytes(), (fn, kind)
+
+
+@pytest.mark.parametrize("w", [128, 200, 256, 512, 640])
+def test_grouped_layer_with_split_gram_products(prism, w):
+    """One layer: the long shapes cut their Gram product into parts, the square one goes with them as one part.  Bits of the
+    single calls."""
+    torch.manual_seed(w)
+    src = [torch.randn(1, m, n, device="cuda").to(torch.bfloat16) for m, n in ((w, w), (w, 4 * w), (4 * w, w), (w, 9 * w), (12 * w, w))]
+    for flags in (0, prism.FLAG_BF16_PLAIN_ITERATE):
+        xs, ys = [t.clone() for t in src], [t.clone() for t in src]
+        infos = prism.run_grouped(prism.FN_POLAR, xs, 5, 8, 16, SEED, 0.0, flags=flags)[1]
+        for g, y in enumerate(ys):
+            rec = prism.polar(y, 5, 8, 16, SEED, 0.0, flags=flags).read()
+            assert torch.equal(xs[g].view(torch.int16), y.view(torch.int16)), (flags, g)
+            assert np.array_equal(rec["alpha"], infos[g].read()["alpha"]), (flags, g)
