@@ -139,6 +139,8 @@ int launch_chain(const float* R, long long strideR, int ldr, const float* Vin, l
 bool chain_takes_small_kernel(int n, int ld, int batch, bool rb);
 // Rb: bf16 copy of R [batch][n][ldr]; D: its exact fp32 diagonal, entry i of matrix b at D[b * strideD + i * ldd]
 // (ldd = ld of R + 1 reads it out of the full fp32 matrix, ldd = 1 out of a compact array)
+int launch_chain_tiny(const float* R, long long strideR, int ldr, const float* V0, long long strideV0, float* Vout,
+                      long long strideJ, long long strideB, int nv, int ld, int batch, const Ctrl* ctrl, hipStream_t s);
 bool chain_bf16_supported(int n, int ld, int batch, int ldr);
 // bf16 R, launches too large for the 16-row kernel: V is read as three bf16 planes (the exact 8 + 8 + 8 bit
 // split of its fp32 entries) laid out [matrix][k / 256][plane][column][unit'][8 k] (chain.hip); Vin (fp32) serves the

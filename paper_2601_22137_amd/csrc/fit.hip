@@ -429,7 +429,10 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
   }
 }
 
-__global__ __launch_bounds__(NT) void solve_kernel(SolveArgs a) { solve_body(a, blockIdx.x); }
+__global__ __launch_bounds__(NT) void solve_kernel(SolveArgs a) {
+  __shared__ double coef[MAXC];   // small matrices: the moments are accumulated right here
+  solve_body(a, blockIdx.x, nullptr, a.ngroups == 1 && a.fn != PRISM_FN_SQRT_NEWTON ? coef : nullptr);
+}
 
 // ---- fp32 polar factor, padded iterate 64 x 64: all iterations in one workgroup ----
 // The products run on v_mfma_f32_16x16x4_f32 (A operand: lane l holds A[m = l % 16][k = l / 16], B
@@ -1096,16 +1099,33 @@ int launch_fit_ld(const FitArgs& a, int batch, hipStream_t s) {
 
 }  // namespace
 
-// Above order 1024 while the workgroups (32 rows, one per CU with bf16 R) fit the chip at a time; with more of them the
-// streaming chain kernels, which also leave more of the chip to the products of the other half, are ahead.  bf16 polar, eight
+// Where the launches are short the fit in one launch is ahead of chain kernels, moments and solve; where they are full its
+// workgroups, which sit through hand-overs and solve, are behind.  The line is drawn by 64-row blocks of the caller's
+// batch.  Time of a call (sign, inverse root, bf16 polar, four or five updates) without / with the fused fit at orders
+// 128, 256, 512, 1024:
+//   sketch 64        128 blocks 1.18-1.27, 1.21-1.38, 1.14-1.43, 1.11-1.42;  256 blocks 0.85-0.88, 0.96-1.00, 0.94-0.98, 0.96-1.00
+//   sketch 16, fp32  256 blocks 1.00-1.11, 1.01-1.04, 1.07, 1.05;  512 blocks 0.86-0.95, 0.96-0.99, 1.03-1.05, 1.01-1.03
+//   sketch 16, bf16  256 blocks 1.10, 1.14, 1.18, 1.16;  512 blocks 0.93, 0.93, 0.98-1.14, 1.00; 1024 blocks 0.88, 0.98, 1.03, 0.93
+//   sketch 32, fp32  256 blocks 0.97-1.06, 1.10, 1.07, 1.05;  512 blocks 0.87-0.98, 1.00, 1.03, 1.01
+//   sketch 32, bf16  256 blocks 1.00, 1.29, 1.16, 1.08;  512 blocks 0.90, 1.01, 0.96, 0.94
+// Above order 1024 the workgroups (32 rows, one per CU with bf16 R) have to fit the chip at a time; the streaming
+// kernels also leave more of the chip to the products of the other half.  bf16 polar, eight
 // updates, ms fused / streaming: 1 x 2048 1.30 / 1.41, 4 x 2048 (256 workgroups) 2.20 / 2.33, 6 x 1536 (288) 1.82 / 1.70,
 // 7 x 1300 (280) 2.48 / 2.29; in halves 8 x 1536 (192 each) 2.11 / 2.25, 12 x 1300 (240) 3.25 / 3.07,
 // 8 x 2048 (256) 3.52 / 3.73 with a sketch of 16 and 3.92 / 3.82 with 32, 16 x 1536 (384) 3.83 / 3.56.  fp32, where the
 // products weigh more: sign 4 x 2048 6.12 / 6.25, 6 x 1536 4.25 / 4.30, 8 x 2048 12.05 / 12.20, 16 x 1536 11.28 / 11.07.
 bool fit_fused_supported(int rows, int ld, int batch, bool b16, bool halves) {
   if (rows % 64) return false;
-  const long long wgs = (long long)(rows / 32) * (halves ? batch / 2 : batch);
-  return rows <= 1024 || (rows <= 2048 && ld <= 32 && wgs <= (b16 ? (halves ? 192 : 256) : 384));
+  const long long blocks = (long long)(rows / 64) * batch;
+  if (rows <= 1024) {
+    if (ld == 64) return blocks <= 128;
+    if (rows <= 192) return blocks <= 256;
+    if (rows <= 320) return blocks <= 384;
+    if (b16 && rows > 512) return blocks <= 256;
+    return ld == 16 || blocks <= 512;
+  }
+  const long long wgs = 2 * (halves ? blocks / 2 : blocks);
+  return rows <= 2048 && ld <= 32 && wgs <= (b16 ? (halves ? 192 : 256) : 384);
 }
 
 int launch_fit(const FitArgs& a, int batch, hipStream_t s) {

@@ -199,7 +199,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   P.o_fit_cpart = P.o_sync + B * FIT_SYNC_WORDS * sizeof(unsigned);
   {
     const long long el = (long long)P.Sp * P.ld;
-    P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);
+    P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);   // 1: done inside the solve kernel
     if (fn == PRISM_FN_SQRT_NEWTON) {   // the moments run over the n x n matrices themselves
       const long long mm = (long long)P.Sp * P.Sp / 65536;
       P.ngroups = mm < 1 ? 1 : (mm > 64 ? 64 : (int)mm);
@@ -340,6 +340,11 @@ struct Run {
             int ldd = 0) {
     const int Sp = P.Sp, ld = P.ld;
     const long long vs = (long long)P.batch * Sp * ld;
+    if (Sp == 64 && !Rb) {   // whole chain in one launch
+      ProfScope ps(PK_CHAIN, s);
+      return launch_chain_tiny(R, (long long)Sp * Sp, Sp, v0 + (long long)(k - first_fit) * Sp * ld, 0, v, vs,
+                               (long long)Sp * ld, P.nv, ld, P.batch, ctrl, s);
+    }
     for (int j = 1; j <= P.nv; ++j) {
       const float* vin = (j == 1) ? v0 + (long long)(k - first_fit) * Sp * ld : v + (j - 2) * vs;
       const long long sin = (j == 1) ? 0 : (long long)Sp * ld;

@@ -162,3 +162,19 @@ def test_sign_coefficients_inside_their_interval(prism, degree, updates):
         assert ks
         for i in (b, b + 1998):
             assert np.abs(rec[i]["alpha"][ks] - alpha[ks]).max() <= 2e-5
+
+
+@pytest.mark.parametrize("n,copies,degree,updates", [(400, 100, 5, 10), (512, 60, 3, 13)])
+def test_sign_coefficients_more_clusters_than_fit_the_chip(prism, n, copies, degree, updates):
+    """Orders at which the fit takes a batch of any size in one launch, 14 to 16 workgroups of 32 rows per matrix."""
+    A = W.sign_indefinite(n=n, batch=2)
+    x = torch.from_numpy(np.tile(A, (copies, 1, 1))).cuda()
+    rec = prism.sign(x, degree, updates, 16, SEED, 0.0).read()
+    for b in range(2):
+        _, oinfo = O.sign(A[b], degree, updates, 16, SEED, 0.0)
+        alpha = np.array(oinfo["alpha"][:updates])
+        ks = _inside(alpha, oinfo["residual"], *((0.5, 1.0) if degree == 3 else (0.375, 1.45)))
+        assert ks
+        assert np.abs(rec[b]["alpha"][ks] - alpha[ks]).max() <= 2e-5
+        assert all(np.array_equal(rec[b]["alpha"], rec[i]["alpha"]) for i in range(b, 2 * copies, 2))
+        assert bool((x[b::2] == x[b]).all())
