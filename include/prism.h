@@ -325,8 +325,8 @@ int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream
  *   prism_gemm_bf16_nt: A [M][K], B [N][K] bf16 bit patterns, C fp32 = A B^T.  `tile` = 128, 256
  *                    (square tiles) or 2561 (256 x 128); + 20000: B is stored [K][N] (row length N);
  *                    + 10000: A is stored [K][M] and B [K][N] (row lengths M and N).
- * M, N must be multiples of 128 (bf16: of the tile's sides; fp32 skinny N = 16, 32, 64 also
- * allowed) and K of 64. */
+ * M, N must be multiples of 64 (bf16: of the tile's sides; fp32 skinny N = 16, 32 also allowed, with M a
+ * multiple of 128) and K of 16 (bf16: of 64). */
 int prism_gemm_f32(const float* A, const float* B, float* C, int batch, int M, int N, int K,
                    int a_km, void* stream);
 int prism_gemm_f64a(const float* A, const double* B, double* C, int batch, int M, int N, int K,

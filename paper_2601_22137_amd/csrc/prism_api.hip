@@ -148,8 +148,11 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
       // to take, in us, from what was measured (order 768, 128 x 128 tiles): a slab of 32 k 0.37 while the CUs have one
       // workgroup each, the second pass 6, and per part 1.6e-6 per entry or the latency of its loads, the update 2.7e-9 per
       // row and squared order (the parts are of equal length and add up to whole tiles, so a number of parts that does
-      // not suit L pads the iterate).  One 768 x 3072 matrix: Gram product 35 -> 20 us; 50257 x 768: 88 -> 73 us; 768 x 768
-      // stays one pass (9 us).
+      // not suit L pads the iterate).  With more workgroups than CUs the slab time is taken to grow in proportion, which
+      // was not measured (three fit a CU); 50257 x 768 stops at one each for it.  One 768 x 3072 matrix: Gram product
+      // 35 -> 20 us; 50257 x 768: 88 -> 73 us; 768 x 768 stays one pass (9 us).  Gain per iteration expected / measured at
+      // other orders: 128 x 1024 1.5 / 2.4 us, 256 x 2048 12.0 / 10.8, 512 x 1024 1.2 / 4.4, 512 x 4096 32.2 / 27.6, 1024 x 2048
+      // 5.1 / 10.2, 1280 x 5120 28.1 / 27.5.
       const double s2 = (double)P.Sp * P.Sp;
       auto cost = [&](long long Kp, int parts) {
         const double load = (double)tri * parts / 256.0;
@@ -594,7 +597,7 @@ int run_polar_bf16(Run& r) {
   // Only with the plain bf16 iterate: with the split one the linear term of Q = R/2 + alpha R^2 keeps
   // the fp32 R (taking it from the bf16 copy raises the residual floor by a few 1e-4, which at
   // tol = 1e-2 cost the reduced config-3 case one more iteration than the oracle).
-  const bool chain_b = !chain_f32 && Sp > 64 && (P.p_s == 0 || chain_bf16_supported(Sp, P.ld, r.sel_batch, Sp));   // order 64: one-launch fp32 chain
+  const bool chain_b = !chain_f32 && (P.p_s == 0 || chain_bf16_supported(Sp, P.ld, r.sel_batch, Sp));
   const bool lean = chain_b && sym && !P.split;
   float* Dg = R;
   const int ntg = Sp / Tg.m;
