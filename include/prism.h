@@ -179,7 +179,7 @@ int prism_polar_ex(void* x, int batch, int m, int n, prism_dtype dt, int degree,
  *     1024 x 1024 bf16 matrix with the split iterate needs 27 MB, sixteen 768 x 768 ones do not
  *     fit) returns PRISM_EUNSUPPORTED before anything is enqueued, with a message in
  *     prism_last_error().
- *     A single bf16 matrix whose Gram product prism_polar_ex would split (its partial products are
+ *     A call whose Gram products prism_polar_ex would split (its partial products are
  *     part of what prism_workspace_bytes reports) is taken here, and by prism_polar_ex with a
  *     workspace too small for them, with the product in one pass if it fits that way: the same
  *     result to rounding.

@@ -12,7 +12,7 @@
 //      safeguarded by bisection, then m
 //      is compared at the end points and those roots; the smallest alpha wins ties.
 // Nothing returns to the host: alpha_k, the done flag and the report stay on the device.
-//   fit_kernel: chain, moments and solve in one launch, for matrices up to order 1024 (2048).
+//   fit_kernel: chain, moments and solve in one launch, where launches do not fill the chip.
 //   small_root_kernel: the whole coupled inverse Newton iteration of a matrix of padded order 64.
 //   small_polar_kernel: for fp32 polar factors whose padded iterate is 64 x 64, the whole method
 //   (residual, chain, fit, update, for all iterations) in one workgroup per matrix.

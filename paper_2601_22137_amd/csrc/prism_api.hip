@@ -391,7 +391,8 @@ struct Run {
     return fit_fused_supported(P.Sp, P.ld, sel_batch, P.dt == PRISM_BF16, in_halves(sel_batch, P.S)) && !small_polar() && !small_root();
   }
   // inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
-  // the launches of that are full: 1024 matrices, p = 4, 0.76 against 1.36 ms)
+  // the launches of that are full: to a tolerance 1024 matrices, p = 4, 0.76 against 1.36 ms, 8192 5.7 against 7.0; with a fixed
+  // budget of four updates it falls behind: 8192 3.87 against 3.70, 16384 7.7 against 7.0)
   bool small_root() const { return P.fn == PRISM_FN_INV_ROOT && P.Sp == 64 && P.p <= 4 && P.ld <= 32; }
   // fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
   bool small_polar() const {
