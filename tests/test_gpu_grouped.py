@@ -283,3 +283,20 @@ def test_grouped_layer_with_split_gram_products(prism, w):
             rec = prism.polar(y, 5, 8, 16, SEED, 0.0, flags=flags).read()
             assert torch.equal(xs[g].view(torch.int16), y.view(torch.int16)), (flags, g)
             assert np.array_equal(rec["alpha"], infos[g].read()["alpha"]), (flags, g)
+
+
+@pytest.mark.parametrize("w,counts", [(768, (24, 8, 4)), (600, (25, 3, 30)), (1024, (3, 17, 2)), (1024, (20, 24))])
+@pytest.mark.parametrize("plain", [False, True])
+def test_grouped_shapes_on_both_sides_of_the_fused_fit(prism, w, counts, plain):
+    """Shapes in unequal numbers: the fit of the few runs in one launch, that of the many in chain kernels, moments and solve.
+    Bits of the single calls, reports in place."""
+    flags = prism.FLAG_BF16_PLAIN_ITERATE if plain else 0
+    torch.manual_seed(w + sum(counts))
+    src = [torch.randn(b, m, n, device="cuda").to(torch.bfloat16) for b, (m, n) in zip(counts, ((w, w), (w, 2 * w), (2 * w, w)))]
+    for tol, iters in ((0.0, 9), (1e-2, 20)):
+        xs, ys = [t.clone() for t in src], [t.clone() for t in src]
+        infos = prism.run_grouped(prism.FN_POLAR, xs, 5, iters, 16, SEED, tol, flags=flags)[1]
+        for g, y in enumerate(ys):
+            rec, got = prism.polar(y, 5, iters, 16, SEED, tol, flags=flags).read(), infos[g].read()
+            assert torch.equal(xs[g].view(torch.int16), y.view(torch.int16)), (tol, g)
+            assert np.array_equal(rec["alpha"], got["alpha"]) and np.array_equal(rec["iters"], got["iters"]), (tol, g)
