@@ -185,7 +185,8 @@ void launch_solve(const SolveArgs& a, int batch, hipStream_t s);
 // The sketch chain, the moments and the solve of one iteration in one launch (fit_kernel), for matrices of padded
 // order up to 2048 (fit_fused_supported).
 constexpr int FIT_MAX_CLUSTER = 64;                       // workgroups per matrix
-constexpr int FIT_SYNC_WORDS = FIT_MAX_CLUSTER + 32;      // per matrix: products done by block of rows, and a counter on a cache line of its own
+// per matrix: products done by block of rows, and on cache lines of their own a counter of them and those of the flow kernel
+constexpr int FIT_SYNC_WORDS = FIT_MAX_CLUSTER + 96;
 constexpr int FIT_EPOCH = 16;                             // more than the products of one launch
 // Polls of a microsecond or two before a workgroup computes itself what it waits for: well above what a partner is late by
 // when other launches run beside this one (16 layers of width 768 in four parts: 3.25 ms with 128 polls, 3.23 with 4096).
@@ -206,6 +207,32 @@ struct FitArgs {
 // batch: the caller's; halves: its launches are for one half of it each, by default
 bool fit_fused_supported(int rows, int ld, int batch, bool b16, bool halves);
 int launch_fit(const FitArgs& a, int batch, hipStream_t s);
+
+// ---- flow.hip : all iterations of an fp32 call in one launch ----
+constexpr int FLOW_MAX_OPS = 4;
+constexpr int FLOW_SLOTS = 256;                           // workgroups of a launch, over all matrices of the caller's batch: one per CU
+struct FlowArgs {
+  FitArgs fit;               // k, mode, V0, epoch and last are filled in per iteration by the kernel
+  // Products of an iteration in order; `residual`: the first one precedes the fit, all others follow it.  What an iteration
+  // writes and a later step reads lies in the set of arrays number k % ring (the next iterate in the following one), ring_bytes
+  // apart; the descriptors and fit.R point into the first set.
+  GemmDesc op[FLOW_MAX_OPS];
+  unsigned char fixed_a[FLOW_MAX_OPS], next_c[FLOW_MAX_OPS];   // A is outside the sets; C (and R32out) lie in the following set
+  int ring; long long ring_bytes;
+  int items[FLOW_MAX_OPS];   // tiles per matrix
+  int tile[FLOW_MAX_OPS];    // ... of 32 x 32 or 64 x 64
+  int start[FLOW_MAX_OPS];   // products behind the fit: tiles behind the fit that must be complete before this one starts;
+                             // -1: starts beside the fit (reads nothing that the others write) and waits for alpha at its end
+  int nops, residual;
+  int first_fit;             // iterations before it, and the one at max_iters, have no chain
+  int warm, sched_len, p_s;
+  int cluster;               // workgroups per matrix
+  const float* rho0; int nparts0;   // without `residual`: partial sums of ||R_0||_F^2 (later ones: fit.sv.rho_part)
+  float sched[PRISM_MAX_ITERS];
+};
+// Tiles per matrix of a product
+int flow_tiles(const GemmDesc& g, int tile);
+int launch_flow(const FlowArgs& a, int batch, hipStream_t s);
 
 // fp32 polar factor of matrices whose padded iterate is 64 x 64: every iteration (residual, sketch
 // chain, fit, update) runs inside one workgroup per matrix, the iterate never leaves the LDS and one
@@ -257,6 +284,7 @@ struct FinalArgs {
   void* dst; void* dst2;                    // caller's arrays (dst2 = inverse square root)
   const Ctrl* ctrl;
   const float* X32[2]; const float* Y32[2];
+  int ring; long long ring_bytes;           // sets of arrays behind X32[0], Y32[0] (flow kernel); 0: two buffers
   const uint16_t* Xa_hi[2]; const uint16_t* Xa_lo[2];
 };
 void launch_finalize(const FinalArgs& a, hipStream_t s);

@@ -363,6 +363,9 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinalArgs a) {
   const Ctrl c = a.ctrl[b];
   if (c.status == PRISM_INFO_NONFINITE || c.status == PRISM_INFO_ZERO) return;
   const int par = c.iters & 1;
+  const long long set = a.ring ? (long long)(c.iters % a.ring) * a.ring_bytes : 0;
+  const float* X = (const float*)((const char*)a.X32[a.ring ? 0 : par] + set);
+  const float* Y = (const float*)((const char*)a.Y32[a.ring ? 0 : par] + set);
   const long long mat = (long long)a.m * a.n;
   const long long i = (long long)blockIdx.x * NT + threadIdx.x;
   if (i >= mat) return;
@@ -370,18 +373,18 @@ __global__ __launch_bounds__(NT) void finalize_kernel(FinalArgs a) {
   const long long o = (long long)b * a.Lp * a.Sp +
                       (a.transpose ? ((long long)col * a.Sp + r) : ((long long)r * a.Sp + col));
   if (a.fn == PRISM_FN_INVERSE) {
-    ((float*)a.dst)[(long long)b * mat + i] = (float)((double)a.X32[par][o] / c.norm);
+    ((float*)a.dst)[(long long)b * mat + i] = (float)((double)X[o] / c.norm);
   } else if (a.fn == PRISM_FN_POLAR) {
-    ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
+    ((float*)a.dst)[(long long)b * mat + i] = X[o];
   } else if (a.fn == PRISM_FN_SQRT_NEWTON) {
-    ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
-    ((float*)a.dst2)[(long long)b * mat + i] = a.Y32[par][o];
+    ((float*)a.dst)[(long long)b * mat + i] = X[o];
+    ((float*)a.dst2)[(long long)b * mat + i] = Y[o];
   } else if (a.fn == PRISM_FN_SQRT) {
     const double rs = sqrt(c.norm);
-    ((float*)a.dst)[(long long)b * mat + i] = (float)((double)a.X32[par][o] * rs);
-    ((float*)a.dst2)[(long long)b * mat + i] = (float)((double)a.Y32[par][o] / rs);
+    ((float*)a.dst)[(long long)b * mat + i] = (float)((double)X[o] * rs);
+    ((float*)a.dst2)[(long long)b * mat + i] = (float)((double)Y[o] / rs);
   } else {
-    ((float*)a.dst)[(long long)b * mat + i] = a.X32[par][o];
+    ((float*)a.dst)[(long long)b * mat + i] = X[o];
   }
 }
 

@@ -89,6 +89,7 @@ struct Plan {
   bool shared_gpu; // PRISM_FLAG_SHARED_GPU
   size_t o_x[2], o_y[2], o_r, o_q, o_t[3];        // fp32 paths (o_y doubles as M64 for inverse root)
   size_t o_xhi[2], o_xlo[2], o_rb, o_qb;          // bf16 polar
+  int ring; long long ring_bytes;                 // fp32: all iterations in one launch (flow.hip), sets of arrays from o_x[0] on
   int ksplit;      // polar: parts of the K loop of X^T X (0 = one pass); partial products at o_gpart
   size_t o_gpart;
   size_t total;
@@ -97,7 +98,40 @@ struct Plan {
 // Internal flag of make_plan: no split-K Gram product.  Its partial products need scratch of their own; a call whose
 // workspace is large enough without them only takes the one-pass product.
 constexpr unsigned FLAG_NO_SPLIT_K = 1u << 31;
+// ... and no flow kernel (whose ring of arrays takes more than the two iterates)
+constexpr unsigned FLAG_NO_FLOW = 1u << 30;
 constexpr long long MAX_ENTRIES = (1ll << 31) - 1;   // of a matrix, sides padded
+
+// Batches that run as two halves unless the caller asks otherwise (run_auto)
+bool in_halves(int batch, int S) { return batch >= 8 && batch % 2 == 0 && S >= 1024; }
+// inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
+// the launches of that are full: to a tolerance 1024 matrices, p = 4, 0.76 against 1.36 ms, 8192 5.7 against 7.0; with a fixed
+// budget of four updates it falls behind: 8192 3.87 against 3.70, 16384 7.7 against 7.0)
+bool takes_small_root(const Plan& P) { return P.fn == PRISM_FN_INV_ROOT && P.Sp == 64 && P.p <= 4 && P.ld <= 32; }
+// fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
+bool takes_small_polar(const Plan& P) {
+  static const int off = ab_switch("PRISM_NO_SMALL_KERNEL");
+  return !off && P.fn == PRISM_FN_POLAR && P.dt == PRISM_F32 && P.Sp == 64 && P.Lp == 64 && P.ngroups == 1;
+}
+bool takes_fused_fit(const Plan& P, int sel_batch) {
+  return fit_fused_supported(P.Sp, P.ld, sel_batch, P.dt == PRISM_BF16, in_halves(sel_batch, P.S)) && !takes_small_polar(P) && !takes_small_root(P);
+}
+// All iterations in one launch (flow.hip): sets of arrays in its ring, 0: a launch per step.  bytes: of one set.
+// A workgroup for every row block of a fit has to be there (launch_flow's cluster), and the tiles must not be those of a
+// launch that fills the chip.  Time with launches / with the flow kernel, budget of 40 to 1e-5 (9 to 13 updates), by 64 x 64 tiles
+// of the update over the batch:
+//   sign          order 256: 16 tiles 2.2, 128 2.0, 256 1.6;  512: 64 1.5, 256 1.5, 512 1.2;  768: 144 1.3, 288 1.1, 576 1.0;  1024: 256 1.0
+//   inverse root  order 256: 16 tiles 2.6, 128 1.7, 256 1.9;  512: 64 1.7, 256 1.5, 512 1.1;  768: 144 1.2, 288 1.2, 576 1.1;  1024: 256 1.2
+//   polar         order 256: 32 tiles 1.7, 256 1.6, 512 1.4;  512: 128 1.6, 512 1.1, 1024 1.0;  768: 288 1.2, 576 1.2;  1024: 512 1.1
+//   square root   order 256: 16 tiles 2.6, 128 2.7, 256 2.0;  512: 64 2.0, 256 1.5, 512 1.2;  768: 144 1.5, 288 1.3;  1024: 256 1.1
+int flow_tiles_of(const Plan& P, int sel_batch) { return (P.Sp / 64) * (P.Lp / 64) * sel_batch; }
+int flow_ring(const Plan& P, int sel_batch, size_t bytes) {
+  static const int off = ab_switch("PRISM_NO_FLOW");
+  if (off || P.dt != PRISM_F32 || P.fn == PRISM_FN_SQRT_NEWTON || (P.fn == PRISM_FN_INV_ROOT && (P.p < 2 || P.p > 4)) || P.ksplit) return 0;
+  if (P.Sp > 768 || (P.ld == 64 && P.Sp > 512) || !takes_fused_fit(P, sel_batch)) return 0;
+  if (flow_tiles_of(P, sel_batch) > (P.Sp <= 512 ? 512 : 320) || FLOW_SLOTS / sel_batch < P.Sp / 16) return 0;
+  return bytes <= (16u << 20) ? 8 : 4;
+}
 
 // shared_shapes: the plan of a launch sequence over several shape groups with the same short side;
 // the iterate buffers are then laid out per group by the caller (offsets o_x* stay 0).  sel_batch: the batch of the
@@ -195,8 +229,8 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   P.o_v0 = take((size_t)PRISM_MAX_ITERS * P.Sp * P.ld * sizeof(float));   // S_k^T for every k, generated once per call
   P.o_v = take((size_t)P.nv * B * P.Sp * P.ld * sizeof(float));
   // Room in V: until the fit begins the norm's partial sums lie at its head (4 KiB a matrix at most, in V_1 .. V_{nv-1}).
-  // fit_kernel does not store V_nv, and has its counters and coefficient partials there (384 + 8.5 Sp bytes
-  // a matrix, of 64 Sp and more).
+  // fit_kernel does not store V_nv, and has its counters and coefficient partials there (640 + 8.5 Sp bytes
+  // a matrix, of 64 Sp and more; with the residual partials of flow_kernel 4 Sp^2 / 1024 more).
   P.o_sumsq = P.o_v;
   P.o_sync = P.o_v + (size_t)(P.nv - 1) * B * P.Sp * P.ld * sizeof(float);
   P.o_fit_cpart = P.o_sync + B * FIT_SYNC_WORDS * sizeof(unsigned);
@@ -222,28 +256,32 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
     P.o_r = take(B * SS * 4);
     P.o_rb = take(B * SS * 2);
     P.o_qb = P.d == 2 ? take(B * SS * 2) : 0;
-  } else if (fn == PRISM_FN_POLAR || fn == PRISM_FN_SIGN) {
-    for (int i = 0; i < 2; ++i) P.o_x[i] = take(B * LS * 4);
-    P.o_r = take(B * SS * 4);
-    P.o_q = P.d == 2 ? take(B * SS * 4) : 0;
   } else if (fn == PRISM_FN_SQRT_NEWTON) {
     for (int i = 0; i < 2; ++i) { P.o_x[i] = take(B * SS * 4); P.o_y[i] = take(B * SS * 4); }
     P.o_r = take(B * SS * 4);        // M_k
     P.o_q = take(B * SS * 4);        // N_k = M_k^{-1}
     P.o_t[0] = take((size_t)spd_inverse_scratch_floats(P.Sp, batch, sel_batch ? sel_batch : batch) * 4 + 256);   // pivot panels of the inverse
-  } else if (fn == PRISM_FN_INVERSE) {
-    for (int i = 0; i < 2; ++i) P.o_x[i] = take(B * SS * 4);
-    P.o_y[0] = take(B * SS * 4);     // A / ||A||_F
-    P.o_r = take(B * SS * 4);
-    P.o_q = take(B * SS * 4);
-  } else if (fn == PRISM_FN_SQRT) {
-    for (int i = 0; i < 2; ++i) { P.o_x[i] = take(B * SS * 4); P.o_y[i] = take(B * SS * 4); }
-    P.o_r = take(B * SS * 4);
-    P.o_q = P.d == 2 ? take(B * SS * 4) : 0;
   } else {
-    for (int i = 0; i < 2; ++i) { P.o_x[i] = take(B * SS * 4); P.o_y[i] = take(B * SS * 8); }
+    if (fn == PRISM_FN_INVERSE) P.o_y[0] = take(B * SS * 4);   // A / ||A||_F
+    const size_t set0 = off;
+    P.o_x[0] = take(B * (fn == PRISM_FN_POLAR ? LS : SS) * 4);
+    if (fn == PRISM_FN_SQRT) P.o_y[0] = take(B * SS * 4);
+    if (fn == PRISM_FN_INV_ROOT) P.o_y[0] = take(B * SS * 8);  // M
+    const size_t iterate = off - set0;
     P.o_r = take(B * SS * 4);
-    for (int i = 0; i < 3; ++i) P.o_t[i] = take(B * SS * 4);
+    if (fn == PRISM_FN_INV_ROOT) for (int i = 0; i < 3; ++i) P.o_t[i] = take(B * SS * 4);
+    else P.o_q = (P.d == 2 || fn == PRISM_FN_INVERSE) ? take(B * SS * 4) : 0;
+    P.ring = (flags & FLAG_NO_FLOW) ? 0 : flow_ring(P, sel_batch ? sel_batch : batch, off - set0);
+    if (P.ring) {
+      P.ring_bytes = (long long)(off - set0);
+      off = set0 + (size_t)P.ring * P.ring_bytes;
+      P.o_x[1] = P.o_x[0] + P.ring_bytes;
+      P.o_y[1] = P.o_y[0] + P.ring_bytes;
+    } else {
+      P.o_x[1] = off;
+      if (fn == PRISM_FN_SQRT || fn == PRISM_FN_INV_ROOT) P.o_y[1] = off + (P.o_y[0] - P.o_x[0]);
+      off += iterate;
+    }
   }
   P.o_gpart = P.ksplit ? take(B * P.ksplit * SS * 4) : 0;
   P.total = off;
@@ -293,9 +331,6 @@ int check_hip() {
   if (e != hipSuccess) { set_last_error(hipGetErrorString(e)); return PRISM_EHIP; }
   return PRISM_OK;
 }
-
-// Batches that run as two halves unless the caller asks otherwise (run_auto)
-bool in_halves(int batch, int S) { return batch >= 8 && batch % 2 == 0 && S >= 1024; }
 
 struct Run {
   Plan P;
@@ -377,6 +412,10 @@ struct Run {
       CHECK_LAUNCH(chain(R, k, Rb, D, strideD, ldd));
       return solve(k, nparts);
     }
+    ProfScope ps(PK_CHAIN, s);
+    return launch_fit(fit_args(k, nparts, R, Rb, D, strideD, ldd), P.batch, s);
+  }
+  FitArgs fit_args(int k, int nparts, const float* R, const uint16_t* Rb, const float* D, long long strideD, int ldd) const {
     FitArgs f = {};
     f.sv = solve_args(k, nparts, 0);
     f.sv.ngroups = P.Sp / 16; f.sv.cpart = at<double>(P.o_fit_cpart);
@@ -384,21 +423,17 @@ struct Run {
     f.D = D; f.strideD = strideD; f.ldd = ldd;
     f.V0 = v0 + (long long)(k - first_fit) * P.Sp * P.ld; f.V = v; f.nv = P.nv;
     f.sync = at<unsigned>(P.o_sync); f.epoch = FIT_EPOCH * (unsigned)k; f.polls = fit_polls;
-    ProfScope ps(PK_CHAIN, s);
-    return launch_fit(f, P.batch, s);
+    return f;
   }
-  bool fused() const {
-    return fit_fused_supported(P.Sp, P.ld, sel_batch, P.dt == PRISM_BF16, in_halves(sel_batch, P.S)) && !small_polar() && !small_root();
+  bool fused() const { return takes_fused_fit(P, sel_batch); }
+  // Without a tolerance no launches follow convergence, and the line lies lower.  Eight updates, launches / flow kernel: sign order
+  // 256, 128 tiles 1.2, 512 0.98; order 512, 128 tiles 1.2, 256 1.0, 512 0.88; inverse root 256 tiles 1.2 and 1.1; polar 256 tiles 1.1
+  // and 1.1, 512 1.0 and 0.90; square root (two updates) 2 x 128 tiles 1.2 and 1.1, 2 x 256 0.93 and 0.89; order 768 0.96 to 1.04.
+  bool flow() const {
+    return P.ring && (tol > 0.0 || (P.Sp <= 512 && flow_tiles_of(P, sel_batch) * (P.fn == PRISM_FN_SQRT ? 2 : 1) <= 256));
   }
-  // inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
-  // the launches of that are full: to a tolerance 1024 matrices, p = 4, 0.76 against 1.36 ms, 8192 5.7 against 7.0; with a fixed
-  // budget of four updates it falls behind: 8192 3.87 against 3.70, 16384 7.7 against 7.0)
-  bool small_root() const { return P.fn == PRISM_FN_INV_ROOT && P.Sp == 64 && P.p <= 4 && P.ld <= 32; }
-  // fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
-  bool small_polar() const {
-    static const int off = ab_switch("PRISM_NO_SMALL_KERNEL");
-    return !off && P.fn == PRISM_FN_POLAR && P.dt == PRISM_F32 && P.Sp == 64 && P.Lp == 64 && P.ngroups == 1;
-  }
+  bool small_root() const { return takes_small_root(P); }
+  bool small_polar() const { return takes_small_polar(P); }
 
   SolveArgs solve_args(int k, int nparts, int phase) const {
     SolveArgs a = {};
@@ -452,6 +487,62 @@ int f32_sym() {
   return off ? 0 : 1;
 }
 
+// The products of an iteration for the flow kernel.  phase: -1 beside the fit (alpha enters at the end), then in order; products of
+// the same phase read nothing of each other.
+struct FlowOp { GemmDesc d; int phase; };
+
+int run_flow(const Run& r, const FlowOp* ops, int nops, bool residual, const float* R, int nparts0) {
+  const Plan& P = r.P;
+  FlowArgs a = {};
+  const int slots = FLOW_SLOTS / r.sel_batch;
+  int widest = 0, nparts = 0;
+  a.nops = nops; a.residual = residual;
+  // phases: -2 the residual, -1 beside the fit, ...
+  auto phase = [&](int i) { return i < (int)residual ? -2 : ops[i].phase; };
+  for (int i = 0; i < nops; ++i) {
+    // 32 x 32 tiles where the phase has workgroups for all of them
+    int fine = 0;
+    for (int j = 0; j < nops; ++j)
+      if (phase(j) == phase(i)) fine += flow_tiles(ops[j].d, 32);
+    static const int forced = ab_switch("PRISM_FLOW_TILE");
+    a.tile[i] = forced ? forced : (fine <= slots && phase(i) != -1 ? 32 : 64);   // beside the fit nobody waits for them
+    a.items[i] = flow_tiles(ops[i].d, a.tile[i]);
+    if (ops[i].d.epi == EPI_RESIDUAL || ops[i].d.epi == EPI_MNEXT) nparts = a.items[i];
+  }
+  for (int i = 0; i < nops; ++i) {
+    int together = phase(i) == -1 ? P.Sp / 16 : 0;
+    a.start[i] = phase(i) == -1 ? -1 : 0;
+    for (int j = residual; j < nops; ++j) {
+      if (phase(i) >= 0 && phase(j) < phase(i)) a.start[i] += a.items[j];
+      if (phase(j) == phase(i)) together += a.items[j];
+    }
+    if (i < (int)residual) together = a.items[i];
+    if (together > widest) widest = together;
+  }
+  a.cluster = widest < slots ? widest : slots;
+  a.fit = r.fit_args(0, nparts, R, nullptr, nullptr, 0, 0);
+  a.rho0 = r.rho; a.nparts0 = nparts0;
+  float* rho = (float*)(r.at<double>(P.o_fit_cpart) + (long long)P.batch * (P.Sp / 16) * 17);   // behind the coefficient partials
+  a.fit.sv.rho_part = rho;
+  a.fit.V0 = r.v0; a.fit.epoch = 0;
+  a.ring = P.ring; a.ring_bytes = P.ring_bytes;
+  const char* set0 = r.at<char>(P.o_x[0]);
+  auto in_ring = [&](const void* p) { return (const char*)p >= set0 && (const char*)p < set0 + P.ring * P.ring_bytes; };
+  for (int i = 0; i < nops; ++i) {
+    a.op[i] = ops[i].d;
+    a.op[i].rho_part = rho;
+    a.fixed_a[i] = !in_ring(ops[i].d.A);
+    // results that the next iteration starts from: the descriptor has them in the second set
+    a.next_c[i] = (const char*)ops[i].d.C >= set0 + P.ring_bytes;
+    if (a.next_c[i]) a.op[i].C = (char*)a.op[i].C - P.ring_bytes;
+  }
+  a.first_fit = P.p_s == 0 || r.first_fit > r.max_iters ? r.max_iters : r.first_fit;
+  a.warm = r.warm; a.sched_len = r.sched_len; a.p_s = P.p_s;
+  for (int i = 0; i < r.sched_len; ++i) a.sched[i] = r.sched[i];
+  ProfScope ps(PK_F32_APPLY, r.s);
+  return launch_flow(a, P.batch, r.s);
+}
+
 int run_polar_f32(Run& r) {
   const Plan& P = r.P;
   const int Sp = P.Sp, Lp = P.Lp;
@@ -478,13 +569,36 @@ int run_polar_f32(Run& r) {
     ProfScope ps(PK_F32_SMALL_POLAR, r.s);
     return launch_small_polar(sa, P.batch, r.s);
   }
-  int cur = 0;
-  for (int k = 0; k <= r.max_iters; ++k) {
-    if (k == r.max_iters && r.tol <= 0.0) break;
-    // G = X^T X; matrix sign: G = X X (any square input, all tiles)
+  // G = X^T X; matrix sign: G = X X (any square input, all tiles)
+  auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, X[cur], Sp, LS, X[cur], Sp, LS, Sp, Sp, Lp, polar ? 1 : 0);
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
+    return g;
+  };
+  auto square = [&]() {
+    GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, polar ? 1 : 0);  // mirrored R: R^2 = R^T R
+    q.sym = sym;
+    q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
+    return q;
+  };
+  auto update = [&](int cur) {
+    GemmDesc a = f32_desc(r, X[cur], Sp, LS, P.d == 2 ? Q : R, Sp, SS, Lp, Sp, Sp, 0);      // X + X Q
+    a.epi = EPI_AXPY; a.C = X[cur ^ 1]; a.strideC = LS; a.ldc = Sp; a.Cin = X[cur]; a.strideCin = LS; a.ldcin = Sp;
+    a.coef_is_alpha = P.d == 1;
+    return a;
+  };
+  if (r.flow()) {
+    if (P.d == 1) {
+      const FlowOp ops[] = {{residual(0), 0}, {update(0), -1}};
+      return run_flow(r, ops, 2, true, R, nparts);
+    }
+    const FlowOp ops[] = {{residual(0), 0}, {square(), -1}, {update(0), 0}};
+    return run_flow(r, ops, 3, true, R, nparts);
+  }
+  int cur = 0;
+  for (int k = 0; k <= r.max_iters; ++k) {
+    if (k == r.max_iters && r.tol <= 0.0) break;
     if (polar && P.ksplit) {
       ProfScope ps(PK_F32_RESID, r.s);
       const int Kp = Lp / P.ksplit;
@@ -503,22 +617,12 @@ int run_polar_f32(Run& r) {
       CHECK_LAUNCH(check_hip());
     } else {
       ProfScope ps(PK_F32_RESID, r.s);
-      CHECK_LAUNCH(launch_gemm_f32(g, r.s));
+      CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s));
     }
     CHECK_LAUNCH(r.fit(k, (polar && P.ksplit) ? gram_reduce_parts(Sp) : nparts, R));
     if (k == r.max_iters) break;
-    const float* Bop = R;
-    if (P.d == 2) {
-      GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, polar ? 1 : 0);  // mirrored R: R^2 = R^T R
-      q.sym = sym;
-      q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
-      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
-      Bop = Q;
-    }
-    GemmDesc a = f32_desc(r, X[cur], Sp, LS, Bop, Sp, SS, Lp, Sp, Sp, 0);      // X + X Q
-    a.epi = EPI_AXPY; a.C = X[cur ^ 1]; a.strideC = LS; a.ldc = Sp; a.Cin = X[cur]; a.strideCin = LS; a.ldcin = Sp;
-    a.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(a, r.s)); }
+    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -701,30 +805,47 @@ int run_sqrt_f32(Run& r) {
   // Y X and R^2 is stable but costs the root an order of magnitude of accuracy from kappa ~ 1e4 on.)
   const int sym = 0;
   const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
-  int cur = 0;
-  for (int k = 0; k <= r.max_iters; ++k) {
-    if (k == r.max_iters && r.tol <= 0.0) break;
+  auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, Y[cur], Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);    // G = Y X
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
-    CHECK_LAUNCH(r.fit(k, nparts, R));
-    if (k == r.max_iters) break;
-    const float* Pm = R;
-    if (P.d == 2) {
-      GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
-      q.sym = sym;
-      q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
-      { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
-      Pm = Q;
-    }
+    return g;
+  };
+  auto square = [&]() {
+    GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
+    q.sym = sym;
+    q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
+    return q;
+  };
+  const float* Pm = P.d == 2 ? Q : R;
+  auto update_x = [&](int cur) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, Pm, Sp, SS, Sp, Sp, Sp, 0);        // X + X Q
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
     ax.coef_is_alpha = P.d == 1;
+    return ax;
+  };
+  auto update_y = [&](int cur) {
     GemmDesc ay = f32_desc(r, Pm, Sp, SS, Y[cur], Sp, SS, Sp, Sp, Sp, 0);        // Y + Q Y
     ay.epi = EPI_AXPY; ay.C = Y[cur ^ 1]; ay.strideC = SS; ay.ldc = Sp; ay.Cin = Y[cur]; ay.strideCin = SS; ay.ldcin = Sp;
     ay.coef_is_alpha = P.d == 1;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32_pair(ax, ay, r.s)); }
+    return ay;
+  };
+  if (r.flow()) {
+    if (P.d == 1) {
+      const FlowOp ops[] = {{residual(0), 0}, {update_x(0), -1}, {update_y(0), -1}};
+      return run_flow(r, ops, 3, true, R, nparts);
+    }
+    const FlowOp ops[] = {{residual(0), 0}, {square(), -1}, {update_x(0), 0}, {update_y(0), 0}};
+    return run_flow(r, ops, 4, true, R, nparts);
+  }
+  int cur = 0;
+  for (int k = 0; k <= r.max_iters; ++k) {
+    if (k == r.max_iters && r.tol <= 0.0) break;
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s)); }
+    CHECK_LAUNCH(r.fit(k, nparts, R));
+    if (k == r.max_iters) break;
+    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32_pair(update_x(cur), update_y(cur), r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -741,22 +862,35 @@ int run_inverse_f32(Run& r) {
   float* Q = r.at<float>(P.o_q);
   const int sym = 0;   // A_s X_k is symmetric up to kappa * eps only: all tiles
   const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
-  int cur = 0;
-  for (int k = 0; k <= r.max_iters; ++k) {
-    if (k == r.max_iters && r.tol <= 0.0) break;
+  auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, As, Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);
     g.sym = sym;
     g.epi = EPI_RESIDUAL; g.C = R; g.strideC = SS; g.ldc = Sp; g.rho_part = r.rho;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(g, r.s)); }
-    CHECK_LAUNCH(r.fit(k, nparts, R));
-    if (k == r.max_iters) break;
+    return g;
+  };
+  auto square = [&]() {
     GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
     q.sym = sym;
     q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 1.0f;
-    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(q, r.s)); }
+    return q;
+  };
+  auto update = [&](int cur) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, Q, Sp, SS, Sp, Sp, Sp, 0);
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(ax, r.s)); }
+    return ax;
+  };
+  if (r.flow()) {
+    const FlowOp ops[] = {{residual(0), 0}, {square(), -1}, {update(0), 0}};
+    return run_flow(r, ops, 3, true, R, nparts);
+  }
+  int cur = 0;
+  for (int k = 0; k <= r.max_iters; ++k) {
+    if (k == r.max_iters && r.tol <= 0.0) break;
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s)); }
+    CHECK_LAUNCH(r.fit(k, nparts, R));
+    if (k == r.max_iters) break;
+    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s)); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -821,49 +955,69 @@ int run_inv_root_f32(Run& r) {
     ProfScope ps(PK_F32_APPLY, r.s);
     return launch_small_root(a, P.batch, r.s);
   }
+  auto update = [&](int cur) {
+    GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
+    ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
+    ax.coef_is_alpha = 1; ax.sym = f32_sym();   // X never re-enters M; the power chain below keeps all tiles
+    return ax;
+  };
+  // (I + alpha R)^q = I + E_q, built on the part beyond the identity so that fp32 rounding acts
+  // on the small quantity only: E_1 = alpha R, squaring E <- 2E + E E, times T: E <- E + E_1 + E E_1.
+  // E_1 itself is never stored: wherever it is an operand R stands in and the epilogue supplies
+  // the powers of alpha.
+  auto square = [&](const float* E /* null: E_1 */, float* dst) {
+    const float* Eop = E ? E : R;
+    GemmDesc sq = f32_desc(r, Eop, Sp, SS, Eop, Sp, SS, Sp, Sp, Sp, 0);
+    sq.epi = EPI_AXPY; sq.C = dst; sq.strideC = SS; sq.ldc = Sp; sq.Cin = Eop; sq.strideCin = SS; sq.ldcin = Sp; sq.c_in = 2.0f;
+    if (!E) { sq.cin_alpha_pow = 1; sq.coef_is_alpha = 2; }
+    return sq;
+  };
+  auto times_t = [&](const float* U, float* dst) {                             // U + alpha R + alpha U R
+    GemmDesc mu = f32_desc(r, U, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
+    mu.epi = EPI_AXPY; mu.C = dst; mu.strideC = SS; mu.ldc = Sp; mu.Cin = U; mu.strideCin = SS; mu.ldcin = Sp; mu.c_in = 1.0f;
+    mu.Cin2 = R; mu.cin2_alpha_pow = 1; mu.coef_is_alpha = 1;
+    return mu;
+  };
+  auto m_times = [&](const float* E, const double* Min, double* Mout, float* Rout) {   // Mout = Min + E Min in fp64
+    GemmDesc mn = {};
+    mn.A = E; mn.strideA = SS; mn.lda = Sp; mn.B = Min; mn.strideB = SS; mn.ldb = Sp;
+    mn.M = Sp; mn.N = Sp; mn.K = Sp; mn.batch = P.batch; mn.n_true = P.S; mn.ctrl = r.ctrl;
+    mn.epi = EPI_MNEXT; mn.C = Mout; mn.strideC = SS; mn.ldc = Sp;
+    mn.Cin = Min; mn.strideCin = SS; mn.ldcin = Sp;
+    mn.R32out = Rout; mn.strideR = SS; mn.ldr = Sp; mn.rho_part = r.rho;
+    return mn;
+  };
+  if (r.flow()) {   // p = 2 .. 4
+    FlowOp ops[FLOW_MAX_OPS];
+    int n = 0;
+    const float* E = Tm[1];
+    auto put = [&](const GemmDesc& d, int phase) { ops[n].d = d; ops[n++].phase = phase; };
+    put(update(0), -1);
+    put(square(nullptr, Tm[1]), -1);
+    if (p == 3) { put(times_t(Tm[1], Tm[2]), 0); E = Tm[2]; }
+    if (p == 4) { put(square(Tm[1], Tm[2]), 0); E = Tm[2]; }
+    put(m_times(E, M[0], M[1], R), 1);
+    return run_flow(r, ops, n, false, R, nparts);
+  }
   int cur = 0, mc = 0;   // current X and M buffers
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
     CHECK_LAUNCH(r.fit(k, k == 0 ? nparts0 : nparts, R));
     if (k == r.max_iters) break;
-    GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
-    ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
-    ax.coef_is_alpha = 1; ax.sym = f32_sym();   // X never re-enters M; the power chain below keeps all tiles
     // The update of X and the first square of the chain below depend on R alone.  Where neither fills the chip they share a
     // launch.
     const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * r.sel_batch <= 1024;
     if (!paired) {
       ProfScope ps(PK_F32_APPLY, r.s);
-      CHECK_LAUNCH(launch_gemm_f32(ax, r.s));
+      CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s));
     }
-    // (I + alpha R)^q = I + E_q, built on the part beyond the identity so that fp32 rounding acts
-    // on the small quantity only: E_1 = alpha R, squaring E <- 2E + E E, times T: E <- E + E_1 + E E_1.
-    // E_1 itself is never stored: wherever it is an operand R stands in and the epilogue supplies
-    // the powers of alpha.
-    auto square = [&](const float* E /* null: E_1 */, float* dst) -> int {
-      const float* Eop = E ? E : R;
-      GemmDesc sq = f32_desc(r, Eop, Sp, SS, Eop, Sp, SS, Sp, Sp, Sp, 0);
-      sq.epi = EPI_AXPY; sq.C = dst; sq.strideC = SS; sq.ldc = Sp; sq.Cin = Eop; sq.strideCin = SS; sq.ldcin = Sp; sq.c_in = 2.0f;
-      if (!E) { sq.cin_alpha_pow = 1; sq.coef_is_alpha = 2; }
+    auto run_square = [&](const float* E, float* dst) -> int {
       ProfScope ps(PK_F32_STORE, r.s);
-      return !E && paired ? launch_gemm_f32_pair(ax, sq, r.s) : launch_gemm_f32(sq, r.s);
+      return !E && paired ? launch_gemm_f32_pair(update(cur), square(E, dst), r.s) : launch_gemm_f32(square(E, dst), r.s);
     };
-    auto times_t = [&](const float* U, float* dst) -> int {                      // U + alpha R + alpha U R
-      GemmDesc mu = f32_desc(r, U, Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);
-      mu.epi = EPI_AXPY; mu.C = dst; mu.strideC = SS; mu.ldc = Sp; mu.Cin = U; mu.strideCin = SS; mu.ldcin = Sp; mu.c_in = 1.0f;
-      mu.Cin2 = R; mu.cin2_alpha_pow = 1; mu.coef_is_alpha = 1;
-      ProfScope ps(PK_F32_STORE, r.s);
-      return launch_gemm_f32(mu, r.s);
-    };
-    auto m_times = [&](const float* E, const double* Min, double* Mout, float* Rout) -> int {   // Mout = Min + E Min in fp64
-      GemmDesc mn = {};
-      mn.A = E; mn.strideA = SS; mn.lda = Sp; mn.B = Min; mn.strideB = SS; mn.ldb = Sp;
-      mn.M = Sp; mn.N = Sp; mn.K = Sp; mn.batch = P.batch; mn.n_true = P.S; mn.ctrl = r.ctrl;
-      mn.epi = EPI_MNEXT; mn.C = Mout; mn.strideC = SS; mn.ldc = Sp;
-      mn.Cin = Min; mn.strideCin = SS; mn.ldcin = Sp;
-      mn.R32out = Rout; mn.strideR = SS; mn.ldr = Sp; mn.rho_part = r.rho;
+    auto run_m_times = [&](const float* E, const double* Min, double* Mout, float* Rout) -> int {
       ProfScope ps(PK_F64_MNEXT, r.s);
-      return launch_gemm_f64a(mn, 64, 64, r.s);
+      return launch_gemm_f64a(m_times(E, Min, Mout, Rout), 64, 64, r.s);
     };
     if (p <= 4) {
       const float* U = nullptr;   // null: E = E_1 = alpha R
@@ -871,11 +1025,11 @@ int run_inv_root_f32(Run& r) {
       while ((p >> (hb + 1)) != 0) ++hb;
       for (int bit = hb - 1; bit >= 0; --bit) {
         float* dst = (U == Tm[1]) ? Tm[2] : Tm[1];
-        CHECK_LAUNCH(square(U, dst));
+        CHECK_LAUNCH(run_square(U, dst));
         U = dst;
         if ((p >> bit) & 1) {
           float* dst2 = (U == Tm[1]) ? Tm[2] : Tm[1];
-          CHECK_LAUNCH(times_t(U, dst2));
+          { ProfScope ps(PK_F32_STORE, r.s); CHECK_LAUNCH(launch_gemm_f32(times_t(U, dst2), r.s)); }
           U = dst2;
         }
       }
@@ -884,7 +1038,7 @@ int run_inv_root_f32(Run& r) {
         CHECK_LAUNCH(check_hip());
         U = Tm[0];
       }
-      CHECK_LAUNCH(m_times(U, M[mc], M[mc ^ 1], R));                               // M' = M + E_p M in fp64
+      CHECK_LAUNCH(run_m_times(U, M[mc], M[mc ^ 1], R));                               // M' = M + E_p M in fp64
       mc ^= 1;
     } else {
       // p = 5 .. 8: (I + alpha R)^p as p / 2 factors (I + E_2), and (I + E_1) for odd p, applied to M
@@ -893,17 +1047,17 @@ int run_inv_root_f32(Run& r) {
       // a 1024 x 1024 matrix came out with a relative error of 2e-5, with two factors (I + E_4) 1.6e-5,
       // with factors of order <= 2 6e-6 (p = 8; 4e-6, 2e-6, 1e-6 for p = 7, 6, 5).
       float* E2 = Tm[1];
-      CHECK_LAUNCH(square(nullptr, E2));
+      CHECK_LAUNCH(run_square(nullptr, E2));
       int left = p / 2 + (p & 1);
       if (p & 1) {
         { ProfScope ps(PK_MAKE_T, r.s); launch_make_e(Tm[0], R, r.ctrl, P.batch, Sp, r.s); }
         CHECK_LAUNCH(check_hip());
         --left;
-        CHECK_LAUNCH(m_times(Tm[0], M[mc], M[mc ^ 1], Tm[2]));   // the residual of an intermediate product goes to a spare array
+        CHECK_LAUNCH(run_m_times(Tm[0], M[mc], M[mc ^ 1], Tm[2]));   // the residual of an intermediate product goes to a spare array
         mc ^= 1;
       }
       for (; left > 0; --left) {
-        CHECK_LAUNCH(m_times(E2, M[mc], M[mc ^ 1], left == 1 ? R : Tm[2]));
+        CHECK_LAUNCH(run_m_times(E2, M[mc], M[mc ^ 1], left == 1 ? R : Tm[2]));
         mc ^= 1;
       }
     }
@@ -946,8 +1100,8 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   if (sel_batch == 0) sel_batch = batch;
   int rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u, false, sel_batch);
   if (rc != PRISM_OK) return rc;
-  if (r.P.ksplit && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
-    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K, false, sel_batch);
+  if ((r.P.ksplit || r.P.ring) && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
+    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW, false, sel_batch);
     if (rc != PRISM_OK) return rc;
   }
   r.s = (hipStream_t)stream;
@@ -997,6 +1151,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
       fa.X32[i] = r.at<float>(P.o_x[i]);
       fa.Y32[i] = (fn == PRISM_FN_SQRT || fn == PRISM_FN_SQRT_NEWTON) ? r.at<float>(P.o_y[i]) : nullptr;
     }
+    fa.ring = r.flow() ? P.ring : 0; fa.ring_bytes = P.ring_bytes;
   }
   { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); }
   if (P.p_s > 0 && max_iters > r.first_fit && fn != PRISM_FN_SQRT_NEWTON) {
@@ -1440,8 +1595,8 @@ int prism_polar_static(void* x, int batch, int m, int n, prism_dtype dt, int deg
     Plan P;
     const int rc = make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags);
     if (rc != PRISM_OK) return rc;
-    if (P.ksplit && P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES)   // as the driver does with a workspace of this size
-      (void)make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags | FLAG_NO_SPLIT_K);
+    if ((P.ksplit || P.ring) && P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES)   // as the driver does with a workspace of this size
+      (void)make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW);
     if (P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES) {
       set_last_error("prism_polar_static: this call needs more than PRISM_STATIC_SCRATCH_BYTES of scratch; use prism_polar_ex");
       return PRISM_EUNSUPPORTED;
