@@ -3,6 +3,7 @@
 // the caller's stream: the whole budget of iterations is enqueued up front and each kernel
 // skips matrices whose `done` flag the on-device solve step has set, so there is no host
 // round trip per iteration.
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <map>
@@ -1320,11 +1321,13 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   return check_hip();
 }
 
-// Internal streams of the grouped call, per device, created on first use (default priority).
+// Streams of the grouped call: the caller's and three of the library's own, per device, created on first use (default
+// priority).  A process has four hardware queues by default; with four streams of its own beside the caller's, which then only
+// waits, two of them shared a queue and ran one after the other.
 constexpr int GROUP_STREAMS = 4;
 struct Fork {
-  hipStream_t streams[GROUP_STREAMS] = {};
-  hipEvent_t forked = nullptr, joined[GROUP_STREAMS] = {};
+  hipStream_t streams[GROUP_STREAMS - 1] = {};
+  hipEvent_t forked = nullptr, joined[GROUP_STREAMS - 1] = {};
   bool ready = false;
 };
 std::mutex g_fork_mu;
@@ -1337,7 +1340,7 @@ int get_fork(Fork** out) {
   Fork& f = g_forks[dev];
   if (!f.ready) {
     if (hipEventCreateWithFlags(&f.forked, hipEventDisableTiming) != hipSuccess) return PRISM_EHIP;
-    for (int i = 0; i < GROUP_STREAMS; ++i) {
+    for (int i = 0; i < GROUP_STREAMS - 1; ++i) {
       if (hipStreamCreateWithFlags(&f.streams[i], hipStreamNonBlocking) != hipSuccess) return PRISM_EHIP;
       if (hipEventCreateWithFlags(&f.joined[i], hipEventDisableTiming) != hipSuccess) return PRISM_EHIP;
     }
@@ -1370,7 +1373,7 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
   if (fn == PRISM_FN_POLAR && dt == PRISM_BF16 && !from_auto_split) {
     // Groups that share the short side run as one launch sequence over all their matrices.  With
     // many matrices the sequence is issued for four quarters (or two halves) of every group on
-    // internal streams: the latency-bound steps of one part (chain, moments, solve, prologues and
+    // streams of their own: the latency-bound steps of one part (chain, moments, solve, prologues and
     // epilogues of short products) then run beside the products of another.  Measured on the
     // Muon-shaped batch of 64 (replayed from a HIP graph / eager): one sequence 4.00 / 3.93 ms, two
     // halves 3.80 / 3.82, four quarters 3.39 / 4.07, one call per group on four streams 3.40 / 4.09.
@@ -1402,11 +1405,11 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
       if (rc != PRISM_OK) return rc;
       if (hipEventRecord(f->forked, user) != hipSuccess) { (void)hipGetLastError(); set_last_error("hipEventRecord failed"); return PRISM_EHIP; }
       int forked = 0, first_error = PRISM_OK;
-      for (; forked < NP; ++forked)
+      for (; forked < NP - 1; ++forked)
         if (hipStreamWaitEvent(f->streams[forked], f->forked, 0) != hipSuccess) { first_error = PRISM_EHIP; break; }
       bool unsupported = false;
       for (int h = 0; h < NP && first_error == PRISM_OK; ++h) {
-        first_error = run_polar_bf16_shapes(half[h], ngroups, degree, max_iters, sketch_dim, seed, tol, f->streams[h], opt, NP);
+        first_error = run_polar_bf16_shapes(half[h], ngroups, degree, max_iters, sketch_dim, seed, tol, h ? f->streams[h - 1] : user, opt, NP);
         if (h == 0 && first_error == PRISM_EUNSUPPORTED) { unsupported = true; first_error = PRISM_OK; break; }   // nothing was enqueued
       }
       for (int i = 0; i < forked; ++i) {
@@ -1432,18 +1435,33 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
   rc = get_fork(&f);
   if (rc != PRISM_OK) return rc;
   const int used = ngroups < GROUP_STREAMS ? ngroups : GROUP_STREAMS;
+  // Longest group first, each to the stream with the least to do: what a group takes is latency per iteration (one workgroup
+  // per matrix up to order 64, then growing with the order) and the work of its products.
+  std::vector<std::pair<double, int>> order;
+  for (int gi = 0; gi < ngroups; ++gi) {
+    const prism_group& g = groups[gi];
+    const double s = g.m < g.n ? g.m : g.n, l = g.m < g.n ? g.n : g.m;
+    order.emplace_back((s <= 64 ? 25.0 : 45.0 + 0.07 * s) + 8.0 * g.batch * l * s * s * 1e-8, gi);
+  }
+  std::stable_sort(order.begin(), order.end(), [](const std::pair<double, int>& x, const std::pair<double, int>& y) { return x.first > y.first; });
   // nothing is forked before this record succeeds
   if (hipEventRecord(f->forked, user) != hipSuccess) { (void)hipGetLastError(); set_last_error("hipEventRecord failed"); return PRISM_EHIP; }
   int first_error = PRISM_OK;
   int forked = 0;   // internal streams that wait for the caller's stream: exactly these are joined again below
-  for (; forked < used; ++forked)
+  for (; forked < used - 1; ++forked)
     if (hipStreamWaitEvent(f->streams[forked], f->forked, 0) != hipSuccess) { first_error = PRISM_EHIP; break; }
-  for (int gi = 0; gi < ngroups && first_error == PRISM_OK; ++gi) {
+  double load[GROUP_STREAMS] = {};
+  for (int i = 0; i < ngroups && first_error == PRISM_OK; ++i) {
+    const int gi = order[i].second;
+    int at = 0;
+    for (int q = 1; q < used; ++q)
+      if (load[q] < load[at]) at = q;
+    load[at] += order[i].first;
     prism_options o = opt ? *opt : prism_options{};
     o.info = groups[gi].info;
     o.flags |= PRISM_FLAG_SHARED_GPU;
     first_error = run(fn, groups[gi].x, groups[gi].inv_out, root_p, groups[gi].batch, groups[gi].m, groups[gi].n, dt,
-                      degree, max_iters, sketch_dim, seed, tol, f->streams[gi % GROUP_STREAMS], &o,
+                      degree, max_iters, sketch_dim, seed, tol, at ? f->streams[at - 1] : user, &o,
                       from_auto_split ? ngroups * groups[gi].batch : 0);
   }
   // Join every forked stream back into the caller's, on every exit: after an error too, and past a
