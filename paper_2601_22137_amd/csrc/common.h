@@ -234,28 +234,21 @@ struct FlowArgs {
 int flow_tiles(const GemmDesc& g, int tile);
 int launch_flow(const FlowArgs& a, int batch, hipStream_t s);
 
-// fp32 polar factor of matrices whose padded iterate is 64 x 64: every iteration (residual, sketch
-// chain, fit, update) runs inside one workgroup per matrix, the iterate never leaves the LDS and one
-// launch replaces the five launches per iteration of the general path.
+// ---- small.hip : whole calls on matrices of padded order 64, one workgroup each, in place ----
+// fp32 polar factor, both sides up to 64
 struct SmallPolarArgs {
-  SolveArgs sv;              // k, mode and sched_alpha are filled in per iteration by the kernel;
-                             // the residual sum and the moments stay in LDS (rho_part, cpart unused)
-  float* X[2];               // [batch][64][64]: input in X[0], result left in X[iterations & 1]
-  const float* V0;           // S_k^T for k = first_fit, first_fit + 1, ...: [.][64][ld]
-  int nv;                    // products in the chain (2 d + 1)
+  SolveArgs sv;              // fn, d, n (the short side), ld, info, tol, max_iters
+  float* x; int m, n, L, transpose;   // the caller's matrices; L: long side; transpose: m < n
+  const float* V0;           // S_k^T for k = first_fit, first_fit + 1, ...: [.][64][ld] in blocks (see launch_sketch)
   int p_s, first_fit, warm, sched_len;
   float sched[PRISM_MAX_ITERS];
 };
 int launch_small_polar(const SmallPolarArgs& a, int batch, hipStream_t s);
-
-// Coupled inverse Newton iteration (root order up to 4, sketch up to 32 columns) of matrices of padded order 64, likewise.
+// Coupled inverse Newton iteration, root order up to 4, sketch up to 32 columns
 struct SmallRootArgs {
-  SolveArgs sv;              // as above; rho_part: residual of M_0
-  float* X[2];               // [batch][64][64]: X_0 in X[0], result left in X[iterations & 1]
-  const double* M;           // M_0
-  const float* R;            // I - M_0
-  const float* V0;           // S_k^T for k = first_fit, first_fit + 1, ...: [.][64][ld]
-  int nv;                    // products in the chain (p + 1)
+  SolveArgs sv;              // as above, and p
+  float* x;                  // the caller's matrices
+  const float* V0;
   int p_s, first_fit, warm, sched_len;
   float sched[PRISM_MAX_ITERS];
 };

@@ -16,6 +16,31 @@ typedef unsigned long long u64;
 constexpr int NT = 256;
 constexpr int MAXC = 2 * PRISM_MAX_ROOT + 1;  // coefficients of m
 
+// x plus what the lanes that CTRL selects hold (lanes it does not reach: 0)
+template <int CTRL, int ROWS> __device__ inline double add_dpp(double x) {
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  u32x2 v;
+  v[0] = __builtin_amdgcn_update_dpp(0, (int)w[0], CTRL, ROWS, 0xF, true);
+  v[1] = __builtin_amdgcn_update_dpp(0, (int)w[1], CTRL, ROWS, 0xF, true);
+  return x + __builtin_bit_cast(double, v);
+}
+// Sum over the wave, in lane 63: rows of 16 lanes by shifts, then row by row.  Without a trip to the LDS crossbar per step.
+__device__ inline double wave_sum(double x) {
+  x = add_dpp<0x111, 0xF>(x);   // row_shr 1, 2, 4, 8
+  x = add_dpp<0x112, 0xF>(x);
+  x = add_dpp<0x114, 0xF>(x);
+  x = add_dpp<0x118, 0xF>(x);
+  x = add_dpp<0x142, 0xA>(x);   // row_bcast 15 into rows 1 and 3
+  return add_dpp<0x143, 0xC>(x);   // row_bcast 31 into rows 2 and 3
+}
+__device__ inline double read_lane(double x, int lane) {
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  u32x2 v;
+  v[0] = (unsigned)__builtin_amdgcn_readlane((int)w[0], lane);
+  v[1] = (unsigned)__builtin_amdgcn_readlane((int)w[1], lane);
+  return __builtin_bit_cast(double, v);
+}
+
 __device__ inline double horner(const double* c, int deg, double x) {
   double v = c[deg];
   for (int i = deg - 1; i >= 0; --i) v = v * x + c[i];
@@ -83,10 +108,8 @@ __device__ void accumulate_coefficients(const SolveArgs& a, int b, int grp, int 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int s = 0; s < NC; ++s) {
-    double x = c[s];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-    if (lane == 0) red[wave][s] = x;
+    const double x = wave_sum(c[s]);
+    if (lane == 63) red[wave][s] = x;
   }
   __syncthreads();
   if (threadIdx.x < MAXC) {
@@ -128,7 +151,8 @@ template <bool COH, typename T, typename V> __device__ inline void coh_store(T* 
 
 // The root of f in [xa, xb], f(xa) = fa and f(xb) of opposite signs: Newton's method kept inside the bracket [l, h] (f(l) has
 // the sign of fa); a step that would leave the bracket, or that shrinks too slowly, is replaced by a bisection step.
-// eval(x, f, df) gives f and its derivative.
+// eval(x, f, df) gives f and its derivative.  The step f / f' is taken with the hardware's reciprocal (relative error 2^-24, far
+// below what is left of a Newton step anyway; an exact division was half the time of an evaluation).
 template <typename E> __device__ inline double bracketed_root(double xa, double xb, double fa, E eval) {
   double l = xa, h = xb;
   double x = 0.5 * (l + h), dx = h - l, dxold = dx, fx, dfx;
@@ -141,7 +165,7 @@ template <typename E> __device__ inline double bracketed_root(double xa, double 
     dxold = dx;
     double xn;
     if (leaves || slow) { dx = 0.5 * (h - l); xn = l + dx; }
-    else { dx = fx / dfx; xn = x - dx; }
+    else { dx = fx * __builtin_amdgcn_rcp(dfx); xn = x - dx; }
     if (xn == x || !(xn > l && xn < h)) break;   // the bracket is down to neighbouring numbers
     x = xn;
     if (fabs(dx) <= 2.0e-16 * fabs(x)) break;
@@ -150,17 +174,33 @@ template <typename E> __device__ inline double bracketed_root(double xa, double 
   return x;
 }
 
-// Minimiser of a quartic on [lo, hi], ties to the smallest: one thread, everything in registers (through LDS, level by
-// level of the derivative chain, the same took 2 us more per iteration in barriers and LDS round trips: one 64 x 32 polar
-// factor 158 -> 139 us, fp32 polar 6 x 500 x 299 760 -> 735).  The roots of
+// Narrows the bracket [xa, xb] of a root of f (the sign changes once in it; neg: f(xa) < 0) by a whole wave: 64 points at a
+// time, twice, so that Newton's method starts within 1/4000 of the bracket's width and needs two or three steps instead of
+// seven to ten.
+template <typename F> __device__ inline void narrow_bracket(double& xa, double& xb, bool neg, F f) {
+  const double at = (double)((threadIdx.x & 63) + 1) * (1.0 / 65.0);
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const double w = xb - xa;
+    const u64 same = __ballot((f(xa + w * at) < 0.0) == neg);
+    const int cnt = ~same ? __builtin_ctzll(~same) : 64;     // points on xa's side of the root
+    const double l = xa + w * ((double)cnt * (1.0 / 65.0)), h = xa + w * ((double)(cnt + 1) * (1.0 / 65.0));
+    if (cnt > 0) xa = l;
+    if (cnt < 64) xb = h;
+  }
+}
+
+// Minimiser of a quartic on [lo, hi], ties to the smallest: one wave, everything in registers (through LDS, level by
+// level of the derivative chain, the same took 2 us more per iteration in barriers and LDS round trips).  The roots of
 // m' lie between lo, the roots of m'' (closed form, the larger in magnitude first and the other from their product)
 // and hi.
 __device__ inline double minimise_quartic(double c0, double c1, double c2, double c3, double c4, double lo, double hi) {
   const double q0 = c1, q1 = 2.0 * c2, q2 = 3.0 * c3, q3 = 4.0 * c4;
   const double b0 = q1, b1 = 2.0 * q2, b2 = 3.0 * q3;
   auto value = [&](double x) { return (((c4 * x + c3) * x + c2) * x + c1) * x + c0; };
+  auto slope1 = [&](double x) { return ((q3 * x + q2) * x + q1) * x + q0; };
   auto slope = [&](double x, double& f, double& df) {
-    f = ((q3 * x + q2) * x + q1) * x + q0;
+    f = slope1(x);
     df = (b2 * x + b1) * x + b0;
   };
   double e0 = hi, e1 = hi;                     // roots of m'' inside (lo, hi), in order; hi: none
@@ -178,14 +218,19 @@ __device__ inline double minimise_quartic(double c0, double c1, double c2, doubl
   e0 = e0 < lo ? lo : (e0 > hi ? hi : e0);
   e1 = e1 < lo ? lo : (e1 > hi ? hi : e1);
   double best = lo, bestv = value(lo);
-  double xa = lo, fa, df;
-  slope(lo, fa, df);
+  double xa = lo, fa = slope1(lo);
   for (int i = 0; i < 3; ++i) {
     const double xb = i == 0 ? e0 : (i == 1 ? e1 : hi);
-    double fb;
-    slope(xb, fb, df);
+    const double fb = slope1(xb);
     if ((fa < 0.0) != (fb < 0.0)) {
-      const double x = fa == 0.0 ? xa : (fb == 0.0 ? xb : bracketed_root(xa, xb, fa, slope));
+      double x;
+      if (fa == 0.0) x = xa;
+      else if (fb == 0.0) x = xb;
+      else {
+        double l = xa, h = xb;
+        narrow_bracket(l, h, fa < 0.0, slope1);
+        x = bracketed_root(l, h, fa, slope);
+      }
       const double v = value(x);
       if (v < bestv) { bestv = v; best = x; }
     }
@@ -197,16 +242,148 @@ __device__ inline double minimise_quartic(double c0, double c1, double c2, doubl
   return best;
 }
 
-// One workgroup (NT threads or more), matrix b: stop rule and coefficient of iteration a.k.  Every return is taken by all
-// threads of the workgroup together.
-// rho_local (LDS, one double) stands in for the residual partials in global memory and c_local
-// (LDS, MAXC doubles) for the coefficient partials when the caller has them on chip.
+// Minimiser of m(alpha) = sum_s c[s] alpha^s, s < nc, on [lo, hi], ties to the smallest, by one wave (all lanes get it); false: c is
+// not usable (not finite, or nothing but zeros).  c: LDS.
+__device__ inline bool minimise(const double* c, int nc, double lo, double hi, double& best) {
+  const int t = threadIdx.x & 63;
+  const int deg = nc - 1;   // degree of m
+  const int dq = deg - 1;   // degree of m'
+  bool bad = false, some = false;
+  if (t < nc) {
+    const double v = c[t];
+    bad = !(v == v) || fabs(v) > 1.0e300;
+    some = fabs(v) >= 1.0e-300;
+  }
+  if (__any(bad) || !__any(some)) return false;
+  if (deg == 4) {   // Newton-Schulz family, DB Newton
+    best = minimise_quartic(c[0], c[1], c[2], c[3], c[4], lo, hi);
+    return true;
+  }
+  auto slope1 = [&](double x) {
+    double f = 0.0;
+    for (int i = deg; i >= 1; --i) f = f * x + (double)i * c[i];
+    return f;
+  };
+  // Without or with one root of m' inside, by the theorem of Budan and Fourier: the roots in (lo, hi] are as many as the sign
+  // changes of the derivatives of m' at lo less those at hi, or fewer by an even number.  Then nothing or one bracket is left
+  // to search; level by level, below, that took 8 us more per iteration at p = 4.
+  {
+    const int j = t;                            // derivative j of m' over (j + 1)!
+    double at[2] = {0.0, 0.0}, power[2] = {1.0, 1.0}, binom = 1.0;
+#pragma unroll
+    for (int i = 0; i < 2 * PRISM_MAX_ROOT; ++i) {
+      if (i > dq) break;                        // uniform
+      const double v = i + j <= dq ? c[i + j + 1] * binom : 0.0;
+      at[0] += v * power[0]; at[1] += v * power[1];
+      power[0] *= lo; power[1] *= hi;
+      binom *= (double)(i + j + 2) * (1.0 / (double)(i + 1));
+    }
+    int changes[2];
+    bool exact = true;
+    for (int e = 0; e < 2; ++e) {
+      const u64 neg = __ballot(j <= dq && at[e] < 0.0);
+      exact = exact && !__any(j <= dq && !(at[e] < 0.0 || at[e] > 0.0));   // a zero: left to the search below
+      changes[e] = __popcll((neg ^ (neg >> 1)) & ((1ull << dq) - 1));
+    }
+    const int roots = changes[0] - changes[1];
+    if (exact && (roots == 0 || roots == 1)) {
+      best = lo;
+      double bestv = horner(c, deg, lo);
+      if (roots == 1) {
+        const double fa = read_lane(at[0], 0);
+        double l = lo, h = hi;
+        narrow_bracket(l, h, fa < 0.0, slope1);
+        const double x = bracketed_root(l, h, fa, [&](double y, double& f, double& df) {
+          f = 0.0; df = 0.0;
+          for (int i = deg; i >= 1; --i) { df = df * y + f; f = f * y + (double)i * c[i]; }
+        });
+        const double v = horner(c, deg, x);
+        if (v < bestv) { bestv = v; best = x; }
+      }
+      if (horner(c, deg, hi) < bestv) best = hi;
+      return true;
+    }
+  }
+  // derivative chain: s_q[j] = (j+1)-th derivative of m, degree deg-1-j; a lane per interval, all in one wave
+  __shared__ double s_q[2 * PRISM_MAX_ROOT][MAXC];
+  __shared__ double s_roots[2][MAXC + 2];
+  __shared__ int s_nroots[2];
+  auto sync = []() {           // LDS written by other lanes of this wave
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (t == 0) {
+    for (int i = 0; i <= dq; ++i) s_q[0][i] = (double)(i + 1) * c[i + 1];
+    for (int j = 1; j < dq; ++j)
+      for (int i = 0; i <= dq - j; ++i) s_q[j][i] = (double)(i + 1) * s_q[j - 1][i + 1];
+    // linear level j = dq-1: a0 + a1 x
+    const double a0 = s_q[dq - 1][0], a1 = s_q[dq - 1][1];
+    int n0 = 0;
+    if (a1 != 0.0) {
+      const double r = -a0 / a1;
+      if (r >= lo && r <= hi) s_roots[(dq - 1) & 1][n0++] = r;
+    }
+    s_nroots[(dq - 1) & 1] = n0;
+  }
+  sync();
+  for (int j = dq - 2; j >= 0; --j) {
+    const int src = (j + 1) & 1, dst = j & 1;
+    const int nr = s_nroots[src];
+    const int pdeg = dq - j;
+    double found = 0.0;
+    bool has = false;
+    if (t <= nr) {  // interval t between consecutive roots of the next derivative
+      const double xa = (t == 0) ? lo : s_roots[src][t - 1];
+      const double xb = (t == nr) ? hi : s_roots[src][t];
+      double fa = horner(s_q[j], pdeg, xa);
+      const double fb = horner(s_q[j], pdeg, xb);
+      if (fa == 0.0) { found = xa; has = true; }
+      else if (t == nr && fb == 0.0) { found = xb; has = true; }
+      else if ((fa < 0.0) != (fb < 0.0) && fb != 0.0) {
+        const double x = bracketed_root(xa, xb, fa, [&](double y, double& f, double& df) {
+          f = horner(s_q[j], pdeg, y);
+          df = horner(s_q[j + 1], pdeg - 1, y);   // the derivative of level j is level j + 1 of the chain
+        });
+        found = x;
+        has = true;
+      }
+    }
+    const u64 all = __ballot(has);
+    if (has) s_roots[dst][__popcll(all & ((1ull << t) - 1))] = found;
+    if (t == 0) s_nroots[dst] = __popcll(all);
+    sync();
+  }
+  const int lvl = (dq >= 2) ? 0 : ((dq - 1) & 1);
+  const int nr = s_nroots[lvl & 1];
+  best = lo;
+  double bestv = horner(c, deg, lo);
+  for (int i = 0; i < nr; ++i) {
+    const double x = s_roots[lvl & 1][i];
+    const double v = horner(c, deg, x);
+    if (v < bestv) { bestv = v; best = x; }
+  }
+  const double vh = horner(c, deg, hi);
+  if (vh < bestv) best = hi;
+  return true;
+}
+
+// The interval of the fit
+__device__ inline void fit_interval(int fn, int p, int d, double& lo, double& hi) {
+  if (fn == PRISM_FN_INV_ROOT) { lo = 1.0 / p; hi = 2.0 / p; }
+  else if (fn == PRISM_FN_INVERSE) { lo = 0.5; hi = 2.0; }
+  else if (fn == PRISM_FN_SQRT_NEWTON) { lo = 0.0; hi = 1.0; }
+  else if (d == 1) { lo = 0.5; hi = 1.0; }
+  else { lo = 0.375; hi = 1.45; }
+}
+
+// One workgroup (NT threads or more), matrix b: stop rule and coefficient of iteration a.k.  Every return but the last is taken
+// by all threads of the workgroup together.
+// c_local (LDS, MAXC doubles): the moments are accumulated right here.
 // ctl_local (LDS): the matrix's control block, when the caller keeps it on chip; it is not done then.  (Nobody may look: thread 0
 // can have set `done` before a late wave gets to the test, and that wave would leave alone.)
 // COH: the partials come from workgroups of the same launch, the report is continued by others of it.
 template <bool COH = false>
-__device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = nullptr, double* c_local = nullptr,
-                           Ctrl* ctl_local = nullptr) {
+__device__ void solve_body(const SolveArgs& a, int b, double* c_local = nullptr, Ctrl* ctl_local = nullptr) {
   const int t = threadIdx.x;
   Ctrl* ctl = ctl_local ? ctl_local : &a.ctrl[b];
   const int done = ctl_local ? 0 : ctl->done;
@@ -215,24 +392,18 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
   prism_info* info = a.info + b;
   __shared__ int s_stop;
   __shared__ double s_c[MAXC];
-  __shared__ double s_q[2 * PRISM_MAX_ROOT][MAXC];   // derivative chain of m'
-  __shared__ double s_roots[2][MAXC + 2];
-  __shared__ int s_nroots[2];
 
   // residual: sum of the per-tile partials, every thread a strided share, then a fixed tree
   __shared__ double s_rho[4];
-  if (!rho_local) {
-    double part = 0.0;
-    for (int i = t; t < NT && i < a.nparts; i += NT) part += (double)coh_load<COH>(a.rho_part + (long long)b * a.nparts + i);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
-    if (t < NT && (t & 63) == 0) s_rho[t >> 6] = part;
-    __syncthreads();
-  }
+  double part = 0.0;
+  for (int i = t; t < NT && i < a.nparts; i += NT) part += (double)coh_load<COH>(a.rho_part + (long long)b * a.nparts + i);
+  part = wave_sum(part);
+  if (t < NT && (t & 63) == 63) s_rho[t >> 6] = part;
+  __syncthreads();
   if (a.phase == 2) {
     if (t == 0) s_stop = 0;          // coefficient only: the stop test of this k has been taken
   } else if (t == 0) {
-    const double rho = rho_local ? *rho_local : (s_rho[0] + s_rho[1]) + (s_rho[2] + s_rho[3]);
+    const double rho = (s_rho[0] + s_rho[1]) + (s_rho[2] + s_rho[3]);
     const double res = sqrt(rho / (double)a.n);
     coh_store<COH>(&info->residual[a.k], (float)res);
     int status = -1;
@@ -283,11 +454,7 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
   }
 
   double lo, hi;
-  if (a.fn == PRISM_FN_INV_ROOT) { lo = 1.0 / a.p; hi = 2.0 / a.p; }
-  else if (a.fn == PRISM_FN_INVERSE) { lo = 0.5; hi = 2.0; }
-  else if (a.fn == PRISM_FN_SQRT_NEWTON) { lo = 0.0; hi = 1.0; }
-  else if (a.d == 1) { lo = 0.5; hi = 1.0; }
-  else { lo = 0.375; hi = 1.45; }
+  fit_interval(a.fn, a.p, a.d, lo, hi);
 
   if (a.mode != 0) {
     if (t == 0) {
@@ -326,139 +493,16 @@ __device__ void solve_body(const SolveArgs& a, int b, const double* rho_local = 
   __syncthreads();
 
   // ---- minimise m(alpha) = sum_s c_s alpha^s on [lo, hi] ----
-  const int deg = nc - 1;   // degree of m
-  const int dq = deg - 1;   // degree of m'
-  bool usable = true;
-  {
-    bool all_tiny = true;
-    for (int s = 0; s < nc; ++s) {
-      const double v = s_c[s];
-      if (!(v == v) || fabs(v) > 1.0e300) usable = false;
-      if (fabs(v) >= 1.0e-300) all_tiny = false;
-    }
-    if (all_tiny) usable = false;
-  }
-  if (!usable) {
-    if (t == 0) { ctl->alpha = (float)lo; coh_store<COH>(&info->alpha[a.k], (float)lo); }
-    return;
-  }
-  if (deg == 4) {   // Newton-Schulz family, DB Newton
-    if (t == 0) {
-      const double best = minimise_quartic(s_c[0], s_c[1], s_c[2], s_c[3], s_c[4], lo, hi);
-      ctl->alpha = (float)best;
-      coh_store<COH>(&info->alpha[a.k], (float)best);
-      if (best < hi - 1e-6) ctl->plain = 1;   // as below
-    }
-    return;
-  }
-  // Without or with one root of m' inside, by the theorem of Budan and Fourier: the roots in (lo, hi] are as many as the sign
-  // changes of the derivatives of m' at lo less those at hi, or fewer by an even number.  Then nothing or one bracket is left
-  // to search; level by level, below, that took 8 us more per iteration at p = 4.
-  {
-    const int j = t & 63;                       // derivative j of m' over (j + 1)!, by every wave
-    double at[2] = {0.0, 0.0}, power[2] = {1.0, 1.0}, binom = 1.0;
-#pragma unroll
-    for (int i = 0; i < 2 * PRISM_MAX_ROOT; ++i) {
-      if (i > dq) break;                        // uniform
-      const double c = i + j <= dq ? s_c[i + j + 1] * binom : 0.0;
-      at[0] += c * power[0]; at[1] += c * power[1];
-      power[0] *= lo; power[1] *= hi;
-      binom *= (double)(i + j + 2) * (1.0 / (double)(i + 1));
-    }
-    int changes[2];
-    bool exact = true;
-    for (int e = 0; e < 2; ++e) {
-      const u64 neg = __ballot(j <= dq && at[e] < 0.0);
-      exact = exact && !__any(j <= dq && !(at[e] < 0.0 || at[e] > 0.0));   // a zero: left to the search below
-      changes[e] = __popcll((neg ^ (neg >> 1)) & ((1ull << dq) - 1));
-    }
-    const int roots = changes[0] - changes[1];
-    if (exact && (roots == 0 || roots == 1)) {
-      if (t == 0) {
-        double best = lo, bestv = horner(s_c, deg, lo);
-        if (roots == 1) {
-          const double x = bracketed_root(lo, hi, at[0], [&](double y, double& f, double& df) {
-            f = 0.0; df = 0.0;
-            for (int i = deg; i >= 1; --i) { df = df * y + f; f = f * y + (double)i * s_c[i]; }
-          });
-          const double v = horner(s_c, deg, x);
-          if (v < bestv) { bestv = v; best = x; }
-        }
-        if (horner(s_c, deg, hi) < bestv) best = hi;
-        ctl->alpha = (float)best;
-        coh_store<COH>(&info->alpha[a.k], (float)best);
-        if (best < hi - 1e-6) ctl->plain = 1;   // as below
-      }
-      return;
-    }
-  }
-  // derivative chain: s_q[j] = (j+1)-th derivative of m, degree deg-1-j
+  if (t >= 64) return;
+  double best = lo;
+  const bool usable = minimise(s_c, nc, lo, hi, best);
   if (t == 0) {
-    for (int i = 0; i <= dq; ++i) s_q[0][i] = (double)(i + 1) * s_c[i + 1];
-    for (int j = 1; j < dq; ++j)
-      for (int i = 0; i <= dq - j; ++i) s_q[j][i] = (double)(i + 1) * s_q[j - 1][i + 1];
-    // linear level j = dq-1: a0 + a1 x
-    const double a0 = s_q[dq - 1][0], a1 = s_q[dq - 1][1];
-    int n0 = 0;
-    if (a1 != 0.0) {
-      const double r = -a0 / a1;
-      if (r >= lo && r <= hi) s_roots[(dq - 1) & 1][n0++] = r;
-    }
-    s_nroots[(dq - 1) & 1] = n0;
-  }
-  __syncthreads();
-  for (int j = dq - 2; j >= 0; --j) {
-    const int src = (j + 1) & 1, dst = j & 1;
-    const int nr = s_nroots[src];
-    const int pdeg = dq - j;
-    double found = 0.0;
-    int has = 0;
-    if (t <= nr) {  // interval t between consecutive roots of the next derivative
-      const double xa = (t == 0) ? lo : s_roots[src][t - 1];
-      const double xb = (t == nr) ? hi : s_roots[src][t];
-      double fa = horner(s_q[j], pdeg, xa);
-      const double fb = horner(s_q[j], pdeg, xb);
-      if (fa == 0.0) { found = xa; has = 1; }
-      else if (t == nr && fb == 0.0) { found = xb; has = 1; }
-      else if ((fa < 0.0) != (fb < 0.0) && fb != 0.0) {
-        const double x = bracketed_root(xa, xb, fa, [&](double y, double& f, double& df) {
-          f = horner(s_q[j], pdeg, y);
-          df = horner(s_q[j + 1], pdeg - 1, y);   // the derivative of level j is level j + 1 of the chain
-        });
-        found = x;
-        has = 1;
-      }
-    }
-    __syncthreads();
-    __shared__ double s_tmp[MAXC + 2];
-    __shared__ int s_has[MAXC + 2];
-    if (t <= nr) { s_tmp[t] = found; s_has[t] = has; }
-    __syncthreads();
-    if (t == 0) {
-      int cnt = 0;
-      for (int i = 0; i <= nr; ++i)
-        if (s_has[i]) s_roots[dst][cnt++] = s_tmp[i];
-      s_nroots[dst] = cnt;
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const int lvl = (dq >= 2) ? 0 : ((dq - 1) & 1);
-    const int nr = s_nroots[lvl & 1];
-    double best = lo, bestv = horner(s_c, deg, lo);
-    for (int i = 0; i < nr; ++i) {
-      const double x = s_roots[lvl & 1][i];
-      const double v = horner(s_c, deg, x);
-      if (v < bestv) { bestv = v; best = x; }
-    }
-    const double vh = horner(s_c, deg, hi);
-    if (vh < bestv) { bestv = vh; best = hi; }
     ctl->alpha = (float)best;
     coh_store<COH>(&info->alpha[a.k], (float)best);
     // The fit has left the upper end of its interval: no eigenvalue of R is close to 1 any more,
     // i.e. no singular value of the iterate is small.  The bf16 polar path stops carrying the low
     // half of the iterate from here on (it exists for the small singular values only).
-    if (best < hi - 1e-6) ctl->plain = 1;
+    if (usable && best < hi - 1e-6) ctl->plain = 1;
   }
 }
 
@@ -532,11 +576,8 @@ __device__ void block_moments(const float* own, int stride, int count, double* o
       for (int l = 0; l < NW; ++l) c[i + l] += w[i] * w[l];
   }
 #pragma unroll
-  for (int s = 0; s < NC; ++s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) c[s] += __shfl_down(c[s], off, 64);
-  }
-  if (lane == 0) {
+  for (int s = 0; s < NC; ++s) c[s] = wave_sum(c[s]);
+  if (lane == 63) {
 #pragma unroll
     for (int s = 0; s < MAXC; ++s) {
       const double v = s < NC ? c[s < NC ? s : 0] : 0.0;

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(NT, 2) void flow_kernel(FlowArgs a) {
         f.sv.last = k == max_iters;
         f.sv.mode = k < a.sched_len ? 3 : (a.p_s == 0 ? 1 : (k < a.warm ? 2 : 0));
         f.sv.sched_alpha = k < a.sched_len ? a.sched[k] : 0.0f;
-        solve_body<true>(f.sv, b, nullptr, nullptr, &s_ctl);
+        solve_body<true>(f.sv, b, nullptr, &s_ctl);
         __syncthreads();
         if (t < CTL_WORDS) coh_store<true>((unsigned*)(f.sv.ctrl + b) + t, ((const unsigned*)&s_ctl)[t]);
         if (t == 0) {

@@ -105,9 +105,9 @@ constexpr long long MAX_ENTRIES = (1ll << 31) - 1;   // of a matrix, sides padde
 
 // Batches that run as two halves unless the caller asks otherwise (run_auto)
 bool in_halves(int batch, int S) { return batch >= 8 && batch % 2 == 0 && S >= 1024; }
-// inverse root of padded order 64: small_root_kernel (one workgroup per CU, and still ahead of the general path when
-// the launches of that are full: to a tolerance 1024 matrices, p = 4, 0.76 against 1.36 ms, 8192 5.7 against 7.0; with a fixed
-// budget of four updates it falls behind: 8192 3.87 against 3.70, 16384 7.7 against 7.0)
+// inverse root of padded order 64: small_root_kernel (one workgroup per CU above order 48, and still ahead of the general path when
+// the launches of that are full: order 64, p = 4, to a tolerance 1024 matrices 0.40 against 1.36 ms, 8192 2.8 against 7.0; with a fixed
+// budget of four updates 8192 2.0 against 3.7)
 bool takes_small_root(const Plan& P) { return P.fn == PRISM_FN_INV_ROOT && P.Sp == 64 && P.p <= 4 && P.ld <= 32; }
 // fp32 polar factor of a 64 x 64 padded iterate: small_polar_kernel
 bool takes_small_polar(const Plan& P) {
@@ -544,6 +544,28 @@ int run_flow(const Run& r, const FlowOp* ops, int nops, bool residual, const flo
   return launch_flow(a, P.batch, r.s);
 }
 
+// Matrices of padded order 64: the whole call from the caller's array to the caller's array (small.hip)
+int run_small(const Run& r, float* x) {
+  const Plan& P = r.P;
+  auto fill = [&](auto& a) {
+    a.sv = r.solve_args(0, 1, 0);
+    a.x = x; a.V0 = r.v0;
+    a.p_s = P.p_s; a.first_fit = r.first_fit; a.warm = r.warm; a.sched_len = r.sched_len;
+    for (int i = 0; i < r.sched_len; ++i) a.sched[i] = r.sched[i];
+  };
+  if (P.fn == PRISM_FN_POLAR) {
+    SmallPolarArgs a = {};
+    fill(a);
+    a.m = P.m; a.n = P.n; a.L = P.L; a.transpose = P.transpose;
+    ProfScope ps(PK_F32_SMALL_POLAR, r.s);
+    return launch_small_polar(a, P.batch, r.s);
+  }
+  SmallRootArgs a = {};
+  fill(a);
+  ProfScope ps(PK_F32_APPLY, r.s);
+  return launch_small_root(a, P.batch, r.s);
+}
+
 int run_polar_f32(Run& r) {
   const Plan& P = r.P;
   const int Sp = P.Sp, Lp = P.Lp;
@@ -554,22 +576,6 @@ int run_polar_f32(Run& r) {
   const bool polar = P.fn != PRISM_FN_SIGN;
   const int sym = polar ? f32_sym() : 0;
   const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
-  if (r.small_polar()) {
-    // the whole iteration in one workgroup per matrix, one launch for all iterations: with five
-    // launches per iteration a call on such matrices is nothing but launch latency
-    SmallPolarArgs sa = {};
-    SolveArgs& v = sa.sv;
-    v.fn = P.fn; v.d = P.d; v.p = P.p; v.n = P.S; v.rows = Sp; v.ld = P.ld;
-    v.V = r.v; v.vstride = (long long)P.batch * Sp * P.ld; v.bstride = (long long)Sp * P.ld;
-    v.rho_part = r.rho; v.nparts = 1;
-    v.ctrl = r.ctrl; v.info = r.info; v.tol = r.tol; v.max_iters = r.max_iters;
-    v.cpart = r.at<double>(P.o_cpart); v.ngroups = 1;
-    sa.X[0] = X[0]; sa.X[1] = X[1]; sa.V0 = r.v0; sa.nv = P.nv;
-    sa.p_s = P.p_s; sa.first_fit = r.first_fit; sa.warm = r.warm; sa.sched_len = r.sched_len;
-    for (int i = 0; i < r.sched_len; ++i) sa.sched[i] = r.sched[i];
-    ProfScope ps(PK_F32_SMALL_POLAR, r.s);
-    return launch_small_polar(sa, P.batch, r.s);
-  }
   // G = X^T X; matrix sign: G = X X (any square input, all tiles)
   auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, X[cur], Sp, LS, X[cur], Sp, LS, Sp, Sp, Lp, polar ? 1 : 0);
@@ -946,16 +952,6 @@ int run_inv_root_f32(Run& r) {
   float* Tm[3] = {r.at<float>(P.o_t[0]), r.at<float>(P.o_t[1]), r.at<float>(P.o_t[2])};
   const int nparts0 = (Sp / 64) * (Sp / 64);  // residual of M_0 comes from the prepare step (64 x 64 tiles)
   const int nparts = (Sp / 64) * (Sp / 64);   // later ones from the fp64 product (64 x 64 tiles)
-  if (r.small_root()) {
-    SmallRootArgs a = {};
-    a.sv = r.solve_args(0, 1, 0);
-    a.sv.last = 0;
-    a.X[0] = X[0]; a.X[1] = X[1]; a.M = M[0]; a.R = R; a.V0 = r.v0; a.nv = P.nv;
-    a.p_s = P.p_s; a.first_fit = r.first_fit; a.warm = r.warm; a.sched_len = r.sched_len;
-    for (int i = 0; i < r.sched_len; ++i) a.sched[i] = r.sched[i];
-    ProfScope ps(PK_F32_APPLY, r.s);
-    return launch_small_root(a, P.batch, r.s);
-  }
   auto update = [&](int cur) {
     GemmDesc ax = f32_desc(r, X[cur], Sp, SS, R, Sp, SS, Sp, Sp, Sp, 0);         // X (I + alpha R)
     ax.epi = EPI_AXPY; ax.C = X[cur ^ 1]; ax.strideC = SS; ax.ldc = Sp; ax.Cin = X[cur]; ax.strideCin = SS; ax.ldcin = Sp;
@@ -1154,14 +1150,16 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
     }
     fa.ring = r.flow() ? P.ring : 0; fa.ring_bytes = P.ring_bytes;
   }
-  { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); }
+  const bool small = r.small_polar() || r.small_root();
+  if (!small) { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); }
   if (P.p_s > 0 && max_iters > r.first_fit && fn != PRISM_FN_SQRT_NEWTON) {
     ProfScope ps(PK_SKETCH, r.s);
-    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s, r.fused());
+    launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s, r.fused() || small);
     if (r.planes()) CHECK_LAUNCH(launch_split_planes(r.v0, r.vp0, P.Sp, P.ld, max_iters - r.first_fit, r.s));
   }
   rc = check_hip();
   if (rc != PRISM_OK) return rc;
+  if (small) return run_small(r, (float*)a);
   if (dt == PRISM_BF16) rc = run_polar_bf16(r);
   else if (fn == PRISM_FN_POLAR || fn == PRISM_FN_SIGN) rc = run_polar_f32(r);
   else if (fn == PRISM_FN_INVERSE) rc = run_inverse_f32(r);
