@@ -207,6 +207,9 @@ struct FitArgs {
 // batch: the caller's; halves: its launches are for one half of it each, by default
 bool fit_fused_supported(int rows, int ld, int batch, bool b16, bool halves);
 int launch_fit(const FitArgs& a, int batch, hipStream_t s);
+// fit_square.hip: the fit and Q = c1 R + alpha R^2 in one launch (q: POLYQ, symmetric, 128 x 128 tiles)
+bool fit_square_supported(const FitArgs& f);
+int launch_fit_square(const FitArgs& f, const Bf16Desc& q, int batch, hipStream_t s);
 
 // ---- flow.hip : all iterations of an fp32 call in one launch ----
 constexpr int FLOW_MAX_OPS = 4;

@@ -776,5 +776,53 @@ __device__ __forceinline__ bool fit_rows(const FitArgs& a, int b, int batch, int
   return s_next != 0;
 }
 
+// ---- a fit and, beside it, the tiles of the product that needs its coefficient at the end only (Q = R / 2 + alpha R^2) ----
+// The fit is latency (hand-overs, a serial solve) on a few workgroups; the product runs on the rest of the chip meanwhile, its
+// tiles keep their sums in registers and wait for the coefficient.  Per matrix `tiles` workgroups more than the fit has; which of the steps
+// one takes is decided by a counter, rows of the fit first: a tile waits for steps that were taken before it, by workgroups that
+// run, so nothing depends on workgroups being resident together.  (Rows wait for each other bounded, see fit_rows.)
+// Words of FitArgs::sync: counter (every launch on a live matrix takes as many numbers as it has steps), then iteration + 1 and
+// beside it the bits of alpha or SQUARE_STOPPED.
+constexpr int SQUARE_TICKET = FIT_MAX_CLUSTER + 32, SQUARE_STATE = FIT_MAX_CLUSTER + 64;
+constexpr unsigned SQUARE_STOPPED = 0xFFFFFFFFu;
+template <bool B16, int LD, int RB, int NCH, class TILE>
+__device__ __forceinline__ void fit_and_tiles(const FitArgs& f, int batch, int tiles, unsigned char* smem, TILE tile) {
+  __shared__ unsigned s_step;
+  __shared__ u64 s_state;
+  const int t = threadIdx.x, G = f.sv.rows / (16 * RB);
+  // the rows of all matrices are dispatched before the tiles
+  const int b = (int)blockIdx.x < G * batch ? blockIdx.x / G : (blockIdx.x - G * batch) / tiles;
+  if (f.sv.ctrl[b].done) return;
+  unsigned* sync = f.sync + (long long)b * FIT_SYNC_WORDS;
+  if (t == 0) s_step = __hip_atomic_fetch_add(sync + SQUARE_TICKET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) % (unsigned)(G + tiles);
+  __syncthreads();
+  const int step = __builtin_amdgcn_readfirstlane((int)s_step);
+  u64* state = (u64*)(sync + SQUARE_STATE);
+  if (step < G) {
+    if (!fit_rows<B16, LD, RB, NCH, 4>(f, b, batch, step, G, (float*)smem)) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the partials of the others
+    solve_body(f.sv, b);
+    __syncthreads();
+    if (t == 0) {
+      const Ctrl& c = f.sv.ctrl[b];
+      unsigned bits = __float_as_uint(c.alpha);
+      if (bits == SQUARE_STOPPED) bits ^= 1u;            // a NaN like another
+      coh_store<true>(state, (u64)(c.done ? SQUARE_STOPPED : bits) << 32 | (unsigned)(f.sv.k + 1));
+    }
+    return;
+  }
+  tile(b, step - G, [&](float& alpha) {
+    if (t == 0) {
+      u64 v;
+      while ((unsigned)(v = coh_load<true>(state)) != (unsigned)(f.sv.k + 1)) __builtin_amdgcn_s_sleep(1);
+      s_state = v;
+    }
+    __syncthreads();
+    const unsigned bits = __builtin_amdgcn_readfirstlane((unsigned)(s_state >> 32));
+    alpha = __uint_as_float(bits);
+    return bits != SQUARE_STOPPED;
+  });
+}
+
 }  // namespace
 }  // namespace prism

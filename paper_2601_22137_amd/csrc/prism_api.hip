@@ -764,21 +764,30 @@ int run_polar_bf16(Run& r) {
         CHECK_LAUNCH(check_hip());
       }
     }
-    if (lean) CHECK_LAUNCH(r.fit(k, nparts, R, Rb, Dg, Sp, 1));
-    else if (chain_b) CHECK_LAUNCH(r.fit(k, nparts, R, Rb, R, SS, Sp + 1));
-    else CHECK_LAUNCH(r.fit(k, nparts, R));
-    if (k == r.max_iters) break;
-    const uint16_t* Bop = Rb;
+    // where the fit reads R: the bf16 copy with the exact diagonal, or the fp32 matrix
+    const uint16_t* fit_b = chain_b ? Rb : nullptr;
+    const float* fit_d = lean ? Dg : (chain_b ? R : nullptr);
+    const long long fit_sd = lean ? Sp : (chain_b ? SS : 0);
+    const int fit_ldd = lean ? 1 : (chain_b ? Sp + 1 : 0);
+    Bf16Desc q = {};
     if (P.d == 2) {   // one launch over the matrices of all groups: R has the same order everywhere
-      Bf16Desc q = {};
       q.A = Rb; q.strideA = SS; q.lda = Sp; q.B = Rb; q.strideB = SS; q.ldb = Sp;
       q.km = 3;   // R is symmetric bit for bit: read as [K][M], whose whole-cache-line loads are the faster ones
       q.M = Sp; q.N = Sp; q.K = Sp; q.batch = P.batch; q.epi = BEPI_POLYQ; q.sym = sym;
       q.C32 = lean ? nullptr : R; q.strideC32 = SS; q.ldc32 = Sp; q.Cb = Qb; q.strideCb = SS; q.ldcb = Sp; q.c1 = 0.5f;
       q.Cin16 = lean ? Rb : nullptr;
       q.ctrl = r.ctrl;
-      { ProfScope ps(PK_BF16_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_bf16(q, Tq.m, Tq.n, r.s)); }
-      Bop = Qb;
+    }
+    const uint16_t* Bop = P.d == 2 ? Qb : Rb;
+    static const int no_square = ab_switch("PRISM_NO_FIT_SQUARE");
+    if (!no_square && P.d == 2 && Tq.m == 128 && Tq.n == 128 && chain_b && r.fit_needed(k) && r.fused() &&
+        fit_square_supported(r.fit_args(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd))) {
+      ProfScope ps(PK_BF16_POLYQ, r.s);
+      CHECK_LAUNCH(launch_fit_square(r.fit_args(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd), q, P.batch, r.s));
+    } else {
+      CHECK_LAUNCH(r.fit(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd));
+      if (k == r.max_iters) break;
+      if (P.d == 2) { ProfScope ps(PK_BF16_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_bf16(q, Tq.m, Tq.n, r.s)); }
     }
     // One pass: the product reads the high half of the iterate only; the epilogue adds the low
     // half's share elementwise (see the kernel) and splits the result again.

@@ -97,6 +97,21 @@ def test_rows_computed_for_a_missing_partner_bf16(prism, n, batch, sketch, plain
     assert np.array_equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("m,n,sketch", [(128, 100, 16), (300, 257, 32), (640, 640, 16), (1024, 1000, 32)])
+def test_square_beside_the_fit_bf16(prism, m, n, sketch):
+    """Q is formed by the launch that fits its coefficient: matrices that stop at different iterations, one that never starts."""
+    A = W.c3_polar_large(n=max(m, n), batch=2, sigma_decades=1.0)[:, :, :n]
+    bits = np.ascontiguousarray(np.concatenate([A, np.zeros_like(A[:1]), A[1:]]))
+    x = torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16)
+    r = prism.polar(x, 5, 20, sketch, SEED, 2e-2).read()
+    out = x.view(torch.int16).cpu().numpy().view(np.uint16)
+    assert int(r[2]["status"]) == prism.INFO_ZERO and not out[2].any() and np.array_equal(out[1], out[3])
+    for b in (0, 1):
+        ref, oinfo = O.polar(W.from_bf16_bits(bits)[b], 5, 20, sketch, SEED, 2e-2)
+        assert abs(int(r[b]["iters"]) - oinfo["iters"]) <= (0 if oinfo["residual"][-1] < 1.8e-2 else 1)
+        assert np.linalg.norm(W.from_bf16_bits(out)[b] - ref) <= 2e-2 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("n,p", [(40, 4), (100, 4), (300, 2), (512, 3), (1000, 5)])
 def test_inverse_root_alone_and_in_a_batch(prism, n, p):
     """One matrix, where the update of X shares a launch with the first square, and a batch, where it does not: the same bits,
