@@ -520,7 +520,11 @@ int run_flow(const Run& r, const FlowOp* ops, int nops, bool residual, const flo
     if (i < (int)residual) together = a.items[i];
     if (together > widest) widest = together;
   }
-  a.cluster = widest < slots ? widest : slots;
+  // beside other groups a quarter of the chip is left to them: their workgroups otherwise wait until this call is through.  Inverse
+  // roots of 16 matrices of 8 orders from 10 to 576, workgroups of a group / us: 256 1170, 192 1070, 128 1245, 64 1670
+  const int share = P.shared_gpu ? 3 * FLOW_SLOTS / 4 / r.sel_batch : slots, least = P.Sp / 16;
+  const int most = share > least ? share : least;
+  a.cluster = widest < most ? widest : most;
   a.fit = r.fit_args(0, nparts, R, nullptr, nullptr, 0, 0);
   a.rho0 = r.rho; a.nparts0 = nparts0;
   float* rho = (float*)(r.at<double>(P.o_fit_cpart) + (long long)P.batch * (P.Sp / 16) * 17);   // behind the coefficient partials

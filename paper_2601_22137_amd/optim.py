@@ -48,8 +48,7 @@ def shampoo_inverse_roots(stats, root_p=4, max_iters=40, sketch_dim=16, seed=221
     stacked = [torch.stack([stats[i] for i in idx]).contiguous() for idx in groups.values()]
     _, infos = prism.run_grouped(prism.FN_INV_ROOT, stacked, 3, max_iters, sketch_dim, seed, tol, root_p=root_p)
     out, iters = [None] * len(stats), [0] * len(stats)
-    for idx, s, h in zip(groups.values(), stacked, infos):
-        rec = h.read()
+    for idx, s, rec in zip(groups.values(), stacked, prism.read_reports(infos)):
         for j, i in enumerate(idx):
             out[i] = s[j]
             iters[i] = int(rec[j]["iters"])

@@ -266,6 +266,19 @@ def run_grouped(fn, xs, degree=5, max_iters=30, sketch_dim=8, seed=22137, tol=1e
     return invs, infos
 
 
+def read_reports(infos):
+    """The reports of the groups of one grouped call, read by one copy (synchronises): a structured array per group.  One copy per
+    group costs its round trip each: eight groups 0.3 ms."""
+    if not infos:
+        return []
+    whole = torch.cat([h.buf for h in infos]).cpu().numpy()
+    out, at = [], 0
+    for h in infos:
+        out.append(whole[at:at + h.buf.numel()].view(INFO_DTYPE).copy())
+        at += h.buf.numel()
+    return out
+
+
 # ---- single steps (unit tests, profiling) ----
 
 def spd_inverse(a):
