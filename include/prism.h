@@ -283,6 +283,13 @@ int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int r
                       int degree, int max_iters, int sketch_dim, uint64_t seed, double tol,
                       void* stream, const prism_options* opt);
 
+/* The same with matrix b of group g read from the device pointer from[g][b] (row-major, contiguous; host arrays, read
+ * during the call) instead of groups[g].x, which only takes the results (and copies of zero and non-finite
+ * matrices).  The gradients of a list of weights need no copy into one array first. */
+int prism_run_grouped_from(prism_fn fn, const prism_group* groups, const void* const* const* from, int ngroups,
+                           int root_p, prism_dtype dt, int degree, int max_iters, int sketch_dim, uint64_t seed,
+                           double tol, void* stream, const prism_options* opt);
+
 /* ---- single steps of the path, exposed for unit tests and profiling ---- */
 
 /* S_k^T (Section 4.2: Gaussian sketch): out[n][sketch_dim] fp32 on the device,

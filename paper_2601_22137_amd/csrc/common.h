@@ -284,11 +284,19 @@ struct FinalArgs {
   const uint16_t* Xa_hi[2]; const uint16_t* Xa_lo[2];
 };
 void launch_finalize(const FinalArgs& a, hipStream_t s);
-struct PrepMulti { PrepArgs d[BF16_MAX_GROUPS]; int start[BF16_MAX_GROUPS + 1]; int ngroups; };
-struct FinalMulti { FinalArgs d[BF16_MAX_GROUPS]; int start[BF16_MAX_GROUPS + 1]; int ngroups; };
+// Where the matrices of a launch come from, if each has an address of its own: those of group g from p[first[g]] on; first[g] < 0:
+// one behind the other
+constexpr int MAX_SOURCES = 160;
+struct Sources { const void* p[MAX_SOURCES]; int first[BF16_MAX_GROUPS]; };
+struct PrepMulti { PrepArgs d[BF16_MAX_GROUPS]; int start[BF16_MAX_GROUPS + 1]; int ngroups; Sources from; };
+struct FinalMulti { FinalArgs d[BF16_MAX_GROUPS]; int start[BF16_MAX_GROUPS + 1]; int ngroups; Sources from; };
+static_assert(sizeof(PrepMulti) <= 4096 && sizeof(FinalMulti) <= 4096, "kernel arguments");
 // one launch each over several shape groups (bf16 polar); false: not applicable, launch group by group
-bool launch_prep_multi(const PrepArgs* groups, int ngroups, hipStream_t s);
-bool launch_finalize_multi(const FinalArgs* groups, int ngroups, hipStream_t s);
+// from (may be null): see Sources
+bool launch_prep_multi(const PrepArgs* groups, int ngroups, const Sources* from, hipStream_t s);
+bool launch_finalize_multi(const FinalArgs* groups, int ngroups, const Sources* from, hipStream_t s);
+// dst[b] <- *from[b], `bytes` each
+void launch_gather(void* dst, const void* const* from, int count, size_t bytes, hipStream_t s);
 
 // The per-matrix reports of a launch sequence over several shape groups sit in one array; each group's
 // part goes to the array its caller gave (one launch instead of a copy per group).

@@ -36,18 +36,19 @@ __device__ inline double total_sumsq(const double* part, int nsum) {
 // An inf or nan entry makes its partial non-finite, which the prepare step reports.
 // bx in [0, gx): the share of the matrix, b: the matrix (the launch geometry of a single group, which
 // the launches over several groups reproduce so that every matrix gets the same partial sums)
-__device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
+// src: the matrix
+__device__ inline void sumsq_body(const PrepArgs& a, const void* src, int bx, int b, int gx) {
   const long long total = (long long)a.m * a.n;
   double acc = 0.0;
   const long long first = (long long)bx * NT + threadIdx.x, step = (long long)gx * NT;
   // 16-byte loads, four in flight, from wherever the matrix starts: which thread adds up which entry follows from the
   // shape, not from the address.  The entries behind the last whole vector go to the first workgroup.
-  auto sweep = [&](auto* src, auto add16, auto add1) {
-    constexpr int PER = 16 / (int)sizeof(*src);
+  auto sweep = [&](auto* x, auto add16, auto add1) {
+    constexpr int PER = 16 / (int)sizeof(*x);
     const long long nv = total / PER;
     auto load = [&](long long i) {
       u32x4 w;
-      __builtin_memcpy(&w, src + i * PER, 16);   // aligned to the element only
+      __builtin_memcpy(&w, x + i * PER, 16);   // aligned to the element only
       return w;
     };
     long long i = first;
@@ -56,10 +57,10 @@ __device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
       add16(w0); add16(w1); add16(w2); add16(w3);
     }
     for (; i < nv; i += step) add16(load(i));
-    if (bx == 0 && nv * PER + threadIdx.x < total) add1(src[nv * PER + threadIdx.x]);
+    if (bx == 0 && nv * PER + threadIdx.x < total) add1(x[nv * PER + threadIdx.x]);
   };
   if (a.dt == PRISM_BF16) {
-    sweep((const unsigned short*)a.src + (long long)b * total,
+    sweep((const unsigned short*)src,
           [&](const u32x4& w) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -69,7 +70,7 @@ __device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
           },
           [&](unsigned short h) { acc += (double)bf2f(h) * (double)bf2f(h); });
   } else {
-    sweep((const float*)a.src + (long long)b * total,
+    sweep((const float*)src,
           [&](const u32x4& w) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc += (double)__uint_as_float(w[e]) * (double)__uint_as_float(w[e]);
@@ -84,14 +85,18 @@ __device__ inline void sumsq_body(const PrepArgs& a, int bx, int b, int gx) {
   __syncthreads();
   if (threadIdx.x == 0) a.sumsq_part[(long long)b * a.nsum + bx] = red[0] + red[1] + red[2] + red[3];
 }
-__global__ __launch_bounds__(NT) void sumsq_kernel(PrepArgs a) { sumsq_body(a, blockIdx.x, blockIdx.y, gridDim.x); }
+__device__ inline const void* source(const PrepArgs& a, int b) {
+  return (const char*)a.src + (long long)b * a.m * a.n * (a.dt == PRISM_BF16 ? 2 : 4);
+}
+__global__ __launch_bounds__(NT) void sumsq_kernel(PrepArgs a) { sumsq_body(a, source(a, blockIdx.y), blockIdx.x, blockIdx.y, gridDim.x); }
 // several shape groups in one launch: workgroup -> (group, matrix, share)
 __global__ __launch_bounds__(NT) void sumsq_multi_kernel(PrepMulti m) {
   int w = blockIdx.x, gi = 0;
   while (gi + 1 < m.ngroups && w >= m.start[gi + 1]) ++gi;
   w -= m.start[gi];
   const PrepArgs& a = m.d[gi];
-  sumsq_body(a, w % a.nsum, w / a.nsum, a.nsum);
+  const int b = w / a.nsum, first = m.from.first[gi];
+  sumsq_body(a, first < 0 ? source(a, b) : m.from.p[first + b], w % a.nsum, b, a.nsum);
 }
 
 // fp32: one workgroup per 64 x 64 tile of the padded internal iterate [Lp][Sp].
@@ -205,10 +210,9 @@ template <bool VEC> __device__ inline u32x4 load8(const unsigned short* row, int
   return w;
 }
 template <bool VEC>
-__device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
+__device__ inline void prepare_bf16_body(const PrepArgs& a, const unsigned short* src, int bx, int b) {
   const int tiles_c = (a.transpose ? a.Lp : a.Sp) / PC;             // tiles over the padded, caller-oriented matrix
   const int tr = bx / tiles_c, tc = bx % tiles_c;
-  const unsigned short* src = (const unsigned short*)a.src + (long long)b * a.m * a.n;
   u32x4 in[4];
 #pragma unroll
   for (int it = 0; it < 4; ++it) {              // 1024 vectors of 8 per tile, requested ahead of the norm
@@ -276,14 +280,17 @@ __device__ inline void prepare_bf16_body(const PrepArgs& a, int bx, int b) {
     if (a.Xa_lo) *(u32x4*)(a.Xa_lo + o) = *(const u32x4*)&tile_lo[lc][rotated(lc, lr, 8)];
   }
 }
-template <bool VEC> __global__ __launch_bounds__(NT) void prepare_bf16_kernel(PrepArgs a) { prepare_bf16_body<VEC>(a, blockIdx.x, blockIdx.y); }
+template <bool VEC> __global__ __launch_bounds__(NT) void prepare_bf16_kernel(PrepArgs a) {
+  prepare_bf16_body<VEC>(a, (const unsigned short*)source(a, blockIdx.y), blockIdx.x, blockIdx.y);
+}
 __global__ __launch_bounds__(NT) void prepare_bf16_multi_kernel(PrepMulti m) {
   int w = blockIdx.x, gi = 0;
   while (gi + 1 < m.ngroups && w >= m.start[gi + 1]) ++gi;
   w -= m.start[gi];
   const PrepArgs& a = m.d[gi];
   const int tiles = (a.Lp / 64) * (a.Sp / PC);
-  prepare_bf16_body<true>(a, w % tiles, w / tiles);
+  const int b = w / tiles, first = m.from.first[gi];
+  prepare_bf16_body<true>(a, (const unsigned short*)(first < 0 ? source(a, b) : m.from.p[first + b]), w % tiles, b);
 }
 
 // bf16 polar, rows of the caller's matrix in 16-byte vectors (VEC; entry by entry otherwise): the result is the high half of
@@ -302,9 +309,18 @@ template <bool VEC> __device__ inline void store8(unsigned short* row, int c, in
   }
 }
 template <bool VEC>
-__device__ inline void finalize_bf16_body(const FinalArgs& a, int bx, int b) {
+__device__ inline void finalize_bf16_body(const FinalArgs& a, const unsigned short* src, int bx, int b) {   // src: the input, where it is not at dst
   const Ctrl c = a.ctrl[b];
-  if (c.status == PRISM_INFO_NONFINITE || c.status == PRISM_INFO_ZERO) return;
+  if (c.status == PRISM_INFO_NONFINITE || c.status == PRISM_INFO_ZERO) {
+    if (!src) return;
+    const int across = (a.n + PC - 1) / PC, row0 = bx / across * 64, col0 = bx % across * PC;
+    for (int v = threadIdx.x; v < 1024; v += NT) {
+      const int r = row0 + (v >> 4), col = col0 + (v & 15) * 8;
+      if (r < a.m && col < a.n)
+        store8<VEC>((unsigned short*)a.dst + ((long long)b * a.m + r) * a.n, col, a.n, load8<VEC>(src + (long long)r * a.n, col, a.n));
+    }
+    return;
+  }
   const int par = c.iters & 1;
   const long long mat_int = (long long)b * a.Lp * a.Sp;
   const unsigned short* hi = a.Xa_hi[par] + mat_int;
@@ -347,14 +363,15 @@ __device__ inline void finalize_bf16_body(const FinalArgs& a, int bx, int b) {
     if (r < a.m && col < a.n) store8<VEC>(dst + (long long)r * a.n, col, a.n, *(const u32x4*)&tile[lr][rotated(lr, lc, 16)]);
   }
 }
-template <bool VEC> __global__ __launch_bounds__(NT) void finalize_bf16_kernel(FinalArgs a) { finalize_bf16_body<VEC>(a, blockIdx.x, blockIdx.y); }
+template <bool VEC> __global__ __launch_bounds__(NT) void finalize_bf16_kernel(FinalArgs a) { finalize_bf16_body<VEC>(a, nullptr, blockIdx.x, blockIdx.y); }
 __global__ __launch_bounds__(NT) void finalize_bf16_multi_kernel(FinalMulti m) {
   int w = blockIdx.x, gi = 0;
   while (gi + 1 < m.ngroups && w >= m.start[gi + 1]) ++gi;
   w -= m.start[gi];
   const FinalArgs& a = m.d[gi];
   const int tiles = ((a.m + 63) / 64) * ((a.n + PC - 1) / PC);
-  finalize_bf16_body<true>(a, w % tiles, w / tiles);
+  const int b = w / tiles, first = m.from.first[gi];
+  finalize_bf16_body<true>(a, first < 0 ? nullptr : (const unsigned short*)m.from.p[first + b], w % tiles, b);
 }
 
 // fp32: one thread per element of the caller's array.
@@ -516,14 +533,20 @@ void launch_prepare(const PrepArgs& a, hipStream_t s) {
 
 // The pre-scaling and copy-out steps of several shape groups in one launch each (bf16 polar, every group
 // on the 16-byte vector path); false: the caller launches them group by group.
-bool launch_prep_multi(const PrepArgs* groups, int ngroups, hipStream_t s) {
+static void set_sources(Sources& to, const Sources* from) {
+  if (from) { to = *from; return; }
+  for (int& f : to.first) f = -1;
+}
+bool launch_prep_multi(const PrepArgs* groups, int ngroups, const Sources* from, hipStream_t s) {
   if (ngroups < 2 || ngroups > BF16_MAX_GROUPS) return false;
   PrepMulti ms = {}, mp = {};
+  set_sources(ms.from, from);
+  set_sources(mp.from, from);
   ms.ngroups = mp.ngroups = ngroups;
   long long ts = 0, tp = 0;
   for (int i = 0; i < ngroups; ++i) {
     const PrepArgs& a = groups[i];
-    if (a.dt != PRISM_BF16 || !bf16_vector_rows(a.n, a.src)) return false;
+    if (a.dt != PRISM_BF16 || !bf16_vector_rows(a.n, from ? nullptr : a.src)) return false;   // sources: their caller has looked
     ms.d[i] = mp.d[i] = a;
     ms.start[i] = (int)ts; mp.start[i] = (int)tp;
     ts += (long long)a.nsum * a.batch;
@@ -536,9 +559,10 @@ bool launch_prep_multi(const PrepArgs* groups, int ngroups, hipStream_t s) {
   return true;
 }
 
-bool launch_finalize_multi(const FinalArgs* groups, int ngroups, hipStream_t s) {
+bool launch_finalize_multi(const FinalArgs* groups, int ngroups, const Sources* from, hipStream_t s) {
   if (ngroups < 2 || ngroups > BF16_MAX_GROUPS) return false;
   FinalMulti mf = {};
+  set_sources(mf.from, from);
   mf.ngroups = ngroups;
   long long t = 0;
   for (int i = 0; i < ngroups; ++i) {
@@ -577,6 +601,34 @@ __global__ __launch_bounds__(256) void scatter_info_kernel(InfoScatter a) {
   }
 }
 }  // namespace
+
+namespace {
+constexpr int GATHER = 64;
+struct GatherArgs { const char* from[GATHER]; char* dst; long long bytes; };
+// one matrix per blockIdx.y, whatever its alignment
+__global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
+  const char* src = a.from[blockIdx.y];
+  char* dst = a.dst + (long long)blockIdx.y * a.bytes;
+  const long long first = (long long)blockIdx.x * 256 + threadIdx.x, step = (long long)gridDim.x * 256;
+  if ((((uintptr_t)src | (uintptr_t)dst | (uintptr_t)a.bytes) & 15) == 0)
+    for (long long i = first; i < a.bytes / 16; i += step) ((u32x4*)dst)[i] = ((const u32x4*)src)[i];
+  else
+    for (long long i = first; i < a.bytes / 2; i += step) ((unsigned short*)dst)[i] = ((const unsigned short*)src)[i];
+}
+}  // namespace
+
+void launch_gather(void* dst, const void* const* from, int count, size_t bytes, hipStream_t s) {
+  if (bytes == 0) return;
+  for (int b0 = 0; b0 < count; b0 += GATHER) {
+    GatherArgs a = {};
+    const int n = count - b0 < GATHER ? count - b0 : GATHER;
+    for (int i = 0; i < n; ++i) a.from[i] = (const char*)from[b0 + i];
+    a.dst = (char*)dst + (size_t)b0 * bytes;
+    a.bytes = (long long)bytes;
+    const size_t blocks = (bytes + 16383) / 16384;
+    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)(blocks > 512 ? 512 : blocks), n), dim3(256), 0, s, a);
+  }
+}
 
 void launch_scatter_info(const InfoScatter& a, hipStream_t s) {
   static_assert(sizeof(prism_info) % 4 == 0, "reports are copied word by word");

@@ -1193,7 +1193,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
 // the kernels its own single-group call would pick.  Returns PRISM_EUNSUPPORTED (nothing enqueued)
 // when the groups do not fit this form; the caller then takes the per-group path.
 int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, int max_iters, int sketch_dim, uint64_t seed,
-                          double tol, void* stream, const prism_options* opt, int batch_scale = 1) {
+                          double tol, void* stream, const prism_options* opt, int batch_scale = 1, const void* const* const* from = nullptr) {
   static const int off = ab_switch("PRISM_NO_SHARED_SHAPES");
   if (off || ngroups < 2 || ngroups > BF16_MAX_GROUPS) return PRISM_EUNSUPPORTED;
   if (max_iters < 0 || max_iters > PRISM_MAX_ITERS || !(tol == tol)) return PRISM_EINVAL;
@@ -1220,6 +1220,16 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     btot += groups[g].batch;
   }
   if (btot > PRISM_MAX_BATCH) return PRISM_EUNSUPPORTED;
+  Sources sources = {};
+  if (from) {   // (the caller has looked at their number and alignment)
+    if (btot > MAX_SOURCES) return PRISM_EUNSUPPORTED;
+    int at = 0;
+    for (int g = 0; g < ngroups; ++g) {
+      if ((uintptr_t)groups[g].x & 15) return PRISM_EUNSUPPORTED;
+      sources.first[g] = at;
+      for (int b = 0; b < groups[g].batch; ++b) sources.p[at++] = from[g][b];
+    }
+  }
   // Beside split Gram products the few other ones go with them, as products of one part (same R): two launches instead of
   // three.  One layer (four shapes), three updates without a fit, us: width 256 170 -> 142 (no split: 143), 512 200 -> 166 (193),
   // 768 286 -> 250 (284), 1280 622 -> 579 (583).
@@ -1295,8 +1305,10 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     PrepArgs pas[BF16_MAX_GROUPS];
     int np = 0;
     for (const Run::XGroup& x : r.xg) { group_args(x, pa, fa); pas[np++] = pa; }
-    if (!launch_prep_multi(pas, np, r.s))
+    if (!launch_prep_multi(pas, np, from ? &sources : nullptr, r.s)) {
+      if (from) return PRISM_EUNSUPPORTED;
       for (int i = 0; i < np; ++i) { launch_sumsq(pas[i], r.s); launch_prepare(pas[i], r.s); }
+    }
   }
   if (P.p_s > 0 && max_iters > r.first_fit) {
     ProfScope ps(PK_SKETCH, r.s);
@@ -1312,7 +1324,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
     FinalArgs fas[BF16_MAX_GROUPS];
     int nf = 0;
     for (const Run::XGroup& x : r.xg) { group_args(x, pa, fa); fas[nf++] = fa; }
-    if (!launch_finalize_multi(fas, nf, r.s))
+    if (!launch_finalize_multi(fas, nf, from ? &sources : nullptr, r.s))
       for (int i = 0; i < nf; ++i) launch_finalize(fas[i], r.s);
   }
   rc = check_hip();
@@ -1362,10 +1374,30 @@ int get_fork(Fork** out) {
 }
 
 int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int dt, int degree, int max_iters,
-                int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, bool from_auto_split = false) {
+                int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, bool from_auto_split = false,
+                const void* const* const* from = nullptr) {
   set_last_error("");
   if (ngroups == 0) return PRISM_OK;
   if (!groups || ngroups < 0) return PRISM_EINVAL;
+  for (int g = 0; from && g < ngroups; ++g) {
+    if (groups[g].batch > 0 && !from[g]) return PRISM_EINVAL;
+    for (int b = 0; b < groups[g].batch; ++b)
+      if (!from[g][b] && groups[g].m > 0 && groups[g].n > 0) return PRISM_EINVAL;
+  }
+  // matrices with addresses of their own, for a path that takes them one behind the other only
+  auto gather = [&]() -> int {
+    if (!from) return PRISM_OK;
+    for (int g = 0; g < ngroups; ++g) {
+      const prism_group& q = groups[g];
+      if (q.batch <= 0 || q.m <= 0 || q.n <= 0) continue;
+      Plan P;
+      if (!q.x) return PRISM_EINVAL;
+      CHECK_LAUNCH(make_plan(P, fn, q.batch, q.m, q.n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u));   // a call that will be refused copies nothing
+      launch_gather(q.x, from[g], q.batch, (size_t)q.m * q.n * (dt == PRISM_BF16 ? 2 : 4), (hipStream_t)stream);
+    }
+    from = nullptr;
+    return check_hip();
+  };
   if (opt && (opt->workspace || opt->info)) return PRISM_EINVAL;
   if (fn == PRISM_FN_INVERSE) degree = 5;                     // fixed polynomial
   if (fn == PRISM_FN_SQRT_NEWTON) { degree = 3; sketch_dim = sketch_dim ? 1 : 0; seed = 0; }
@@ -1374,6 +1406,7 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
   if (ngroups == 1) {
     prism_options o = opt ? *opt : prism_options{};
     o.info = groups[0].info;
+    CHECK_LAUNCH(gather());
     return run(fn, groups[0].x, groups[0].inv_out, root_p, groups[0].batch, groups[0].m, groups[0].n, dt, degree,
                max_iters, sketch_dim, seed, tol, stream, &o);
   }
@@ -1398,17 +1431,26 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
     }
     const int NP = (parts_sw == 2 || parts_sw == 4) ? (common >= parts_sw ? parts_sw : common) : common;
     const bool even = ngroups <= BF16_MAX_GROUPS && NP >= 2 && !single_stream;
+    // sources that the launches over several groups read where they are: aligned to vectors, with a place in their arguments
+    bool direct = btot / (even && btot >= 32 && !no_halves ? NP : 1) <= MAX_SOURCES;
+    for (int gi = 0; from && direct && gi < ngroups; ++gi) {
+      direct = groups[gi].n % 8 == 0;
+      for (int b = 0; b < groups[gi].batch; ++b) direct = direct && ((uintptr_t)from[gi][b] & 15) == 0;
+    }
+    if (!direct) CHECK_LAUNCH(gather());
     if (!even || btot < 32 || no_halves) {
-      rc = run_polar_bf16_shapes(groups, ngroups, degree, max_iters, sketch_dim, seed, tol, stream, opt);
+      rc = run_polar_bf16_shapes(groups, ngroups, degree, max_iters, sketch_dim, seed, tol, stream, opt, 1, from);
       if (rc != PRISM_EUNSUPPORTED) return rc;
     } else {
       prism_group half[4][BF16_MAX_GROUPS];   // NP <= 4 parts
+      const void* const* half_from[4][BF16_MAX_GROUPS];
       for (int gi = 0; gi < ngroups; ++gi) {
         const size_t bytes = (size_t)(groups[gi].batch / NP) * groups[gi].m * groups[gi].n * 2;
         for (int h = 0; h < NP; ++h) {
           half[h][gi] = groups[gi];
           half[h][gi].batch = groups[gi].batch / NP;
           half[h][gi].x = (char*)groups[gi].x + h * bytes;
+          half_from[h][gi] = from ? from[gi] + h * (groups[gi].batch / NP) : nullptr;
           half[h][gi].info = groups[gi].info ? groups[gi].info + h * (groups[gi].batch / NP) : nullptr;
         }
       }
@@ -1420,7 +1462,8 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
         if (hipStreamWaitEvent(f->streams[forked], f->forked, 0) != hipSuccess) { first_error = PRISM_EHIP; break; }
       bool unsupported = false;
       for (int h = 0; h < NP && first_error == PRISM_OK; ++h) {
-        first_error = run_polar_bf16_shapes(half[h], ngroups, degree, max_iters, sketch_dim, seed, tol, h ? f->streams[h - 1] : user, opt, NP);
+        first_error = run_polar_bf16_shapes(half[h], ngroups, degree, max_iters, sketch_dim, seed, tol, h ? f->streams[h - 1] : user, opt, NP,
+                                            from ? half_from[h] : nullptr);
         if (h == 0 && first_error == PRISM_EUNSUPPORTED) { unsupported = true; first_error = PRISM_OK; break; }   // nothing was enqueued
       }
       for (int i = 0; i < forked; ++i) {
@@ -1433,6 +1476,7 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
     }
     set_last_error("");
   }
+  CHECK_LAUNCH(gather());
   if (single_stream) {
     for (int gi = 0; gi < ngroups; ++gi) {
       prism_options o = opt ? *opt : prism_options{};
@@ -1700,6 +1744,12 @@ int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream
 int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int root_p, prism_dtype dt, int degree,
                       int max_iters, int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt) {
   return run_grouped((int)fn, groups, ngroups, root_p, (int)dt, degree, max_iters, sketch_dim, seed, tol, stream, opt);
+}
+
+int prism_run_grouped_from(prism_fn fn, const prism_group* groups, const void* const* const* from, int ngroups, int root_p, prism_dtype dt,
+                           int degree, int max_iters, int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt) {
+  if (ngroups > 0 && !from) return PRISM_EINVAL;
+  return run_grouped((int)fn, groups, ngroups, root_p, (int)dt, degree, max_iters, sketch_dim, seed, tol, stream, opt, false, from);
 }
 
 int prism_sketch(float* out, int n, int sketch_dim, uint64_t seed, int k, int fn, void* stream) {

@@ -26,7 +26,7 @@ INFO_DTYPE = np.dtype([("iters", np.int32), ("status", np.int32),
                        ("residual", np.float32, (MAX_ITERS + 1,)), ("alpha", np.float32, (MAX_ITERS,))])
 
 EXPORTS = ("prism_workspace_bytes", "prism_release_workspaces", "prism_polar", "prism_polar_ex", "prism_polar_static", "prism_sqrt", "prism_sqrt_ex",
-           "prism_inv_root", "prism_inv_root_ex", "prism_sign", "prism_sign_ex", "prism_inverse", "prism_inverse_ex", "prism_sqrt_newton", "prism_sqrt_newton_ex", "prism_spd_inverse", "prism_run_grouped",
+           "prism_inv_root", "prism_inv_root_ex", "prism_sign", "prism_sign_ex", "prism_inverse", "prism_inverse_ex", "prism_sqrt_newton", "prism_sqrt_newton_ex", "prism_spd_inverse", "prism_run_grouped", "prism_run_grouped_from",
            "prism_sketch", "prism_gauss_parts", "prism_chain_product", "prism_chain_product_bf16", "prism_gemm_f32",
            "prism_gemm_f64a", "prism_gemm_bf16_nt", "prism_profile_enable", "prism_profile_collect",
            "prism_last_error")
@@ -78,6 +78,7 @@ def lib():
         L.prism_sqrt_newton_ex.argtypes = L.prism_sqrt_newton.argtypes + [ctypes.POINTER(Options)]
         L.prism_spd_inverse.argtypes = [vp, vp, i, i, vp]
         L.prism_run_grouped.argtypes = [i, ctypes.POINTER(Group), i, i, i, i, i, i, u64, dbl, vp, ctypes.POINTER(Options)]
+        L.prism_run_grouped_from.argtypes = [i, ctypes.POINTER(Group), vp, i, i, i, i, i, i, u64, dbl, vp, ctypes.POINTER(Options)]
         L.prism_sketch.argtypes = [vp, i, i, u64, i, i, vp]
         L.prism_gauss_parts.argtypes = [ctypes.c_uint32, ctypes.c_uint32, vp, vp, vp, vp]
         L.prism_chain_product.argtypes = [vp, vp, vp, i, i, i, vp]
@@ -238,8 +239,9 @@ def sqrt_newton(a, max_iters=30, tol=1e-6, fit=True, workspace=None, alpha_sched
 
 
 def run_grouped(fn, xs, degree=5, max_iters=30, sketch_dim=8, seed=22137, tol=1e-6, root_p=0, flags=0, warm_iters=0,
-                alpha_schedule=None):
-    """One call over tensors of different shapes (each [batch, m, n], all of one dtype), in place.
+                alpha_schedule=None, sources=None):
+    """One call over tensors of different shapes (each [batch, m, n], all of one dtype), in place.  sources: per tensor
+    of xs a list of `batch` contiguous [m, n] tensors that are read instead; xs then only takes the results.
     Returns (inverse outputs or None per group, info handles per group)."""
     if len(xs) == 0:
         _check(lib().prism_run_grouped(fn, None, 0, root_p, F32, degree, max_iters, sketch_dim, seed, tol, _stream(), None))
@@ -261,8 +263,17 @@ def run_grouped(fn, xs, degree=5, max_iters=30, sketch_dim=8, seed=22137, tol=1e
         o._sched = (ctypes.c_float * len(alpha_schedule))(*[float(a) for a in alpha_schedule])
         o.alpha_schedule = ctypes.cast(o._sched, ctypes.POINTER(ctypes.c_float))
         o.schedule_len = len(alpha_schedule)
-    _check(lib().prism_run_grouped(fn, groups, len(xs), root_p, _dtype_code(xs[0]), degree, max_iters, sketch_dim, seed, tol,
-                                   _stream(), ctypes.byref(o)))
+    rest = (len(xs), root_p, _dtype_code(xs[0]), degree, max_iters, sketch_dim, seed, tol, _stream(), ctypes.byref(o))
+    if sources is None:
+        _check(lib().prism_run_grouped(fn, groups, *rest))
+        return invs, infos
+    for x, ts in zip(xs, sources):
+        if len(ts) != x.shape[0] or any(t.shape != x.shape[1:] or t.dtype != x.dtype or t.device != x.device or not t.is_contiguous() for t in ts):
+            raise PrismError("expected per group one contiguous tensor [m, n] per matrix, of the dtype and on the device of the results")
+    if len(sources) != len(xs):
+        raise PrismError("expected sources for every group")
+    lists = [(ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts]) for ts in sources]
+    _check(lib().prism_run_grouped_from(fn, groups, (ctypes.c_void_p * len(lists))(*[ctypes.addressof(a) for a in lists]), *rest))
     return invs, infos
 
 

@@ -300,3 +300,32 @@ def test_grouped_shapes_on_both_sides_of_the_fused_fit(prism, w, counts, plain):
             rec, got = prism.polar(y, 5, iters, 16, SEED, tol, flags=flags).read(), infos[g].read()
             assert torch.equal(xs[g].view(torch.int16), y.view(torch.int16)), (tol, g)
             assert np.array_equal(rec["alpha"], got["alpha"]) and np.array_equal(rec["iters"], got["iters"]), (tol, g)
+
+
+@pytest.mark.parametrize("shapes,odd", [([(64, 96)], False), ([(128, 128), (128, 512), (512, 128)], False), ([(768, 768), (768, 3072)] * 16, False),
+                                        ([(128, 132), (300, 128)], False), ([(256, 256), (256, 512)], True), ([(32, 64)] * 90 + [(64, 32)] * 90, False)])
+def test_sources_where_they_are(prism, shapes, odd):
+    """A list of matrices read from their own addresses: the bits of the stacked call, inputs untouched; a zero and a non-finite matrix
+    come back as they are.  odd: addresses that no vector load takes."""
+    rng = np.random.default_rng(len(shapes))
+    mats = []
+    for i, (m, n) in enumerate(shapes):
+        buf = torch.from_numpy(rng.standard_normal(m * n + 1).astype(np.float32)).cuda().to(torch.bfloat16)
+        mats.append((buf[1:] if odd and i == 0 else buf[:-1]).view(m, n))
+    mats[-1].zero_()
+    if len(mats) > 2:
+        mats[1][0, 0] = float("inf")
+    before = [t.clone() for t in mats]
+    groups = {}
+    for t in mats:
+        groups.setdefault(tuple(t.shape), []).append(t)
+    stacked = [torch.stack(ts) for ts in groups.values()]
+    plain = prism.FLAG_BF16_PLAIN_ITERATE
+    _, ref = prism.run_grouped(prism.FN_POLAR, stacked, 5, 5, 16, SEED, 0.0, flags=plain)
+    out = [torch.full_like(s, 7.0) for s in stacked]
+    _, got = prism.run_grouped(prism.FN_POLAR, out, 5, 5, 16, SEED, 0.0, flags=plain, sources=list(groups.values()))
+    for s, o, a, b in zip(stacked, out, ref, got):
+        assert torch.equal(s.view(torch.int16), o.view(torch.int16))
+        assert np.array_equal(a.read()["status"], b.read()["status"])
+    for t, b in zip(mats, before):
+        assert torch.equal(t.view(torch.int16), b.view(torch.int16))
