@@ -11,7 +11,7 @@
 // byte of the matrix they sweep; with blocks of 64 the sweep is HBM bound), each inverted by the same
 // elimination with pivots of 64, which one workgroup inverts in fp64 (larger ones would be fewer steps, but an
 // inverse of order 128 rounded to fp32 costs the ill-conditioned cases accuracy: 2.9e-4 against 2e-4 at cond 1e4).
-// The new row and column panels of an outer block go to scratch and are copied back.
+// The new row panel of an outer block goes to scratch; from there the row and, transposed, the column are written.
 #include "common.h"
 
 namespace prism {
@@ -44,10 +44,18 @@ template <int L> __device__ inline double from_lane(double v) {   // uniform
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
-// One elimination step of the 16 x 16 inverse below: pivot P.
+// 1 / x, x finite and not 0 (else not a number): the hardware's approximation (2^-24) and two Newton steps, to an ulp
+__device__ inline double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+// One elimination step of the 16 x 16 inverse below: pivot P.  A chain of latencies, 16 of them in each of the four steps of a 64 x 64
+// inverse: with an exact division 2 x 512^2 160 us, not 152.  (The pivot column by exchanges of lane halves and rows instead of the
+// shuffle: 164.)
 template <int P> __device__ inline void invert16_step(double (&e)[4], int lr, int lq) {
   constexpr int G = P >> 2, C = P & 3;           // the pivot column sits in lane group G, register C
-  const double inv = 1.0 / from_lane<G * 16 + P>(e[C]);
+  const double inv = reciprocal(from_lane<G * 16 + P>(e[C]));
   const double f = __shfl(e[C], G * 16 + lr, 64);
   double rw[4];
 #pragma unroll
@@ -202,7 +210,7 @@ __device__ inline void mma64(const float* As, const float* Bs, int m0, int n0, f
 // finish meanwhile), on large ones the sweep of S and D.  Every workgroup forms P S_kj for itself, twice the
 // products of the update alone, instead of a launch of its own for the pivot row and one for the column.
 // 2 x 2048^2, a block of 512: 8 steps of 17 us; the pivot kernel of one barrier per row (87 us) and the three products
-// that this replaces took 8 times 105 us.  A call of four iterations: 18.8 -> 7.0 ms.
+// that this replaces took 8 times 105 us.
 struct StepArgs {
   const float* S; long long sstride; int sld;
   float* D; long long dstride; int dld;
@@ -357,10 +365,11 @@ __global__ __launch_bounds__(NT) void db_moments_kernel(const float* __restrict_
 // entries of its spectrum, which is what the large components of X = A^(1/2) inherit.  Pass 0: w = N v.
 // Pass 1: partial sums of (M w - v)^2 into slot 16 of the coefficient partials, which the solve
 // kernel adds up.
-// grid (groups, batch); a wave takes 16 rows at a time (16-byte loads, 16 KiB in flight per wave).  The
+// grid (groups, batch); a wave takes 4 rows at a time, four columns of loads (16 bytes a lane) in flight.  HBM or Infinity Cache bound once the
+// chip has a workgroup per CU: 2 x 2048^2 39 us with 16 rows per wave (64 workgroups).  The
 // padding needs no mask: M and N are the identity there, so padded rows reproduce v exactly.
 __device__ inline float probe_entry(int c) { return ((unsigned)c * 2654435761u >> 16) & 1u ? 1.0f : -1.0f; }
-constexpr int PR = 16;   // rows per wave and sweep
+constexpr int PR = 4;   // rows per wave and sweep
 __global__ __launch_bounds__(NT) void db_probe_kernel(const float* __restrict__ A, int np, const Ctrl* __restrict__ ctrl,
                                                       float* __restrict__ w, double* __restrict__ cpart, int pass) {
   const int b = blockIdx.y, grp = blockIdx.x, ngrp = gridDim.x;
@@ -373,6 +382,7 @@ __global__ __launch_bounds__(NT) void db_probe_kernel(const float* __restrict__ 
     double dot[PR];
 #pragma unroll
     for (int k = 0; k < PR; ++k) dot[k] = 0.0;
+#pragma unroll 4
     for (int c = lane * 4; c < np; c += 256) {
       float4 x;
       if (pass == 0) x = make_float4(probe_entry(c), probe_entry(c + 1), probe_entry(c + 2), probe_entry(c + 3));
@@ -443,18 +453,36 @@ __global__ __launch_bounds__(NT) void db_update_m_kernel(float* __restrict__ M, 
   if (threadIdx.x == 0) rho_part[(long long)b * gridDim.x + blockIdx.x] = (float)((red[0] + red[1]) + (red[2] + red[3]));
 }
 
-// rows [r0, r0 + nr) x cols [c0, c0 + nc) of every matrix: dst <- src (different leading dimensions)
-__global__ __launch_bounds__(NT) void panel_copy_kernel(const float* __restrict__ src, long long sstride, int sld,
-                                                        float* __restrict__ dst, long long dstride, int dld, int nr, int nc,
-                                                        int skip0, int skip1, int skip_rows, const Ctrl* __restrict__ ctrl) {
+// The new row panel T = P A_k,: ([nr][np], nr rows from row k0 on) into the matrix, and the new column panel -A_:,k P from it: A_ik is the
+// transpose of A_ki, with the other sign where i has been swept and k has not, so -A_ik P is T_i^T for i < k and -T_i^T beyond.
+// One workgroup per 64 x 64 tile.  (A product of its own for the column panel and a copy of each: 2 x 2048^2, 16 outer blocks in a call,
+// 2 x 22 + 2 x 6 us per block, now 22 + 9.)
+__global__ __launch_bounds__(NT) void panels_kernel(const float* __restrict__ T, float* __restrict__ N, int np, int nr, int k0,
+                                                    const Ctrl* __restrict__ ctrl) {
   const int b = blockIdx.y;
   if (ctrl && ctrl[b].done) return;
-  const long long i = ((long long)blockIdx.x * NT + threadIdx.x) * 4;
-  if (i >= (long long)nr * nc) return;
-  const int r = (int)(i / nc), c = (int)(i % nc);
-  const int key = skip_rows ? r : c;
-  if (key >= skip0 && key < skip1) return;       // the pivot block itself is already in place
-  *(float4*)(dst + (long long)b * dstride + (long long)r * dld + c) = *(const float4*)(src + (long long)b * sstride + (long long)r * sld + c);
+  __shared__ float tile[BS][BS + 1];
+  const int tiles_c = np / BS, tr = blockIdx.x / tiles_c, c0 = (blockIdx.x % tiles_c) * BS;
+  if (c0 >= k0 && c0 < k0 + nr) return;          // the pivot block itself is already in place
+  const float sign = c0 < k0 ? 1.0f : -1.0f;
+  const float* src = T + ((long long)b * nr + tr * BS) * np + c0;
+  float* M = N + (long long)b * np * np;
+  const int r = threadIdx.x >> 4, c = (threadIdx.x & 15) * 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const f32x4 v = *(const f32x4*)(src + (long long)(r + 16 * q) * np + c);
+    *(f32x4*)(M + (long long)(k0 + tr * BS + r + 16 * q) * np + c0 + c) = v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[r + 16 * q][c + e] = sign * v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = tile[c + e][r + 16 * q];
+    *(f32x4*)(M + (long long)(c0 + r + 16 * q) * np + k0 + tr * BS + c) = v;
+  }
 }
 
 // Inverse of n x n SPD matrices by block Gauss-Jordan with pivots of 64, n a multiple of 64: from src to out, through
@@ -484,10 +512,10 @@ int outer_block(int np, int batch) {
 
 }  // namespace
 
-// pivot inverses, the second buffer of the elimination and, with outer blocks, the new row and column panels
+// pivot inverses, the second buffer of the elimination and, with outer blocks, the new row panel
 long long spd_inverse_scratch_floats(int np, int batch, int sel_batch) {
   const long long OB = outer_block(np, sel_batch), n = OB ? OB : np;
-  return (2ll * BS * BS + n * n + 2 * OB * np) * batch;
+  return (2ll * BS * BS + n * n + OB * np) * batch;
 }
 
 int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, hipStream_t s) {
@@ -509,8 +537,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
   }
   if (M != N) copy(M, N);
   float* Trow = tmp.p + tn * tn * batch;                  // [batch][OB][np]: P A_k,:
-  float* Ucol = Trow + (long long)batch * OB * np;        // [batch][np][OB]: -A_:,k P
-  const long long tstride = (long long)OB * np, ustride = (long long)np * OB;
+  const long long tstride = (long long)OB * np;
   for (int k = 0; k < np / OB; ++k) {
     float* Pk = N + (long long)k * OB * np + k * OB;
     float* rowk = N + (long long)k * OB * np;
@@ -534,16 +561,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
     u.sym = 1; u.sym_skew_bound = k * OB;
     rc = launch_gemm_f32(u, s);
     if (rc != PRISM_OK) return rc;
-    GemmDesc c = g;                                      // U = -A_:,k P
-    c.A = colk; c.strideA = per_mat; c.lda = np; c.B = Pk; c.strideB = per_mat; c.ldb = np;
-    c.C = Ucol; c.strideC = ustride; c.ldc = OB; c.M = np; c.N = OB; c.acc_neg = 1;
-    c.skip_m0 = k * OB; c.skip_m1 = (k + 1) * OB;
-    rc = launch_gemm_f32(c, s);
-    if (rc != PRISM_OK) return rc;
-    hipLaunchKernelGGL(panel_copy_kernel, dim3((unsigned)(((long long)OB * np / 4 + NT - 1) / NT), batch), dim3(NT), 0, s,
-                       Trow, tstride, np, rowk, per_mat, np, OB, np, k * OB, (k + 1) * OB, 0, ctrl);
-    hipLaunchKernelGGL(panel_copy_kernel, dim3((unsigned)(((long long)np * OB / 4 + NT - 1) / NT), batch), dim3(NT), 0, s,
-                       Ucol, ustride, OB, colk, per_mat, np, np, OB, k * OB, (k + 1) * OB, 1, ctrl);
+    hipLaunchKernelGGL(panels_kernel, dim3((unsigned)((OB / BS) * (np / BS)), batch), dim3(NT), 0, s, Trow, N, np, OB, k * OB, ctrl);
   }
   return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
 }

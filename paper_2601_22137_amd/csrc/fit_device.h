@@ -255,6 +255,14 @@ __device__ inline bool minimise(const double* c, int nc, double lo, double hi, d
     some = fabs(v) >= 1.0e-300;
   }
   if (__any(bad) || !__any(some)) return false;
+  if (deg == 2) {   // Chebyshev inverse
+    best = lo;
+    double bestv = horner(c, 2, lo);
+    const double x = -0.5 * c[1] / c[2];
+    if (c[2] != 0.0 && x >= lo && x <= hi && horner(c, 2, x) < bestv) { bestv = horner(c, 2, x); best = x; }
+    if (horner(c, 2, hi) < bestv) best = hi;
+    return true;
+  }
   if (deg == 4) {   // Newton-Schulz family, DB Newton
     best = minimise_quartic(c[0], c[1], c[2], c[3], c[4], lo, hi);
     return true;
@@ -440,10 +448,11 @@ __device__ void solve_body(const SolveArgs& a, int b, double* c_local = nullptr,
     // Slot 16 of the partials holds ||M_k N_k v - v||^2 for a probe vector v of +-1 entries, an
     // estimate of ||M_k N_k - I||_F^2: above 10 % relative the matrix stops as diverged, before the
     // update that would use N_k.
-    if (t == 0) {
+    if (t < 64) {
       double e2 = 0.0;
-      for (int gidx = 0; gidx < a.ngroups; ++gidx) e2 += a.cpart[((long long)b * a.ngroups + gidx) * MAXC + 16];
-      if (!(e2 <= 0.01 * (double)a.n)) {
+      for (int gidx = t; gidx < a.ngroups; gidx += 64) e2 += a.cpart[((long long)b * a.ngroups + gidx) * MAXC + 16];
+      e2 = wave_sum(e2);
+      if (t == 63 && !(e2 <= 0.01 * (double)a.n)) {
         ctl->status = PRISM_INFO_DIVERGED; ctl->iters = a.k; ctl->done = 1;
         coh_store<COH>(&info->status, PRISM_INFO_DIVERGED); coh_store<COH>(&info->iters, a.k);
         s_stop = 1;

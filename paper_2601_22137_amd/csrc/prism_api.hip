@@ -239,8 +239,8 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
     const long long el = (long long)P.Sp * P.ld;
     P.ngroups = el <= 4096 ? 1 : (int)(el / 4096 > 64 ? 64 : el / 4096);   // 1: done inside the solve kernel
     if (fn == PRISM_FN_SQRT_NEWTON) {   // the moments run over the n x n matrices themselves
-      const long long mm = (long long)P.Sp * P.Sp / 65536;
-      P.ngroups = mm < 1 ? 1 : (mm > 64 ? 64 : (int)mm);
+      const long long mm = (long long)P.Sp * P.Sp / 16384;   // 64 entries a thread (2 x 2048^2: 64 groups 39 us)
+      P.ngroups = mm < 1 ? 1 : (mm > 256 ? 256 : (int)mm);
     }
   }
   P.o_cpart = take(B * P.ngroups * 17 * sizeof(double));
