@@ -38,8 +38,7 @@ __global__ __launch_bounds__(64 * KW, !B16 && RB * NCH * LD >= 256 ? 1 : 2) void
   const int b = blockIdx.y;
   if (a.sv.ctrl[b].done) return;
   if (!fit_rows<B16, LD, RB, NCH, KW>(a, b, gridDim.y, blockIdx.x, gridDim.x, fit_lds)) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the partials of the others
-  solve_body(a.sv, b);
+  solve_body<true>(a.sv, b);
 }
 
 template <bool B16, int LD, int RB, int NCH, int KW>

@@ -809,8 +809,7 @@ __device__ __forceinline__ void fit_and_tiles(const FitArgs& f, int batch, int t
   u64* state = (u64*)(sync + SQUARE_STATE);
   if (step < G) {
     if (!fit_rows<B16, LD, RB, NCH, 4>(f, b, batch, step, G, (float*)smem)) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the partials of the others
-    solve_body(f.sv, b);
+    solve_body<true>(f.sv, b);
     __syncthreads();
     if (t == 0) {
       const Ctrl& c = f.sv.ctrl[b];
