@@ -48,7 +48,7 @@
  *     it) until prism_release_workspaces().  Exception: prism_run_grouped, and
  *     single-shape calls that the library splits into two half batches (an even
  *     batch >= 8 of matrices with min(m, n) >= 1024 and no caller workspace), run
- *     on four library-owned streams per device, each with a cached workspace of
+ *     on the caller's stream and three library-owned ones per device, each with a cached workspace of
  *     its own, whatever the caller's stream.  Such calls are enqueued one at a
  *     time (a process-wide lock) and are ordered after one another on those
  *     streams, so eager calls from different caller streams are safe but do not
