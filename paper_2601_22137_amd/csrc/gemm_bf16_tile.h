@@ -69,7 +69,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
   const unsigned short* A1 = g.A + (long long)b * g.strideA + (KMA ? (long long)m0 : (long long)m0 * g.lda);
   const unsigned short* Bb = g.B + (long long)b * g.strideB + (KMB ? (long long)n0 : (long long)n0 * g.ldb);
 
-  const int KT = g.K / BF_BK;
+  const int KT = g.K / BF_BK, lda = g.lda, ldb = g.ldb;   // values: not read again past the memory clobbers of the loop
 
   // Global -> LDS without passing through registers (global_load_lds_dwordx4): one wave
   // instruction moves 64 lanes x 16 bytes into 1 KiB of consecutive LDS = 16 rows of a slab.
@@ -85,27 +85,27 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
 #pragma unroll
     for (int it = 0; it < LDA; ++it) {
       const int k = (it * NW + wave) * (64 / URA) + lane / URA, c = (lane % URA) ^ (4 * (k & 3));
-      aoff[it] = (unsigned)(k * g.lda + c * 8) * 2u;
+      aoff[it] = (unsigned)(k * lda + c * 8) * 2u;
     }
   } else {
 #pragma unroll
-    for (int it = 0; it < LDA; ++it) aoff[it] = (unsigned)(((it * NW + wave) * 16 + 4 * lq + (lu >> 2)) * g.lda + (lu & 3) * 8) * 2u;
+    for (int it = 0; it < LDA; ++it) aoff[it] = (unsigned)(((it * NW + wave) * 16 + 4 * lq + (lu >> 2)) * lda + (lu & 3) * 8) * 2u;
   }
   if constexpr (KMB) {
     constexpr int URB = TN / 8;
 #pragma unroll
     for (int it = 0; it < LDB; ++it) {
       const int k = (it * NW + wave) * (64 / URB) + lane / URB, c = (lane % URB) ^ (4 * (k & 3));
-      boff[it] = (unsigned)(k * g.ldb + c * 8) * 2u;
+      boff[it] = (unsigned)(k * ldb + c * 8) * 2u;
     }
   } else {
 #pragma unroll
-    for (int it = 0; it < LDB; ++it) boff[it] = (unsigned)(((it * NW + wave) * 16 + 4 * lq + (lu >> 2)) * g.ldb + (lu & 3) * 8) * 2u;
+    for (int it = 0; it < LDB; ++it) boff[it] = (unsigned)(((it * NW + wave) * 16 + 4 * lq + (lu >> 2)) * ldb + (lu & 3) * 8) * 2u;
   }
   // load instruction u in [0, NL): first the LDA of A, then the LDB of B
   auto issue_load = [&](int kt, int slot, int u) {
-    const long long ka = KMA ? (long long)kt * BF_BK * g.lda : (long long)kt * BF_BK;
-    const long long kb = KMB ? (long long)kt * BF_BK * g.ldb : (long long)kt * BF_BK;
+    const long long ka = KMA ? (long long)kt * BF_BK * lda : (long long)kt * BF_BK;
+    const long long kb = KMB ? (long long)kt * BF_BK * ldb : (long long)kt * BF_BK;
     if (u < LDA) {
       unsigned char* dst = smem + slot * BUF_BYTES + wave * 1024 + u * (1024 * NW);
       __builtin_amdgcn_global_load_lds((gptr_t)((const char*)(A1 + ka) + aoff[u]), (lptr_t)dst, 16, 0, 0);
