@@ -790,22 +790,29 @@ __device__ __forceinline__ bool fit_rows(const FitArgs& a, int b, int batch, int
 // tiles keep their sums in registers and wait for the coefficient.  Per matrix `tiles` workgroups more than the fit has; which of the steps
 // one takes is decided by a counter, rows of the fit first: a tile waits for steps that were taken before it, by workgroups that
 // run, so nothing depends on workgroups being resident together.  (Rows wait for each other bounded, see fit_rows.)
-// Words of FitArgs::sync: counter (every launch on a live matrix takes as many numbers as it has steps), then iteration + 1 and
+// Words of FitArgs::sync: counter (every launch that leaves the matrix live takes as many numbers as it has steps), then iteration + 1 and
 // beside it the bits of alpha or SQUARE_STOPPED.
 constexpr int SQUARE_TICKET = FIT_MAX_CLUSTER + 32, SQUARE_STATE = FIT_MAX_CLUSTER + 64;
 constexpr unsigned SQUARE_STOPPED = 0xFFFFFFFFu;
 template <bool B16, int LD, int RB, int NCH, class TILE>
 __device__ __forceinline__ void fit_and_tiles(const FitArgs& f, int batch, int tiles, unsigned char* smem, TILE tile) {
-  __shared__ unsigned s_step;
+  __shared__ int s_step;
   __shared__ u64 s_state;
   const int t = threadIdx.x, G = f.sv.rows / (16 * RB);
   // the rows of all matrices are dispatched before the tiles
   const int b = (int)blockIdx.x < G * batch ? blockIdx.x / G : (blockIdx.x - G * batch) / tiles;
-  if (f.sv.ctrl[b].done) return;
   unsigned* sync = f.sync + (long long)b * FIT_SYNC_WORDS;
-  if (t == 0) s_step = __hip_atomic_fetch_add(sync + SQUARE_TICKET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) % (unsigned)(G + tiles);
+  // Whether the matrix is done is one thread's to see, for the whole workgroup: whoever solves sets it while others of this launch
+  // may only be starting, and waves that look for themselves could part ways (those that stay would find no step in LDS).
+  // The step is taken in the same breath, wanted or not: nobody counts on the numbers of a matrix that is done.
+  if (t == 0) {
+    const unsigned ticket = __hip_atomic_fetch_add(sync + SQUARE_TICKET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int done = coh_load<true>(&f.sv.ctrl[b].done);
+    s_step = done ? -1 : (int)(ticket % (unsigned)(G + tiles));
+  }
   __syncthreads();
-  const int step = __builtin_amdgcn_readfirstlane((int)s_step);
+  const int step = __builtin_amdgcn_readfirstlane(s_step);
+  if (step < 0) return;
   u64* state = (u64*)(sync + SQUARE_STATE);
   if (step < G) {
     if (!fit_rows<B16, LD, RB, NCH, 4>(f, b, batch, step, G, (float*)smem)) return;
