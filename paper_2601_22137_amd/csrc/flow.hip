@@ -32,12 +32,11 @@ enum { FLOW_GRAM, FLOW_FULL, FLOW_ROOT };
 template <int FAM, int LD, int NCH>
 __global__ __launch_bounds__(NT, 2) void flow_kernel(FlowArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  __shared__ unsigned s_ticket;
+  __shared__ int s_ticket;
   __shared__ u64 s_state;
   __shared__ Ctrl s_ctl;
   constexpr int CTL_WORDS = (int)(sizeof(Ctrl) / 4);
   const int b = blockIdx.x / a.cluster, batch = gridDim.x / a.cluster, t = threadIdx.x;
-  if (a.fit.sv.ctrl[b].done) return;
   unsigned* sync = a.fit.sync + (long long)b * FIT_SYNC_WORDS;
   unsigned* count = sync + FLOW_STATE;
   const int max_iters = a.fit.sv.max_iters, G = a.fit.sv.rows / 16;
@@ -68,7 +67,7 @@ __global__ __launch_bounds__(NT, 2) void flow_kernel(FlowArgs a) {
     alpha = __uint_as_float(bits);
     return bits != FLOW_STOPPED;
   };
-  auto take = [&]() { return __hip_atomic_fetch_add(sync + FLOW_TICKET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto take = [&]() { return (int)__hip_atomic_fetch_add(sync + FLOW_TICKET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   // The step is complete: its stores have reached memory.
   auto finish = [&]() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -76,10 +75,17 @@ __global__ __launch_bounds__(NT, 2) void flow_kernel(FlowArgs a) {
     if (t == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
 
-  if (t == 0) s_ticket = take();
+  // Whether the matrix is done (never begun: zero or not finite; or stopped while this workgroup had no place on the chip) is one
+  // thread's to see, for the whole workgroup: whoever solves sets it in this launch, and waves that look for themselves could part
+  // ways.  The number is taken in the same breath: nobody counts on those of a matrix that is done.
+  if (t == 0) {
+    const int first = take();
+    s_ticket = coh_load<true>(&a.fit.sv.ctrl[b].done) ? -1 : first;
+  }
   __syncthreads();
   for (;;) {
-    const int ticket = __builtin_amdgcn_readfirstlane((int)s_ticket);
+    const int ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+    if (ticket < 0) return;
     int k, base;
     if (ticket < t1) { k = ticket / na; base = k * na; }
     else { k = (ticket - t1) / nb; base = t1 + k * nb; k += a.first_fit; }
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(NT, 2) void flow_kernel(FlowArgs a) {
     g.R32out = (float*)((char*)g.R32out + next);
     const bool beside = op >= a.residual && a.start[op] < 0;
     if (!wait_for(op < a.residual ? base : (beside ? base + nres : known + a.start[op]))) return;
-    unsigned upcoming = 0;
+    int upcoming = 0;
     if (t == 0) upcoming = take();                                // on its way while this tile is computed
     const int tile = a.tile[op], tiles_m = g.M / tile, tiles_n = g.N / tile;
     int tm, tn, per_mat;

@@ -31,11 +31,11 @@ def _body(name, start):
     raise AssertionError("unbalanced braces")
 
 
-@pytest.mark.parametrize("name,start", [("fit_device.h", "void fit_and_tiles(")])
+@pytest.mark.parametrize("name,start", [("fit_device.h", "void fit_and_tiles("), ("flow.hip", "void flow_kernel(")])
 def test_done_is_read_by_one_thread(name, start):
     body = _body(name, start)
     assert not re.search(r"if \([^;{]*\bdone\s*\)\s*return", body)
-    assert "done" in body.split("__syncthreads();")[0]      # thread 0 has looked before the first barrier
+    assert re.search(r"if \(t == 0\) \{[^}]*\bdone\b", body)      # thread 0 looks
 
 
 @pytest.fixture(scope="module")
@@ -73,3 +73,20 @@ def test_square_beside_the_fit(prism, n, batch):
     x = torch.from_numpy(np.tile(A, ((batch + 2) // 3, 1, 1))[:batch].copy().view(np.int16)).cuda().view(torch.bfloat16)
     rec = _on_streams(lambda y: prism.polar(y, 5, 20, 16, SEED, 2e-2), x)
     assert len(set(rec["iters"])) > 1 and (rec["status"] == prism.INFO_CONVERGED).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,batch", [(256, 16), (320, 6), (576, 3)])
+def test_all_iterations_in_one_launch(prism, n, batch):
+    """Three calls at once of about one workgroup per CU each, matrices that stop at different iterations and one that never starts."""
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((batch, n, n))
+    A = (A + A.transpose(0, 2, 1)) / 2.0
+    for b in range(batch):                          # condition numbers from 1 to 100
+        w, v = np.linalg.eigh(A[b])
+        A[b] = (v * (np.where(w < 0.0, -1.0, 1.0) * 10.0 ** (-2.0 * b / batch * rng.random(n)))) @ v.T
+    A = A.astype(np.float32)
+    A[batch - 1] = 0.0
+    rec = _on_streams(lambda y: prism.sign(y, 5, 40, 16, SEED, 1e-5), torch.from_numpy(A).cuda())
+    assert len(set(rec["iters"][:-1])) > 1 and (rec["status"][:-1] == prism.INFO_CONVERGED).all()
+    assert rec["status"][-1] == prism.INFO_ZERO
