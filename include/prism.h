@@ -48,10 +48,11 @@
  *     it) until prism_release_workspaces().  Exception: prism_run_grouped, and
  *     single-shape calls that the library splits into two half batches (an even
  *     batch >= 8 of matrices with min(m, n) >= 1024 and no caller workspace), run
- *     on the caller's stream and three library-owned ones per device, each with a cached workspace of
- *     its own, whatever the caller's stream.  Such calls are enqueued one at a
- *     time (a process-wide lock) and are ordered after one another on those
- *     streams, so eager calls from different caller streams are safe but do not
+ *     on the caller's stream and three library-owned ones per device.  Their four
+ *     cached workspaces per device belong to these parts of a call, whatever the
+ *     caller's stream: a call from another stream allocates nothing.  Such calls are enqueued one at a
+ *     time (a process-wide lock) and each part is ordered after the same part of the call before,
+ *     so eager calls from different caller streams are safe but do not
  *     overlap; HIP graphs captured from such calls share those workspaces and
  *     must not be replayed concurrently with each other or with another such
  *     call.  Pass a workspace through prism_options to keep a call on its own
@@ -259,12 +260,14 @@ int prism_sqrt_newton_ex(void* a, void* inv_out, int batch, int m, int n, prism_
  *     whole call, and the Gram product and the update take all shapes in one launch each (the
  *     kernel maps its workgroup index to group, matrix and tile).  When every group's batch is a
  *     multiple of 4 (of 2) the sequence is issued for the quarters (halves) of every group on
- *     internal streams, so that the latency-bound steps of one part run beside the products of
+ *     streams of their own (the caller's and up to three internal ones), so that the latency-bound steps of one part run beside the products of
  *     another.
- *   - any other combination runs each group as its own call on one of four internal streams.
+ *   - any other combination runs each group as its own call on one of four streams: the caller's and
+ *     three internal ones.
  * The internal streams have default priority and fork from and join back into `stream` (event
  * record / wait only: the call stays asynchronous and capturable once the library's workspaces
- * exist, i.e. after one eager call with the same arguments on the same stream).  Every group is
+ * exist, i.e. after one eager call with the same arguments; calls that stay on the caller's stream - a single
+ * group, or one launch sequence that is not issued in parts - need it on the same stream).  Every group is
  * computed exactly as by its own single-group call: same kernels, same bits (the residuals in the reports of bf16
  * calls agree to rounding: their partial sums follow the tiles of the launch). */
 typedef struct {
@@ -276,8 +279,8 @@ typedef struct {
 
 /* fn selects the iteration (PRISM_FN_*); root_p is used by PRISM_FN_INV_ROOT only, degree by the
  * Newton-Schulz family, sketch_dim by all but PRISM_FN_SQRT_NEWTON (where non-zero means "fit").
- * opt may be NULL; its workspace and info fields must be NULL (each internal stream keeps its own
- * cached workspace).  Returns the first error of any group; nothing is enqueued for the groups
+ * opt may be NULL; its workspace and info fields must be NULL (the parts of a call have cached workspaces,
+ * see above).  Returns the first error of any group; nothing is enqueued for the groups
  * after it. */
 int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int root_p, prism_dtype dt,
                       int degree, int max_iters, int sketch_dim, uint64_t seed, double tol,

@@ -289,14 +289,14 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   return PRISM_OK;
 }
 
-// Grow-only workspace per (device, stream).  A block that has become too small is kept until
+// Grow-only workspace per (device, stream or other owner).  A block that has become too small is kept until
 // prism_release_workspaces(): work enqueued earlier, and HIP graphs captured from earlier calls,
 // still hold its address.
 struct Cached { void* ptr = nullptr; size_t bytes = 0; std::vector<void*> retired; };
 std::mutex g_mu;
-std::map<std::pair<int, void*>, Cached> g_cache;
+std::map<std::pair<int, const void*>, Cached> g_cache;
 
-int get_workspace(size_t bytes, hipStream_t stream, const prism_options* opt, char** out) {
+int get_workspace(size_t bytes, const void* owner, const prism_options* opt, char** out) {
   if (opt && opt->workspace) {
     if (opt->workspace_bytes < bytes || ((uintptr_t)opt->workspace & 255)) return PRISM_ENOMEM;
     *out = (char*)opt->workspace;
@@ -305,7 +305,7 @@ int get_workspace(size_t bytes, hipStream_t stream, const prism_options* opt, ch
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { set_last_error("hipGetDevice failed"); return PRISM_EHIP; }
   std::lock_guard<std::mutex> lock(g_mu);
-  Cached& c = g_cache[std::make_pair(dev, (void*)stream)];
+  Cached& c = g_cache[std::make_pair(dev, owner)];
   if (c.bytes < bytes) {
     void* fresh = nullptr;
     if (hipMalloc(&fresh, bytes) != hipSuccess) {
@@ -1094,7 +1094,7 @@ void bf16_prep_final(const Plan& P, const Run::XGroup& x, PrepArgs& pa, FinalArg
 }
 
 int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int dt, int degree, int max_iters,
-        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, int sel_batch = 0) {
+        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, int sel_batch = 0, const void* owner = nullptr) {
   set_last_error("");
   const bool empty = batch == 0 || m == 0 || n == 0;   // nothing to compute; the arguments are still checked
   if (batch < 0 || m < 0 || n < 0) return PRISM_EINVAL;
@@ -1115,7 +1115,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
     if (rc != PRISM_OK) return rc;
   }
   r.s = (hipStream_t)stream;
-  rc = get_workspace(r.P.total, r.s, opt, &r.ws);
+  rc = get_workspace(r.P.total, owner ? owner : stream, opt, &r.ws);
   if (rc != PRISM_OK) return rc;
   const Plan& P = r.P;
   r.ctrl = r.at<Ctrl>(P.o_ctrl);
@@ -1193,7 +1193,8 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
 // the kernels its own single-group call would pick.  Returns PRISM_EUNSUPPORTED (nothing enqueued)
 // when the groups do not fit this form; the caller then takes the per-group path.
 int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, int max_iters, int sketch_dim, uint64_t seed,
-                          double tol, void* stream, const prism_options* opt, int batch_scale = 1, const void* const* const* from = nullptr) {
+                          double tol, void* stream, const prism_options* opt, int batch_scale = 1, const void* const* const* from = nullptr,
+                          const void* owner = nullptr) {
   static const int off = ab_switch("PRISM_NO_SHARED_SHAPES");
   if (off || ngroups < 2 || ngroups > BF16_MAX_GROUPS) return PRISM_EUNSUPPORTED;
   if (max_iters < 0 || max_iters > PRISM_MAX_ITERS || !(tol == tol)) return PRISM_EINVAL;
@@ -1258,7 +1259,7 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
   }
   P.total = off_bytes;
   r.s = (hipStream_t)stream;
-  rc = get_workspace(P.total, r.s, nullptr, &r.ws);
+  rc = get_workspace(P.total, owner ? owner : stream, nullptr, &r.ws);
   if (rc != PRISM_OK) return rc;
   r.ctrl = r.at<Ctrl>(P.o_ctrl);
   r.info = r.at<prism_info>(P.o_info);
@@ -1347,11 +1348,29 @@ int run_polar_bf16_shapes(const prism_group* groups, int ngroups, int degree, in
 // Streams of the grouped call: the caller's and three of the library's own, per device, created on first use (default
 // priority).  A process has four hardware queues by default; with four streams of its own beside the caller's, which then only
 // waits, two of them shared a queue and ran one after the other.
+// The part on the caller's stream has a workspace of its own too (its owner is the Fork), so that a call from another stream allocates
+// nothing; such parts are ordered after one another by an event, as the others are by their streams.
 constexpr int GROUP_STREAMS = 4;
 struct Fork {
   hipStream_t streams[GROUP_STREAMS - 1] = {};
   hipEvent_t forked = nullptr, joined[GROUP_STREAMS - 1] = {};
+  hipEvent_t own_part = nullptr;   // end of the latest eager part on a caller's stream
+  bool own_recorded = false;
   bool ready = false;
+
+  // Before and after the part on the caller's stream.  A call under capture leaves the event alone: what it waits for would lie
+  // outside the graph (graphs share the workspaces and are the caller's to order).
+  static bool capturing(hipStream_t user) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(user, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
+  }
+  bool begin_own(hipStream_t user) { return !own_recorded || capturing(user) || hipStreamWaitEvent(user, own_part, 0) == hipSuccess; }
+  bool end_own(hipStream_t user) {
+    if (capturing(user)) return true;
+    own_recorded = hipEventRecord(own_part, user) == hipSuccess;
+    return own_recorded;
+  }
 };
 std::mutex g_fork_mu;
 std::map<int, Fork> g_forks;
@@ -1363,6 +1382,7 @@ int get_fork(Fork** out) {
   Fork& f = g_forks[dev];
   if (!f.ready) {
     if (hipEventCreateWithFlags(&f.forked, hipEventDisableTiming) != hipSuccess) return PRISM_EHIP;
+    if (hipEventCreateWithFlags(&f.own_part, hipEventDisableTiming) != hipSuccess) return PRISM_EHIP;
     for (int i = 0; i < GROUP_STREAMS - 1; ++i) {
       if (hipStreamCreateWithFlags(&f.streams[i], hipStreamNonBlocking) != hipSuccess) return PRISM_EHIP;
       if (hipEventCreateWithFlags(&f.joined[i], hipEventDisableTiming) != hipSuccess) return PRISM_EHIP;
@@ -1456,15 +1476,23 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
       }
       rc = get_fork(&f);
       if (rc != PRISM_OK) return rc;
-      if (hipEventRecord(f->forked, user) != hipSuccess) { (void)hipGetLastError(); set_last_error("hipEventRecord failed"); return PRISM_EHIP; }
+      if (!f->begin_own(user) || hipEventRecord(f->forked, user) != hipSuccess) {
+        (void)hipGetLastError();
+        set_last_error("hipEventRecord failed");
+        return PRISM_EHIP;
+      }
       int forked = 0, first_error = PRISM_OK;
       for (; forked < NP - 1; ++forked)
         if (hipStreamWaitEvent(f->streams[forked], f->forked, 0) != hipSuccess) { first_error = PRISM_EHIP; break; }
       bool unsupported = false;
       for (int h = 0; h < NP && first_error == PRISM_OK; ++h) {
         first_error = run_polar_bf16_shapes(half[h], ngroups, degree, max_iters, sketch_dim, seed, tol, h ? f->streams[h - 1] : user, opt, NP,
-                                            from ? half_from[h] : nullptr);
+                                            from ? half_from[h] : nullptr, h ? nullptr : f);
         if (h == 0 && first_error == PRISM_EUNSUPPORTED) { unsupported = true; first_error = PRISM_OK; break; }   // nothing was enqueued
+      }
+      if (!f->end_own(user)) {
+        (void)hipGetLastError();
+        if (first_error == PRISM_OK) { set_last_error("hipEventRecord failed"); first_error = PRISM_EHIP; }
       }
       for (int i = 0; i < forked; ++i) {
         if (hipEventRecord(f->joined[i], f->streams[i]) != hipSuccess || hipStreamWaitEvent(user, f->joined[i], 0) != hipSuccess) {
@@ -1500,7 +1528,7 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
   }
   std::stable_sort(order.begin(), order.end(), [](const std::pair<double, int>& x, const std::pair<double, int>& y) { return x.first > y.first; });
   // nothing is forked before this record succeeds
-  if (hipEventRecord(f->forked, user) != hipSuccess) { (void)hipGetLastError(); set_last_error("hipEventRecord failed"); return PRISM_EHIP; }
+  if (!f->begin_own(user) || hipEventRecord(f->forked, user) != hipSuccess) { (void)hipGetLastError(); set_last_error("hipEventRecord failed"); return PRISM_EHIP; }
   int first_error = PRISM_OK;
   int forked = 0;   // internal streams that wait for the caller's stream: exactly these are joined again below
   for (; forked < used - 1; ++forked)
@@ -1517,7 +1545,11 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
     o.flags |= PRISM_FLAG_SHARED_GPU;
     first_error = run(fn, groups[gi].x, groups[gi].inv_out, root_p, groups[gi].batch, groups[gi].m, groups[gi].n, dt,
                       degree, max_iters, sketch_dim, seed, tol, at ? f->streams[at - 1] : user, &o,
-                      from_auto_split ? ngroups * groups[gi].batch : 0);
+                      from_auto_split ? ngroups * groups[gi].batch : 0, at ? nullptr : f);
+  }
+  if (!f->end_own(user)) {
+    (void)hipGetLastError();
+    if (first_error == PRISM_OK) { set_last_error("hipEventRecord failed"); first_error = PRISM_EHIP; }
   }
   // Join every forked stream back into the caller's, on every exit: after an error too, and past a
   // failing record or wait of one stream (the others are still joined, so that no forked work is
@@ -1735,7 +1767,7 @@ int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream
   char* ws = nullptr;
   const size_t bytes = (size_t)spd_inverse_scratch_floats(n, batch, batch) * 4;
   if (bytes) {
-    const int rc = get_workspace(bytes, (hipStream_t)stream, nullptr, &ws);
+    const int rc = get_workspace(bytes, stream, nullptr, &ws);
     if (rc != PRISM_OK) return rc;
   }
   return launch_spd_inverse(a, out, n, batch, batch, nullptr, (float*)ws, (hipStream_t)stream);

@@ -329,3 +329,47 @@ def test_sources_where_they_are(prism, shapes, odd):
         assert np.array_equal(a.read()["status"], b.read()["status"])
     for t, b in zip(mats, before):
         assert torch.equal(t.view(torch.int16), b.view(torch.int16))
+
+
+def test_calls_in_parts_from_other_streams(prism):
+    """Grouped calls in quarters, mixed groups, and a batch that the library halves, from streams that never made such a call: nothing is
+    allocated, calls that follow each other on different streams without a wait keep out of each other's workspaces, and the
+    first call on a stream may be the captured one."""
+    plain = prism.FLAG_BF16_PLAIN_ITERATE
+    quarters = [_bf16(W.c2_muon_group(i, batch=8, scale=4)) for i in range(4)]
+    mixed = [torch.from_numpy(W.c4_shampoo_spd(n=n, batch=1, data_seed=n)).cuda() for n in (40, 130, 200, 300, 80)]
+    halves = [_bf16(np.repeat(W.c3_polar_large(n=1024, batch=1, sigma_decades=1.0), 8, axis=0))]
+    kinds = [(quarters, lambda xs: prism.run_grouped(prism.FN_POLAR, xs, 5, 5, 16, SEED, 0.0, flags=plain)),
+             (mixed, lambda xs: prism.run_grouped(prism.FN_INV_ROOT, xs, 3, 40, 16, SEED, 1e-5, root_p=4)),
+             (halves, lambda xs: prism.polar(xs[0], 5, 5, 16, SEED, 0.0))]
+    for src, call in kinds:
+        want = [t.clone() for t in src]
+        call(want)
+        torch.cuda.synchronize()
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        got = [[t.clone() for t in src] for _ in streams]
+        call([t.clone() for t in src])              # torch's allocator has the reports' memory
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for s, xs in zip(streams, got):
+            with torch.cuda.stream(s):
+                call(xs)
+        torch.cuda.synchronize()
+        assert free - torch.cuda.mem_get_info()[0] < (16 << 20)     # (torch: a segment of 2 MiB per stream for the reports)
+        for xs in got:
+            for x, w in zip(xs, want):
+                assert torch.equal(x.view(torch.int16), w.view(torch.int16))
+        side, graph, xs = torch.cuda.Stream(), torch.cuda.CUDAGraph(), [t.clone() for t in src]
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            call(xs)
+        for _ in range(3):
+            with torch.cuda.stream(side):
+                for x, t in zip(xs, src):
+                    x.copy_(t)
+                graph.replay()
+                side.synchronize()
+            call([t.clone() for t in src])          # eager work between the replays
+            torch.cuda.synchronize()
+            for x, w in zip(xs, want):
+                assert torch.equal(x.view(torch.int16), w.view(torch.int16))
