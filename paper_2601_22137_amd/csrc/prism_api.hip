@@ -1093,11 +1093,10 @@ void bf16_prep_final(const Plan& P, const Run::XGroup& x, PrepArgs& pa, FinalArg
   (void)P;
 }
 
-int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int dt, int degree, int max_iters,
-        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, int sel_batch = 0, const void* owner = nullptr) {
-  set_last_error("");
-  const bool empty = batch == 0 || m == 0 || n == 0;   // nothing to compute; the arguments are still checked
+// The arguments of a call on one array, but for those that make_plan looks at
+int check_arguments(int fn, const void* a, const void* inv_out, int batch, int m, int n, int max_iters, double tol, const prism_options* opt) {
   if (batch < 0 || m < 0 || n < 0) return PRISM_EINVAL;
+  const bool empty = batch == 0 || m == 0 || n == 0;
   if (!empty && !a) return PRISM_EINVAL;
   if (!empty && (fn == PRISM_FN_SQRT || fn == PRISM_FN_SQRT_NEWTON) && !inv_out) return PRISM_EINVAL;
   if (max_iters < 0 || max_iters > PRISM_MAX_ITERS) return PRISM_EINVAL;
@@ -1105,10 +1104,19 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   if (opt && opt->warm_iters < 0) return PRISM_EINVAL;
   if (opt && (opt->schedule_len < 0 || opt->schedule_len > PRISM_MAX_ITERS || (opt->schedule_len > 0 && !opt->alpha_schedule)))
     return PRISM_EINVAL;
+  return PRISM_OK;
+}
+
+int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int dt, int degree, int max_iters,
+        int sketch_dim, uint64_t seed, double tol, void* stream, const prism_options* opt, int sel_batch = 0, const void* owner = nullptr) {
+  set_last_error("");
+  const bool empty = batch == 0 || m == 0 || n == 0;   // nothing to compute; the arguments are still checked
+  int rc = check_arguments(fn, a, inv_out, batch, m, n, max_iters, tol, opt);
+  if (rc != PRISM_OK) return rc;
   Run r;
   if (empty) return make_plan(r.P, fn, 1, m ? m : 1, n ? n : 1, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u);
   if (sel_batch == 0) sel_batch = batch;
-  int rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u, false, sel_batch);
+  rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u, false, sel_batch);
   if (rc != PRISM_OK) return rc;
   if ((r.P.ksplit || r.P.ring) && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
     rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW, false, sel_batch);
@@ -1404,16 +1412,21 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
     for (int b = 0; b < groups[g].batch; ++b)
       if (!from[g][b] && groups[g].m > 0 && groups[g].n > 0) return PRISM_EINVAL;
   }
-  // matrices with addresses of their own, for a path that takes them one behind the other only
+  // matrices with addresses of their own, for a path that takes them one behind the other only.  A call that will be refused,
+  // for whichever group, copies nothing.
   auto gather = [&]() -> int {
     if (!from) return PRISM_OK;
     for (int g = 0; g < ngroups; ++g) {
       const prism_group& q = groups[g];
-      if (q.batch <= 0 || q.m <= 0 || q.n <= 0) continue;
+      const bool empty = q.batch == 0 || q.m == 0 || q.n == 0;
       Plan P;
-      if (!q.x) return PRISM_EINVAL;
-      CHECK_LAUNCH(make_plan(P, fn, q.batch, q.m, q.n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u));   // a call that will be refused copies nothing
-      launch_gather(q.x, from[g], q.batch, (size_t)q.m * q.n * (dt == PRISM_BF16 ? 2 : 4), (hipStream_t)stream);
+      CHECK_LAUNCH(check_arguments(fn, q.x, q.inv_out, q.batch, q.m, q.n, max_iters, tol, opt));
+      CHECK_LAUNCH(make_plan(P, fn, empty ? 1 : q.batch, q.m ? q.m : 1, q.n ? q.n : 1, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u));
+    }
+    for (int g = 0; g < ngroups; ++g) {
+      const prism_group& q = groups[g];
+      if (q.batch > 0 && q.m > 0 && q.n > 0)
+        launch_gather(q.x, from[g], q.batch, (size_t)q.m * q.n * (dt == PRISM_BF16 ? 2 : 4), (hipStream_t)stream);
     }
     from = nullptr;
     return check_hip();

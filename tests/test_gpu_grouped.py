@@ -373,3 +373,18 @@ def test_calls_in_parts_from_other_streams(prism):
             torch.cuda.synchronize()
             for x, w in zip(xs, want):
                 assert torch.equal(x.view(torch.int16), w.view(torch.int16))
+
+
+def test_sources_of_a_refused_call_are_not_copied(prism):
+    """The results' arrays of a call that is refused, for its arguments or for one of its groups, keep what they hold."""
+    src = [torch.full((40, 30), 2.0, device="cuda"), torch.full((50, 50), 3.0, device="cuda")]
+    out = [torch.full((1, 40, 30), 7.0, device="cuda"), torch.full((1, 50, 50), 7.0, device="cuda")]
+    sources = [[t] for t in src]
+    for fn, args, kw in [(prism.FN_POLAR, (5, 65, 8, SEED, 1e-5), {}), (prism.FN_POLAR, (5, 10, 8, SEED, float("nan")), {}),
+                         (prism.FN_POLAR, (5, 10, 8, SEED, 1e-5), {"warm_iters": -1}), (prism.FN_POLAR, (4, 10, 8, SEED, 1e-5), {}),
+                         (prism.FN_INV_ROOT, (3, 10, 8, SEED, 1e-5), {"root_p": 2})]:
+        for order in ((0, 1), (1, 0)):              # inverse root: the second or the first group is not square
+            with pytest.raises(prism.PrismError):
+                prism.run_grouped(fn, [out[i] for i in order], *args, sources=[sources[i] for i in order], **kw)
+            torch.cuda.synchronize()
+            assert bool((out[0] == 7.0).all()) and bool((out[1] == 7.0).all())
