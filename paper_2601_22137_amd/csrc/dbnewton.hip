@@ -44,8 +44,11 @@ template <int L> __device__ inline double from_lane(double v) {   // uniform
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
-// 1 / x, x finite and not 0 (else not a number): the hardware's approximation (2^-24) and two Newton steps, to an ulp
+// 1 / x, the same in all lanes: the hardware's approximation (2^-24) and two Newton steps, to an ulp.  Where those would leave the
+// range of normal numbers, an infinite or a vanishing pivot among them, by division (a scalar branch).
 __device__ inline double reciprocal(double x) {
+  const unsigned exponent = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 52) & 0x7FFu;
+  if (exponent - 24u > 2000u) return 1.0 / x;
   double r = __builtin_amdgcn_rcp(x);
   r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
   return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);

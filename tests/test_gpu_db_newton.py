@@ -147,3 +147,13 @@ def test_sqrt_newton_stops_when_the_fp32_inverse_is_worthless(prism, fit):
     rx, ry, oinfo = O.sqrt_db_newton(A[1], 40, 1e-5, fit=fit)
     assert info[1]["status"] == prism.INFO_CONVERGED and info[1]["iters"] == oinfo["iters"]
     assert _rel(x.cpu().numpy()[1], rx) <= 1e-5 and _rel(inv.cpu().numpy()[1], ry) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [64, 192])
+def test_spd_inverse_pivots_at_the_ends_of_the_range(prism, n):
+    """Diagonal matrices: every reciprocal to the last bit of fp32, that of an infinite pivot 0, as division has it."""
+    d = (10.0 ** np.random.default_rng(n).uniform(-37.0, 37.0, n)).astype(np.float32)
+    d[[0, 17, n - 1]] = np.inf
+    d[[5, n - 2]] = np.float32(2.0 ** -126), np.float32(3.0e38)
+    out = prism.spd_inverse(torch.from_numpy(np.diag(d)[None].copy()).cuda()).cpu().numpy()[0]
+    assert np.array_equal(out, np.diag((1.0 / d.astype(np.float64)).astype(np.float32)))
