@@ -30,7 +30,7 @@ def muon_orthogonalize(grads, degree=5, iters=5, sketch_dim=16, seed=22137, warm
     # stacking 64 gradients of width 768 takes 0.2 ms of a call of 3
     sources = None
     if all(type(g) in (torch.Tensor, torch.nn.Parameter) and g.dtype == torch.bfloat16 and g.is_cuda and g.dim() == 2 and g.is_contiguous()
-           and not (g.requires_grad and torch.is_grad_enabled()) and g.device == grads[0].device for g in grads):
+           and not g.is_neg() and not (g.requires_grad and torch.is_grad_enabled()) and g.device == grads[0].device for g in grads):
         sources = [[grads[i] for i in idx] for idx in groups.values()]
         stacked = [torch.empty((len(ts),) + tuple(ts[0].shape), dtype=ts[0].dtype, device=ts[0].device) for ts in sources]
     else:

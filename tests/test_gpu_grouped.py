@@ -388,3 +388,14 @@ def test_sources_of_a_refused_call_are_not_copied(prism):
                 prism.run_grouped(fn, [out[i] for i in order], *args, sources=[sources[i] for i in order], **kw)
             torch.cuda.synchronize()
             assert bool((out[0] == 7.0).all()) and bool((out[1] == 7.0).all())
+
+
+def test_negative_views_among_the_gradients(prism):
+    """A tensor whose values are those in memory with the other sign (a lazy negation) is not read where it is."""
+    from paper_2601_22137_amd import optim
+    rng = np.random.default_rng(11)
+    grads = [torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda().to(torch.bfloat16) for s in ((96, 64), (64, 96), (96, 64))]
+    want = optim.muon_orthogonalize([grads[0], -grads[1], grads[2]])
+    got = optim.muon_orthogonalize([grads[0], torch._neg_view(grads[1]), grads[2]])
+    for w, o in zip(want, got):
+        assert torch.equal(w, o)
