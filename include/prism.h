@@ -348,9 +348,9 @@ int prism_gemm_bf16_nt(const uint16_t* A, const uint16_t* B, float* C, int batch
  * bracketed by a HIP event pair on the caller's stream.  prism_profile_enable(on) also discards
  * what was recorded so far.  prism_profile_collect waits for the recorded events and returns the
  * summed milliseconds and the launch counts per kernel kind (host arrays of PRISM_PROFILE_KINDS
- * entries; nkinds >= PRISM_PROFILE_KINDS).  Meant for a single benchmarking thread; calls from
+ * entries; nkinds >= PRISM_PROFILE_KINDS, or 20: without the kinds that came after those).  Meant for a single benchmarking thread; calls from
  * other threads while it is enabled are recorded too (the record list is locked). */
-#define PRISM_PROFILE_KINDS 20
+#define PRISM_PROFILE_KINDS 23
 int prism_profile_enable(int on);
 int prism_profile_collect(double* ms_by_kind, long long* launches_by_kind, int nkinds);
 

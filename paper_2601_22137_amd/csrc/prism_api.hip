@@ -544,7 +544,7 @@ int run_flow(const Run& r, const FlowOp* ops, int nops, bool residual, const flo
   a.first_fit = P.p_s == 0 || r.first_fit > r.max_iters ? r.max_iters : r.first_fit;
   a.warm = r.warm; a.sched_len = r.sched_len; a.p_s = P.p_s;
   for (int i = 0; i < r.sched_len; ++i) a.sched[i] = r.sched[i];
-  ProfScope ps(PK_F32_APPLY, r.s);
+  ProfScope ps(PK_FLOW, r.s);
   return launch_flow(a, P.batch, r.s);
 }
 
@@ -566,7 +566,7 @@ int run_small(const Run& r, float* x) {
   }
   SmallRootArgs a = {};
   fill(a);
-  ProfScope ps(PK_F32_APPLY, r.s);
+  ProfScope ps(PK_SMALL_ROOT, r.s);
   return launch_small_root(a, P.batch, r.s);
 }
 
@@ -786,7 +786,7 @@ int run_polar_bf16(Run& r) {
     static const int no_square = ab_switch("PRISM_NO_FIT_SQUARE");
     if (!no_square && P.d == 2 && Tq.m == 128 && Tq.n == 128 && chain_b && r.fit_needed(k) && r.fused() &&
         fit_square_supported(r.fit_args(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd))) {
-      ProfScope ps(PK_BF16_POLYQ, r.s);
+      ProfScope ps(PK_FIT_SQUARE, r.s);
       CHECK_LAUNCH(launch_fit_square(r.fit_args(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd), q, P.batch, r.s));
     } else {
       CHECK_LAUNCH(r.fit(k, nparts, R, fit_b, fit_d, fit_sd, fit_ldd));
@@ -1670,13 +1670,14 @@ int prism_profile_enable(int on) {
 }
 
 int prism_profile_collect(double* ms_by_kind, long long* launches_by_kind, int nkinds) {
-  if (!ms_by_kind || !launches_by_kind || nkinds < PK_COUNT) return PRISM_EINVAL;
+  if (!ms_by_kind || !launches_by_kind || (nkinds < PK_COUNT && nkinds != PK_FIT_SQUARE)) return PRISM_EINVAL;   // (that many: see prism.h)
   std::lock_guard<std::mutex> lock(g_prof_mu);
   for (int i = 0; i < nkinds; ++i) { ms_by_kind[i] = 0.0; launches_by_kind[i] = 0; }
   for (auto& r : g_prof) {
     if (hipEventSynchronize(r.b) != hipSuccess) return PRISM_EHIP;
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, r.a, r.b) != hipSuccess) return PRISM_EHIP;
+    if (r.kind >= nkinds) continue;
     ms_by_kind[r.kind] += ms;
     launches_by_kind[r.kind] += 1;
   }

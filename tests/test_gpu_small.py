@@ -58,3 +58,22 @@ def test_inverse_root(prism, n, p, sketch):
     r = prism.inv_root(X, p, 3, 0, SEED, 0.0, warm_iters=1).read()
     ref, oinfo = O.inv_root(A, p, 3, 0, SEED, 0.0)
     assert int(r[0]["iters"]) == 3 and np.linalg.norm(X.cpu().numpy()[0] - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+def test_profile_kinds_of_the_combined_launches(prism):
+    """A launch that does the work of several steps is booked as itself, not as one of the products in it."""
+    bf16 = torch.from_numpy(W.c2_muon_group(1, batch=1).view(np.int16)).cuda().view(torch.bfloat16)
+    spd = {n: torch.from_numpy(W.c4_shampoo_spd(n=n, batch=1)).cuda() for n in (48, 200)}
+    calls = [("fit_square", 5, ("bf16_polyq", "chain"), lambda: prism.polar(bf16.clone(), 5, 5, 16, SEED, 0.0, flags=prism.FLAG_BF16_PLAIN_ITERATE)),
+             ("flow", 1, ("f32_apply", "f32_store", "f64_mnext"), lambda: prism.inv_root(spd[200].clone(), 4, 40, 16, SEED, 1e-5)),
+             ("small_root", 1, ("f32_apply", "f32_store", "f64_mnext"), lambda: prism.inv_root(spd[48].clone(), 4, 40, 16, SEED, 1e-5))]
+    for kind, count, others, call in calls:
+        prism.profile_enable(True)
+        try:
+            call()
+            torch.cuda.synchronize()
+            prof = prism.profile_collect()
+        finally:
+            prism.profile_enable(False)
+        assert prof[kind][1] == count and prof[kind][0] > 0.0
+        assert not any(prof[k][1] for k in others)
