@@ -149,29 +149,29 @@ template <bool COH, typename T, typename V> __device__ inline void coh_store(T* 
   else *p = v;
 }
 
-// The root of f in [xa, xb], f(xa) = fa and f(xb) of opposite signs: Newton's method kept inside the bracket [l, h] (f(l) has
-// the sign of fa); a step that would leave the bracket, or that shrinks too slowly, is replaced by a bisection step.
-// eval(x, f, df) gives f and its derivative.  The step f / f' is taken with the hardware's reciprocal (relative error 2^-24, far
-// below what is left of a Newton step anyway; an exact division was half the time of an evaluation).
+// The root of f in [xa, xb], f(xa) = fa and f(xb) of opposite signs; eval(x, f, df) gives f and its derivative.  Newton's steps, each
+// from a point that has at most half the |f| of the one before it and to a point inside what the signs have left of the interval;
+// anywhere else the middle of that.  So every other evaluation at least halves |f| or the interval.  A step of 1e-9 is the last one:
+// it leaves an error of its square (over the distance to the next root).  The quotient f / f' is taken with the
+// hardware's reciprocal (relative error 2^-24, which scales that last step only; an exact division was half the time of
+// an evaluation).
 template <typename E> __device__ inline double bracketed_root(double xa, double xb, double fa, E eval) {
-  double l = xa, h = xb;
-  double x = 0.5 * (l + h), dx = h - l, dxold = dx, fx, dfx;
-  eval(x, fx, dfx);
-  for (int it = 0; it < 200; ++it) {
-    if (fx == 0.0) break;
-    if ((fx < 0.0) == (fa < 0.0)) l = x; else h = x;
-    const bool leaves = !((((x - h) * dfx - fx) * ((x - l) * dfx - fx)) < 0.0);
-    const bool slow = fabs(2.0 * fx) > fabs(dxold * dfx);
-    dxold = dx;
-    double xn;
-    if (leaves || slow) { dx = 0.5 * (h - l); xn = l + dx; }
-    else { dx = fx * __builtin_amdgcn_rcp(dfx); xn = x - dx; }
-    if (xn == x || !(xn > l && xn < h)) break;   // the bracket is down to neighbouring numbers
-    x = xn;
-    if (fabs(dx) <= 2.0e-16 * fabs(x)) break;
-    eval(x, fx, dfx);
+  double at = 0.5 * (xa + xb), before = __builtin_inf();
+  for (int evals = 0; evals < 200; ++evals) {
+    double f, slope;
+    eval(at, f, slope);
+    if (f == 0.0) break;
+    if ((f < 0.0) == (fa < 0.0)) xa = at;
+    else xb = at;
+    double next = at - f * __builtin_amdgcn_rcp(slope);
+    const bool inside = next > xa && next < xb;
+    if (fabs(next - at) <= 1.0e-9 * fabs(at)) return inside ? next : at;
+    if (!inside || !(2.0 * fabs(f) <= before)) next = 0.5 * (xa + xb);
+    if (!(next > xa && next < xb)) break;          // neighbouring numbers
+    before = fabs(f);
+    at = next;
   }
-  return x;
+  return at;
 }
 
 // Narrows the bracket [xa, xb] of a root of f (the sign changes once in it; neg: f(xa) < 0) by a whole wave: 64 points at a
