@@ -112,6 +112,25 @@ def test_square_beside_the_fit_bf16(prism, m, n, sketch):
         assert np.linalg.norm(W.from_bf16_bits(out)[b] - ref) <= 2e-2 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("batch,m,n,sketch", [(1, 768, 3072, 16), (2, 128, 100, 16), (3, 300, 257, 32), (2, 640, 640, 16), (16, 768, 768, 16), (2, 1024, 1000, 32)])
+def test_square_beside_the_fit_bits(prism, batch, m, n, sketch):
+    """The coefficients that a call reports, given to another one: that one forms Q in a launch of its own, and the bits are the same.
+    (Plain iterate: with the split one the fit also decides when its low half is left out.)"""
+    rng = np.random.default_rng(m + n)
+    A = (rng.standard_normal((batch, m, n)) * np.exp(rng.standard_normal((batch, m, 1)))).astype(np.float32)
+    x = torch.from_numpy(A).cuda().to(torch.bfloat16)
+    plain = prism.FLAG_BF16_PLAIN_ITERATE
+    for b in range(batch):               # a schedule holds for all matrices of a call
+        x[b] = x[0]
+    y = x.clone()
+    r = prism.polar(x, 5, 6, sketch, SEED, 0.0, flags=plain).read()
+    alpha = r[0]["alpha"][:6]
+    assert all(np.array_equal(r[b]["alpha"][:6], alpha) for b in range(batch)) and len(set(alpha)) > 2
+    q = prism.polar(y, 5, 6, sketch, SEED, 0.0, flags=plain, alpha_schedule=alpha).read()
+    assert np.array_equal(q["residual"][:, :6], r["residual"][:, :6])
+    assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
 @pytest.mark.parametrize("n,p", [(40, 4), (100, 4), (300, 2), (512, 3), (1000, 5)])
 def test_inverse_root_alone_and_in_a_batch(prism, n, p):
     """One matrix, where the update of X shares a launch with the first square, and a batch, where it does not: the same bits,

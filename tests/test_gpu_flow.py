@@ -1,6 +1,6 @@
 """All iterations of an fp32 call in one launch: the results of a launch per step, bit for bit, and the oracle's, at the edges of
-its variants (orders with and without a remainder in the slab ring, both tile sizes, 16 to 64 sketch columns, no sketch, more
-iterations than the ring of arrays has sets), for every function that takes it.
+its variants (orders with and without a remainder in the slab ring, fewer slabs than it has places, both tile sizes, 16 to 64 sketch
+columns, no sketch, more iterations than the ring of arrays has sets), for every function that takes it.
 
 A caller's workspace that is too small for the ring of arrays gets the launches.  The products sum in the same order on
 both ways; the residual is summed by tile, whose size differs: relative error of fp32 partial sums, 1e-6.
@@ -48,7 +48,8 @@ def _both(prism, call, fn, A, degree, sketch, p=0):
 
 @pytest.mark.parametrize("batch,m,n,degree,sketch,tol,iters,warm", [
     (1, 100, 70, 5, 8, 1e-5, 40, 0), (3, 500, 299, 5, 8, 1e-5, 40, 0), (2, 180, 400, 3, 16, 1e-5, 40, 2), (1, 900, 600, 5, 32, 1e-5, 40, 0),
-    (2, 300, 200, 5, 40, 1e-5, 40, 0), (2, 256, 128, 5, 0, 1e-5, 40, 0), (1, 512, 512, 5, 16, 0.0, 12, 3), (4, 300, 190, 5, 16, 1e-5, 0, 0), (2, 300, 190, 3, 16, 0.0, 1, 0)])
+    (2, 300, 200, 5, 40, 1e-5, 40, 0), (2, 256, 128, 5, 0, 1e-5, 40, 0), (1, 512, 512, 5, 16, 0.0, 12, 3), (4, 300, 190, 5, 16, 1e-5, 0, 0), (2, 300, 190, 3, 16, 0.0, 1, 0),
+    (2, 300, 60, 5, 8, 1e-5, 40, 0), (1, 33, 200, 3, 16, 1e-5, 40, 0), (3, 65, 20, 5, 32, 1e-5, 40, 0)])
 def test_polar(prism, batch, m, n, degree, sketch, tol, iters, warm):
     rng = np.random.default_rng(m + n)
     A = (rng.standard_normal((batch, m, n)) * 10.0 ** (-rng.random((batch, 1, n)))).astype(np.float32)
@@ -65,7 +66,7 @@ def test_polar(prism, batch, m, n, degree, sketch, tol, iters, warm):
 
 @pytest.mark.parametrize("batch,n,p,sketch,tol,iters", [
     (2, 100, 4, 16, 1e-5, 40), (1, 144, 3, 16, 1e-5, 40), (9, 256, 2, 32, 1e-5, 40), (2, 577, 4, 16, 1e-5, 40), (1, 768, 4, 32, 1e-5, 40),
-    (3, 300, 4, 64, 1e-5, 40), (2, 400, 4, 0, 1e-5, 60), (5, 200, 3, 8, 0.0, 11)])
+    (3, 300, 4, 64, 1e-5, 40), (2, 400, 4, 0, 1e-5, 60), (5, 200, 3, 8, 0.0, 11), (2, 60, 4, 40, 1e-5, 40), (1, 64, 2, 64, 1e-5, 40), (3, 17, 3, 33, 1e-5, 40)])
 def test_inverse_root(prism, batch, n, p, sketch, tol, iters):
     A = np.repeat(W.c4_shampoo_spd(n=n, batch=1), batch, axis=0)
     xs, r = _both(prism, lambda x, ws: prism.inv_root(x, p, iters, sketch, SEED, tol, workspace=ws), prism.FN_INV_ROOT, A, 3, sketch, p)
@@ -75,7 +76,8 @@ def test_inverse_root(prism, batch, n, p, sketch, tol, iters):
     assert np.linalg.norm(xs[0][0] - ref) <= 1e-5 * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("batch,n,degree,sketch,iters", [(1, 130, 5, 16, 40), (2, 500, 3, 16, 40), (4, 256, 5, 32, 40), (1, 700, 5, 16, 40), (2, 350, 5, 50, 40)])
+@pytest.mark.parametrize("batch,n,degree,sketch,iters", [(1, 130, 5, 16, 40), (2, 500, 3, 16, 40), (4, 256, 5, 32, 40), (1, 700, 5, 16, 40), (2, 350, 5, 50, 40),
+                                                         (1, 64, 5, 16, 40), (3, 50, 3, 32, 40), (2, 20, 5, 40, 40)])
 def test_square_root_sign_and_inverse(prism, batch, n, degree, sketch, iters):
     A = _spd(n, batch, n)
     xs, r = _both(prism, lambda x, ws: prism.sqrt(x, degree, iters, sketch, SEED, 1e-5, workspace=ws), prism.FN_SQRT, A, degree, sketch)
@@ -90,7 +92,8 @@ def test_square_root_sign_and_inverse(prism, batch, n, degree, sketch, iters):
     Cm = (A + 0.2 * rng.standard_normal(A.shape) / np.sqrt(n)).astype(np.float32)   # not symmetric
     xs, r = _both(prism, lambda x, ws: prism.inverse(x, iters, sketch, SEED, 1e-5, workspace=ws), prism.FN_INVERSE, Cm, 5, sketch)
     ref, oinfo = O.inverse(Cm[0], iters, sketch, SEED, 1e-5)
-    if int(r[0]["status"]) == oinfo["status"] == 0:
+    assert int(r[0]["status"]) == oinfo["status"]
+    if oinfo["status"] == 0:
         assert np.linalg.norm(xs[0][0] - ref) <= 1e-4 * np.linalg.norm(ref)
 
 
@@ -102,3 +105,20 @@ def test_coefficient_schedule(prism):
     ref, oinfo = O.sign(A[0], 5, 20, 16, SEED, 1e-5, alpha_schedule=sched)
     assert np.allclose(r[0]["alpha"][:3], sched) and int(r[0]["iters"]) == oinfo["iters"]
     assert np.linalg.norm(xs[0][0] - ref) <= 1e-4 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,batch", [(256, 16), (320, 12)])
+def test_both_sides_of_the_largest_batch(prism, n, batch):
+    """With one matrix more there is no workgroup left for every row block of a fit, and the call takes a launch per step: the same bits
+    for the others, and iteration counts."""
+    A = np.concatenate([W.sign_indefinite(n=n, batch=2), W.sign_indefinite(n=n, batch=1, data_seed=77)])
+    A = np.tile(A, (batch // 3 + 2, 1, 1))
+    res = []
+    for count in (batch, batch + 1):
+        x = torch.from_numpy(A[:count].copy()).cuda()
+        r = prism.sign(x, 5, 40, 16, SEED, 1e-5).read()
+        res.append((x[:batch].cpu().numpy(), r[:batch]))
+    (x, r), (y, q) = res
+    assert np.array_equal(x, y) and np.array_equal(r["iters"], q["iters"]) and np.array_equal(r["alpha"], q["alpha"])
+    ref, oinfo = O.sign(A[0], 5, 40, 16, SEED, 1e-5)
+    assert int(r[0]["iters"]) == oinfo["iters"] and np.linalg.norm(x[0] - ref) <= 1e-4 * np.linalg.norm(ref)
