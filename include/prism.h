@@ -288,7 +288,9 @@ int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int r
 
 /* The same with matrix b of group g read from the device pointer from[g][b] (row-major, contiguous; host arrays, read
  * during the call) instead of groups[g].x, which only takes the results (and copies of zero and non-finite
- * matrices).  The gradients of a list of weights need no copy into one array first. */
+ * matrices).  The gradients of a list of weights need no copy into one array first.  A matrix must not overlap any
+ * part of the results but its own place (results are written while other matrices are still read).  A call that returns
+ * PRISM_EINVAL or PRISM_EUNSUPPORTED has written nothing. */
 int prism_run_grouped_from(prism_fn fn, const prism_group* groups, const void* const* const* from, int ngroups,
                            int root_p, prism_dtype dt, int degree, int max_iters, int sketch_dim, uint64_t seed,
                            double tol, void* stream, const prism_options* opt);

@@ -119,7 +119,8 @@ bool takes_fused_fit(const Plan& P, int sel_batch) {
 }
 // All iterations in one launch (flow.hip): sets of arrays in its ring, 0: a launch per step.  bytes: of one set.
 // A workgroup for every row block of a fit has to be there (launch_flow's cluster), and the tiles must not be those of a
-// launch that fills the chip.  Time with launches / with the flow kernel, budget of 40 to 1e-5 (9 to 13 updates), by 64 x 64 tiles
+// launch that fills the chip.  (The first line - batch times order / 16 within the slots - is that of one 16-row block per
+// workgroup, not one where both sides are equal: at 16 matrices of order 256 the flow kernel is still far ahead, below.)  Time with launches / with the flow kernel, budget of 40 to 1e-5 (9 to 13 updates), by 64 x 64 tiles
 // of the update over the batch:
 //   sign          order 256: 16 tiles 2.2, 128 2.0, 256 1.6;  512: 64 1.5, 256 1.5, 512 1.2;  768: 144 1.3, 288 1.1, 576 1.0;  1024: 256 1.0
 //   inverse root  order 256: 16 tiles 2.6, 128 1.7, 256 1.9;  512: 64 1.7, 256 1.5, 512 1.1;  768: 144 1.2, 288 1.2, 576 1.1;  1024: 256 1.2
@@ -183,8 +184,9 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
       // to take, in us, from what was measured (order 768, 128 x 128 tiles): a slab of 32 k 0.37 while the CUs have one
       // workgroup each, the second pass 6, and per part 1.6e-6 per entry or the latency of its loads, the update 2.7e-9 per
       // row and squared order (the parts are of equal length and add up to whole tiles, so a number of parts that does
-      // not suit L pads the iterate).  With more workgroups than CUs the slab time is taken to grow in proportion, which
-      // was not measured (three fit a CU); 50257 x 768 stops at one each for it.  One 768 x 3072 matrix: Gram product
+      // not suit L pads the iterate).  With more workgroups than CUs the slab time is taken to grow in proportion.  That was
+      // not measured for this product and is probably too much (three fit a CU; a slab of other 128 x 128 products takes 0.65 to 0.75
+      // where two or three do), and it is why 50257 x 768 stops at one each.  One 768 x 3072 matrix: Gram product
       // 35 -> 20 us; 50257 x 768: 88 -> 73 us; 768 x 768 stays one pass (9 us).  Gain per iteration expected / measured at
       // other orders: 128 x 1024 1.5 / 2.4 us, 256 x 2048 12.0 / 10.8, 512 x 1024 1.2 / 4.4, 512 x 4096 32.2 / 27.6, 1024 x 2048
       // 5.1 / 10.2, 1280 x 5120 28.1 / 27.5.
@@ -521,7 +523,8 @@ int run_flow(const Run& r, const FlowOp* ops, int nops, bool residual, const flo
     if (together > widest) widest = together;
   }
   // beside other groups a quarter of the chip is left to them: their workgroups otherwise wait until this call is through.  Inverse
-  // roots of 16 matrices of 8 orders from 10 to 576, workgroups of a group / us: 256 1170, 192 1070, 128 1245, 64 1670
+  // roots of 16 matrices of 8 orders from 10 to 576, workgroups of a group / us: 256 1170, 192 1070, 128 1245, 64 1670 (the one mix
+  // that this was measured on)
   const int share = P.shared_gpu ? 3 * FLOW_SLOTS / 4 / r.sel_batch : slots, least = P.Sp / 16;
   const int most = share > least ? share : least;
   a.cluster = widest < most ? widest : most;
@@ -1532,7 +1535,7 @@ int run_grouped(int fn, const prism_group* groups, int ngroups, int root_p, int 
   if (rc != PRISM_OK) return rc;
   const int used = ngroups < GROUP_STREAMS ? ngroups : GROUP_STREAMS;
   // Longest group first, each to the stream with the least to do: what a group takes is latency per iteration (one workgroup
-  // per matrix up to order 64, then growing with the order) and the work of its products.
+  // per matrix up to order 64, then growing with the order) and the work of its products, roughly: the ranking is what counts.
   std::vector<std::pair<double, int>> order;
   for (int gi = 0; gi < ngroups; ++gi) {
     const prism_group& g = groups[gi];

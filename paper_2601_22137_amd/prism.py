@@ -241,7 +241,8 @@ def sqrt_newton(a, max_iters=30, tol=1e-6, fit=True, workspace=None, alpha_sched
 def run_grouped(fn, xs, degree=5, max_iters=30, sketch_dim=8, seed=22137, tol=1e-6, root_p=0, flags=0, warm_iters=0,
                 alpha_schedule=None, sources=None):
     """One call over tensors of different shapes (each [batch, m, n], all of one dtype), in place.  sources: per tensor
-    of xs a list of `batch` contiguous [m, n] tensors that are read instead; xs then only takes the results.
+    of xs a list of `batch` contiguous [m, n] tensors that are read instead; xs then only takes the results, and no such tensor may
+    overlap any part of xs but its own place.
     Returns (inverse outputs or None per group, info handles per group)."""
     if len(xs) == 0:
         _check(lib().prism_run_grouped(fn, None, 0, root_p, F32, degree, max_iters, sketch_dim, seed, tol, _stream(), None))
