@@ -62,6 +62,10 @@ struct GemmDesc {
   int skip_n0, skip_n1; // likewise for columns
   float* rho_part;      // [batch][tiles] partial sums of R^2 (RESIDUAL / MNEXT)
   const Ctrl* ctrl;     // may be null (test entry points)
+  // fp32 matrices as three bf16 planes (gemm_split.hip): plane q of the operand at A3 + q psA, laid out like A (strideA, lda).
+  // With A3 and B3 the product is taken from the planes; with C3 the result is (also) written as planes, and C may be null.
+  const uint16_t* A3; const uint16_t* B3; uint16_t* C3;
+  long long psA, psB, psC;
 };
 
 // Two products of the same shape and kind in one launch: workgroups [0, first) belong to the first
@@ -74,6 +78,12 @@ int launch_gemm_f32(const GemmDesc& g, hipStream_t s);
 int f32_tiles(int M, int N, int batch, int sym);
 // both products in one launch: same M, N, K, batch, epilogue and operand layout; symmetric: both, neither or the first
 int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
+// ---- gemm_split.hip : fp32 products on the bf16 matrix cores ----
+// Both operands in planes; M, N multiples of 128, K of 32.  b: a second product of the same shape and kind (null: none)
+int launch_gemm_split(const GemmDesc& a, const GemmDesc* b, hipStream_t s);
+int split_tiles(int M, int N, int batch, int sym);   // tiles of one matrix, i.e. residual partial sums
+// planes of `count` (a multiple of 8) entries
+void launch_split3(const float* x, uint16_t* p, long long count, long long ps, hipStream_t s);
 int launch_gemm_f64a(const GemmDesc& g, int tile_m, int tile_n, hipStream_t s);  // A float, B/C double
 
 // ---- gemm_bf16.hip : bf16 matrix-core NT GEMMs (both operands K-contiguous) ----

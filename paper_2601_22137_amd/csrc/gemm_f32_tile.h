@@ -19,7 +19,7 @@
 #pragma once
 #include <type_traits>
 
-#include "common.h"
+#include "split3.h"
 
 namespace prism {
 namespace {
@@ -442,6 +442,11 @@ __device__ inline void gemm_tile(const GemmDesc& g, bool sym, int b, int rem, in
     if (sym && tm != tn) part *= 2.0f;
   } else {
     // register r of lane l: row 4 r + lq of the block, column lr
+    // With planes of the residual, the wave passes it through a strip of its own (the ring is free), for rows in runs of eight columns.
+    constexpr int WTM = TM / WGM, WTN = TN / WGN, SW = WTN + 4;
+    const bool planes = !COH && EPI == EPI_MNEXT && g.C3;
+    float* strip = (float*)smem + wave * WTM * SW;
+    static_assert(EPI != EPI_MNEXT || WGM * WGN * WTM * SW * 4 <= ST * STAGE, "strips in the ring");
 #pragma unroll
     for (int i = 0; i < BM; ++i)
 #pragma unroll
@@ -459,10 +464,29 @@ __device__ inline void gemm_tile(const GemmDesc& g, bool sym, int b, int rem, in
             v += min[i][j][r];
             store_f64<COH>(Cb, oc, in ? v : (TC)0);
             const TC res = in ? ((gi == gj ? (TC)1 : (TC)0) - v) : (TC)0;
-            store_f32<COH>(g.R32out + (long long)b * g.strideR, (long long)gi * g.ldr + gj, (float)res);
+            if (planes) strip[(i * 16 + 4 * r + lq) * SW + j * 16 + lr] = (float)res;
+            else store_f32<COH>(g.R32out + (long long)b * g.strideR, (long long)gi * g.ldr + gj, (float)res);
             part = __builtin_fma(res, res, part);
           }
         }
+    if (planes) {
+      constexpr int LPR = WTN / 8, RPI = 64 / LPR;
+#pragma unroll
+      for (int it = 0; it < WTM / RPI; ++it) {
+        const int row = it * RPI + lane / LPR, col = (lane % LPR) * 8;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = strip[row * SW + col + e];
+        const long long o = (long long)b * g.strideR + (long long)(m0 + wm0 + row) * g.ldr + n0 + wn0 + col;
+        *(f32x4*)(g.R32out + o) = (f32x4){v[0], v[1], v[2], v[3]};
+        *(f32x4*)(g.R32out + o + 4) = (f32x4){v[4], v[5], v[6], v[7]};
+        s3_u32x4 q[3];
+        split3(v, q);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(s3_u32x4*)(g.C3 + k * g.psC + o) = q[k];
+      }
+      __syncthreads();   // the partial sums take the place of the strips
+    }
   }
   if (EPI == EPI_RESIDUAL || EPI == EPI_MNEXT) {
     TC* red = (TC*)smem;                 // the ring is free behind the last barrier

@@ -90,6 +90,8 @@ struct Plan {
   bool shared_gpu; // PRISM_FLAG_SHARED_GPU
   size_t o_x[2], o_y[2], o_r, o_q, o_t[3];        // fp32 paths (o_y doubles as M64 for inverse root)
   size_t o_xhi[2], o_xlo[2], o_rb, o_qb;          // bf16 polar
+  bool x3;                                        // fp32: products from bf16 planes (gemm_split.hip)
+  size_t o_x3[2], o_y3[2], o_r3, o_t3;            // ... of the arrays above (Q: planes only, at o_q; t: T_1 of the inverse root)
   int ring; long long ring_bytes;                 // fp32: all iterations in one launch (flow.hip), sets of arrays from o_x[0] on
   int ksplit;      // polar: parts of the K loop of X^T X (0 = one pass); partial products at o_gpart
   size_t o_gpart;
@@ -101,6 +103,8 @@ struct Plan {
 constexpr unsigned FLAG_NO_SPLIT_K = 1u << 31;
 // ... and no flow kernel (whose ring of arrays takes more than the two iterates)
 constexpr unsigned FLAG_NO_FLOW = 1u << 30;
+// ... and no planes of fp32 operands
+constexpr unsigned FLAG_NO_PLANES = 1u << 29;
 constexpr long long MAX_ENTRIES = (1ll << 31) - 1;   // of a matrix, sides padded
 
 // Batches that run as two halves unless the caller asks otherwise (run_auto)
@@ -133,6 +137,26 @@ int flow_ring(const Plan& P, int sel_batch, size_t bytes) {
   if (P.Sp > 768 || (P.ld == 64 && P.Sp > 512) || !takes_fused_fit(P, sel_batch)) return 0;
   if (flow_tiles_of(P, sel_batch) > (P.Sp <= 512 ? 512 : 320) || FLOW_SLOTS / sel_batch < P.Sp / 16) return 0;
   return bytes <= (16u << 20) ? 8 : 4;
+}
+
+// fp32 products from bf16 planes (gemm_split.hip), where the calls are not a launch of their own (flow_ring).  Padding: whole tiles of 128 where
+// they cost less than the smaller tiles do (about a fifth per product).  us from fp32 operands / from planes, tolerance 1e-5:
+//   sign          16 x 512 1311 / 1103, 64 x 512 3901 / 3390, 768: 4 1397 / 1193, 16 3423 / 3203, 1000: 1 943 / 840, 4 2184 / 1633, 2 x 1900 6220 / 4535, 4096 24945 / 16177
+//   square root   16 x 512 1096 / 914, 1000: 1 737 / 676, 4 1702 / 1299, 2 x 1900 5116 / 3767, 4096 20907 / 13747; inverse much like sign
+//   polar         64 x 768 x 512 3591 / 3553, 1500 x 1000: 1 974 / 820, 4 2089 / 1671, 6144 x 4096 24429 / 18109
+//   inverse root  p = 4, 1000: 1 943 / 881, 4 2287 / 2026, 8 4074 / 3744, 2 x 1900 6801 / 5746, 4096 32118 / 26841; 512 and 768 equal
+// Inverse roots: by the order alone, so that a matrix has the same bits alone and in any batch; its fp64 product pays for the padding and gains nothing (order 1088
+// would be 1152).  Not for tall polar factors, whose Gram product runs in parts, nor for p = 1, where the iterate has the scale of the input.
+int planes_unit(const Plan& P) {
+  const double s = round_up(P.S, 128) / (double)round_up(P.S, 64), l = round_up(P.L, 128) / (double)round_up(P.L, 64), grown = s * s * l;
+  if (P.fn == PRISM_FN_INV_ROOT) return grown < 1.1 ? 128 : 0;
+  return grown < 1.19 ? 128 : 64;
+}
+bool takes_planes(const Plan& P, int sel_batch) {
+  static const int off = ab_switch("PRISM_NO_F32_PLANES");
+  if (off || P.dt != PRISM_F32 || P.ksplit || P.fn == PRISM_FN_SQRT_NEWTON || (P.fn == PRISM_FN_POLAR && P.L > 8192 - 128)) return false;
+  if (P.fn == PRISM_FN_INV_ROOT ? P.p < 2 || P.Sp <= 768 || !planes_unit(P) : P.Sp < 384) return false;
+  return !flow_ring(P, sel_batch, 0);
 }
 
 // shared_shapes: the plan of a launch sequence over several shape groups with the same short side;
@@ -213,6 +237,13 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
       }
     }
   }
+  if (!(flags & FLAG_NO_PLANES) && takes_planes(P, sel_batch ? sel_batch : batch) &&
+      (long long)round_up(P.S, 128) * round_up(P.L, 128) <= MAX_ENTRIES) {
+    P.x3 = true;
+    const int unit = planes_unit(P);
+    P.Sp = round_up(P.S, unit);
+    P.Lp = round_up(P.L, unit);
+  }
   if ((long long)P.Sp * P.Lp > MAX_ENTRIES) {   // the kernels keep some offsets within a matrix in 32 bits
     set_last_error("a matrix may hold at most 2^31 - 1 entries after its sides are rounded up to tile multiples");
     return PRISM_EUNSUPPORTED;
@@ -273,8 +304,8 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
     const size_t iterate = off - set0;
     P.o_r = take(B * SS * 4);
     if (fn == PRISM_FN_INV_ROOT) for (int i = 0; i < 3; ++i) P.o_t[i] = take(B * SS * 4);
-    else P.o_q = (P.d == 2 || fn == PRISM_FN_INVERSE) ? take(B * SS * 4) : 0;
-    P.ring = (flags & FLAG_NO_FLOW) ? 0 : flow_ring(P, sel_batch ? sel_batch : batch, off - set0);
+    else P.o_q = (P.d == 2 || fn == PRISM_FN_INVERSE) ? take(B * SS * (P.x3 ? 6 : 4)) : 0;
+    P.ring = (flags & FLAG_NO_FLOW) || P.x3 ? 0 : flow_ring(P, sel_batch ? sel_batch : batch, off - set0);
     if (P.ring) {
       P.ring_bytes = (long long)(off - set0);
       off = set0 + (size_t)P.ring * P.ring_bytes;
@@ -284,6 +315,14 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
       P.o_x[1] = off;
       if (fn == PRISM_FN_SQRT || fn == PRISM_FN_INV_ROOT) P.o_y[1] = off + (P.o_y[0] - P.o_x[0]);
       off += iterate;
+    }
+    if (P.x3) {
+      for (int i = 0; i < 2; ++i) {
+        P.o_x3[i] = take(B * (fn == PRISM_FN_POLAR ? LS : SS) * 6);
+        if (fn == PRISM_FN_SQRT || (fn == PRISM_FN_INVERSE && i == 0)) P.o_y3[i] = take(B * SS * 6);
+      }
+      P.o_r3 = take(B * SS * 6);
+      if (P.p == 3 || P.p == 4) P.o_t3 = take(B * SS * 6);
     }
   }
   P.o_gpart = P.ksplit ? take(B * P.ksplit * SS * 4) : 0;
@@ -373,6 +412,53 @@ struct Run {
   int sel_batch = 0;
 
   template <typename T> T* at(size_t off) const { return (T*)(ws + off); }
+
+  // The planes of an fp32 array (P.x3)
+  struct Planes { const float* x; uint16_t* p; long long ps; bool only; };   // only: there is no fp32 array, x is its name
+  std::vector<Planes> split;
+  const Planes* planes_of(const void* x) const {
+    for (const Planes& q : split)
+      if (q.x == x) return &q;
+    return nullptr;
+  }
+  void list_planes() {
+    if (!P.x3) return;
+    const long long SS = (long long)P.batch * P.Sp * P.Sp, LS = (long long)P.batch * P.Lp * P.Sp;
+    auto add = [&](size_t o, size_t o3, long long ps) { if (o3) split.push_back({at<float>(o), at<uint16_t>(o3), ps, o == o3}); };
+    for (int i = 0; i < 2; ++i) {
+      add(P.o_x[i], P.o_x3[i], P.fn == PRISM_FN_POLAR ? LS : SS);
+      add(P.o_y[i], P.o_y3[i], SS);
+    }
+    add(P.o_r, P.o_r3, SS);
+    add(P.o_q, P.o_q, SS);
+    add(P.o_t[1], P.o_t3, SS);
+  }
+  // what the first products read, from the arrays that the prepare step has written
+  void split_start() {
+    for (const Planes& q : split) {
+      const bool start = q.x == at<float>(P.o_x[0]) || (P.o_y3[0] && q.x == at<float>(P.o_y[0])) || (P.fn == PRISM_FN_INV_ROOT && q.x == at<float>(P.o_r));
+      if (start) launch_split3(q.x, q.p, q.ps, q.ps, s);
+    }
+  }
+  GemmDesc with_planes(GemmDesc g) const {
+    const Planes *a = planes_of(g.A), *b = planes_of(g.B), *c = planes_of(g.C);
+    if (!a || !b) return g;
+    g.A3 = a->p; g.psA = a->ps; g.B3 = b->p; g.psB = b->ps;
+    if (c) {
+      g.C3 = c->p; g.psC = c->ps;
+      if (c->only) g.C = nullptr;
+    }
+    return g;
+  }
+  int gemm(const GemmDesc& g) const {
+    const GemmDesc q = with_planes(g);
+    return q.A3 ? launch_gemm_split(q, nullptr, s) : launch_gemm_f32(g, s);
+  }
+  int gemm_pair(const GemmDesc& a, const GemmDesc& b) const {
+    const GemmDesc qa = with_planes(a), qb = with_planes(b);
+    return qa.A3 && qb.A3 ? launch_gemm_split(qa, &qb, s) : launch_gemm_f32_pair(a, b, s);
+  }
+  int tiles(int M, int N, int sym) const { return P.x3 ? split_tiles(M, N, sel_batch, sym) : f32_tiles(M, N, sel_batch, sym); }
 
   // sketch + chain V_j = R V_{j-1} (fp32 matrix cores, skinny N = padded sketch width)
   // Rb: bf16 copy of R (bf16 polar path): the products then read it instead of R, except the diagonal,
@@ -582,7 +668,7 @@ int run_polar_f32(Run& r) {
   float* Q = P.d == 2 ? r.at<float>(P.o_q) : nullptr;
   const bool polar = P.fn != PRISM_FN_SIGN;
   const int sym = polar ? f32_sym() : 0;
-  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
+  const int nparts = r.tiles(Sp, Sp, sym);
   // G = X^T X; matrix sign: G = X X (any square input, all tiles)
   auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, X[cur], Sp, LS, X[cur], Sp, LS, Sp, Sp, Lp, polar ? 1 : 0);
@@ -631,12 +717,12 @@ int run_polar_f32(Run& r) {
       CHECK_LAUNCH(check_hip());
     } else {
       ProfScope ps(PK_F32_RESID, r.s);
-      CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s));
+      CHECK_LAUNCH(r.gemm(residual(cur)));
     }
     CHECK_LAUNCH(r.fit(k, (polar && P.ksplit) ? gram_reduce_parts(Sp) : nparts, R));
     if (k == r.max_iters) break;
-    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s)); }
+    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(r.gemm(square())); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(r.gemm(update(cur))); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -827,7 +913,7 @@ int run_sqrt_f32(Run& r) {
   // X_k and Y_k commute up to kappa * eps only: every product keeps all its tiles.  (Mirroring only
   // Y X and R^2 is stable but costs the root an order of magnitude of accuracy from kappa ~ 1e4 on.)
   const int sym = 0;
-  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
+  const int nparts = r.tiles(Sp, Sp, sym);
   auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, Y[cur], Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);    // G = Y X
     g.sym = sym;
@@ -864,11 +950,11 @@ int run_sqrt_f32(Run& r) {
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s)); }
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(r.gemm(residual(cur))); }
     CHECK_LAUNCH(r.fit(k, nparts, R));
     if (k == r.max_iters) break;
-    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32_pair(update_x(cur), update_y(cur), r.s)); }
+    if (P.d == 2) { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(r.gemm(square())); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(r.gemm_pair(update_x(cur), update_y(cur))); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -884,7 +970,7 @@ int run_inverse_f32(Run& r) {
   float* R = r.at<float>(P.o_r);
   float* Q = r.at<float>(P.o_q);
   const int sym = 0;   // A_s X_k is symmetric up to kappa * eps only: all tiles
-  const int nparts = f32_tiles(Sp, Sp, r.sel_batch, sym);
+  const int nparts = r.tiles(Sp, Sp, sym);
   auto residual = [&](int cur) {
     GemmDesc g = f32_desc(r, As, Sp, SS, X[cur], Sp, SS, Sp, Sp, Sp, 0);
     g.sym = sym;
@@ -909,11 +995,11 @@ int run_inverse_f32(Run& r) {
   int cur = 0;
   for (int k = 0; k <= r.max_iters; ++k) {
     if (k == r.max_iters && r.tol <= 0.0) break;
-    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(launch_gemm_f32(residual(cur), r.s)); }
+    { ProfScope ps(PK_F32_RESID, r.s); CHECK_LAUNCH(r.gemm(residual(cur))); }
     CHECK_LAUNCH(r.fit(k, nparts, R));
     if (k == r.max_iters) break;
-    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(launch_gemm_f32(square(), r.s)); }
-    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s)); }
+    { ProfScope ps(PK_F32_POLYQ, r.s); CHECK_LAUNCH(r.gemm(square())); }
+    { ProfScope ps(PK_F32_APPLY, r.s); CHECK_LAUNCH(r.gemm(update(cur))); }
     cur ^= 1;
   }
   return PRISM_OK;
@@ -998,6 +1084,7 @@ int run_inv_root_f32(Run& r) {
     mn.epi = EPI_MNEXT; mn.C = Mout; mn.strideC = SS; mn.ldc = Sp;
     mn.Cin = Min; mn.strideCin = SS; mn.ldcin = Sp;
     mn.R32out = Rout; mn.strideR = SS; mn.ldr = Sp; mn.rho_part = r.rho;
+    if (const Run::Planes* q = r.planes_of(Rout)) { mn.C3 = q->p; mn.psC = q->ps; }
     return mn;
   };
   if (r.flow()) {   // p = 2 .. 4
@@ -1022,11 +1109,11 @@ int run_inv_root_f32(Run& r) {
     const bool paired = p >= 2 && 2ll * (Sp / 64) * (Sp / 64) * r.sel_batch <= 1024;
     if (!paired) {
       ProfScope ps(PK_F32_APPLY, r.s);
-      CHECK_LAUNCH(launch_gemm_f32(update(cur), r.s));
+      CHECK_LAUNCH(r.gemm(update(cur)));
     }
     auto run_square = [&](const float* E, float* dst) -> int {
       ProfScope ps(PK_F32_STORE, r.s);
-      return !E && paired ? launch_gemm_f32_pair(update(cur), square(E, dst), r.s) : launch_gemm_f32(square(E, dst), r.s);
+      return !E && paired ? r.gemm_pair(update(cur), square(E, dst)) : r.gemm(square(E, dst));
     };
     auto run_m_times = [&](const float* E, const double* Min, double* Mout, float* Rout) -> int {
       ProfScope ps(PK_F64_MNEXT, r.s);
@@ -1042,7 +1129,7 @@ int run_inv_root_f32(Run& r) {
         U = dst;
         if ((p >> bit) & 1) {
           float* dst2 = (U == Tm[1]) ? Tm[2] : Tm[1];
-          { ProfScope ps(PK_F32_STORE, r.s); CHECK_LAUNCH(launch_gemm_f32(times_t(U, dst2), r.s)); }
+          { ProfScope ps(PK_F32_STORE, r.s); CHECK_LAUNCH(r.gemm(times_t(U, dst2))); }
           U = dst2;
         }
       }
@@ -1121,13 +1208,20 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
   if (sel_batch == 0) sel_batch = batch;
   rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt ? opt->flags : 0u, false, sel_batch);
   if (rc != PRISM_OK) return rc;
-  if ((r.P.ksplit || r.P.ring) && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
-    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW, false, sel_batch);
+  const unsigned plain = FLAG_NO_SPLIT_K | FLAG_NO_FLOW | FLAG_NO_PLANES;
+  if ((r.P.ksplit || r.P.ring || r.P.x3) && opt && opt->workspace && opt->workspace_bytes < r.P.total) {
+    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, opt->flags | plain, false, sel_batch);
     if (rc != PRISM_OK) return rc;
   }
   r.s = (hipStream_t)stream;
   rc = get_workspace(r.P.total, owner ? owner : stream, opt, &r.ws);
+  if (rc == PRISM_ENOMEM && r.P.x3) {   // the planes are what did not fit
+    rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, (opt ? opt->flags : 0u) | plain, false, sel_batch);
+    if (rc != PRISM_OK) return rc;
+    rc = get_workspace(r.P.total, owner ? owner : stream, opt, &r.ws);
+  }
   if (rc != PRISM_OK) return rc;
+  r.list_planes();
   const Plan& P = r.P;
   r.ctrl = r.at<Ctrl>(P.o_ctrl);
   r.info = (opt && opt->info) ? opt->info : r.at<prism_info>(P.o_info);
@@ -1175,7 +1269,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
     fa.ring = r.flow() ? P.ring : 0; fa.ring_bytes = P.ring_bytes;
   }
   const bool small = r.small_polar() || r.small_root();
-  if (!small) { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); }
+  if (!small) { ProfScope ps(PK_PREP, r.s); launch_sumsq(pa, r.s); launch_prepare(pa, r.s); r.split_start(); }
   if (P.p_s > 0 && max_iters > r.first_fit && fn != PRISM_FN_SQRT_NEWTON) {
     ProfScope ps(PK_SKETCH, r.s);
     launch_sketch(r.v0, P.Sp, P.S, P.ld, P.p_s, seed, r.first_fit, max_iters - r.first_fit, P.fn, r.s, r.fused() || small);
@@ -1717,8 +1811,8 @@ int prism_polar_static(void* x, int batch, int m, int n, prism_dtype dt, int deg
     Plan P;
     const int rc = make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags);
     if (rc != PRISM_OK) return rc;
-    if ((P.ksplit || P.ring) && P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES)   // as the driver does with a workspace of this size
-      (void)make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW);
+    if ((P.ksplit || P.ring || P.x3) && P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES)   // as the driver does with a workspace of this size
+      (void)make_plan(P, PRISM_FN_POLAR, batch, m, n, (int)dt, degree, sketch_dim, 0, o.flags | FLAG_NO_SPLIT_K | FLAG_NO_FLOW | FLAG_NO_PLANES);
     if (P.total > (size_t)PRISM_STATIC_SCRATCH_BYTES) {
       set_last_error("prism_polar_static: this call needs more than PRISM_STATIC_SCRATCH_BYTES of scratch; use prism_polar_ex");
       return PRISM_EUNSUPPORTED;
