@@ -147,16 +147,19 @@ int flow_ring(const Plan& P, int sel_batch, size_t bytes) {
 //   inverse root  p = 4, 1000: 1 943 / 881, 4 2287 / 2026, 8 4074 / 3744, 2 x 1900 6801 / 5746, 4096 32118 / 26841; 512 and 768 equal
 // Inverse roots: by the order alone, so that a matrix has the same bits alone and in any batch; its fp64 product pays for the padding and gains nothing (order 1088
 // would be 1152).  Not for tall polar factors, whose Gram product runs in parts, nor for p = 1, where the iterate has the scale of the input.
-int planes_unit(const Plan& P) {
+int planes_unit(const Plan& P, int sel_batch) {
   const double s = round_up(P.S, 128) / (double)round_up(P.S, 64), l = round_up(P.L, 128) / (double)round_up(P.L, 64), grown = s * s * l;
   if (P.fn == PRISM_FN_INV_ROOT) return grown < 1.1 ? 128 : 0;
-  return grown < 1.19 ? 128 : 64;
+  if (grown < 1.19) return 128;
+  // 64 x 64 tiles gain 10 % in one round (512) and nothing in more (sign of 2 x 1000 1361 / 1192, 8 x 1000 3700 / 3382; square root of 4 x 808, 1.3
+  // rounds and 2.6 for the pair of updates, 1471 / 1648)
+  return (long long)((P.S + 63) / 64) * ((P.L + 63) / 64) * sel_batch <= 512 ? 64 : 0;
 }
 bool takes_planes(const Plan& P, int sel_batch) {
   static const int off = ab_switch("PRISM_NO_F32_PLANES");
   if (off || P.dt != PRISM_F32 || P.ksplit || P.fn == PRISM_FN_SQRT_NEWTON || (P.fn == PRISM_FN_POLAR && P.L > 8192 - 128)) return false;
-  if (P.fn == PRISM_FN_INV_ROOT ? P.p < 2 || P.Sp <= 768 || !planes_unit(P) : P.Sp < 384) return false;
-  return !flow_ring(P, sel_batch, 0);
+  if (P.fn == PRISM_FN_INV_ROOT ? P.p < 2 || P.Sp <= 768 : P.Sp < 384) return false;
+  return planes_unit(P, sel_batch) && !flow_ring(P, sel_batch, 0);
 }
 
 // shared_shapes: the plan of a launch sequence over several shape groups with the same short side;
@@ -240,7 +243,7 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   if (!(flags & FLAG_NO_PLANES) && takes_planes(P, sel_batch ? sel_batch : batch) &&
       (long long)round_up(P.S, 128) * round_up(P.L, 128) <= MAX_ENTRIES) {
     P.x3 = true;
-    const int unit = planes_unit(P);
+    const int unit = planes_unit(P, sel_batch ? sel_batch : batch);
     P.Sp = round_up(P.S, unit);
     P.Lp = round_up(P.L, unit);
   }
