@@ -32,17 +32,17 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void g
   extern __shared__ __align__(1024) unsigned char smem[];
   // Workgroup -> (group, tile).  The hardware deals consecutive workgroups round-robin to the 8
   // XCDs, each with its own L2.  xcd_private (set by the launcher for small matrices, or when all
-  // operands of the launch fit the Infinity Cache together): every XCD gets a contiguous range of
-  // tiles, i.e. whole matrices, so that the tiles sharing a panel share an L2 (without this the
-  // 768-sized Gram fetched 7x its algorithmic bytes).  Otherwise workgroup i runs tile i: all XCDs
+  // operands of the launch fit the Infinity Cache together): every XCD gets a contiguous range of the
+  // tiles of each group, i.e. whole matrices, so that the tiles sharing a panel share an L2 (without this the
+  // 768-sized Gram fetched 7x its algorithmic bytes).  Of each group, not of the launch: the groups differ in K, and
+  // four XCDs of eight had all of the long ones.  Otherwise workgroup i runs tile i: all XCDs
   // sweep the same matrix and share its panels through the Infinity Cache (private ranges measured
   // 20 % slower at 8 x 4096^2, where eight matrices at once overflow that cache).
   int wg = blockIdx.x;
-  const int total = mg.tile_start[mg.ngroups];
-  if ((total & 7) == 0 && mg.xcd_private) wg = (wg & 7) * (total >> 3) + (wg >> 3);
   int gi = 0;
   while (gi + 1 < mg.ngroups && wg >= mg.tile_start[gi + 1]) ++gi;
   wg -= mg.tile_start[gi];
+  if (mg.xcd_private) wg = (wg & 7) * ((mg.tile_start[gi + 1] - mg.tile_start[gi]) >> 3) + (wg >> 3);   // starts are multiples of 8
   const Bf16Desc& g = mg.d[gi];
 
   // SYM: A == B and the result is symmetric (Gram matrix, R^2): only the tiles that reach the
@@ -51,6 +51,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void g
   const int tiles_m = g.M / TM, tiles_n = g.N / TN;
   const int per_mat = SYM ? RT * tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int b = wg / per_mat;
+  if (b >= g.batch) return;   // the group's tiles are rounded up to whole rounds of the XCDs
   const int rem = wg - b * per_mat;
   int tm, tn;
   if (SYM) {       // row tm of the upper triangle holds tiles_n - RT * tm tiles
@@ -86,9 +87,21 @@ long long tiles_per_matrix(const Bf16Desc& g) {
 template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW>
 int launch_tw(Bf16Multi& mg, hipStream_t s) {
   long long total = 0;
+  // A launch whose tiles are no multiple of eight is rounded up where the operands are large enough for their fetches past the L2s to be what
+  // it waits for (Gram product of 50257 x 768 in 12 parts, 252 tiles of 77 MB: 64 -> 52 us); small ones are faster in plain order (one
+  // 768 x 3072 in 6 parts, 126 tiles of 5 MB: 10.2 against 11.6).  Nothing in between was measured.
+  double operand_bytes = 0.0;
+  for (int i = 0; i < mg.ngroups; ++i) {
+    const Bf16Desc& g = mg.d[i];
+    total += tiles_per_matrix<TM, TN, SYM>(g) * g.batch;
+    operand_bytes += 2.0 * g.batch * ((double)g.M * g.K + (g.A == g.B ? 0.0 : (double)g.N * g.K));
+  }
+  if (total % 8 != 0 && operand_bytes < 32.0 * 1024 * 1024) mg.xcd_private = 0;
+  total = 0;
   for (int i = 0; i < mg.ngroups; ++i) {
     mg.tile_start[i] = (int)total;
     total += tiles_per_matrix<TM, TN, SYM>(mg.d[i]) * mg.d[i].batch;
+    if (mg.xcd_private) total = (total + 7) & ~7ll;
     if (total > 0x7fffffff) return PRISM_EUNSUPPORTED;
   }
   mg.tile_start[mg.ngroups] = (int)total;
