@@ -3,9 +3,20 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "prism.h"
 
 namespace prism {
+
+template <int D, typename F>
+__device__ inline void unrolled(F&& f) {
+  if constexpr (D > 0) {
+    unrolled<D - 1>(f);
+    f(std::integral_constant<int, D - 1>{});
+  }
+}
+
 
 // Per-matrix control block, device resident.  Written by the prepare and solve
 // kernels, read by every kernel of the iteration (done != 0 => the matrix is skipped).

@@ -26,7 +26,7 @@ namespace prism {
 namespace {
 
 template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW>
-__global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : wgs_per_cu(TM, TN))) void gemm_bf16_kernel(Bf16Multi mg) {
+__global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : (long_slabs(TM, TN, EPI, KMA) ? 2 : wgs_per_cu(TM, TN)))) void gemm_bf16_kernel(Bf16Multi mg) {
   constexpr int RT = TM / TN;                    // SYM: tile columns per tile row height
   static_assert(RT == 1 || RT == 2, "tile shape");
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -105,7 +105,7 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
     if (total > 0x7fffffff) return PRISM_EUNSUPPORTED;
   }
   mg.tile_start[mg.ngroups] = (int)total;
-  const size_t lds = (size_t)stages_of(TM, TN) * (TM + TN) * 64;   // ring of STAGES x (A slab + B slab)
+  const size_t lds = ring_bytes(TM, TN, EPI, KMA);
   const int rc = allow_dynamic_lds((const void*)gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW>, (int)lds);
   if (rc != PRISM_OK) return rc;
   hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW>), dim3((unsigned)total), dim3(64 * NW), lds, s, mg);
@@ -132,6 +132,7 @@ int launch_t(Bf16Multi& mg, hipStream_t s) {
     if (g.sym && (g.M != g.N || g.A != g.B)) return PRISM_EINVAL;
     if ((g.epi == BEPI_GRAM || g.epi == BEPI_POLYQ) && !g.sym) return PRISM_EINVAL;   // symmetric products only
     if (g.epi == BEPI_STORE && (!g.C32 || (g.sym && km != 3))) return PRISM_EINVAL;
+    if (g.epi == BEPI_APPLY && TM == 128 && TN == 128 && (g.K % 64 || g.K < 128)) return PRISM_EINVAL;   // slabs of 64
     // without the fp32 matrix: GRAM with a diagonal array, POLYQ with R in bf16
     if (g.epi == BEPI_GRAM && ((!g.C32 && !g.diag) || g.rho_stride < tiles_per_matrix<TM, TN, true>(g))) return PRISM_EINVAL;
     if (g.epi == BEPI_POLYQ && !g.C32 && !g.Cin16) return PRISM_EINVAL;

@@ -30,9 +30,142 @@ typedef void __attribute__((address_space(3)))* lptr_t;
 constexpr int stages_of(int TM, int TN) { return (TM == 256 && TN == 256) ? 4 : 3; }
 constexpr int wgs_per_cu(int TM, int TN) { return (TM == 256 && TN == 256) ? 1 : (TM == 256 ? 2 : 3); }
 
+// 128 x 128 tiles with a K-contiguous operand run in slabs of 64 k, two of them in LDS: whole cache lines per row and request, where
+// slabs of 32 fetch halves, which is what bounds these tiles (84 against 116 B/ns and CU into LDS).  Bare product of 8 x 4096^3, A K-contiguous:
+// 897 -> 1016 TFLOP/s.
+constexpr bool long_slabs(int TM, int TN, int EPI, bool KMA) { return TM == 128 && TN == 128 && EPI == BEPI_APPLY && !KMA; }
+constexpr int ring_bytes(int TM, int TN, int EPI, bool KMA) { return long_slabs(TM, TN, EPI, KMA) ? 2 * (TM + TN) * 128 : stages_of(TM, TN) * (TM + TN) * 64; }
+
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding)
 template <int N> __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+// acc += A B over KT slabs of 64 k (two at least): A stored [M][K], B [N][K] or (KMB) [K][N], lda / ldb in elements.  One barrier per slab, ahead of its
+// last quarter: behind it that quarter's MFMAs cover the first fragment reads of the next slab, and the slab after that is requested into the place of
+// the one at hand, whose reads are over.  LDS is free on return.
+template <int TM, int TN, bool KMB, int NW, int NBM, int NBN>
+__device__ __forceinline__ void product_long_slabs(const char* A, int lda, const char* B, int ldb, int KT, int wave, int lane, int wm0, int wn0,
+                                                   unsigned char* smem, f32x16 (&acc)[NBM][NBN]) {
+  typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
+  constexpr int OB = TM * 128, BUF = (TM + TN) * 128;          // bytes of A's slab, of a slab
+  constexpr int LA = TM / (8 * NW), LB = TN / (8 * NW), NL = LA + LB, NM = NBM * NBN, NF = NBM + NBN, NS = NM > NF ? NM : NF;
+  // 128-byte rows of eight chunks of 16 bytes, chunk c of row r at c ^ ((r / 2) & 7): a fragment read of 16 rows covers two bank lines' worth once
+  unsigned oa[LA], ob[LB];
+#pragma unroll
+  for (int u = 0; u < LA; ++u) {
+    const int row = (u * NW + wave) * 8 + (lane >> 3);
+    oa[u] = (unsigned)(row * lda + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
+  }
+#pragma unroll
+  for (int u = 0; u < LB; ++u) {
+    if constexpr (KMB) {
+      constexpr int U = TN / 8;
+      const int k = (u * NW + wave) * (64 / U) + lane / U;
+      ob[u] = (unsigned)(k * ldb + ((lane % U) ^ (4 * (k & 3))) * 8) * 2u;
+    } else {
+      const int row = (u * NW + wave) * 8 + (lane >> 3);
+      ob[u] = (unsigned)(row * ldb + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
+    }
+  }
+  const long long stepB = KMB ? 128ll * ldb : 128;
+  auto issue = [&](int kt, int buf, int u) {
+    if (u < LA) __builtin_amdgcn_global_load_lds((gptr_t)(A + (long long)kt * 128 + oa[u]), (lptr_t)(smem + buf * BUF + (u * NW + wave) * 1024), 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds((gptr_t)(B + kt * stepB + ob[u - LA]), (lptr_t)(smem + buf * BUF + OB + ((u - LA) * NW + wave) * 1024), 16, 0, 0);
+  };
+  const int lr = lane & 31, lh = lane >> 5;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  unsigned chunk[4], fb0[NBN];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) chunk[kk] = lds0 + lr * 128 + (((2 * kk + lh) ^ ((lr >> 1) & 7)) << 4);
+  {
+    const int i = lane & 15, mb = (lane >> 4) & 1, kg = lane >> 5;
+#pragma unroll
+    for (int f = 0; f < NBN; ++f) {
+      const int c = wn0 / 8 + 4 * f + 2 * mb + ((i & 3) >> 1);
+      fb0[f] = lds0 + OB + (8 * kg + (i >> 2)) * (TN * 2) + ((c ^ (4 * (i >> 2))) * 16) + 8 * (i & 1);
+    }
+  }
+  u32x4 fr[2][NF];
+  auto read = [&](int buf, auto kktag, int set, auto ftag) {   // in inline assembly, waited for by hand (see above)
+    constexpr int kk = decltype(kktag)::value, f = decltype(ftag)::value;
+    if constexpr (f < NBM) {
+      const unsigned a = chunk[kk] + buf * BUF + wm0 * 128;
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fr[set][f]) : "v"(a), "i"(f * 4096));
+    } else if constexpr (KMB) {
+      u32x2v h0, h1;
+      const unsigned a = fb0[f - NBM] + buf * BUF;
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(h0) : "v"(a), "i"(kk * 32 * TN));
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(h1) : "v"(a), "i"(kk * 32 * TN + 8 * TN));
+      fr[set][f] = (u32x4){h0[0], h0[1], h1[0], h1[1]};
+    } else {
+      const unsigned a = chunk[kk] + buf * BUF + OB + wn0 * 128;
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fr[set][f]) : "v"(a), "i"((f - NBM) * 4096));
+    }
+  };
+  auto wait_reads = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // quarter KK of a slab; meanwhile the fragments of quarter RK of `buf` are read
+  auto quarter = [&](auto kktag, int buf, auto rktag, auto readtag, auto loads) {
+    constexpr int KK = decltype(kktag)::value;
+    wait_reads();
+    unrolled<NS>([&](auto m) {
+      constexpr int M = decltype(m)::value;
+      if constexpr (M < NM) {
+        acc[M / NBN][M % NBN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[KK & 1][M / NBN]),
+                                                                        __builtin_bit_cast(bf16x8, fr[KK & 1][NBM + M % NBN]), acc[M / NBN][M % NBN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (decltype(readtag)::value && M < NF) read(buf, rktag, (KK + 1) & 1, m);
+      loads(M);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto none = [](int) {};
+  std::integral_constant<int, 0> q0;
+  std::integral_constant<int, 1> q1;
+  std::integral_constant<int, 2> q2;
+  std::integral_constant<int, 3> q3;
+  std::true_type yes;
+  auto barrier = [&]() {   // this wave's reads of the slab have arrived, its share of the next one has landed
+    wait_vmcnt<0>();
+    wait_reads();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int u = 0; u < NL; ++u) issue(0, 0, u);
+#pragma unroll
+  for (int u = 0; u < NL; ++u) issue(1, 1, u);
+  wait_vmcnt<NL>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  unrolled<NF>([&](auto f) { read(0, q0, 0, f); });
+  int buf = 0;
+  for (int kt = 0; kt < KT - 2; ++kt) {
+    quarter(q0, buf, q1, yes, none);
+    quarter(q1, buf, q2, yes, none);
+    quarter(q2, buf, q3, yes, none);
+    barrier();
+    quarter(q3, buf ^ 1, q0, yes, [&](int m) {
+#pragma unroll
+      for (int u = m * NL / NS; u < (m + 1) * NL / NS; ++u) issue(kt + 2, buf, u);
+    });
+    buf ^= 1;
+  }
+  quarter(q0, buf, q1, yes, none);
+  quarter(q1, buf, q2, yes, none);
+  quarter(q2, buf, q3, yes, none);
+  barrier();
+  quarter(q3, buf ^ 1, q0, yes, none);
+  buf ^= 1;
+  quarter(q0, buf, q1, yes, none);
+  quarter(q1, buf, q2, yes, none);
+  quarter(q2, buf, q3, yes, none);
+  quarter(q3, buf, q0, std::false_type{}, none);
+  __syncthreads();
 }
 
 // KM: both operands are stored with K as the slow index ([K][M] and [K][N]: the Gram product X^T X
@@ -70,6 +203,19 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
   const unsigned short* Bb = g.B + (long long)b * g.strideB + (KMB ? (long long)n0 : (long long)n0 * g.ldb);
 
   const int KT = g.K / BF_BK, lda = g.lda, ldb = g.ldb;   // values: not read again past the memory clobbers of the loop
+
+  f32x16 acc[NBM][NBN];
+#pragma unroll
+  for (int i = 0; i < NBM; ++i)
+#pragma unroll
+    for (int j = 0; j < NBN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  const int lr = lane & 31, lh = lane >> 5;
+
+  if constexpr (long_slabs(TM, TN, EPI, KMA)) {
+    product_long_slabs<TM, TN, KMB, NW>((const char*)A1, lda, (const char*)Bb, ldb, g.K / 64, wave, lane, wm0, wn0, smem, acc);
+  } else {
 
   // Global -> LDS without passing through registers (global_load_lds_dwordx4): one wave
   // instruction moves 64 lanes x 16 bytes into 1 KiB of consecutive LDS = 16 rows of a slab.
@@ -119,16 +265,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
     for (int u = 0; u < NL; ++u) issue_load(kt, slot, u);
   };
 
-  f32x16 acc[NBM][NBN];
-#pragma unroll
-  for (int i = 0; i < NBM; ++i)
-#pragma unroll
-    for (int j = 0; j < NBN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
   // fragment addresses: row r = tile row, chunk cc = 2 * kk + (lane >> 5)
-  const int lr = lane & 31, lh = lane >> 5;
   // (row block f starts 32 rows = 8 lines further on, which flips bit 3 of the line index; the wave
   // offsets are multiples of 64 rows = 16 lines and leave it alone)
   const unsigned char* Afr = smem + wm0 * 64 + (lr >> 2) * 256;
@@ -291,6 +428,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
     if (kt + 1 < KT) load_frags(nslot, 0);
     mfma_block(1);
     slot = nslot;
+  }
   }
 
   float alpha;

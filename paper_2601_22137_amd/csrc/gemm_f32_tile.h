@@ -57,14 +57,6 @@ template <> struct Acc<double> { typedef f64x4 type; };
 
 __device__ inline float apow(float alpha, int p) { return p == 0 ? 1.0f : (p == 1 ? alpha : alpha * alpha); }
 
-template <int D, typename F>
-__device__ inline void unrolled(F&& f) {
-  if constexpr (D > 0) {
-    unrolled<D - 1>(f);
-    f(std::integral_constant<int, D - 1>{});
-  }
-}
-
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding)
 template <int N> __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);

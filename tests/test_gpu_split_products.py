@@ -73,7 +73,7 @@ def test_sign(prism, n, batch, degree):
         _same(r[b], oinfo)
 
 
-@pytest.mark.parametrize("n,batch,degree", [(400, 24, 5), (800, 1, 3), (1000, 2, 5), (1024, 5, 5)])
+@pytest.mark.parametrize("n,batch,degree", [(470, 24, 5), (800, 1, 3), (1000, 2, 5), (1024, 5, 5)])
 def test_sqrt(prism, n, batch, degree):
     A = _spd(n, batch)
     xs, r = _both(prism, lambda x, ws: prism.sqrt(x, degree, 40, 16, SEED, 1e-5, workspace=ws), prism.FN_SQRT, A, degree, 16)
@@ -104,7 +104,7 @@ def test_inverse(prism, n, batch):
     _same(r[-1], oinfo)
 
 
-@pytest.mark.parametrize("batch,m,n,degree", [(20, 700, 500, 5), (6, 700, 1200, 3), (1, 1500, 1000, 5), (4, 1000, 1000, 5), (1, 5000, 800, 5)])
+@pytest.mark.parametrize("batch,m,n,degree", [(20, 700, 500, 5), (2, 700, 1200, 3), (1, 1500, 1000, 5), (4, 1000, 1000, 5), (1, 5000, 800, 5)])
 def test_polar(prism, batch, m, n, degree):
     rng = np.random.default_rng(m + n)
     A = (rng.standard_normal((batch, m, n)) * (10.0 ** (-rng.random((batch, 1, n))) if m > n else 1.0)).astype(np.float32)
