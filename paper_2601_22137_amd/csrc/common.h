@@ -354,9 +354,9 @@ void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np
 // ---- dbnewton.hip : pieces of the DB Newton iteration (App. A.2) ----
 // N = M^{-1} of the SPD matrices M[batch][np][np] by block Gauss-Jordan.  scratch: spd_inverse_scratch_floats(np, batch)
 // floats, 16-byte aligned.
-// sel_batch: the batch that picks blocks and tiles, where these matrices are a part of a larger one.
+// sel_batch: the batch that picks blocks and tiles, where these matrices are a part of a larger one.  sync: [batch][FIT_SYNC_WORDS].
 long long spd_inverse_scratch_floats(int np, int batch, int sel_batch);
-int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, hipStream_t s);
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, unsigned* sync, hipStream_t s);
 // partial sums of <D0,D0>, <D0,D2>, <D2,D2> (D0 = M - I, D2 = M + N - 2I) -> the five coefficient partials
 void launch_db_moments(const float* M, const float* N, int np, int n_true, int batch, const Ctrl* ctrl, double* cpart,
                        int ngroups, hipStream_t s);

@@ -154,12 +154,14 @@ __device__ inline void invert64(f64x4 (&acc)[4], Inv64Lds& m) {
   }
 }
 
-// P = inverse of the leading 64 x 64 block of every matrix (the first pivot of an elimination)
+// P = inverse of the leading 64 x 64 block of every matrix (the first pivot of an elimination); sync (may be null) is zeroed
 __global__ __launch_bounds__(NT) void first_pivot_kernel(const float* __restrict__ S, long long stride, int ld,
-                                                         float* __restrict__ P, const Ctrl* __restrict__ ctrl) {
+                                                         float* __restrict__ P, unsigned* __restrict__ sync, const Ctrl* __restrict__ ctrl) {
   const int b = blockIdx.x;
   if (ctrl && ctrl[b].done) return;
   __shared__ Inv64Lds m;
+  if (sync && threadIdx.x < FIT_SYNC_WORDS) sync[(long long)b * FIT_SYNC_WORDS + threadIdx.x] = 0u;
+  static_assert(FIT_SYNC_WORDS <= NT, "one pass");
   const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4, w = threadIdx.x >> 6;
   const float* blk = S + (long long)b * stride + (long long)(16 * w + lq) * ld + lr;
   f64x4 acc[4];
@@ -204,13 +206,103 @@ __device__ inline void mma64(const float* As, const float* Bs, int m0, int n0, f
   }
 }
 
-// One elimination step with the 64 x 64 pivot k of every n x n matrix, from S to D (a tile is read by many
-// workgroups, so not in place): one workgroup per 64 x 64 tile,
+// One elimination step with the 64 x 64 pivot k of an n x n matrix, from S to D (a tile is read by many
+// workgroups, so not in place), tile (ti, tj):
 //   D_kk = P, D_kj = P S_kj, D_ik = -S_ik P, D_ij = S_ij - S_ik (P S_kj),
-// P = S_kk^-1 from the step before.  The workgroup of tile (k + 1, k + 1), the first of its matrix, goes on to
-// invert it: P of the next step.  What bounds it: on small matrices that inverse (a serial chain; the other tiles
-// finish meanwhile), on large ones the sweep of S and D.  Every workgroup forms P S_kj for itself, twice the
-// products of the update alone, instead of a launch of its own for the pivot row and one for the column.
+// P = S_kk^-1 from the step before.  `pivot` (tile (k + 1, k + 1)): inverts its result, P of the next step.
+// Every tile forms P S_kj for itself, twice the products of the update alone, instead of a launch of its own for the pivot row and
+// one for the column.  COH: the other tiles are done by workgroups of the same launch: past the caches that are not coherent
+// between XCDs (sc1, as agent-scope atomics have it).
+union JordanLds {
+  float t[3][BS * SL];                       // P, S_kj (later P S_kj), S_ik (later the result)
+  Inv64Lds inv;                              // over the first two
+};
+static_assert(sizeof(Inv64Lds) <= 2 * BS * SL * sizeof(float), "the inverse leaves the third array alone");
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline __amdgpu_buffer_rsrc_t past_caches(const void* base) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7ffffff0, 0x00027000); }
+template <bool COH> __device__ inline f32x4 get4(const float* base, int at) {   // at: less than 2^29
+  if constexpr (COH) return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(past_caches(base), at * 4, 0, 16));
+  else return *(const f32x4*)(base + at);
+}
+template <bool COH> __device__ inline void put4(float* base, int at, f32x4 v) {
+  if constexpr (COH) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), past_caches(base), at * 4, 0, 16);
+  else *(f32x4*)(base + at) = v;
+}
+template <bool COH>
+__device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, const float* P, float* Pnext, int k, int ti, int tj, bool pivot, JordanLds& m) {
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4, w = t >> 6;
+  const bool prow = ti == k, pcol = tj == k;
+  const int r0 = t >> 4, c0 = (t & 15) * 4;   // copies: 16 rows of 16 bytes per thread and pass
+  f32x4 vp[4], vb[4], va[4], old[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + 16 * q;
+    vp[q] = get4<COH>(P, r * BS + c0);
+    vb[q] = pcol ? vp[q] : get4<COH>(S, (k * BS + r) * sld + tj * BS + c0);
+    va[q] = prow ? vp[q] : get4<COH>(S, (ti * BS + r) * sld + k * BS + c0);
+    old[q] = !prow && !pcol ? get4<COH>(S, (ti * BS + r) * sld + tj * BS + c0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  if (prow && pcol) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) put4<COH>(D, (ti * BS + r0 + 16 * q) * dld + tj * BS + c0, vp[q]);
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int o = (r0 + 16 * q) * SL + c0;
+    *(f32x4*)&m.t[0][o] = vp[q]; *(f32x4*)&m.t[1][o] = vb[q]; *(f32x4*)&m.t[2][o] = va[q];
+  }
+  __syncthreads();
+  const int m0 = (w >> 1) * 32, n0 = (w & 1) * 32;
+  f32x4 acc[2][2];
+  auto into = [&](float* x) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[(m0 + 16 * i + 4 * lq + r) * SL + n0 + 16 * j + lr] = acc[i][j][r];
+  };
+  if (!pcol) {                               // T = P S_kj
+    mma64(m.t[0], m.t[1], m0, n0, acc);
+    if (!prow) {
+      __syncthreads();
+      into(m.t[1]);
+      __syncthreads();
+    }
+  }
+  if (!prow) mma64(m.t[2], m.t[1], m0, n0, acc);   // S_ik T, or S_ik P
+  __syncthreads();
+  into(m.t[2]);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float* p = &m.t[2][(r0 + 16 * q) * SL + c0];
+    f32x4 v = *(const f32x4*)p;
+    if (!prow) v = old[q] - v;
+    put4<COH>(D, (ti * BS + r0 + 16 * q) * dld + tj * BS + c0, v);
+    if (pivot) *(f32x4*)p = v;
+  }
+  if (!pivot) return;
+  __syncthreads();
+  f64x4 v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[j][r] = (double)m.t[2][(16 * w + 4 * r + lq) * SL + 16 * j + lr];
+  invert64(v, m.inv);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m.t[2][(16 * w + 4 * r + lq) * SL + 16 * j + lr] = (float)v[j][r];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) put4<COH>(Pnext, (r0 + 16 * q) * BS + c0, *(const f32x4*)&m.t[2][(r0 + 16 * q) * SL + c0]);
+}
+
+// A step for all tiles of every matrix: one workgroup each, the pivot the first of its matrix.  What bounds it: on small matrices that
+// inverse (a serial chain; the other tiles finish meanwhile), on large ones the sweep of S and D.
 // 2 x 2048^2, a block of 512: 8 steps of 17 us; the pivot kernel of one barrier per row (87 us) and the three products
 // that this replaces took 8 times 105 us.
 struct StepArgs {
@@ -223,101 +315,97 @@ struct StepArgs {
 __global__ __launch_bounds__(NT) void jordan_step_kernel(StepArgs g) {
   const int b = blockIdx.y;
   if (g.ctrl && g.ctrl[b].done) return;
-  __shared__ __align__(16) union {
-    float t[3][BS * SL];                     // P, S_kj (later P S_kj), S_ik (later the new tile)
-    Inv64Lds inv;                            // over the first two
-  } m;
-  static_assert(sizeof(Inv64Lds) <= 2 * BS * SL * sizeof(float), "the inverse leaves the third array alone");
-  const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4, w = t >> 6;
-  const int next = g.k + 1 < g.nt ? (g.k + 1) * (g.nt + 1) : 0;
+  __shared__ __align__(16) JordanLds m;
+  const bool more = g.k + 1 < g.nt;
+  const int next = more ? (g.k + 1) * (g.nt + 1) : 0;
   const int idx = blockIdx.x == 0 ? next : ((int)blockIdx.x == next ? 0 : (int)blockIdx.x);
-  const int ti = idx / g.nt, tj = idx - ti * g.nt;
-  const bool prow = ti == g.k, pcol = tj == g.k;
-  const float* S = g.S + (long long)b * g.sstride;
-  const float* P = g.P + ((long long)b * 2 + (g.k & 1)) * BS * BS;
-  float* D = g.D + (long long)b * g.dstride + (long long)(ti * BS) * g.dld + tj * BS;
-  const int r0 = t >> 4, c0 = (t & 15) * 4;   // copies: 16 rows of 16 bytes per thread and pass
-  f32x4 vp[4], vb[4], va[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = r0 + 16 * q;
-    vp[q] = *(const f32x4*)(P + r * BS + c0);
-    vb[q] = pcol ? vp[q] : *(const f32x4*)(S + (long long)(g.k * BS + r) * g.sld + tj * BS + c0);
-    va[q] = prow ? vp[q] : *(const f32x4*)(S + (long long)(ti * BS + r) * g.sld + g.k * BS + c0);
-  }
-  if (prow && pcol) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) *(f32x4*)(D + (long long)(r0 + 16 * q) * g.dld + c0) = vp[q];
-    return;
-  }
-  const int m0 = (w >> 1) * 32, n0 = (w & 1) * 32;
-  f32x4 old[2][2], acc[2][2];
-  if (!prow && !pcol) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          old[i][j][r] = S[(long long)(ti * BS + m0 + 16 * i + 4 * lq + r) * g.sld + tj * BS + n0 + 16 * j + lr];
-  } else {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) old[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int o = (r0 + 16 * q) * SL + c0;
-    *(f32x4*)&m.t[0][o] = vp[q]; *(f32x4*)&m.t[1][o] = vb[q]; *(f32x4*)&m.t[2][o] = va[q];
-  }
+  float* P = g.P + (long long)b * 2 * BS * BS;
+  jordan_tile<false>(g.S + (long long)b * g.sstride, g.sld, g.D + (long long)b * g.dstride, g.dld, P + (g.k & 1) * BS * BS, P + (~g.k & 1) * BS * BS, g.k,
+                     idx / g.nt, idx % g.nt, more && blockIdx.x == 0, m);
+}
+
+// All steps in one launch.  A launch per step leaves 5 of its 17 us to the launch, the loads at its start and the stores at its end, and is there
+// again for every iteration enqueued past convergence.  Here one workgroup of a matrix does the pivot tiles, one after the other, and waits
+// for nothing but the tiles of the step before; the others take tiles by number.  2 x 512^2 (8 steps): 152 -> 108 us.
+// Waits end wherever the workgroups are: who waits holds a tile of step k and waits for steps before k, whose tiles have lower numbers and
+// were taken by workgroups that run; the pivot workgroup, before it waits, takes what nobody has taken yet.
+struct SweepArgs {
+  const float* S; long long sstride; int sld;   // step k reads S (k = 0) or what k - 1 wrote, and writes tmp and out in turn, the last one out
+  float* out; long long ostride; int old;
+  float* tmp; long long tstride; int tld;
+  float* P;                                  // as above
+  unsigned* sync;                            // [batch][FIT_SYNC_WORDS], zeroed by the launch before: tiles taken, tiles done
+  int nt;                                    // two at least
+  const Ctrl* ctrl;
+};
+__global__ __launch_bounds__(NT, 3) void jordan_sweep_kernel(SweepArgs g) {
+  const int b = blockIdx.y, t = threadIdx.x, nt = g.nt, all = nt * nt;
+  if (g.ctrl && g.ctrl[b].done) return;
+  __shared__ __align__(16) JordanLds m;
+  __shared__ int s_job;
+  constexpr int PIVOT = -1, LEAVE = -2;
+  unsigned* taken = g.sync + (long long)b * FIT_SYNC_WORDS;
+  unsigned* done = taken + 32;
+  auto load = [](unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto take = [&]() { return (int)__hip_atomic_fetch_add(taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - 1; };
+  // tiles by number: all - 1 in a step (without the next pivot), all in the last one
+  const int total = nt * (all - 1) + 1;
+  auto step_of = [&](int id) { const int k = id / (all - 1); return k < nt ? k : nt - 1; };
+  auto wait = [&](int id) {                  // one thread: until all steps before that of tile id are done
+    const unsigned need = (unsigned)(step_of(id) * all);
+    while (load(done) < need) __builtin_amdgcn_s_sleep(1);
+  };
+  if (t == 0) s_job = take();
   __syncthreads();
-  if (!pcol) {                               // T = P S_kj
-    mma64(m.t[0], m.t[1], m0, n0, acc);
-    if (!prow) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) m.t[1][(m0 + 16 * i + 4 * lq + r) * SL + n0 + 16 * j + lr] = acc[i][j][r];
-      __syncthreads();
+  int id = __builtin_amdgcn_readfirstlane(s_job), kp = 0;
+  bool chain = id < 0;                       // the first of its matrix: pivots, step kp next
+  __syncthreads();
+  float* P = g.P + (long long)b * 2 * BS * BS;
+  for (;;) {
+    if (t == 0) {
+      if (chain) {
+        for (;;) {
+          if (load(done) >= (unsigned)(kp * all)) { s_job = PIVOT; break; }
+          unsigned n = load(taken);          // one more than the tiles taken
+          if ((int)n - 1 < kp * (all - 1)) {
+            if (__hip_atomic_compare_exchange_strong(taken, &n, n + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+              wait((int)n - 1);
+              s_job = (int)n - 1;
+              break;
+            }
+          } else {
+            __builtin_amdgcn_s_sleep(1);
+          }
+        }
+      } else {
+        if (id < 0) id = take();
+        if (id >= total) s_job = LEAVE;
+        else { wait(id); s_job = id; }
+      }
     }
+    __syncthreads();
+    const int job = __builtin_amdgcn_readfirstlane(s_job);
+    if (job == LEAVE) return;
+    int k, idx;
+    if (job == PIVOT) {
+      k = kp;
+      idx = (k + 1) * (nt + 1);
+    } else {
+      k = step_of(job);
+      idx = job - k * (all - 1);
+      if (k + 1 < nt && idx >= (k + 1) * (nt + 1)) ++idx;
+    }
+    const bool to_tmp = (nt - 1 - k) & 1;
+    const float* S = k == 0 ? g.S + (long long)b * g.sstride : (to_tmp ? g.out + (long long)b * g.ostride : g.tmp + (long long)b * g.tstride);
+    const int sld = k == 0 ? g.sld : (to_tmp ? g.old : g.tld);
+    float* D = to_tmp ? g.tmp + (long long)b * g.tstride : g.out + (long long)b * g.ostride;
+    jordan_tile<true>(S, sld, D, to_tmp ? g.tld : g.old, P + (k & 1) * BS * BS, P + (~k & 1) * BS * BS, k, idx / nt, idx % nt, job == PIVOT, m);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the tile has reached memory
+    __syncthreads();
+    if (t == 0) __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (job == PIVOT && ++kp == nt - 1) chain = false;
+    id = -1;
   }
-  if (!prow) {                               // old - S_ik T, or -S_ik P
-    mma64(m.t[2], m.t[1], m0, n0, acc);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = old[i][j] - acc[i][j];
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) D[(long long)(m0 + 16 * i + 4 * lq + r) * g.dld + n0 + 16 * j + lr] = acc[i][j][r];
-  if (g.k + 1 >= g.nt || blockIdx.x != 0) return;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) m.t[2][(m0 + 16 * i + 4 * lq + r) * SL + n0 + 16 * j + lr] = acc[i][j][r];
-  __syncthreads();
-  f64x4 v[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[j][r] = (double)m.t[2][(16 * w + 4 * r + lq) * SL + 16 * j + lr];
-  invert64(v, m.inv);
-  float* out = g.P + ((long long)b * 2 + ((g.k + 1) & 1)) * BS * BS;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[(16 * w + 4 * r + lq) * BS + 16 * j + lr] = (float)v[j][r];
 }
 
 // grid (groups, batch): partial sums of the three inner products over the true n x n part; the
@@ -490,9 +578,19 @@ __global__ __launch_bounds__(NT) void panels_kernel(const float* __restrict__ T,
 // Inverse of n x n SPD matrices by block Gauss-Jordan with pivots of 64, n a multiple of 64: from src to out, through
 // tmp (each with its leading dimension and batch stride).  src may be out if n / 64 is even, tmp if it is odd.
 struct Mat { float* p; long long stride; int ld; };
-void gauss_jordan_64(Mat src, Mat out, Mat tmp, float* P, int n, int batch, const Ctrl* ctrl, hipStream_t s) {
+// In one launch up to two workgroups per CU, by the batch of the whole group.  More of them wait in each other's way (order 1728, 729 workgroups: 0.59 ms, in one
+// launch 1.55).
+void gauss_jordan_64(Mat src, Mat out, Mat tmp, float* P, unsigned* sync, int n, int batch, int sel_batch, const Ctrl* ctrl, hipStream_t s) {
   const int nt = n / BS;
-  hipLaunchKernelGGL(first_pivot_kernel, dim3(batch), dim3(NT), 0, s, src.p, src.stride, src.ld, P, ctrl);
+  const bool one = nt > 1 && (long long)nt * nt * sel_batch <= 512;
+  hipLaunchKernelGGL(first_pivot_kernel, dim3(batch), dim3(NT), 0, s, src.p, src.stride, src.ld, P, one ? sync : nullptr, ctrl);
+  if (one) {
+    SweepArgs a = {};
+    a.S = src.p; a.sstride = src.stride; a.sld = src.ld; a.out = out.p; a.ostride = out.stride; a.old = out.ld;
+    a.tmp = tmp.p; a.tstride = tmp.stride; a.tld = tmp.ld; a.P = P; a.sync = sync; a.nt = nt; a.ctrl = ctrl;
+    hipLaunchKernelGGL(jordan_sweep_kernel, dim3(nt * nt, batch), dim3(NT), 0, s, a);
+    return;
+  }
   for (int k = 0; k < nt; ++k) {
     const Mat dst = ((nt - 1 - k) & 1) ? tmp : out;
     StepArgs a = {};
@@ -520,8 +618,8 @@ long long spd_inverse_scratch_floats(int np, int batch, int sel_batch) {
   return (2ll * BS * BS + n * n + OB * np) * batch;
 }
 
-int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, hipStream_t s) {
-  if (np % BS || batch <= 0 || !scratch) return PRISM_EINVAL;
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, unsigned* sync, hipStream_t s) {
+  if (np % BS || batch <= 0 || !scratch || !sync) return PRISM_EINVAL;
   const long long per_mat = (long long)np * np;
   const int OB = outer_block(np, sel_batch);
   float* P = scratch;
@@ -534,7 +632,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
     const Mat out = {N, per_mat, np};
     Mat src = {const_cast<float*>(M), per_mat, np};
     if (M == N && ((np / BS) & 1)) { copy(M, tmp.p); src = tmp; }
-    gauss_jordan_64(src, out, tmp, P, np, batch, ctrl, s);
+    gauss_jordan_64(src, out, tmp, P, sync, np, batch, sel_batch, ctrl, s);
     return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
   }
   if (M != N) copy(M, N);
@@ -545,7 +643,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
     float* rowk = N + (long long)k * OB * np;
     float* colk = N + k * OB;
     const Mat piv = {Pk, per_mat, np};
-    gauss_jordan_64(piv, piv, tmp, P, OB, batch, ctrl, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
+    gauss_jordan_64(piv, piv, tmp, P, sync, OB, batch, sel_batch, ctrl, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
     GemmDesc g = {};
     g.batch = batch; g.sel_batch = sel_batch; g.ctrl = ctrl; g.K = OB; g.epi = EPI_STORE; g.c_in = 1.0f;
     GemmDesc r = g;                                      // T = P A_k,:
