@@ -131,11 +131,13 @@ struct Bf16Desc {
 // One launch over up to BF16_MAX_GROUPS products of the same kind (epilogue, symmetry) and
 // different shapes: workgroup index -> (group, matrix, tile) through the running tile counts.
 constexpr int BF16_MAX_GROUPS = 8;
+enum { XCD_LAUNCH = 1, XCD_GROUPS = 2 };
 struct Bf16Multi {
   Bf16Desc d[BF16_MAX_GROUPS];
   int tile_start[BF16_MAX_GROUPS + 1];               // set by the launcher
   int ngroups;
-  int xcd_private;                                   // set by the launcher: contiguous tile ranges per XCD
+  int xcd_private;                                   // set by the launcher: contiguous tile ranges per XCD, of each group or of the launch
+  // (XCD_GROUPS: starts are multiples of 8)
   int waves8;                                        // set by the launcher: 256 x 256 tiles run with eight wavefronts
 };
 // tile_m x tile_n: 256 x 256, 256 x 128 or 128 x 128; M, N of every group must be multiples of them

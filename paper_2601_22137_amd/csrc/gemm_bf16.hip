@@ -35,14 +35,15 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : (long_slabs(TM, TN, EPI, KM
   // operands of the launch fit the Infinity Cache together): every XCD gets a contiguous range of the
   // tiles of each group, i.e. whole matrices, so that the tiles sharing a panel share an L2 (without this the
   // 768-sized Gram fetched 7x its algorithmic bytes).  Of each group, not of the launch: the groups differ in K, and
-  // four XCDs of eight had all of the long ones.  Otherwise workgroup i runs tile i: all XCDs
+  // four XCDs of eight had all of the long ones (small launches: of the launch, see launch_tw).  Otherwise workgroup i runs tile i: all XCDs
   // sweep the same matrix and share its panels through the Infinity Cache (private ranges measured
   // 20 % slower at 8 x 4096^2, where eight matrices at once overflow that cache).
   int wg = blockIdx.x;
+  if (mg.xcd_private == XCD_LAUNCH) wg = (wg & 7) * (mg.tile_start[mg.ngroups] >> 3) + (wg >> 3);
   int gi = 0;
   while (gi + 1 < mg.ngroups && wg >= mg.tile_start[gi + 1]) ++gi;
   wg -= mg.tile_start[gi];
-  if (mg.xcd_private) wg = (wg & 7) * ((mg.tile_start[gi + 1] - mg.tile_start[gi]) >> 3) + (wg >> 3);   // starts are multiples of 8
+  if (mg.xcd_private == XCD_GROUPS) wg = (wg & 7) * ((mg.tile_start[gi + 1] - mg.tile_start[gi]) >> 3) + (wg >> 3);   // starts are multiples of 8
   const Bf16Desc& g = mg.d[gi];
 
   // SYM: A == B and the result is symmetric (Gram matrix, R^2): only the tiles that reach the
@@ -96,12 +97,14 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
     total += tiles_per_matrix<TM, TN, SYM>(g) * g.batch;
     operand_bytes += 2.0 * g.batch * ((double)g.M * g.K + (g.A == g.B ? 0.0 : (double)g.N * g.K));
   }
-  if (total % 8 != 0 && operand_bytes < 32.0 * 1024 * 1024) mg.xcd_private = 0;
+  // Launches of several rounds are rounded up too, small ones keep whole ranges of the launch (three updates of five layers of width 320, update of 465 tiles
+  // and Gram product of 120: 182 us with plain order and groups, 168 with groups and the launch).
+  if (mg.xcd_private) mg.xcd_private = operand_bytes >= 32.0 * 1024 * 1024 || total > 256 ? XCD_GROUPS : (total % 8 == 0 ? XCD_LAUNCH : 0);
   total = 0;
   for (int i = 0; i < mg.ngroups; ++i) {
     mg.tile_start[i] = (int)total;
     total += tiles_per_matrix<TM, TN, SYM>(mg.d[i]) * mg.d[i].batch;
-    if (mg.xcd_private) total = (total + 7) & ~7ll;
+    if (mg.xcd_private == XCD_GROUPS) total = (total + 7) & ~7ll;
     if (total > 0x7fffffff) return PRISM_EUNSUPPORTED;
   }
   mg.tile_start[mg.ngroups] = (int)total;
