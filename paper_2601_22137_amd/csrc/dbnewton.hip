@@ -324,9 +324,10 @@ __global__ __launch_bounds__(NT) void jordan_step_kernel(StepArgs g) {
                      idx / g.nt, idx % g.nt, more && blockIdx.x == 0, m);
 }
 
-// All steps in one launch.  A launch per step leaves 5 of its 17 us to the launch, the loads at its start and the stores at its end, and is there
-// again for every iteration enqueued past convergence.  Here one workgroup of a matrix does the pivot tiles, one after the other, and waits
-// for nothing but the tiles of the step before; the others take tiles by number.  2 x 512^2 (8 steps): 152 -> 108 us.
+// All steps in one launch: between steps a hand-over instead of a launch, and one launch instead of nt for every iteration enqueued past convergence.
+// One workgroup of a matrix does the pivot tiles, one after the other, and waits for nothing but the tiles of the step before; the others take
+// tiles by number.  What bounds it: the inverse of a pivot, 10 of 15 us per step.  2 x 512^2 (8 steps) 144 -> 135 us, 768 x 2 231 -> 211; in calls of DB
+// Newton, whose budget is mostly past convergence, 2 x 2048^2 5.71 -> 5.22 ms, 2 x 512^2 0.995 -> 0.882.
 // Waits end wherever the workgroups are: who waits holds a tile of step k and waits for steps before k, whose tiles have lower numbers and
 // were taken by workgroups that run; the pivot workgroup, before it waits, takes what nobody has taken yet.
 struct SweepArgs {

@@ -396,7 +396,7 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* x, uint16_t* p
 }
 
 // Tile of a launch, from the rounds it takes.  A round is 256 workgroups of the larger tiles, one per CU, and 512 of the smallest, two per CU, in
-// 0.6 of the time of 256 of 128 x 128; one of 128 x 256 takes 1.9 of it.  Sign of n = 1000 (1024), us, tiles of 64 / 128 / 128 x 256: one matrix 841 / 1301 / 1978,
+// 0.6 of the time of 256 of 128 x 128; one of 128 x 256 takes 1.9 of it.  Sign of n = 1000 (1024), us, tiles of 64 / 128 / 256 x 128 (128 x 256 is 2 % faster): one matrix 841 / 1301 / 1978,
 // two 1192 / 1374 / 1996, four 1967 / 1693 / 2122, eight 3382 / 3034 / 2853; of 2048, one 3419 / 2896 / 3623, two 6190 / 5182 / 4884.
 struct SplitTile { int m, n; };
 SplitTile split_tile(int M, int N, int batch, int sym) {
