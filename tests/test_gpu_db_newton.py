@@ -157,3 +157,20 @@ def test_spd_inverse_pivots_at_the_ends_of_the_range(prism, n):
     d[[5, n - 2]] = np.float32(2.0 ** -126), np.float32(3.0e38)
     out = prism.spd_inverse(torch.from_numpy(np.diag(d)[None].copy()).cuda()).cpu().numpy()[0]
     assert np.array_equal(out, np.diag((1.0 / d.astype(np.float64)).astype(np.float32)))
+
+
+@pytest.mark.parametrize("n,few,many", [(128, 128, 129), (512, 8, 9), (448, 1, 11), (1024, 2, 3)])
+def test_eliminations_in_one_launch_and_in_steps(prism, n, few, many):
+    """Up to 512 tiles (n / 64 squared per matrix) all steps are one launch, beyond each is its own: the same operations, the same bits.
+    (Order 1024: from two matrices on with outer blocks or without, by the batch; compared with numpy only.)"""
+    rng = np.random.default_rng(n)
+    w = rng.standard_normal((n, 2 * n))
+    A = (w @ w.T / (2 * n) + 0.05 * np.eye(n)).astype(np.float32)
+    outs = [prism.spd_inverse(torch.from_numpy(A).cuda().repeat(b, 1, 1)) for b in (few, many)]
+    if n != 1024:
+        assert torch.equal(outs[0][0], outs[1][0])
+    for o in outs:
+        assert all(torch.equal(o[0], o[i]) for i in range(1, o.shape[0]))
+        x = o[0].cpu().numpy().astype(np.float64)
+        ref = np.linalg.inv(A.astype(np.float64))
+        assert np.linalg.norm(x - ref) / np.linalg.norm(ref) <= 1e-5
