@@ -220,11 +220,16 @@ union JordanLds {
 static_assert(sizeof(Inv64Lds) <= 2 * BS * SL * sizeof(float), "the inverse leaves the third array alone");
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ inline __amdgpu_buffer_rsrc_t past_caches(const void* base) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7ffffff0, 0x00027000); }
-template <bool COH> __device__ inline f32x4 get4(const float* base, int at) {   // at: less than 2^29
+// Entry (row, col) of a matrix with leading dimension ld.  A matrix may have more than 2^31 entries where a step is a launch; one that is swept in one
+// launch has 512 tiles at most, and offsets below 2^29.
+template <bool COH> using offset_t = std::conditional_t<COH, int, long long>;
+template <bool COH> __host__ __device__ constexpr offset_t<COH> offset_of(int row, int ld, int col) { return (offset_t<COH>)row * ld + col; }
+static_assert(offset_of<false>(46399, 46400, 46336) == 46399ll * 46400 + 46336, "in 64 bits");
+template <bool COH> __device__ inline f32x4 get4(const float* base, offset_t<COH> at) {
   if constexpr (COH) return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(past_caches(base), at * 4, 0, 16));
   else return *(const f32x4*)(base + at);
 }
-template <bool COH> __device__ inline void put4(float* base, int at, f32x4 v) {
+template <bool COH> __device__ inline void put4(float* base, offset_t<COH> at, f32x4 v) {
   if constexpr (COH) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), past_caches(base), at * 4, 0, 16);
   else *(f32x4*)(base + at) = v;
 }
@@ -238,13 +243,13 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
   for (int q = 0; q < 4; ++q) {
     const int r = r0 + 16 * q;
     vp[q] = get4<COH>(P, r * BS + c0);
-    vb[q] = pcol ? vp[q] : get4<COH>(S, (k * BS + r) * sld + tj * BS + c0);
-    va[q] = prow ? vp[q] : get4<COH>(S, (ti * BS + r) * sld + k * BS + c0);
-    old[q] = !prow && !pcol ? get4<COH>(S, (ti * BS + r) * sld + tj * BS + c0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    vb[q] = pcol ? vp[q] : get4<COH>(S, offset_of<COH>(k * BS + r, sld, tj * BS + c0));
+    va[q] = prow ? vp[q] : get4<COH>(S, offset_of<COH>(ti * BS + r, sld, k * BS + c0));
+    old[q] = !prow && !pcol ? get4<COH>(S, offset_of<COH>(ti * BS + r, sld, tj * BS + c0)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
   if (prow && pcol) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) put4<COH>(D, (ti * BS + r0 + 16 * q) * dld + tj * BS + c0, vp[q]);
+    for (int q = 0; q < 4; ++q) put4<COH>(D, offset_of<COH>(ti * BS + r0 + 16 * q, dld, tj * BS + c0), vp[q]);
     return;
   }
 #pragma unroll
@@ -280,7 +285,7 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
     float* p = &m.t[2][(r0 + 16 * q) * SL + c0];
     f32x4 v = *(const f32x4*)p;
     if (!prow) v = old[q] - v;
-    put4<COH>(D, (ti * BS + r0 + 16 * q) * dld + tj * BS + c0, v);
+    put4<COH>(D, offset_of<COH>(ti * BS + r0 + 16 * q, dld, tj * BS + c0), v);
     if (pivot) *(f32x4*)p = v;
   }
   if (!pivot) return;

@@ -119,3 +119,30 @@ def test_matrix_near_the_largest_extent(prism):
     assert abs(ref2 - n) <= 1e-6 * n            # the reference itself has orthonormal columns
     with pytest.raises(prism.PrismError):       # one tile row more crosses the limit
         prism.workspace_bytes(prism.FN_POLAR, 1, 4_194_400, 500, prism.F32, 5, 8)
+
+
+def test_spd_inverse_of_more_than_2_31_entries(prism):
+    """Order 46400 (no multiple of 256: pivots of 64 all the way, a launch per step): the last rows lie past 2^31 entries.  A diagonal matrix
+    but for a dense block on 96 rows spread over the whole order, so that the inverse is known: that of the block, reciprocals, zeros."""
+    n = 46400
+    rng = np.random.default_rng(6100)
+    idx = np.unique(np.concatenate([[0, 1, 63, 64, n - 65, n - 64, n - 1], rng.choice(n, 89, replace=False)]))
+    w = rng.standard_normal((idx.size, 2 * idx.size))
+    block = (w @ w.T / (2 * idx.size) + 0.1 * np.eye(idx.size)).astype(np.float32)
+    d = (1.0 + rng.random(n)).astype(np.float32)
+    a = torch.zeros((1, n, n), device="cuda")
+    a[0].diagonal().copy_(torch.from_numpy(d))
+    ti = torch.from_numpy(idx).cuda()
+    a[0][ti[:, None], ti[None, :]] = torch.from_numpy(block).cuda()
+    out = prism.spd_inverse(a)
+    del a
+    got = out[0][ti[:, None], ti[None, :]].cpu().numpy()
+    assert _rel(got, np.linalg.inv(block.astype(np.float64))) <= 1e-5
+    out[0][ti[:, None], ti[None, :]] = 0.0
+    rest = np.setdiff1d(np.arange(n), idx)
+    diag = out[0].diagonal()
+    assert np.abs(diag.cpu().numpy().astype(np.float64)[rest] * d[rest] - 1.0).max() <= 2.0 ** -23     # reciprocals, rounded (a few products with zeros)
+    diag.zero_()
+    assert not any(bool(out[0, r:r + 1024].any()) for r in range(0, n, 1024))
+    del out, diag
+    prism.release_workspaces()
