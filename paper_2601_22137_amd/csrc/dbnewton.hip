@@ -212,7 +212,8 @@ __device__ inline void mma64(const float* As, const float* Bs, int m0, int n0, f
 // P = S_kk^-1 from the step before.  `pivot` (tile (k + 1, k + 1)): inverts its result, P of the next step.
 // Every tile forms P S_kj for itself, twice the products of the update alone, instead of a launch of its own for the pivot row and
 // one for the column.  COH: the other tiles are done by workgroups of the same launch: past the caches that are not coherent
-// between XCDs (sc1, as agent-scope atomics have it).
+// between XCDs (sc1, as agent-scope atomics have it), in rows of 16 bytes per lane through LDS; otherwise straight from the
+// registers of the product (through LDS a launch of 400 tiles took 3 % longer: order 1280 391 -> 402 us).
 union JordanLds {
   float t[3][BS * SL];                       // P, S_kj (later P S_kj), S_ik (later the result)
   Inv64Lds inv;                              // over the first two
@@ -238,19 +239,28 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
   const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lq = lane >> 4, w = t >> 6;
   const bool prow = ti == k, pcol = tj == k;
   const int r0 = t >> 4, c0 = (t & 15) * 4;   // copies: 16 rows of 16 bytes per thread and pass
-  f32x4 vp[4], vb[4], va[4], old[4];
+  const int m0 = (w >> 1) * 32, n0 = (w & 1) * 32;
+  f32x4 vp[4], vb[4], va[4], old[4];          // old: rows, or blocks (i, j) of the product at 2 i + j
+  auto entry = [&](int i, int j, int r, int ld) { return offset_of<COH>(ti * BS + m0 + 16 * i + 4 * lq + r, ld, tj * BS + n0 + 16 * j + lr); };
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int r = r0 + 16 * q;
     vp[q] = get4<COH>(P, r * BS + c0);
     vb[q] = pcol ? vp[q] : get4<COH>(S, offset_of<COH>(k * BS + r, sld, tj * BS + c0));
     va[q] = prow ? vp[q] : get4<COH>(S, offset_of<COH>(ti * BS + r, sld, k * BS + c0));
-    old[q] = !prow && !pcol ? get4<COH>(S, offset_of<COH>(ti * BS + r, sld, tj * BS + c0)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    old[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (COH && !prow && !pcol) old[q] = get4<COH>(S, offset_of<COH>(ti * BS + r, sld, tj * BS + c0));
   }
   if (prow && pcol) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) put4<COH>(D, offset_of<COH>(ti * BS + r0 + 16 * q, dld, tj * BS + c0), vp[q]);
     return;
+  }
+  if (!COH && !prow && !pcol) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) old[q][r] = S[entry(q >> 1, q & 1, r, sld)];
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -258,7 +268,6 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
     *(f32x4*)&m.t[0][o] = vp[q]; *(f32x4*)&m.t[1][o] = vb[q]; *(f32x4*)&m.t[2][o] = va[q];
   }
   __syncthreads();
-  const int m0 = (w >> 1) * 32, n0 = (w & 1) * 32;
   f32x4 acc[2][2];
   auto into = [&](float* x) {
 #pragma unroll
@@ -277,18 +286,31 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
     }
   }
   if (!prow) mma64(m.t[2], m.t[1], m0, n0, acc);   // S_ik T, or S_ik P
-  __syncthreads();
-  into(m.t[2]);
-  __syncthreads();
+  if constexpr (COH) {
+    __syncthreads();
+    into(m.t[2]);
+    __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float* p = &m.t[2][(r0 + 16 * q) * SL + c0];
-    f32x4 v = *(const f32x4*)p;
-    if (!prow) v = old[q] - v;
-    put4<COH>(D, offset_of<COH>(ti * BS + r0 + 16 * q, dld, tj * BS + c0), v);
-    if (pivot) *(f32x4*)p = v;
+    for (int q = 0; q < 4; ++q) {
+      float* p = &m.t[2][(r0 + 16 * q) * SL + c0];
+      f32x4 v = *(const f32x4*)p;
+      if (!prow) v = old[q] - v;
+      put4<COH>(D, offset_of<COH>(ti * BS + r0 + 16 * q, dld, tj * BS + c0), v);
+      if (pivot) *(f32x4*)p = v;
+    }
+    if (!pivot) return;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4& a = acc[q >> 1][q & 1];
+      if (!prow) a = old[q] - a;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) D[entry(q >> 1, q & 1, r, dld)] = a[r];
+    }
+    if (!pivot) return;
+    __syncthreads();
+    into(m.t[2]);
   }
-  if (!pivot) return;
   __syncthreads();
   f64x4 v[4];
 #pragma unroll
@@ -296,6 +318,13 @@ __device__ inline void jordan_tile(const float* S, int sld, float* D, int dld, c
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[j][r] = (double)m.t[2][(16 * w + 4 * r + lq) * SL + 16 * j + lr];
   invert64(v, m.inv);
+  if constexpr (!COH) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Pnext[(16 * w + 4 * r + lq) * BS + 16 * j + lr] = (float)v[j][r];
+    return;
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 4; ++j)
