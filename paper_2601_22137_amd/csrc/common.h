@@ -358,7 +358,8 @@ void launch_make_e(float* E, const float* R, const Ctrl* ctrl, int batch, int np
 // floats, 16-byte aligned.
 // sel_batch: the batch that picks blocks and tiles, where these matrices are a part of a larger one.  sync: [batch][FIT_SYNC_WORDS].
 long long spd_inverse_scratch_floats(int np, int batch, int sel_batch);
-int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, unsigned* sync, hipStream_t s);
+// may_end: the matrices may be done (ctrl) before this launch.
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, bool may_end, float* scratch, unsigned* sync, hipStream_t s);
 // partial sums of <D0,D0>, <D0,D2>, <D2,D2> (D0 = M - I, D2 = M + N - 2I) -> the five coefficient partials
 void launch_db_moments(const float* M, const float* N, int np, int n_true, int batch, const Ctrl* ctrl, double* cpart,
                        int ngroups, hipStream_t s);

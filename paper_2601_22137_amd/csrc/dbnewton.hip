@@ -613,11 +613,20 @@ __global__ __launch_bounds__(NT) void panels_kernel(const float* __restrict__ T,
 // Inverse of n x n SPD matrices by block Gauss-Jordan with pivots of 64, n a multiple of 64: from src to out, through
 // tmp (each with its leading dimension and batch stride).  src may be out if n / 64 is even, tmp if it is odd.
 struct Mat { float* p; long long stride; int ld; };
-// In one launch up to two workgroups per CU, by the batch of the whole group.  More of them wait in each other's way (order 1728, 729 workgroups: 0.59 ms, in one
-// launch 1.55).
-void gauss_jordan_64(Mat src, Mat out, Mat tmp, float* P, unsigned* sync, int n, int batch, int sel_batch, const Ctrl* ctrl, hipStream_t s) {
+// Where all steps are one launch, by the workgroups of the whole group's batch.  Up to one per CU (256) it is ahead: us by steps / in one launch, order 1024 287 / 271,
+// 704 x 2 196 / 188, 448 x 5 132 / 123, 192 x 28 61 / 58.  With two per CU the reads past the L2s cost more than the launches (not the polling: longer sleeps
+// change nothing), most where one matrix has them all: 1408 (484) 436 / 856, 1280 (400) 391 / 589, 1152 (324) 349 / 380, 960 x 2 297 / 345, 768 x 3 245 / 261, 320 x 12
+// 105 / 115.  Orders of a power of two are still ahead (steps of theirs fall off there: 1024 x 2 422 / 374, 512 x 5 207 / 173, 512 x 8 213 / 191, 256 x 32 111 / 97).
+// In an iteration that may end before its budget many launches come behind its end, and an empty one instead of nt is worth more than that up to 324 workgroups
+// per matrix: budget of 12 to 1e-5, 384 x 10 796 / 730, 640 x 4 1111 / 986, 768 x 3 1276 / 1167, 1152 1681 / 1547, but 1280 1859 / 2187, 1408 2027 / 2924 (five
+// updates whatever the residual: 768 x 3 1615 / 1733, 1152 2157 / 2352).
+bool sweeps_in_one_launch(int nt, int batch, bool may_end) {
+  const long long wgs = (long long)nt * nt * batch;
+  return nt > 1 && (wgs <= 256 || (wgs <= 512 && ((nt & (nt - 1)) == 0 || (may_end && nt <= 18))));
+}
+void gauss_jordan_64(Mat src, Mat out, Mat tmp, float* P, unsigned* sync, int n, int batch, int sel_batch, const Ctrl* ctrl, bool may_end, hipStream_t s) {
   const int nt = n / BS;
-  const bool one = nt > 1 && (long long)nt * nt * sel_batch <= 512;
+  const bool one = sweeps_in_one_launch(nt, sel_batch, may_end);
   hipLaunchKernelGGL(first_pivot_kernel, dim3(batch), dim3(NT), 0, s, src.p, src.stride, src.ld, P, one ? sync : nullptr, ctrl);
   if (one) {
     SweepArgs a = {};
@@ -653,7 +662,8 @@ long long spd_inverse_scratch_floats(int np, int batch, int sel_batch) {
   return (2ll * BS * BS + n * n + OB * np) * batch;
 }
 
-int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, float* scratch, unsigned* sync, hipStream_t s) {
+int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batch, const Ctrl* ctrl, bool may_end, float* scratch, unsigned* sync,
+                       hipStream_t s) {
   if (np % BS || batch <= 0 || !scratch || !sync) return PRISM_EINVAL;
   const long long per_mat = (long long)np * np;
   const int OB = outer_block(np, sel_batch);
@@ -667,7 +677,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
     const Mat out = {N, per_mat, np};
     Mat src = {const_cast<float*>(M), per_mat, np};
     if (M == N && ((np / BS) & 1)) { copy(M, tmp.p); src = tmp; }
-    gauss_jordan_64(src, out, tmp, P, sync, np, batch, sel_batch, ctrl, s);
+    gauss_jordan_64(src, out, tmp, P, sync, np, batch, sel_batch, ctrl, may_end, s);
     return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
   }
   if (M != N) copy(M, N);
@@ -678,7 +688,7 @@ int launch_spd_inverse(const float* M, float* N, int np, int batch, int sel_batc
     float* rowk = N + (long long)k * OB * np;
     float* colk = N + k * OB;
     const Mat piv = {Pk, per_mat, np};
-    gauss_jordan_64(piv, piv, tmp, P, sync, OB, batch, sel_batch, ctrl, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
+    gauss_jordan_64(piv, piv, tmp, P, sync, OB, batch, sel_batch, ctrl, may_end, s);   // P = A_kk^{-1}, in place: 8 or 4 pivots
     GemmDesc g = {};
     g.batch = batch; g.sel_batch = sel_batch; g.ctrl = ctrl; g.K = OB; g.epi = EPI_STORE; g.c_in = 1.0f;
     GemmDesc r = g;                                      // T = P A_k,:

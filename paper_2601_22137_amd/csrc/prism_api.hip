@@ -1026,7 +1026,7 @@ int run_sqrt_newton_f32(Run& r) {
     if (k == r.max_iters && r.tol <= 0.0) break;
     CHECK_LAUNCH(r.solve(k, k == 0 ? nparts0 : nparts, 1));
     if (k == r.max_iters) break;
-    { ProfScope ps(PK_SPD_INVERSE, r.s); CHECK_LAUNCH(launch_spd_inverse(M, N, Sp, P.batch, r.sel_batch, r.ctrl, r.at<float>(P.o_t[0]), r.at<unsigned>(P.o_sync), r.s)); }
+    { ProfScope ps(PK_SPD_INVERSE, r.s); CHECK_LAUNCH(launch_spd_inverse(M, N, Sp, P.batch, r.sel_batch, r.ctrl, r.tol > 0.0, r.at<float>(P.o_t[0]), r.at<unsigned>(P.o_sync), r.s)); }
     {   // also without a fit: the probe of the inverse shares the partials with the moments
       ProfScope ps(PK_DB_MOMENTS, r.s);
       launch_db_moments(M, N, Sp, P.S, P.batch, r.ctrl, r.at<double>(P.o_cpart), P.ngroups, r.s);
@@ -1882,7 +1882,7 @@ int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream
   const size_t bytes = (size_t)spd_inverse_scratch_floats(n, batch, batch) * 4;
   const int rc = get_workspace(bytes + (size_t)batch * FIT_SYNC_WORDS * sizeof(unsigned), stream, nullptr, &ws);
   if (rc != PRISM_OK) return rc;
-  return launch_spd_inverse(a, out, n, batch, batch, nullptr, (float*)ws, (unsigned*)(ws + bytes), (hipStream_t)stream);
+  return launch_spd_inverse(a, out, n, batch, batch, nullptr, false, (float*)ws, (unsigned*)(ws + bytes), (hipStream_t)stream);
 }
 
 int prism_run_grouped(prism_fn fn, const prism_group* groups, int ngroups, int root_p, prism_dtype dt, int degree,

@@ -159,18 +159,30 @@ def test_spd_inverse_pivots_at_the_ends_of_the_range(prism, n):
     assert np.array_equal(out, np.diag((1.0 / d.astype(np.float64)).astype(np.float32)))
 
 
-@pytest.mark.parametrize("n,few,many", [(128, 128, 129), (512, 8, 9), (448, 1, 11), (1024, 2, 3)])
+@pytest.mark.parametrize("n,few,many", [(128, 128, 129), (192, 28, 29), (448, 5, 6), (512, 8, 9), (1024, 2, 3), (1088, 0, 1), (2048, 8, 9)])
 def test_eliminations_in_one_launch_and_in_steps(prism, n, few, many):
-    """Up to 512 tiles (n / 64 squared per matrix) all steps are one launch, beyond each is its own: the same operations, the same bits.
-    (Order 1024: from two matrices on with outer blocks or without, by the batch; compared with numpy only.)"""
+    """The same operations, the same bits on both sides of the rule that makes all steps of an elimination one launch: up to 256 workgroups, (n / 64) squared per
+    matrix, up to 512 for orders of a power of two.  Order 2048 has outer blocks of 512, swept in place inside the matrix."""
     rng = np.random.default_rng(n)
     w = rng.standard_normal((n, 2 * n))
     A = (w @ w.T / (2 * n) + 0.05 * np.eye(n)).astype(np.float32)
-    outs = [prism.spd_inverse(torch.from_numpy(A).cuda().repeat(b, 1, 1)) for b in (few, many)]
-    if n != 1024:
-        assert torch.equal(outs[0][0], outs[1][0])
-    for o in outs:
-        assert all(torch.equal(o[0], o[i]) for i in range(1, o.shape[0]))
-        x = o[0].cpu().numpy().astype(np.float64)
-        ref = np.linalg.inv(A.astype(np.float64))
-        assert np.linalg.norm(x - ref) / np.linalg.norm(ref) <= 1e-5
+    outs = [prism.spd_inverse(torch.from_numpy(A).cuda().repeat(b, 1, 1)) for b in (few, many) if b]
+    assert all(torch.equal(outs[0][0], o[i]) for o in outs for i in range(o.shape[0]))
+    x = outs[0][0].cpu().numpy().astype(np.float64)
+    ref = np.linalg.inv(A.astype(np.float64))
+    assert np.linalg.norm(x - ref) / np.linalg.norm(ref) <= 1e-5
+
+
+@pytest.mark.parametrize("n,batch", [(768, 3), (640, 5), (1152, 1), (1280, 1)])
+def test_sqrt_newton_with_and_without_a_tolerance(prism, n, batch):
+    """An iteration that may end early takes eliminations of up to 512 workgroups in one launch, a fixed budget in steps (order 1280: both in steps):
+    the same bits after as many updates."""
+    rng = np.random.default_rng(n)
+    w = rng.standard_normal((n, 2 * n))
+    A = torch.from_numpy((w @ w.T / (2 * n) + 0.05 * np.eye(n)).astype(np.float32)).cuda().repeat(batch, 1, 1)
+    x, y = A.clone(), A.clone()
+    inv, info = prism.sqrt_newton(x, 12, 1e-5)
+    iters = info.read()["iters"]
+    assert (iters == iters[0]).all() and 0 < iters[0] < 12
+    inv2, _ = prism.sqrt_newton(y, int(iters[0]), 0.0)
+    assert torch.equal(x, y) and torch.equal(inv, inv2)
