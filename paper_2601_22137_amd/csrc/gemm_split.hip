@@ -63,12 +63,15 @@ __global__ __launch_bounds__(64 * WR * WC, TM == 64 ? 2 : 1) void gemm_split_ker
   }
   const GemmDesc& g = [&]() -> const GemmDesc& { if constexpr (PAIR) return arg.d[which]; else return arg; }();
 
-  // tile, as in gemm_kernel: one XCD has a contiguous range of tiles, here in blocks of 8 x 4 (32 CUs, one workgroup each)
+  // Tile: one XCD has a contiguous range of the product's tiles, here in blocks of 8 x 4 (32 CUs, one workgroup each).  Launches are rounded up to
+  // multiples of eight for that: in plain order, which products of another number of tiles had, the panels come past the L2s (us in plain order / so: 64 x 64 tiles,
+  // order 448 x 10 28 / 20, both updates of a square root in one launch 60 / 34, 704 x 20 139 / 102; 128 x 128 tiles, 640 x 10 46 / 37, 896 x 20 212 / 174).
   const bool sym = SYM || (PAIR && TM == TN && g.sym);
   const int tiles_m = g.M / TM, tiles_n = g.N / TN;
   const int per_mat = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int total = per_mat * g.batch;
-  if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);
+  wg = (wg & 7) * ((total + 7) >> 3) + (wg >> 3);
+  if (wg >= total) return;
   const int b = wg / per_mat, rem = wg - b * per_mat;
   int tm, tn;
   if (sym) {
@@ -439,7 +442,7 @@ int launch_cfg(GemmPair& g, hipStream_t s) {
     const int tm = d.M / TM, tn = d.N / TN;
     g.first = (int)total;
     d.tile_blocks = !d.sym && tm % 8 == 0 && tn % 4 == 0 && tm * tn > 32;
-    total += (d.sym ? (long long)tm * (tm + 1) / 2 : (long long)tm * tn) * d.batch;
+    total += ((d.sym ? (long long)tm * (tm + 1) / 2 : (long long)tm * tn) * d.batch + 7) & ~7ll;
     if (total > 0x3fffffff) return PRISM_EINVAL;
   }
   if (total <= 0) return PRISM_EINVAL;
