@@ -150,9 +150,11 @@ int flow_ring(const Plan& P, int sel_batch, size_t bytes) {
 int planes_unit(const Plan& P, int sel_batch) {
   const double s = round_up(P.S, 128) / (double)round_up(P.S, 64), l = round_up(P.L, 128) / (double)round_up(P.L, 64), grown = s * s * l;
   if (P.fn == PRISM_FN_INV_ROOT) return grown < 1.1 ? 128 : 0;
+  // Order 384: the products are all epilogue, and full launches are behind (both updates of 64 square roots 119 / 148, of 40 87 / 85)
+  if (P.Sp < 512 && (long long)(P.Sp / 64) * (P.Lp / 64) * sel_batch > 1536) return 0;
   if (grown < 1.19) return 128;
-  // 64 x 64 tiles gain 10 % in one round (512) and nothing in more (sign of 2 x 1000 1361 / 1192, 8 x 1000 3700 / 3382; square root of 4 x 808, 1.3
-  // rounds and 2.6 for the pair of updates, 1471 / 1648)
+  // 64 x 64 tiles: one round (512).  A product of 10 x 448 23 / 20 us, 6 x 576 26 / 24, 3 x 832 34 / 29.  Beyond a round they are ahead too (4 x 832 46 / 38), but there
+  // the calls have not been compared.
   return (long long)((P.S + 63) / 64) * ((P.L + 63) / 64) * sel_batch <= 512 ? 64 : 0;
 }
 bool takes_planes(const Plan& P, int sel_batch) {

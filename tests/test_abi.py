@@ -111,3 +111,10 @@ def test_largest_batches_of_the_static_entry_point(lib, batch, m, n, dtype, degr
     not take that."""
     from paper_2601_22137_amd import prism as P
     assert P.workspace_bytes(P.FN_POLAR, batch, m, n, dtype, degree, sketch) <= P.STATIC_SCRATCH_BYTES
+
+
+def test_full_launches_of_order_384_keep_fp32_operands(lib):
+    """Up to 1536 tiles of 64 x 64 the products come from planes, which take scratch; from there on they do not."""
+    from paper_2601_22137_amd import prism as P
+    size = lambda batch: P.workspace_bytes(P.FN_SQRT, batch, 384, 384, P.F32, 5, 16)
+    assert size(42) / 42 > 1.5 * size(43) / 43
