@@ -25,8 +25,8 @@
 namespace prism {
 namespace {
 
-template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW>
-__global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : (long_slabs(TM, TN, EPI, KMA) ? 2 : wgs_per_cu(TM, TN)))) void gemm_bf16_kernel(Bf16Multi mg) {
+template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW, bool LONG>
+__global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : (LONG ? 2 : wgs_per_cu(TM, TN)))) void gemm_bf16_kernel(Bf16Multi mg) {
   constexpr int RT = TM / TN;                    // SYM: tile columns per tile row height
   static_assert(RT == 1 || RT == 2, "tile shape");
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 ? 1 : (long_slabs(TM, TN, EPI, KM
   const int cb = g.ctrl_parts ? b / g.ctrl_parts : b;   // split-K launches: the batch entries are parts of matrices
   if (g.ctrl && g.ctrl[cb].done) return;
   const float alpha = g.ctrl ? g.ctrl[cb].alpha : 1.0f;
-  gemm_bf16_tile<TM, TN, EPI, SYM, KMA, KMB, NW>(g, b, rem, per_mat, tm, tn, smem, [&](float& out) { out = alpha; return true; });
+  gemm_bf16_tile<TM, TN, EPI, SYM, KMA, KMB, NW, LONG>(g, b, rem, per_mat, tm, tn, smem, [&](float& out) { out = alpha; return true; });
 }
 
 // tiles of one matrix
@@ -85,9 +85,15 @@ long long tiles_per_matrix(const Bf16Desc& g) {
   return SYM ? (TM / TN) * tm * (tm + 1) / 2 : tm * tn;
 }
 
+// Slabs of 64 k or of 32 for an update of `tiles` tiles with K = k: two workgroups per CU against three.  Up to one round of the longer ones (512), and from K = 768 on
+// beyond one of the shorter (768).  Us, slabs of 32 / 64: K = 384, 384 tiles 15.4 / 15.2, 576 22.3 / 24.0, 1152 29.2 / 30.6; K = 512, 512 tiles 17.7 / 16.8, 640 22.5 / 23.6, 4096 105 / 110;
+// K = 768, 576 tiles 31.3 / 34.0, 720 35.8 / 38.3, 2304 71.6 / 68.9; K = 1024, 640 38.0 / 40.2, 1024 43.9 / 40.2.
+bool slabs_of_64(long long tiles, int k) { return tiles <= 512 || (k >= 768 && tiles > 768); }
+
 template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW>
 int launch_tw(Bf16Multi& mg, hipStream_t s) {
   long long total = 0;
+  bool lines = true;   // K in whole slabs of 64, two at least
   // A launch whose tiles are no multiple of eight is rounded up where the operands are large enough for their fetches past the L2s to be what
   // it waits for (Gram product of 50257 x 768 in 12 parts, 252 tiles of 77 MB: 64 -> 52 us); small ones are faster in plain order (one
   // 768 x 3072 in 6 parts, 126 tiles of 5 MB: 10.2 against 11.6).  Nothing in between was measured.
@@ -96,7 +102,9 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
     const Bf16Desc& g = mg.d[i];
     total += tiles_per_matrix<TM, TN, SYM>(g) * g.batch;
     operand_bytes += 2.0 * g.batch * ((double)g.M * g.K + (g.A == g.B ? 0.0 : (double)g.N * g.K));
+    lines = lines && g.K % 64 == 0 && g.K >= 128;
   }
+  const bool wide = lines && slabs_of_64(total, mg.d[0].K);
   // Launches of several rounds are rounded up too, small ones keep whole ranges of the launch (three updates of five layers of width 320, update of 465 tiles
   // and Gram product of 120: 182 us with plain order and groups, 168 with groups and the launch).
   if (mg.xcd_private) mg.xcd_private = operand_bytes >= 32.0 * 1024 * 1024 || total > 256 ? XCD_GROUPS : (total % 8 == 0 ? XCD_LAUNCH : 0);
@@ -108,11 +116,16 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
     if (total > 0x7fffffff) return PRISM_EUNSUPPORTED;
   }
   mg.tile_start[mg.ngroups] = (int)total;
-  const size_t lds = ring_bytes(TM, TN, EPI, KMA);
-  const int rc = allow_dynamic_lds((const void*)gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW>, (int)lds);
-  if (rc != PRISM_OK) return rc;
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW>), dim3((unsigned)total), dim3(64 * NW), lds, s, mg);
-  return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+  auto launch = [&](auto kern, int lds) -> int {
+    const int rc = allow_dynamic_lds((const void*)kern, lds);
+    if (rc != PRISM_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * NW), lds, s, mg);
+    return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+  };
+  if constexpr (long_slabs(TM, TN, EPI, KMA)) {
+    if (wide) return launch(gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW, true>, ring_bytes(TM, TN, true));
+  }
+  return launch(gemm_bf16_kernel<TM, TN, EPI, SYM, KMA, KMB, NW, false>, ring_bytes(TM, TN, false));
 }
 
 // 256 x 256 tiles run with eight wavefronts (mg.waves8), every other shape with four
@@ -135,7 +148,6 @@ int launch_t(Bf16Multi& mg, hipStream_t s) {
     if (g.sym && (g.M != g.N || g.A != g.B)) return PRISM_EINVAL;
     if ((g.epi == BEPI_GRAM || g.epi == BEPI_POLYQ) && !g.sym) return PRISM_EINVAL;   // symmetric products only
     if (g.epi == BEPI_STORE && (!g.C32 || (g.sym && km != 3))) return PRISM_EINVAL;
-    if (g.epi == BEPI_APPLY && TM == 128 && TN == 128 && (g.K % 64 || g.K < 128)) return PRISM_EINVAL;   // slabs of 64
     // without the fp32 matrix: GRAM with a diagonal array, POLYQ with R in bf16
     if (g.epi == BEPI_GRAM && ((!g.C32 && !g.diag) || g.rho_stride < tiles_per_matrix<TM, TN, true>(g))) return PRISM_EINVAL;
     if (g.epi == BEPI_POLYQ && !g.C32 && !g.Cin16) return PRISM_EINVAL;

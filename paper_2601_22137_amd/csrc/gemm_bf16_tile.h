@@ -30,11 +30,11 @@ typedef void __attribute__((address_space(3)))* lptr_t;
 constexpr int stages_of(int TM, int TN) { return (TM == 256 && TN == 256) ? 4 : 3; }
 constexpr int wgs_per_cu(int TM, int TN) { return (TM == 256 && TN == 256) ? 1 : (TM == 256 ? 2 : 3); }
 
-// 128 x 128 tiles with a K-contiguous operand run in slabs of 64 k, two of them in LDS: whole cache lines per row and request, where
-// slabs of 32 fetch halves, which is what bounds these tiles (84 against 116 B/ns and CU into LDS).  Bare product of 8 x 4096^3, A K-contiguous:
+// 128 x 128 updates with a K-contiguous iterate can run in slabs of 64 k, two of them in LDS and two workgroups per CU (LONG): whole cache lines per row and
+// request, where slabs of 32 fetch halves, which is what bounds these tiles (84 against 116 B/ns and CU into LDS).  Bare product of 8 x 4096^3, A K-contiguous:
 // 897 -> 1016 TFLOP/s.
 constexpr bool long_slabs(int TM, int TN, int EPI, bool KMA) { return TM == 128 && TN == 128 && EPI == BEPI_APPLY && !KMA; }
-constexpr int ring_bytes(int TM, int TN, int EPI, bool KMA) { return long_slabs(TM, TN, EPI, KMA) ? 2 * (TM + TN) * 128 : stages_of(TM, TN) * (TM + TN) * 64; }
+constexpr int ring_bytes(int TM, int TN, bool LONG) { return LONG ? 2 * (TM + TN) * 128 : stages_of(TM, TN) * (TM + TN) * 64; }
 
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding)
 template <int N> __device__ inline void wait_vmcnt() {
@@ -177,7 +177,7 @@ __device__ __forceinline__ void product_long_slabs(const char* A, int lda, const
 // a barrier, for its fragments or for a slab).
 // Tile (tm, tn), number `rem` of the per_mat that are computed of entry b of the batch.  alpha_of(alpha) is called by all threads behind
 // the main loop, where the LDS is free: false leaves the result alone.
-template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW, typename ALPHA>
+template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW, bool LONG = false, typename ALPHA>
 __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem, int per_mat, int tm, int tn, unsigned char* smem, ALPHA alpha_of) {
   constexpr bool KM = KMA || KMB;   // some fragment reads are transposing ones
   constexpr int STAGES = stages_of(TM, TN);
@@ -213,7 +213,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const Bf16Desc& g, int b, int rem
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
   const int lr = lane & 31, lh = lane >> 5;
 
-  if constexpr (long_slabs(TM, TN, EPI, KMA)) {
+  if constexpr (LONG) {
     product_long_slabs<TM, TN, KMB, NW>((const char*)A1, lda, (const char*)Bb, ldb, g.K / 64, wave, lane, wm0, wn0, smem, acc);
   } else {
 

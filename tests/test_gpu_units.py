@@ -214,3 +214,18 @@ def test_gemm_row_offsets_beyond_32_bits(prism, f64):
     C = (prism.gemm_f64a if f64 else prism.gemm_f32)(A, B)
     want = 3.0 * torch.outer(torch.arange(1, M + 1), torch.arange(1, N + 1)).double()
     assert torch.equal(C[0].double().cpu(), want)
+
+
+@pytest.mark.parametrize("plain", [False, True])
+@pytest.mark.parametrize("n,batches", [(384, (56, 57)), (512, (32, 33)), (768, (14, 15, 22))])
+def test_updates_in_slabs_of_32_and_of_64(prism, n, batches, plain):
+    """Launches of 128 x 128 update tiles on both sides of the rule that picks the length of the slabs (512 tiles, 768 from order 768 on): the order of the sums
+    is the same, and so are the bits.  Fixed coefficients, so that nothing else goes by the batch."""
+    rng = np.random.default_rng(n)
+    bits = W.to_bf16_bits((rng.standard_normal((2, n, n)) * np.exp(rng.standard_normal((2, n, 1))) / n).astype(np.float32))
+    outs = []
+    for b in batches:
+        x = _dev(np.resize(bits, (b, n, n)).view(np.int16)).view(torch.bfloat16)
+        prism.polar(x, 5, 4, 16, W.SKETCH_SEED, 0.0, flags=prism.FLAG_BF16_PLAIN_ITERATE if plain else 0, warm_iters=4)
+        outs.append(x.view(torch.int16))
+    assert all(torch.equal(o[i], outs[0][i % 2]) for o in outs for i in range(o.shape[0]))
