@@ -13,6 +13,7 @@
 #include <utility>
 
 #include "common.h"
+#include "workspace_cache.h"
 
 namespace prism {
 
@@ -335,14 +336,11 @@ int make_plan(Plan& P, int fn, int batch, int m, int n, int dt, int degree, int 
   return PRISM_OK;
 }
 
-// Grow-only workspace per (device, stream or other owner).  A block that has become too small is kept until
-// prism_release_workspaces(): work enqueued earlier, and HIP graphs captured from earlier calls,
-// still hold its address.
-struct Cached { void* ptr = nullptr; size_t bytes = 0; std::vector<void*> retired; };
 std::mutex g_mu;
-std::map<std::pair<int, const void*>, Cached> g_cache;
+WorkspaceCache g_cache;
 
-int get_workspace(size_t bytes, const void* owner, const prism_options* opt, char** out) {
+// optional: the caller takes a plan that needs less if there is no such memory
+int get_workspace(size_t bytes, const void* owner, const prism_options* opt, char** out, bool optional = false) {
   if (opt && opt->workspace) {
     if (opt->workspace_bytes < bytes || ((uintptr_t)opt->workspace & 255)) return PRISM_ENOMEM;
     *out = (char*)opt->workspace;
@@ -351,19 +349,17 @@ int get_workspace(size_t bytes, const void* owner, const prism_options* opt, cha
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { set_last_error("hipGetDevice failed"); return PRISM_EHIP; }
   std::lock_guard<std::mutex> lock(g_mu);
-  Cached& c = g_cache[std::make_pair(dev, owner)];
-  if (c.bytes < bytes) {
+  void* p = g_cache.get(dev, owner, bytes, optional, [](size_t n) -> void* {
     void* fresh = nullptr;
-    if (hipMalloc(&fresh, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      set_last_error("hipMalloc of the workspace failed");
-      return PRISM_ENOMEM;
-    }
-    if (c.ptr) c.retired.push_back(c.ptr);
-    c.ptr = fresh;
-    c.bytes = bytes;
+    if (hipMalloc(&fresh, n) == hipSuccess) return fresh;
+    (void)hipGetLastError();
+    return nullptr;
+  });
+  if (!p) {
+    if (!optional) set_last_error("hipMalloc of the workspace failed");
+    return PRISM_ENOMEM;
   }
-  *out = (char*)c.ptr;
+  *out = (char*)p;
   return PRISM_OK;
 }
 
@@ -1219,7 +1215,7 @@ int run(int fn, void* a, void* inv_out, int root_p, int batch, int m, int n, int
     if (rc != PRISM_OK) return rc;
   }
   r.s = (hipStream_t)stream;
-  rc = get_workspace(r.P.total, owner ? owner : stream, opt, &r.ws);
+  rc = get_workspace(r.P.total, owner ? owner : stream, opt, &r.ws, r.P.x3);
   if (rc == PRISM_ENOMEM && r.P.x3) {   // the planes are what did not fit
     rc = make_plan(r.P, fn, batch, m, n, dt, degree, sketch_dim, root_p, (opt ? opt->flags : 0u) | plain, false, sel_batch);
     if (rc != PRISM_OK) return rc;
@@ -1751,13 +1747,13 @@ int prism_release_workspaces(void) {
   std::lock_guard<std::mutex> lock(g_mu);
   int rc = PRISM_OK, current = 0;
   const bool have_current = hipGetDevice(&current) == hipSuccess;
-  for (auto& kv : g_cache) {
+  for (auto& kv : g_cache.blocks) {
     if (hipSetDevice(kv.first.first) != hipSuccess) { rc = PRISM_EHIP; continue; }
     for (void* p : kv.second.retired)
       if (hipFree(p) != hipSuccess) rc = PRISM_EHIP;
     if (kv.second.ptr && hipFree(kv.second.ptr) != hipSuccess) rc = PRISM_EHIP;
   }
-  g_cache.clear();
+  g_cache.blocks.clear();
   if (have_current) (void)hipSetDevice(current);
   if (rc != PRISM_OK) { (void)hipGetLastError(); set_last_error("hipFree of a cached workspace failed"); }
   return rc;
