@@ -23,8 +23,10 @@
  *     sides are tile multiples may be used as scratch for intermediate iterates
  *     between the moment its input has been read and the end of the call.
  *   - `dt` is the storage type of the caller's matrices.  PRISM_F32 computes
- *     with fp32 matrix instructions (the inverse-root recurrence for M_k in
- *     fp64); PRISM_BF16 computes with bf16 matrix instructions accumulating in
+ *     in fp32: with fp32 matrix instructions, or, larger products, with bf16
+ *     ones on three exact bf16 planes per operand (six of their nine products,
+ *     accumulated in fp32; no larger error), and the inverse-root recurrence
+ *     for M_k in fp64; PRISM_BF16 computes with bf16 matrix instructions accumulating in
  *     fp32 and is available for prism_polar only (the iterate is carried as
  *     a pair of bf16 matrices while small singular values need it).
  *   - `degree` is the degree of the update in X: 3 (d = 1) or 5 (d = 2).
@@ -39,6 +41,11 @@
  *   - `stream` is a hipStream_t (NULL = the default stream).  Calls only
  *     enqueue work on it and return; nothing synchronises with the host and
  *     there is no host round trip per iteration.
+ *   - Kernels are chosen by the shape and the batch of the caller's group,
+ *     never by what lies beside it: a call repeated gives the same bits, whole,
+ *     in parts or as a group of a grouped call.  The same matrix in a batch of
+ *     another size may be computed by other kernels (for instance from planes
+ *     or not) and then agrees to rounding.
  *   - The return value reports errors the host can detect (prism_status).
  *     Numerical outcomes are reported per matrix in prism_info.status.
  *   - Unless a workspace is passed through prism_options, the library keeps
@@ -155,7 +162,11 @@ typedef struct {
  * no HIP graph captured from one will be launched again.  The next call allocates anew. */
 int prism_release_workspaces(void);
 
-/* Device bytes a call with these arguments needs (host-only computation). */
+/* Device bytes a call with these arguments takes (host-only computation).  Part of them may be optional: partial sums of split Gram
+ * products, the ring of fp32 calls in one launch, and the bf16 planes of fp32 operands, which more than double the workspace of
+ * the calls that have them (square root of order 8192 1.6 -> 3.6 GiB).  A call that is given less but enough without them, or for
+ * which the device has no more, runs without: other kernels, the same result to rounding, slower.  A device that had no more
+ * is not asked again for that stream until prism_release_workspaces(). */
 int prism_workspace_bytes(int fn, int batch, int m, int n, prism_dtype dt, int degree,
                           int sketch_dim, int root_p, size_t* out_bytes);
 
@@ -169,21 +180,20 @@ int prism_polar_ex(void* x, int batch, int m, int n, prism_dtype dt, int degree,
 
 /* prism_polar_ex for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the
- * same results as prism_polar_ex on one stream, but every intermediate (iterates, R, Q, sketches,
+ * same results as prism_polar_ex on one stream with a workspace of PRISM_STATIC_SCRATCH_BYTES, but every intermediate (iterates, R, Q, sketches,
  * chain vectors, control blocks) lives in a static device array of PRISM_STATIC_SCRATCH_BYTES
  * that is part of the library's code object: each GPU the library runs on holds its own copy
  * until the process ends.  The call makes no hipMalloc / hipFree, creates no stream or event and
  * records no hipMemsetAsync; it enqueues kernels on `stream` and returns.
  *   - opt may be NULL; opt->workspace must be NULL (PRISM_EINVAL otherwise).  opt->info, flags,
  *     warm_iters and the coefficient schedule work as in prism_polar_ex.
- *   - A call whose intermediates need more than the array (prism_workspace_bytes tells; e.g. one
+ *   - A call whose intermediates need more than the array (e.g. one
  *     1024 x 1024 bf16 matrix with the split iterate needs 27 MB, sixteen 768 x 768 ones do not
  *     fit) returns PRISM_EUNSUPPORTED before anything is enqueued, with a message in
- *     prism_last_error().
- *     A call whose Gram products prism_polar_ex would split (its partial products are
- *     part of what prism_workspace_bytes reports) is taken here, and by prism_polar_ex with a
- *     workspace too small for them, with the product in one pass if it fits that way: the same
- *     result to rounding.
+ *     prism_last_error().  What prism_workspace_bytes reports fits if it is no more than the array; a call that is reported
+ *     to take more is taken nevertheless if it fits without its optional part (see there; e.g. one 1000 x 1000 fp32 matrix, 40 MiB with
+ *     the planes, 20 without), and then does what prism_polar_ex does with a workspace of the size of the array: the same
+ *     result to rounding as with a larger one.
  *   - All calls on one GPU share that GPU's array, which keeps the contents of the last call;
  *     every call initialises what it reads.  Two calls that overlap in time on one GPU (different
  *     streams, or concurrent replays of graphs captured from them) race: order them.

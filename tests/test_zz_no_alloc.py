@@ -1,6 +1,6 @@
 """prism_polar_static (the entry point that allocates nothing: its intermediates live in a static
-device array) against prism_polar_ex, through the C-ABI.  Same kernels, same plan: the outputs must
-be the same bits, and both within the parity bar of the oracle.  Two calls in a row per case, the
+device array) against prism_polar_ex, through the C-ABI.  Same kernels, same plan (for calls whose optional scratch does not fit the
+array: that of a workspace of its size): the outputs must be the same bits, and both within the parity bar of the oracle.  Two calls in a row per case, the
 second with a smaller input, so that the contents the first call leaves in the array are what the
 second one starts from.  Collected last (file name): a failure here must not hide other tests.
 """
@@ -105,3 +105,29 @@ def test_static_rejects_what_does_not_fit_and_a_caller_workspace(prism):
     assert lib.prism_polar_static(None, 0, 64, 32, prism.F32, 5, 10, 8, SEED, 1e-6, None, None) == prism.OK
     torch.cuda.synchronize()
     assert torch.all(y == 1.0)
+
+
+@pytest.mark.parametrize("batch,m,n,same", [(1, 1000, 1000, False), (1, 1500, 900, False), (2, 700, 640, True), (1, 3072, 768, False)])
+def test_static_without_the_optional_scratch(prism, batch, m, n, same):
+    """fp32 calls that take planes (the third: all iterations in one launch; bf16, the last: a split Gram product) when there is room: reported as larger than the array, taken in it without, with the
+    bits of prism_polar_ex in a workspace of that size and the result of one that has room to rounding (one launch or many: to the bit)."""
+    bf16 = m == 3072
+    rng = np.random.default_rng(m)
+    A = rng.standard_normal((batch, m, n)).astype(np.float32)
+    if m == n:
+        A += 2.0 * np.sqrt(n) * np.eye(n, dtype=np.float32)
+    host = W.to_bf16_bits(A) if bf16 else A
+    mk = (lambda: _bf16_tensor(host.copy())) if bf16 else (lambda: torch.from_numpy(host.copy()).cuda())
+    args = (5, 40, 16, SEED, 1e-2 if bf16 else 1e-5)
+    assert prism.workspace_bytes(prism.FN_POLAR, batch, m, n, prism.BF16 if bf16 else prism.F32, 5, 16) > prism.STATIC_SCRATCH_BYTES
+    xs = [mk() for _ in range(3)]
+    infos = [prism.new_info(batch), prism.polar(xs[1], *args, workspace=torch.empty(prism.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")),
+             prism.polar(xs[2], *args)]
+    prism.polar_static(xs[0], *args, info=infos[0])
+    r = [i.read() for i in infos]
+    assert torch.equal(xs[0].view(torch.int16), xs[1].view(torch.int16)) and r[0].tobytes() == r[1].tobytes()
+    assert torch.equal(xs[0].view(torch.int16), xs[2].view(torch.int16)) == same
+    out = [_bf16_to_f64(x) if bf16 else x.cpu().numpy().astype(np.float64) for x in (xs[0], xs[2])]
+    assert _rel(out[0], out[1]) <= (2e-2 if bf16 else 1e-5)
+    ref, oinfo = O.polar(W.from_bf16_bits(host[0]) if bf16 else host[0], *args)
+    assert _rel(out[0][0], ref) <= (2e-2 if bf16 else 1e-5) and int(r[0][0]["iters"]) == oinfo["iters"] == int(r[2][0]["iters"])
