@@ -90,7 +90,8 @@ int f32_tiles(int M, int N, int batch, int sym);
 // both products in one launch: same M, N, K, batch, epilogue and operand layout; symmetric: both, neither or the first
 int launch_gemm_f32_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
 // ---- gemm_split.hip : fp32 products on the bf16 matrix cores ----
-// Both operands in planes; M, N multiples of 128, K of 32.  b: a second product of the same shape and kind (null: none)
+// Both operands in planes; M, N multiples of 64 (a tile of 128 or 256 is taken where it divides them), K of 32 and 96 at least.  RESIDUAL and POLYQ: symmetric with A stored
+// [K][M], or neither; AXPY: A stored [M][K], without acc_neg and cin_one_minus_alpha.  b: a second update of the same shape, not symmetric (null: none)
 int launch_gemm_split(const GemmDesc& a, const GemmDesc* b, hipStream_t s);
 int split_tiles(int M, int N, int batch, int sym);   // tiles of one matrix, i.e. residual partial sums
 // planes of `count` (a multiple of 8) entries

@@ -290,11 +290,11 @@ __global__ __launch_bounds__(64 * WR * WC, TM == 64 ? 2 : 1) void gemm_split_ker
   const bool mirror = sym && (tm != tn || wm0 / 64 < wn0 / 64);
   float* C = g.C ? (float*)g.C + (long long)b * g.strideC : nullptr;
   uint16_t* C3 = g.C3 ? g.C3 + (long long)b * g.strideC : nullptr;
-  constexpr bool ADDENDS = EPI == EPI_POLYQ || EPI == EPI_AXPY;
+  constexpr bool ADDENDS = EPI != EPI_RESIDUAL;
   const float* cin = (const float*)g.Cin + (long long)b * g.strideCin;
   const float* cin2 = g.Cin2 + (long long)b * g.strideCin;
-  const float wc = EPI == EPI_POLYQ ? g.c1 : (g.cin_one_minus_alpha ? (1.0f - alpha) : g.c_in * apow(alpha, g.cin_alpha_pow));
-  const float wa = EPI == EPI_POLYQ ? alpha : (g.acc_neg ? -apow(alpha, g.coef_is_alpha) : apow(alpha, g.coef_is_alpha));
+  const float wc = EPI == EPI_POLYQ ? g.c1 : g.c_in * apow(alpha, g.cin_alpha_pow);
+  const float wa = EPI == EPI_POLYQ ? alpha : apow(alpha, g.coef_is_alpha);
   const float wc2 = apow(alpha, g.cin2_alpha_pow);
   float part = 0.0f;
   if (lower && EPI != EPI_RESIDUAL) return;
@@ -334,12 +334,7 @@ __global__ __launch_bounds__(64 * WR * WC, TM == 64 ? 2 : 1) void gemm_split_ker
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = sp[e];
-      if constexpr (EPI == EPI_STORE) {
-        if (g.acc_neg) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = -v[e];
-        }
-      } else if constexpr (EPI == EPI_RESIDUAL) {
+      if constexpr (EPI == EPI_RESIDUAL) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           v[e] = (gi < g.n_true && gj + e < g.n_true) ? ((gi == gj + e ? 1.0f : 0.0f) - v[e]) : 0.0f;
@@ -415,20 +410,6 @@ SplitTile split_tile(int M, int N, int batch, int sym) {
   return {128, 128};
 }
 
-template <int TM, int TN, int WR, int WC, int EPI, bool A_KM, bool SYM>
-int launch_t(const GemmPair& g, int total, hipStream_t s) {
-  constexpr int lds = ring_of(TM, TN) * slab_bytes(TM, TN);
-  auto launch = [&](auto kern, const auto& arg) -> int {
-    const int rc = allow_dynamic_lds((const void*)kern, lds);
-    if (rc != PRISM_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WR * WC), lds, s, arg);
-    return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
-  };
-  if (g.d[1].batch == 0) return launch(gemm_split_kernel<TM, TN, WR, WC, EPI, A_KM, SYM, false>, g.d[0]);
-  if constexpr (EPI == EPI_AXPY && !A_KM) return launch(gemm_split_kernel<TM, TN, WR, WC, EPI, A_KM, SYM, true>, g);
-  return PRISM_EINVAL;
-}
-
 template <int TM, int TN, int WR, int WC>
 int launch_cfg(GemmPair& g, hipStream_t s) {
   long long total = 0;
@@ -437,7 +418,7 @@ int launch_cfg(GemmPair& g, hipStream_t s) {
     if (d.M % TM || d.N % TN || d.K % SLAB || d.K / SLAB < ring_of(TM, TN) || d.lda % 8 || d.ldb % 8 || d.ldc % 8 || !d.A3 || !d.B3 || (!d.C && !d.C3)) return PRISM_EINVAL;
     if ((d.epi == EPI_POLYQ || d.epi == EPI_AXPY) && (!d.Cin || d.ldcin % 4)) return PRISM_EINVAL;
     if (d.sym && (TM != TN || d.M != d.N)) return PRISM_EINVAL;
-    if (d.ctrl_parts || d.skip_m1 || d.skip_n1 || d.sym_skew_bound) return PRISM_EINVAL;
+    if (d.ctrl_parts || d.skip_m1 || d.skip_n1 || d.sym_skew_bound || d.acc_neg || d.cin_one_minus_alpha) return PRISM_EINVAL;
     if ((unsigned long long)(d.a_km ? 32ull * d.lda + TM : (unsigned long long)TM * d.lda) * 2 > 0xffffffffull || (32ull * d.ldb + TN) * 2 > 0xffffffffull) return PRISM_EINVAL;
     const int tm = d.M / TM, tn = d.N / TN;
     g.first = (int)total;
@@ -447,19 +428,33 @@ int launch_cfg(GemmPair& g, hipStream_t s) {
   }
   if (total <= 0) return PRISM_EINVAL;
   const GemmDesc& d = g.d[0];
-  auto epi = [&](auto e) -> int {
+  auto launch = [&](auto kern, const auto& arg) -> int {
+    constexpr int lds = ring_of(TM, TN) * slab_bytes(TM, TN);
+    const int rc = allow_dynamic_lds((const void*)kern, lds);
+    if (rc != PRISM_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WR * WC), lds, s, arg);
+    return hipGetLastError() == hipSuccess ? PRISM_OK : PRISM_EHIP;
+  };
+  // the products there are: symmetric ones (the polar iteration) of an operand stored [K][M], others of one stored [M][K], updates of one stored [M][K]
+  const bool pair = g.d[1].batch != 0;
+  auto residual_or_square = [&](auto e) -> int {
     constexpr int E = decltype(e)::value;
-    const bool all_sym = d.sym && (g.d[1].batch == 0 || g.d[1].sym);
     if constexpr (TM == TN) {
-      if (all_sym) return d.a_km ? launch_t<TM, TN, WR, WC, E, true, true>(g, (int)total, s) : launch_t<TM, TN, WR, WC, E, false, true>(g, (int)total, s);
+      if (d.a_km && d.sym && !pair) return launch(gemm_split_kernel<TM, TN, WR, WC, E, true, true, false>, d);
     }
-    return d.a_km ? launch_t<TM, TN, WR, WC, E, true, false>(g, (int)total, s) : launch_t<TM, TN, WR, WC, E, false, false>(g, (int)total, s);
+    if (d.a_km || d.sym || pair) return PRISM_EINVAL;
+    return launch(gemm_split_kernel<TM, TN, WR, WC, E, false, false, false>, d);
   };
   switch (d.epi) {
-    case EPI_STORE: return epi(std::integral_constant<int, EPI_STORE>{});
-    case EPI_RESIDUAL: return epi(std::integral_constant<int, EPI_RESIDUAL>{});
-    case EPI_POLYQ: return epi(std::integral_constant<int, EPI_POLYQ>{});
-    case EPI_AXPY: return epi(std::integral_constant<int, EPI_AXPY>{});
+    case EPI_RESIDUAL: return residual_or_square(std::integral_constant<int, EPI_RESIDUAL>{});
+    case EPI_POLYQ: return residual_or_square(std::integral_constant<int, EPI_POLYQ>{});
+    case EPI_AXPY:
+      if (d.a_km) return PRISM_EINVAL;
+      if (pair) return launch(gemm_split_kernel<TM, TN, WR, WC, EPI_AXPY, false, false, true>, g);
+      if constexpr (TM == TN) {
+        if (d.sym) return launch(gemm_split_kernel<TM, TN, WR, WC, EPI_AXPY, false, true, false>, d);
+      }
+      return d.sym ? PRISM_EINVAL : launch(gemm_split_kernel<TM, TN, WR, WC, EPI_AXPY, false, false, false>, d);
   }
   return PRISM_EINVAL;
 }
@@ -473,7 +468,7 @@ int split_tiles(int M, int N, int batch, int sym) {
 }
 
 int launch_gemm_split(const GemmDesc& a, const GemmDesc* b, hipStream_t s) {
-  if (b && (b->M != a.M || b->N != a.N || b->K != a.K || b->batch != a.batch || b->epi != a.epi || b->a_km != a.a_km || (b->sym && !a.sym))) return PRISM_EINVAL;
+  if (b && (b->M != a.M || b->N != a.N || b->K != a.K || b->batch != a.batch || b->epi != a.epi || b->a_km != a.a_km || b->sym)) return PRISM_EINVAL;
   GemmPair g = {};
   g.d[0] = a;
   if (b) g.d[1] = *b;

@@ -159,7 +159,7 @@ int planes_unit(const Plan& P, int sel_batch) {
   return (long long)((P.S + 63) / 64) * ((P.L + 63) / 64) * sel_batch <= 512 ? 64 : 0;
 }
 bool takes_planes(const Plan& P, int sel_batch) {
-  static const int off = ab_switch("PRISM_NO_F32_PLANES");
+  static const int off = ab_switch("PRISM_NO_F32_PLANES") || ab_switch("PRISM_F32_NO_SYM");   // (no such kernel)
   if (off || P.dt != PRISM_F32 || P.ksplit || P.fn == PRISM_FN_SQRT_NEWTON || (P.fn == PRISM_FN_POLAR && P.L > 8192 - 128)) return false;
   if (P.fn == PRISM_FN_INV_ROOT ? P.p < 2 || P.Sp <= 768 : P.Sp < 384) return false;
   return planes_unit(P, sel_batch) && !flow_ring(P, sel_batch, 0);
