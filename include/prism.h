@@ -351,6 +351,11 @@ int prism_spd_inverse(const float* a, float* out, int batch, int n, void* stream
  * multiple of 128) and K of 16 (bf16: of 64). */
 int prism_gemm_f32(const float* A, const float* B, float* C, int batch, int M, int N, int K,
                    int a_km, void* stream);
+/* The same from three bf16 planes per operand, as the larger fp32 iterations take their products; M, N multiples of 64, K of 32 and 96 at least.
+ * a_km = 0: C += A B.  a_km = 1: A is stored [K][M], and the caller asserts that A B is symmetric (M = N): C = I - A B, tiles on and above
+ * the diagonal and their mirror image.  The planes lie in the cached workspace of the stream. */
+int prism_gemm_f32_planes(const float* A, const float* B, float* C, int batch, int M, int N, int K,
+                          int a_km, void* stream);
 int prism_gemm_f64a(const float* A, const double* B, double* C, int batch, int M, int N, int K,
                     void* stream);
 int prism_gemm_bf16_nt(const uint16_t* A, const uint16_t* B, float* C, int batch, int M, int N,

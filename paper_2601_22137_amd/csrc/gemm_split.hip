@@ -1,9 +1,14 @@
-// fp32 products on the bf16 matrix cores.  Each operand comes as three bf16 planes that add up to it exactly (split3.h); of the
-// nine products of planes the six largest are formed (what is left out is 2^-26 of a term and of either sign), exact in fp32
-// like all products of two bf16 numbers, so that only the accumulation rounds.  It is closed every 256 k into a second set of
-// registers, as in gemm_f32_tile.h; the error against 64 bits is then no larger than that of the fp32 matrix cores with the same
-// windows: relative Frobenius error at K = 1024, 4096, 8192, Gaussian operands 2.4, 2.6, 2.7e-7 (fp32 cores 2.9, 3.0, 3.1), positive
-// ones 1.1, 0.8, 0.96e-7 (1.3, 0.9, 1.0), identity plus 1 % 2.1, 2.2, 2.3e-7 (3.2, 3.4, 3.0), over six decades 1.7, 1.8, 2.0e-7 (2.7, 2.6, 2.6).
+// fp32 products on the bf16 matrix cores.  Each operand comes as three bf16 planes h + m + l that add up to it exactly (split3.h; |m| up to 2^-8 of it, |l| up to
+// 2^-17); of the nine products of planes the six largest are formed.  The two m l and l l are left out: together up to 2^-24 of a term, of either
+// sign, 2^-27.6 rms (5e-9).  Products of two bf16 numbers are exact in fp32, so that only the accumulation rounds.  It is closed every 256 k into a second set of
+// registers, as in gemm_f32_tile.h; the error against 64 bits is then below that of the fp32 matrix cores with the same
+// windows: relative Frobenius error at K = 256, 1024, 4096, 8192, Gaussian operands 2.4, 2.4, 2.6, 2.7e-7 (fp32 cores 2.9, 2.9, 3.0, 3.1), positive
+// ones 2.0, 1.1, 0.83, 0.97e-7 (2.5, 1.3, 0.90, 1.0), identity plus 1 % 1.9, 2.1, 2.3, 2.5e-7 (2.7, 3.1, 3.2, 3.4), over six decades 0.51, 1.2, 2.0, 2.2e-7 (0.84, 1.6,
+// 2.5, 2.7).  Sums of one term (diagonal operands) round once per plane product: 3.1e-8 (2.5).
+//
+// Within a sum entry (i, j) of X^T X meets m_i h_j before h_i m_j and entry (j, i) the other way round, so a symmetric product is symmetric to rounding only (1e-8 of its
+// norm) unless one half is stored as the mirror image of the other: whole 64 x 64 blocks below the diagonal are, the blocks on it are not.  Its skew part is
+// less than the rounding of the product, so a square of it taken as R^T R is within rounding of R R.
 //
 // What bounds it: the matrix pipe at the clock the power limit leaves (1.6 GHz; 1.3 to 1.4 PFLOP/s of bf16 work, a sixth of
 // that in fp32 flops).  8192^3 220 TFLOP/s, 32 x 1024^3 203, 4 x 1024^3 190, against 147, 138 and 115 on the fp32 cores.
@@ -11,7 +16,8 @@
 // One workgroup of eight wavefronts computes a 128 x 256 tile (2 x 4 wavefronts of 64 x 64) or a 128 x 128 one (64 x 32 each), one of four a
 // 64 x 64 one (2 x 2 of 32 x 32), where there are too few of the others.  K runs in slabs of 32 moved straight into an LDS ring of two (144 KiB) or three slabs; a fragment of a plane serves two or three of the six
 // products, so per MFMA the LDS and the loads have half the traffic of a plain bf16 product.  B is stored [K][N] and read with transposing
-// reads, A as [M][K] or [K][M].
+// reads, A as [M][K] or [K][M].  Splitting fp32 into three bf16 numbers is a published method (Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019).
 #include <type_traits>
 
 #include "split3.h"

@@ -678,7 +678,7 @@ int run_polar_f32(Run& r) {
     return g;
   };
   auto square = [&]() {
-    GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, polar ? 1 : 0);  // mirrored R: R^2 = R^T R
+    GemmDesc q = f32_desc(r, R, Sp, SS, R, Sp, SS, Sp, Sp, Sp, polar ? 1 : 0);  // mirrored R: R^2 = R^T R (from planes: to rounding, see gemm_split.hip)
     q.sym = sym;
     q.epi = EPI_POLYQ; q.C = Q; q.strideC = SS; q.ldc = Sp; q.Cin = R; q.strideCin = SS; q.ldcin = Sp; q.c1 = 0.5f;
     return q;
@@ -1938,6 +1938,29 @@ int prism_gemm_f32(const float* A, const float* B, float* C, int batch, int M, i
   const int tn = (N == 16 || N == 32 || N == 64) ? N : 128;
   if (tn == 128) return launch_gemm_f32(g, (hipStream_t)stream);
   return launch_gemm_f32(g, (tn == 64 && M % 128) ? 64 : 128, tn, (hipStream_t)stream);
+}
+
+int prism_gemm_f32_planes(const float* A, const float* B, float* C, int batch, int M, int N, int K, int a_km, void* stream) {
+  if (!A || !B || !C || batch <= 0 || batch > PRISM_MAX_BATCH || M <= 0 || N <= 0 || M % 64 || N % 64 || K < 96 || K % 32) return PRISM_EINVAL;
+  if ((a_km != 0 && a_km != 1) || (a_km && M != N)) return PRISM_EINVAL;
+  if ((long long)M * K > MAX_ENTRIES || (long long)K * N > MAX_ENTRIES || (long long)M * N > MAX_ENTRIES) return PRISM_EUNSUPPORTED;
+  const long long ca = (long long)batch * M * K, cb = (long long)batch * K * N;
+  const int tiles = split_tiles(M, N, batch, a_km);
+  char* ws = nullptr;
+  const int rc = get_workspace((size_t)(ca + cb) * 6 + (size_t)batch * tiles * sizeof(float), stream, nullptr, &ws);
+  if (rc != PRISM_OK) return rc;
+  uint16_t *pa = (uint16_t*)ws, *pb = pa + 3 * ca;
+  launch_split3(A, pa, ca, ca, (hipStream_t)stream);
+  launch_split3(B, pb, cb, cb, (hipStream_t)stream);
+  GemmDesc g = {};
+  g.A3 = pa; g.psA = ca; g.strideA = (long long)M * K; g.lda = a_km ? M : K;
+  g.B3 = pb; g.psB = cb; g.strideB = (long long)K * N; g.ldb = N;
+  g.M = M; g.N = N; g.K = K; g.a_km = g.sym = a_km; g.batch = batch; g.n_true = M;
+  g.C = C; g.strideC = (long long)M * N; g.ldc = N;
+  g.epi = a_km ? EPI_RESIDUAL : EPI_AXPY;
+  g.Cin = C; g.strideCin = g.strideC; g.ldcin = N; g.c_in = 1.0f;
+  g.rho_part = (float*)(pb + 3 * cb);
+  return launch_gemm_split(g, nullptr, (hipStream_t)stream);
 }
 
 int prism_gemm_f64a(const float* A, const double* B, double* C, int batch, int M, int N, int K, void* stream) {

@@ -27,7 +27,7 @@ INFO_DTYPE = np.dtype([("iters", np.int32), ("status", np.int32),
 
 EXPORTS = ("prism_workspace_bytes", "prism_release_workspaces", "prism_polar", "prism_polar_ex", "prism_polar_static", "prism_sqrt", "prism_sqrt_ex",
            "prism_inv_root", "prism_inv_root_ex", "prism_sign", "prism_sign_ex", "prism_inverse", "prism_inverse_ex", "prism_sqrt_newton", "prism_sqrt_newton_ex", "prism_spd_inverse", "prism_run_grouped", "prism_run_grouped_from",
-           "prism_sketch", "prism_gauss_parts", "prism_chain_product", "prism_chain_product_bf16", "prism_gemm_f32",
+           "prism_sketch", "prism_gauss_parts", "prism_chain_product", "prism_chain_product_bf16", "prism_gemm_f32", "prism_gemm_f32_planes",
            "prism_gemm_f64a", "prism_gemm_bf16_nt", "prism_profile_enable", "prism_profile_collect",
            "prism_last_error")
 
@@ -84,6 +84,7 @@ def lib():
         L.prism_chain_product.argtypes = [vp, vp, vp, i, i, i, vp]
         L.prism_chain_product_bf16.argtypes = [vp, vp, vp, vp, vp, i, i, i, vp]
         L.prism_gemm_f32.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
+        L.prism_gemm_f32_planes.argtypes = L.prism_gemm_f32.argtypes
         L.prism_gemm_f64a.argtypes = [vp, vp, vp, i, i, i, i, vp]
         L.prism_gemm_bf16_nt.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
         L.prism_profile_enable.argtypes = [i]
@@ -346,6 +347,16 @@ def gemm_f32(A, B, a_km=False, sym=False):
     C = torch.empty((batch, M, N), dtype=torch.float32, device=A.device)
     _check(lib().prism_gemm_f32(A.data_ptr(), B.data_ptr(), C.data_ptr(), batch, M, N, K, int(a_km) | (2 if sym else 0), _stream()))
     return C
+
+
+def gemm_f32_planes(A, B, C=None):
+    """C + A B (A [batch][M][K]), or without C: I - A^T B (A stored [batch][K][M], the product symmetric), from three bf16 planes per operand."""
+    batch, a, b = A.shape
+    M, K = (b, a) if C is None else (a, b)
+    N = B.shape[2]
+    out = torch.empty((batch, M, N), dtype=torch.float32, device=A.device) if C is None else C.clone()
+    _check(lib().prism_gemm_f32_planes(A.data_ptr(), B.data_ptr(), out.data_ptr(), batch, M, N, K, int(C is None), _stream()))
+    return out
 
 
 def gemm_f64a(A, B):

@@ -2,7 +2,7 @@
 batches that get each of the tiles (64 x 64, 128 x 128, 128 x 256), in whole and in partial rounds, in numbers that eight XCDs share evenly and not, against the oracle and against the products of
 fp32 operands (what a workspace too small for the planes gets).
 
-Bars: 1e-5 against the oracle, as for every fp32 path; the two ways differ by their rounding, a few 1e-7 per product, and by a stop
+Bars: 5e-7 for a single product against 64 bits; calls 1e-5 against the oracle, as for every fp32 path; the two ways differ by their rounding, a few 1e-7 per product, and by a stop
 that rounding decides (at most half the tolerance)."""
 import numpy as np
 import pytest
@@ -20,6 +20,67 @@ def prism():
     from paper_2601_22137_amd import prism as P
     P.lib()
     return P
+
+
+def _operands(kind, batch, m, k, n, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    a, b = (torch.randn(batch, *s, generator=g, device="cuda") for s in ((m, k), (k, n)))
+    if kind == "positive":
+        a, b = a.abs(), b.abs()
+    elif kind == "identity":                  # iterates close to their limit
+        a, b = (torch.eye(*x.shape[1:], device="cuda") + 0.01 * x for x in (a, b))
+    elif kind == "decades":                   # six of them, along k
+        a = a * torch.logspace(-3, 3, k, device="cuda")[None, None, :]
+    elif kind == "one":                       # one term per sum, all mantissas
+        a, b = (torch.zeros_like(x).scatter_(2, torch.arange(x.shape[1], device="cuda").remainder(x.shape[2])[None, :, None].expand(batch, -1, 1),
+                                             1.0 + torch.rand(batch, x.shape[1], 1, generator=g, device="cuda")) for x in (a, b))
+    return a, b
+
+
+# M, K, N, batch: every tile (64 x 64 in one round and in launches of no multiple of 128, 128 x 128, 128 x 256), K of the shortest ring, of partial
+# windows of 256 and of whole ones, tile counts that are no multiple of eight
+@pytest.mark.parametrize("kind", ["gauss", "positive", "identity", "decades", "one"])
+@pytest.mark.parametrize("m,k,n,batch", [(64, 96, 64, 1), (192, 128, 320, 3), (448, 448, 448, 10), (576, 288, 64, 2), (1024, 1056, 1024, 1), (1024, 1024, 1024, 4), (1152, 96, 1152, 3),
+                                         (1024, 512, 1280, 9), (1024, 4128, 1024, 8)])
+def test_single_product_against_64_bits(prism, kind, m, k, n, batch):
+    """Three planes hold an fp32 number exactly, and the three products of planes that are left out are at most 2^-24 of a term together (2^-25 for either m l, 2^-34 for l l;
+    rms 2^-27.6), so that a product is as close as fp32 accumulation in windows of 256 makes it: 3e-7.  With the least of the six missing Gaussian operands would be at 2.5e-6."""
+    a, b = _operands(kind, batch, m, k, n, m + k + n)
+    c = torch.randn(batch, m, n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)) * 0.125
+    out = prism.gemm_f32_planes(a, b, c)
+    err = ref2 = 0.0
+    for i in range(batch):
+        ref = c[i].double() + a[i].double() @ b[i].double()
+        err += float(((out[i].double() - ref) ** 2).sum())
+        ref2 += float((ref ** 2).sum())
+    assert np.sqrt(err / ref2) <= 5e-7, np.sqrt(err / ref2)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "positive", "decades"])
+@pytest.mark.parametrize("m,k,batch", [(64, 96, 1), (192, 320, 3), (448, 672, 9), (1024, 1056, 1), (1024, 1536, 7), (1152, 1184, 8)])
+def test_gram_product_against_64_bits(prism, kind, m, k, batch):
+    """I - A^T A with A stored [K][M]: whole 64 x 64 blocks below the diagonal are the mirror image of those above, to the bit; within a block on the diagonal the two
+    halves are computed each for itself (see gemm_split.hip) and agree to rounding (1e-8 of the norm)."""
+    at, _ = _operands(kind, batch, k, m, 8, m + k)
+    if kind == "decades":                     # along the columns here: the sums keep their range
+        at = at / torch.logspace(-3, 3, m, device="cuda")[None, None, :]
+    at = at.contiguous()
+    out = prism.gemm_f32_planes(at, at)
+    ref = torch.eye(m, device="cuda", dtype=torch.float64) - torch.stack([x.double().t().contiguous() @ x.double() for x in at])
+    assert float((out.double() - ref).norm() / ref.norm()) <= 5e-7
+    blocks = out.view(batch, m // 64, 64, m // 64, 64)
+    mirror = out.transpose(1, 2).contiguous().view(batch, m // 64, 64, m // 64, 64)
+    diag = torch.eye(m // 64, dtype=torch.bool, device="cuda")[None, :, None, :, None]
+    assert bool(((blocks == mirror) | diag).all())
+    assert float((out - out.transpose(1, 2)).double().norm() / ref.norm()) <= 5e-8
+
+
+def test_products_of_planes_that_are_refused(prism):
+    a = torch.zeros(1, 64, 96, device="cuda")
+    lib = prism.lib()
+    call = lambda m, n, k, km: lib.prism_gemm_f32_planes(a.data_ptr(), a.data_ptr(), a.data_ptr(), 1, m, n, k, km, None)
+    assert [call(*x) for x in ((32, 64, 96, 0), (64, 96, 96, 0), (64, 64, 64, 0), (64, 64, 100, 0), (64, 64, 96, 2), (64, 128, 96, 1))] == [prism.EINVAL] * 6
 
 
 def _rel(x, ref):
