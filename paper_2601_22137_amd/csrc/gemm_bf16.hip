@@ -96,7 +96,8 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
   bool lines = true;   // K in whole slabs of 64, two at least
   // A launch whose tiles are no multiple of eight is rounded up where the operands are large enough for their fetches past the L2s to be what
   // it waits for (Gram product of 50257 x 768 in 12 parts, 252 tiles of 77 MB: 64 -> 52 us); small ones are faster in plain order (one
-  // 768 x 3072 in 6 parts, 126 tiles of 5 MB: 10.2 against 11.6).  Nothing in between was measured.
+  // 768 x 3072 in 6 parts, 126 tiles of 5 MB: 10.2 against 11.6).  One-pass Gram products in plain order / rounded up, us: 12 x 3072 x 768 (252 tiles, 54 MB) 53 / 39,
+  // 2 x 6144 x 1536 (156, 36 MB) 67 / 64, 3 x 5120 x 1280 (165, 38 MB) 58 / 55; of several rounds 20 x 768 x 768 (420, 22 MB) 31 / 23, 6 x 1280 x 1280 (330, 19 MB) 34 / 27.
   double operand_bytes = 0.0;
   for (int i = 0; i < mg.ngroups; ++i) {
     const Bf16Desc& g = mg.d[i];

@@ -142,12 +142,18 @@ int flow_ring(const Plan& P, int sel_batch, size_t bytes) {
 
 // fp32 products from bf16 planes (gemm_split.hip), where the calls are not a launch of their own (flow_ring).  Padding: whole tiles of 128 where
 // they cost less than the smaller tiles do (about a fifth per product).  us from fp32 operands / from planes, tolerance 1e-5:
-//   sign          16 x 512 1311 / 1103, 64 x 512 3901 / 3390, 768: 4 1397 / 1193, 16 3423 / 3203, 1000: 1 943 / 840, 4 2184 / 1633, 2 x 1900 6220 / 4535, 4096 24945 / 16177
-//   square root   16 x 512 1096 / 914, 1000: 1 737 / 676, 4 1702 / 1299, 2 x 1900 5116 / 3767, 4096 20907 / 13747; inverse much like sign
-//   polar         64 x 768 x 512 3591 / 3553, 1500 x 1000: 1 974 / 820, 4 2089 / 1671, 6144 x 4096 24429 / 18109
-//   inverse root  p = 4, 1000: 1 943 / 881, 4 2287 / 2026, 8 4074 / 3744, 2 x 1900 6801 / 5746, 4096 32118 / 26841; 512 and 768 equal
+//   sign          24 x 384 1059 / 911, 16 x 512 1340 / 1125, 64 x 512 4082 / 3455, 768: 4 1361 / 1154, 16 3722 / 3334, 1000: 1 961 / 856, 4 2256 / 1676, 2 x 1900
+//                 6837 / 4558, 4096 25082 / 16976; padded to 64: 10 x 448 824 / 756, 6 x 576 1002 / 890, 2 x 832 1180 / 986
+//   square root   24 x 384 981 / 879, 16 x 512 1174 / 951, 1000: 1 778 / 697, 4 1916 / 1370, 2 x 1900 5608 / 3929, 4096 21024 / 14124; padded to 64: 10 x 448 752 / 706,
+//                 6 x 576 826 / 753
+//   inverse       24 x 384 1335 / 1129, 16 x 512 1620 / 1332, 1000: 1 1125 / 987, 4 2902 / 2113
+//   polar         24 x 576 x 384 1061 / 997, 64 x 768 x 512 3924 / 3734, 1500 x 1000: 1 1011 / 859, 4 2178 / 1784, 6144 x 4096 24706 / 18894
+//   inverse root  p = 4, 4 x 896 2059 / 1813, 1000: 1 978 / 924, 4 2457 / 2202, 8 4308 / 3916, 2 x 1900 7167 / 6002, 4096 32383 / 28820; p = 2, 12 x 896 4436 / 4302,
+//                 4 x 1000 2200 / 2010; 512 and 768 equal
 // Inverse roots: by the order alone, so that a matrix has the same bits alone and in any batch; its fp64 product pays for the padding and gains nothing (order 1088
-// would be 1152).  Not for tall polar factors, whose Gram product runs in parts, nor for p = 1, where the iterate has the scale of the input.
+// would be 1152).  Not for p = 1, where the iterate has the scale of the input, nor for polar factors of more than 8064 rows: the Gram products of up to
+// eight such matrices run in parts (P.ksplit), which have no planes; of others (larger batches, orders above 1152) only the products were compared, not the calls.
+// The others go by the caller's batch too, so that their bits may depend on it (sign of order 512: one launch on fp32 operands for 8 matrices, planes for 9).
 int planes_unit(const Plan& P, int sel_batch) {
   const double s = round_up(P.S, 128) / (double)round_up(P.S, 64), l = round_up(P.L, 128) / (double)round_up(P.L, 64), grown = s * s * l;
   if (P.fn == PRISM_FN_INV_ROOT) return grown < 1.1 ? 128 : 0;
