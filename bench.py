@@ -154,7 +154,9 @@ def make_workload(name, args, prism, W):
         wl.call = lambda x: prism.polar(x, 5, 30, 8, wl.seed, 1e-6)
         wl.ld, wl.nv, wl.r_bytes = 16, 5, 4
     wl.n_matrices = sum(h.shape[0] for h in wl.host)
-    wl.peak = "f32_planes" if name in ("c4", "c5", "sign", "inverse") else wl.dtype   # the rate the products of the workload are priced against
+    wl.peak = "f32_planes" if name in ("c4", "c5", "sign", "inverse") else wl.dtype   # the rate its products are priced against
+    # ... and a whole call: config 4 has three fp32 products and one in fp64 per iteration
+    wl.call_peak = 4.0 / (3.0 / PEAK["f32_planes"] + 1.0 / PEAK["f64"]) if name == "c4" else PEAK[wl.peak]
     return wl
 
 
@@ -417,8 +419,8 @@ def run_config(name, K, Wm, args, torch, prism, W):
         "ms_per_step": round(ms_per_step, 4), "ms_per_step_median": round(float(np.median(per_call)), 4),
         "ms_per_step_min": round(float(per_call.min()), 4),
         "tflops_algorithmic": round(tflops_algo, 2), "tflops_executed": round(tflops_exec, 2),
-        "frac_of_mfma_peak": round(tflops_exec / PEAK[wl.peak], 4),
-        "frac_of_mfma_peak_algorithmic": round(tflops_algo / PEAK[wl.peak], 4),
+        "frac_of_mfma_peak": round(tflops_exec / wl.call_peak, 4),
+        "frac_of_mfma_peak_algorithmic": round(tflops_algo / wl.call_peak, 4),
         "iterations": {"min": min(iters_all), "max": max(iters_all)},
         "stop_margin": margin, "kernel_ms_per_step": kernel_ms,
         "roofline": roofline, "hbm_bound_kernels": hbm, "cpu_baseline": cpu, "parity": parity,
