@@ -85,15 +85,16 @@ long long tiles_per_matrix(const Bf16Desc& g) {
   return SYM ? (TM / TN) * tm * (tm + 1) / 2 : tm * tn;
 }
 
-// Slabs of 64 k or of 32 for an update of `tiles` tiles with K = k: two workgroups per CU against three.  Up to one round of the longer ones (512), and from K = 768 on
-// beyond one of the shorter (768).  Us, slabs of 32 / 64: K = 384, 384 tiles 15.4 / 15.2, 576 22.3 / 24.0, 1152 29.2 / 30.6; K = 512, 512 tiles 17.7 / 16.8, 640 22.5 / 23.6, 4096 105 / 110;
-// K = 768, 576 tiles 31.3 / 34.0, 720 35.8 / 38.3, 2304 71.6 / 68.9; K = 1024, 640 38.0 / 40.2, 1024 43.9 / 40.2.
-bool slabs_of_64(long long tiles, int k) { return tiles <= 512 || (k >= 768 && tiles > 768); }
+// Slabs of 64 k or of 32 for an update of `tiles` tiles with K = k: two workgroups per CU against three.  From K = 512 on up to one round of the longer ones (512 tiles), and
+// from K = 768 on beyond one of the shorter (768).  Us, slabs of 32 / 64: K = 512, 512 tiles 17.7 / 16.8, 640 22.5 / 23.6, 4096 105 / 110; K = 768, 576 tiles 31.3 / 34.0, 720
+// 35.8 / 38.3, 2304 71.6 / 68.9; K = 1024, 640 38.0 / 40.2, 1024 43.9 / 40.2.  Below K = 512 a single launch gains 0.3 us, but beside the launches of another part of a
+// grouped call, whose workgroups find less room, it loses more: 14 layers of width 151 (K = 256) 633 / 656, 8 of 384 719 / 747, 10 of 300 760 / 791, 16 of 256 697 / 713.
+bool slabs_of_64(long long tiles, int k) { return k >= 512 && (tiles <= 512 || (k >= 768 && tiles > 768)); }
 
 template <int TM, int TN, int EPI, bool SYM, bool KMA, bool KMB, int NW>
 int launch_tw(Bf16Multi& mg, hipStream_t s) {
   long long total = 0;
-  bool lines = true;   // K in whole slabs of 64, two at least
+  bool lines = true;   // K in whole slabs of 64
   // A launch whose tiles are no multiple of eight is rounded up where the operands are large enough for their fetches past the L2s to be what
   // it waits for (Gram product of 50257 x 768 in 12 parts, 252 tiles of 77 MB: 64 -> 52 us); small ones are faster in plain order (one
   // 768 x 3072 in 6 parts, 126 tiles of 5 MB: 10.2 against 11.6).  One-pass Gram products in plain order / rounded up, us: 12 x 3072 x 768 (252 tiles, 54 MB) 53 / 39,
@@ -103,7 +104,7 @@ int launch_tw(Bf16Multi& mg, hipStream_t s) {
     const Bf16Desc& g = mg.d[i];
     total += tiles_per_matrix<TM, TN, SYM>(g) * g.batch;
     operand_bytes += 2.0 * g.batch * ((double)g.M * g.K + (g.A == g.B ? 0.0 : (double)g.N * g.K));
-    lines = lines && g.K % 64 == 0 && g.K >= 128;
+    lines = lines && g.K % 64 == 0;
   }
   const bool wide = lines && slabs_of_64(total, mg.d[0].K);
   // Launches of several rounds are rounded up too, small ones keep whole ranges of the launch (three updates of five layers of width 320, update of 465 tiles

@@ -217,9 +217,9 @@ def test_gemm_row_offsets_beyond_32_bits(prism, f64):
 
 
 @pytest.mark.parametrize("plain", [False, True])
-@pytest.mark.parametrize("n,batches", [(384, (56, 57)), (512, (32, 33)), (768, (14, 15, 22))])
+@pytest.mark.parametrize("n,batches", [(512, (32, 33)), (768, (14, 15, 22)), (1024, (8, 9, 13))])
 def test_updates_in_slabs_of_32_and_of_64(prism, n, batches, plain):
-    """Launches of 128 x 128 update tiles on both sides of the rule that picks the length of the slabs (512 tiles, 768 from order 768 on): the order of the sums
+    """Launches of 128 x 128 update tiles on both sides of the rule that picks the length of the slabs (512 tiles, and 768 from order 768 on; the numbers of matrices are their counts over 16, 36 and 64 tiles each): the order of the sums
     is the same, and so are the bits.  Fixed coefficients, so that nothing else goes by the batch."""
     rng = np.random.default_rng(n)
     bits = W.to_bf16_bits((rng.standard_normal((2, n, n)) * np.exp(rng.standard_normal((2, n, 1))) / n).astype(np.float32))
