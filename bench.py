@@ -386,7 +386,8 @@ def run_config(name, K, Wm, args, torch, prism, W):
             S, L = min(m, n), max(m, n)
             per_iter = {"bf16_apply": 2.0 * L * S * S, "bf16_gram": 2.0 * L * S * S, "bf16_polyq": 2.0 * S ** 3,
                         "f32_resid": 2.0 * L * S * S, "f32_polyq": 2.0 * S ** 3,
-                        "f32_apply": (4.0 if wl.name in ("c5", "sqrt-newton") else 2.0) * L * S * S,
+                        # (both updates of the square roots; those of DB Newton are symmetric and run half of their tiles)
+                        "f32_apply": (4.0 if wl.name == "c5" else 2.0) * L * S * S,
                         "f32_store": 4.0 * S ** 3, "f64_mnext": 2.0 * S ** 3, "spd_inverse": 2.0 * S ** 3,
                         # one launch runs every iteration: Gram, R^2 and the update
                         "f32_small_polar": 4.0 * L * S * S + 2.0 * S ** 3}[dom]
